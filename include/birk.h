@@ -90,7 +90,7 @@ typedef struct birk_plan birk_plan;
  * hip_stream is a hipStream_t (NULL = the device's null stream); the plan is bound to
  * the device current at creation.  Allocates all scratch, the CGL weights and the
  * transform tables (CC weights computed on the device through B^aT e_N).
- * Consecutive instances with the same power-of-two N >= 512 share the launches of the
+ * Consecutive instances with the same power-of-two N >= 4096 share the launches of the
  * three-pass product; all other instances, whatever their sizes, are covered by one
  * fixed set of launches per product (work lists built here).
  * Errors: BIRK_ERR_ARG (out/arrays NULL, bad precision), BIRK_ERR_SIZE (batch < 1,
@@ -105,7 +105,7 @@ birk_status birk_plan_destroy(birk_plan* plan);
 /* Total vector length sum_i n_x[i] * N_n[i] of the plan (elements, not bytes). */
 int64_t birk_plan_length(const birk_plan* plan);
 
-/* Autotuner of the product schedules.  Power-of-two path (N = 2^p >= 512): for each group of
+/* Autotuner of the product schedules.  Power-of-two path (N = 2^p >= 4096): for each group of
  * same-length components it times B^a (FastBV box) in the plan's precision over a
  * fixed set of tile schedules: both splits 2N = L1 L2 of the two-step DCTs, two or four
  * rows per middle-pass tile, the plain or XCD-grouped tile order, four- or eight-column

@@ -141,7 +141,7 @@ constexpr size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 // buffers (two for power-of-two groups only, three when the general path runs) and the
 // c^_0 partials, each 256-byte aligned.
 size_t noalloc_need(const birk_plan* p, int* nbuf) {
-  *nbuf = (p->gen[0].host.empty() && p->gen[1].host.empty()) ? 2 : 3;
+  *nbuf = p->noalloc_nbuf;
   return (size_t)*nbuf * align256((size_t)std::max<int64_t>(p->total_work, 1) * sizeof(double2)) +
          align256((size_t)std::max<int64_t>(p->total_part, 1) * sizeof(double));
 }
@@ -279,7 +279,9 @@ birk_status birk_plan_create(birk_plan** out, int32_t batch, const int64_t* n_no
   const int64_t woff = std::max<int64_t>(p->total_work, 1), poff = p->total_part;
 
   hipError_t e = hipSuccess;
-  for (int b = 0; b < 3 && e == hipSuccess; ++b) e = hipMalloc(&p->work[b], woff * sizeof(double2));
+  // (a few elements over: the set-up transform of the shortest filter, N = 2, is longer than
+  // the slot its pair counts for)
+  for (int b = 0; b < 3 && e == hipSuccess; ++b) e = hipMalloc(&p->work[b], (woff + 16) * sizeof(double2));
   for (int b = 0; b < 4 && e == hipSuccess; ++b) e = hipMalloc(&p->tmp_vec[b], off * sizeof(double));
   if (e == hipSuccess) e = hipMalloc(&p->partials, std::max<int64_t>(poff, 1) * sizeof(double));
   if (e == hipSuccess) e = hipMalloc(&p->scan, std::max<int64_t>(soff, 1) * sizeof(double));

@@ -21,6 +21,9 @@
 // [-(L - 1), N]: the filter holds lags 0..N at the start and -1..-(L - 1) at the end of
 // the circular buffer, which do not meet once M >= N + L.
 //
+// Products whose transforms fit one workgroup (N <= 2048 a power of two, any N with
+// 3N <= 4096) run in one launch (birk_lds.hip); the rest of this file covers the others.
+//
 // Batching: the pairs of all instances of one kind (plain power of two, or Bluestein)
 // form a PairSet.  Each phase of the product (pack, FFT passes, filter, stencil, c^_0,
 // unpack) is ONE launch over the whole set, whatever the mix of sizes: the grid is a
@@ -584,68 +587,6 @@ __device__ __forceinline__ cplx<T> sget(const T* sm, int t, int n) {
     default: break;                                                            \
   }
 
-// Whole convolutions of length M = 2^LOGM <= kLdsMax, kLdsMax / M pairs per block (the
-// tile's pairs share M; the remaining transforms of the block run on zeros).
-template <typename T, int LOGM>
-__device__ __forceinline__ void blu_lds_body(const T* __restrict__ x, const cplx<T>* __restrict__ dz,
-                                             cplx<T>* __restrict__ Y, const PairDesc* __restrict__ pd, int2 tile,
-                                             const cplx<T>* __restrict__ tw, int src_x, int ends2, T* sm) {
-  constexpr int pi = prec_index<T>();
-  constexpr int M = 1 << LOGM;
-  constexpr int COUNT = kLdsMax >> LOGM;
-  constexpr int PER = kLdsMax / kBluThreads;
-  // the inputs, the filter spectra and the chirp of the outputs are read in one batch
-  cplx<T> v[PER], fv[PER], cv[PER];
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = (int)threadIdx.x + i * kBluThreads;
-    const int t = e >> LOGM, n = e & (M - 1);
-    v[i] = fv[i] = cv[i] = mk<T>(T(0), T(0));
-    if (t < tile.y) {
-      const PairDesc& d = pd[tile.x + t];
-      const cplx<T>* chirp = (const cplx<T>*)d.chirp[pi];
-      v[i] = blu_in<T>(d, x, dz, src_x, ends2, chirp, n);
-      fv[i] = ((const cplx<T>*)d.filt[pi])[n];
-      if (n <= d.N) cv[i] = chirp[n];
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = (int)threadIdx.x + i * kBluThreads;
-    sput<T, LOGM>(sm, e >> LOGM, e & (M - 1), v[i]);
-  }
-  __syncthreads();
-  fast::fft_ct<T, LOGM, COUNT>(sm, tw);
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = (int)threadIdx.x + i * kBluThreads;
-    const int t = e >> LOGM, k = e & (M - 1);
-    if (t < tile.y) sput<T, LOGM>(sm, t, k, cconj<T>(cmul<T>(sget<T, LOGM>(sm, t, k), fv[i])));
-  }
-  __syncthreads();
-  fast::fft_ct<T, LOGM, COUNT>(sm, tw);
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = (int)threadIdx.x + i * kBluThreads;
-    const int t = e >> LOGM, k = e & (M - 1);
-    if (t < tile.y) {
-      const PairDesc& d = pd[tile.x + t];
-      if (k <= d.N) Y[d.work + k] = cmul<T>(cconj<T>(sget<T, LOGM>(sm, t, k)), cv[i]);
-    }
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBluThreads) void k_blu_lds(const T* __restrict__ x, const cplx<T>* __restrict__ dz,
-                                                        cplx<T>* __restrict__ Y, const PairDesc* __restrict__ pd,
-                                                        const int2* __restrict__ tiles, const cplx<T>* __restrict__ tw,
-                                                        int src_x, int ends2) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  T* sm = reinterpret_cast<T*>(smem_raw);
-  const int2 tile = tiles[blockIdx.x];
-  BIRK_LOG_SWITCH(pd[tile.x].logM, 3, (blu_lds_body<T, LG>(x, dz, Y, pd, tile, tw, src_x, ends2, sm)))
-}
-
 // Columns pass: n = M2 n1 + n2; the W = kLdsMax / M1 columns [c0, c0 + W) of the padded
 // input, FFT over n1, twiddle W_M^(n2 k1), tmp[k1 M2 + n2].  tile = (pair, column block).
 template <typename T, int LOGM1>
@@ -854,16 +795,12 @@ static hipError_t dct_blu(birk_plan* p, const PairSet& ps, const T* x, const cpl
   const size_t lds = (size_t)kBluLdsReals * sizeof(T);
   static const bool attr = [] {  // above the default dynamic LDS limit in double
     constexpr int b = (int)(kBluLdsReals * sizeof(T));
-    (void)hipFuncSetAttribute((const void*)k_blu_lds<T>, hipFuncAttributeMaxDynamicSharedMemorySize, b);
     (void)hipFuncSetAttribute((const void*)k_blu_cols<T>, hipFuncAttributeMaxDynamicSharedMemorySize, b);
     (void)hipFuncSetAttribute((const void*)k_blu_rows<T>, hipFuncAttributeMaxDynamicSharedMemorySize, b);
     (void)hipFuncSetAttribute((const void*)k_blu_icols<T>, hipFuncAttributeMaxDynamicSharedMemorySize, b);
     return true;
   }();
   (void)attr;
-  if (ps.n_lds > 0)
-    hipLaunchKernelGGL(k_blu_lds<T>, dim3(ps.n_lds), dim3(kBluThreads), lds, s, x, dz, Y, ps.dev, ps.tiles_lds, tw,
-                       src_x, ends2);
   if (ps.n_c4 > 0) {
     hipLaunchKernelGGL(k_blu_cols<T>, dim3(ps.n_c4), dim3(kBluThreads), lds, s, x, dz, tmp, ps.dev, ps.tiles_c4, tw,
                        src_x, ends2);
@@ -899,7 +836,8 @@ hipError_t apply_product(birk_plan* p, const T* v, T* out, int transpose, hipStr
     hipError_t e = fast_product<T>(p, g, v, out, transpose, s);
     if (e != hipSuccess) return e;
   }
-  hipError_t e = product_set<T>(p, p->gen[0], v, out, transpose, s);
+  hipError_t e = product_lds<T>(p, v, out, transpose, s);
+  if (e == hipSuccess) e = product_set<T>(p, p->gen[0], v, out, transpose, s);
   if (e == hipSuccess) e = product_blu<T>(p, p->gen[1], v, out, transpose, s);
   return e;
 }
@@ -933,7 +871,7 @@ static void expi_pi(int64_t num, int64_t den, double* c, double* s) {
   *s = -(sgn_s * sn);
 }
 
-static hipError_t upload_raw(birk_plan* p, const void* h, size_t bytes, void** d) {
+hipError_t upload_raw(birk_plan* p, const void* h, size_t bytes, void** d) {
   *d = nullptr;
   hipError_t e = hipMalloc(d, std::max<size_t>(bytes, 16));
   if (e != hipSuccess) return e;
@@ -1016,7 +954,7 @@ static PairDesc make_pair(int64_t src, int64_t Nn, int has2, const int* split) {
   d.Nn = Nn;
   d.N = Nn - 1;
   d.L = 2 * d.N;
-  const bool pow2 = (d.L & (d.L - 1)) == 0;
+  const bool pow2 = (d.L & (d.L - 1)) == 0 && d.L >= 8;   // the shortest compiled transform
   d.M = pow2 ? d.L : (int64_t(1) << ilog2_ceil(d.N + d.L));
   d.logM = ilog2_ceil(d.M);
   if (d.logM > kLdsMaxLog) {
@@ -1029,8 +967,7 @@ static PairDesc make_pair(int64_t src, int64_t Nn, int has2, const int* split) {
   return d;
 }
 
-// Sort the pairs by M (so that pairs of one LDS-sized M are adjacent), then give each
-// its work slot and partials.
+// Sort the pairs by M, then give each its work slot and partials.
 static void layout_set(PairSet& ps, int64_t& woff, int64_t& poff) {
   std::stable_sort(ps.host.begin(), ps.host.end(),
                    [](const PairDesc& a, const PairDesc& b) { return a.M < b.M; });
@@ -1046,10 +983,20 @@ static void layout_set(PairSet& ps, int64_t& woff, int64_t& poff) {
   }
 }
 
+// Longest power-of-two N whose products run in one workgroup's LDS (2N <= kLdsMax).  Up to
+// there one launch that reads v and writes out once beats the three passes and their two
+// intermediate arrays at every batch size (double, N = 512 / 1024 / 2048: 24 / 26 / 30 us in
+// three passes, 12.6 / 15.2 / 20.5 us here at six components, and 25 / 28 / 32 against
+// 12.8 / 15.4 / 21 us at 192; double-float at 192 and N = 2048 65 against 46 us).
+constexpr int64_t kLdsMaxN = kLdsMax / 2;
+
 void plan_products(birk_plan* p) {
   p->fgroups.clear();
-  p->gen[0] = PairSet();
-  p->gen[1] = PairSet();
+  for (int k = 0; k < 2; ++k) {
+    p->gen[k] = PairSet();
+    p->lds[k] = LdsSet();
+  }
+  p->noalloc_nbuf = 2;
   int64_t woff = 0, poff = 0;
   const int B = (int)p->inst.size();
   for (int i = 0; i < B;) {
@@ -1064,6 +1011,17 @@ void plan_products(birk_plan* p) {
       while (j < B && p->inst[j].N == in.N) g.nc += p->inst[j++].nx;
       int64_t fw = 0, fp = 0;
       fast_sizes(p, g.N, g.nc, &fw, &fp);
+      if (g.N <= kLdsMaxN) {
+        // no workspace used; the plan's size (what birk_apply_noalloc accepts) counts it
+        // as for the three-pass groups
+        for (; i < j; ++i)
+          for (int q = 0; q < (p->inst[i].nx + 1) / 2; ++q)
+            p->lds[0].host.push_back(make_pair(p->inst[i].off + 2 * (int64_t)q * in.Nn, in.Nn,
+                                               2 * q + 1 < p->inst[i].nx, p->blu_split));
+        woff += fw;
+        poff += fp;
+        continue;
+      }
       g.work_off = woff;
       g.part_off = poff;
       woff += fw;
@@ -1075,7 +1033,18 @@ void plan_products(birk_plan* p) {
     const int np = (in.nx + 1) / 2;
     for (int q = 0; q < np; ++q) {
       PairDesc d = make_pair(in.off + 2 * (int64_t)q * in.Nn, in.Nn, 2 * q + 1 < in.nx, p->blu_split);
-      p->gen[(d.L == d.M) ? 0 : 1].host.push_back(d);
+      const int chirp = d.L == d.M ? 0 : 1;
+      p->noalloc_nbuf = 3;
+      if (d.logM > kLdsMaxLog) {
+        p->gen[chirp].host.push_back(d);
+        continue;
+      }
+      // whole product in LDS: a work slot only for the filter's set-up at plan creation
+      // (and in the plan's size)
+      d.work = woff;
+      woff += d.L == 4 ? 4 : d.M;
+      poff += 2 * (int64_t)d.nblk;
+      p->lds[chirp].host.push_back(d);
     }
     ++i;
   }
@@ -1322,7 +1291,11 @@ hipError_t build_tables(birk_plan* p) {
   };
   std::map<int64_t, Blue> blue;
   PairSet fs;  // one pair per distinct L: the filter FFTs
-  for (const PairDesc& d : p->gen[1].host) {
+  std::vector<PairDesc*> chirped;
+  for (PairDesc& d : p->gen[1].host) chirped.push_back(&d);
+  for (PairDesc& d : p->lds[1].host) chirped.push_back(&d);
+  for (const PairDesc* dp : chirped) {
+    const PairDesc& d = *dp;
     if (blue.count(d.L)) continue;
     Blue b{};
     std::vector<double> re(d.L), im(d.L);
@@ -1378,16 +1351,18 @@ hipError_t build_tables(birk_plan* p) {
       b.filt[2] = d2;
     }
     if ((e = hipStreamSynchronize(p->stream)) != hipSuccess) return e;
-    for (PairDesc& d : p->gen[1].host) {
-      const Blue& b = blue[d.L];
+    for (PairDesc* d : chirped) {
+      const Blue& b = blue[d->L];
       for (int pi = 0; pi < kNumPrec; ++pi) {
-        d.chirp[pi] = b.chirp[pi];
-        d.filt[pi] = b.filt[pi];
+        d->chirp[pi] = b.chirp[pi];
+        d->filt[pi] = b.filt[pi];
       }
     }
   }
   for (int k = 0; k < 2; ++k)
-    if (!p->gen[k].host.empty() && (e = finalize_set(p, p->gen[k])) != hipSuccess) return e;
+    if ((!p->gen[k].host.empty() && (e = finalize_set(p, p->gen[k])) != hipSuccess) ||
+        (e = finalize_lds(p, p->lds[k])) != hipSuccess)
+      return e;
   return hipGetLastError();
 }
 

@@ -36,6 +36,7 @@
 
 #include "birk_fft.h"
 #include "birk_internal.h"
+#include "birk_mid.h"
 
 namespace birk {
 
@@ -664,22 +665,6 @@ __global__ __launch_bounds__(1 << (LOGL2 - 3)) void k_fastB2(
     }
     __syncthreads();
   }
-}
-
-// Reciprocal of a positive integer-valued x: the hardware estimate refined by two Newton
-// steps in double (within an ulp of 1/x, several times cheaper than a division); a plain
-// division for the other storage types.
-template <typename T>
-__device__ __forceinline__ T recip_int(T x) {
-  return T(1) / x;
-}
-template <>
-__device__ __forceinline__ double recip_int<double>(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = __builtin_fma(-x, r, 1.0);
-  r = __builtin_fma(r, e, r);
-  e = __builtin_fma(-x, r, 1.0);
-  return __builtin_fma(r, e, r);
 }
 
 // stencil_fwd and stencil_tr with one or two reciprocals per element in place of their

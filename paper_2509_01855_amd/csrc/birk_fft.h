@@ -118,6 +118,7 @@ __device__ __forceinline__ void load_tw_stage(cplx<T> (&w)[3], int logL, int log
 }
 
 // ---- fixed-length transforms: COUNT transforms of length 2^LOGL, blockDim = COUNT 2^LOGL / 8 ----
+// (COUNT = 0: 8 blockDim / 2^LOGL of them, blockDim known at run time)
 // Transform t has its real part in row 2t and its imaginary part in row 2t + 1 of a
 // split array with padded rows of padded_ld(2^LOGL) reals.  With the length known at
 // compile time every LDS address of a butterfly is the padded position of its first
@@ -130,7 +131,7 @@ __device__ __forceinline__ void stage_ct(T* __restrict__ buf, const cplx<T> (&w)
   constexpr int NB = kPPT / R;             // butterflies per thread
   constexpr int LOGNBF = LOGL - logR;
   constexpr int NBF = 1 << LOGNBF;         // butterflies per transform
-  constexpr int NTHR = COUNT << (LOGL - 3);  // threads (blockDim)
+  const int NTHR = COUNT > 0 ? COUNT << (LOGL - 3) : (int)blockDim.x;  // threads
   constexpr int NS = 1 << LOGNS;
   constexpr int LD = padded_ld(1 << LOGL);
   T vr[NB][R], vi[NB][R];

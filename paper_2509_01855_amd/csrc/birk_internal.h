@@ -132,6 +132,17 @@ struct PairSet {
   int64_t parts = 0;          // doubles of partials needed
 };
 
+// Pairs whose whole product runs in one workgroup's LDS (birk_lds.hip): one launch over the
+// tiles (first pair, count) of pairs of one length.
+struct LdsSet {
+  std::vector<PairDesc> host;
+  PairDesc* dev = nullptr;
+  int2* tiles = nullptr;
+  int ntiles = 0;
+  int threads = 0;    // workgroup size: an eighth of the longest length, at least one wave
+  int lds_reals = 0;  // dynamic LDS of a workgroup
+};
+
 // Inverse-preconditioner scan of one instance (birk_solve.hip): level sizes and the
 // offsets of its aggregates and start states in the plan's scan scratch.
 constexpr int kPinvMaxLevels = 8;
@@ -201,6 +212,8 @@ struct birk_plan {
   std::vector<birk::Instance> inst;
   std::vector<birk::FastGroup> fgroups;
   birk::PairSet gen[2];           // general-path pairs: [0] 2N a power of two, [1] Bluestein
+  birk::LdsSet lds[2];            // pairs that fit one workgroup: [0] 2N a power of two, [1] Bluestein
+  int noalloc_nbuf = 3;           // work buffers that birk_apply_noalloc accounts for
   std::vector<birk::PinvClass> pclass;  // preconditioner scan schedule, one class per n_x
   birk::SegSet seg;               // Krylov segmentation of the batch
   std::vector<void*> allocs;      // device tables owned by the plan
@@ -290,6 +303,15 @@ hipError_t apply_product(birk_plan* p, const T* v, T* out, int transpose, hipStr
 void plan_products(birk_plan* p);
 // Allocate and fill every transform table and work list (after the work buffers exist).
 hipError_t build_tables(birk_plan* p);
+
+// A device array of the plan (in p->allocs) holding a copy of `bytes` host bytes.
+hipError_t upload_raw(birk_plan* p, const void* h, size_t bytes, void** d);
+
+// ---- whole products in LDS (birk_lds.hip) ----
+// Sort the set's pairs by length and upload its descriptors and tile list.
+hipError_t finalize_lds(birk_plan* p, LdsSet& ls);
+template <typename T>
+hipError_t product_lds(birk_plan* p, const T* v, T* out, int transpose, hipStream_t s);
 
 // ---- power-of-two three-pass path (birk_fast.hip) ----
 bool fast_eligible(int64_t N);

@@ -1,0 +1,295 @@
+// Products whose transforms fit one workgroup (gfx950): N <= 2048 a power of two, or any N
+// with 3N <= 4096.  One launch takes a pair of components from v to out: DCT-I, the
+// coefficient stencil with c^_0, DCT-I, all in LDS, so that a product reads v and writes
+// out once and a small product is one launch instead of five (Bluestein) to seven (pack,
+// transform, stencil, c^_0, transform, unpack).
+//
+// A DCT-I is half the DFT of the even extension, of length L = 2N (see birk_dct.hip): L a
+// power of two is transformed as it is, any other L by Bluestein's convolution in a
+// power-of-two length M >= 3N.  A thread holds eight elements n = tid + i blockDim of its
+// pairs' M-long buffers from the first load to the last store; the chirp (even, so its
+// N + 1 first values serve every n) and the filter spectrum are read once for both DCTs.
+//
+// What bounds it: at few pairs the chain of LDS stages behind barriers (four transforms of
+// four stages at M = 1024); with many pairs LDS bandwidth.  A pair of components per
+// workgroup (M / 8 threads) keeps the chain short and uses as many CUs as there are pairs;
+// plans whose largest M is below 512 put 512 / M pairs in one wave.  Measured per product,
+// six components in double, before (five to seven launches, or three passes from N = 512)
+// and after: N = 255 (M = 1024) 36.6 -> 16.5 us, 256 28.4 -> 11.2, 999 (M = 4096)
+// 36.1 -> 29.7, 1024 26.0 -> 15.2, 2048 29.8 -> 20.5; 192 components: N = 256
+// 46.2 -> 11.5 us, 2048 32.1 -> 21.
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "birk_fft.h"
+#include "birk_internal.h"
+#include "birk_mid.h"
+
+namespace birk {
+namespace {
+
+constexpr int kPPT = fast::kPPT;
+
+template <typename T, int LOGM>
+__device__ __forceinline__ void put(T* sm, int t, int n, cplx<T> v) {
+  constexpr int LD = fast::padded_ld(1 << LOGM);
+  sm[2 * t * LD + fast::pad(n)] = v.x;
+  sm[(2 * t + 1) * LD + fast::pad(n)] = v.y;
+}
+
+template <typename T, int LOGM>
+__device__ __forceinline__ cplx<T> get(const T* sm, int t, int n) {
+  constexpr int LD = fast::padded_ld(1 << LOGM);
+  return fast::mk<T>(sm[2 * t * LD + fast::pad(n)], sm[(2 * t + 1) * LD + fast::pad(n)]);
+}
+
+// The pairs [tile.x, tile.x + tile.y) of one length M = 2^LOGM; CHIRP: Bluestein.
+// sm: 8 blockDim complex values in split padded rows; red: the c^_0 partial sums.
+template <typename T, int LOGM, bool CHIRP>
+__device__ __forceinline__ void lds_product(const T* __restrict__ x, T* __restrict__ out,
+                                            const PairDesc* __restrict__ pd, int2 tile,
+                                            const cplx<T>* __restrict__ tw, int trans, T* sm, double* red) {
+  constexpr int pi = prec_index<T>();
+  constexpr int M = 1 << LOGM;
+  constexpr int G = M < 64 ? M : 64;   // lanes of a wave that share a pair
+  const int tid = (int)threadIdx.x, nthr = (int)blockDim.x;
+  // element i of the thread: entry n of pair t (wave-uniform from M = 64 on)
+  auto where = [&](int i, int& t, int& n) {
+    const int e = tid + i * nthr;
+    t = e >> LOGM;
+    if constexpr (LOGM >= 6) t = __builtin_amdgcn_readfirstlane(t);
+    n = e & (M - 1);
+  };
+  cplx<T> v[kPPT], fv[CHIRP ? kPPT : 1], cv[CHIRP ? kPPT : 1];
+#pragma unroll
+  for (int i = 0; i < kPPT; ++i) {
+    int t, n;
+    where(i, t, n);
+    v[i] = fast::mk<T>(T(0), T(0));
+    if constexpr (CHIRP) fv[i] = cv[i] = v[i];
+    if (t >= tile.y) continue;
+    const PairDesc& d = pd[tile.x + t];
+    const int N = (int)d.N, L = 2 * N;
+    if constexpr (CHIRP) fv[i] = ((const cplx<T>*)d.filt[pi])[n];
+    if (n >= L) continue;
+    const int k = n <= N ? n : L - n;
+    const T* xa = x + d.src;
+    T a = xa[k];
+    T b = d.has2 ? xa[d.Nn + k] : T(0);
+    if (trans && (k == 0 || k == N)) {
+      a = a + a;
+      b = b + b;
+    }
+    v[i] = fast::mk<T>(a, b);
+    if constexpr (CHIRP) cv[i] = ((const cplx<T>*)d.chirp[pi])[k];
+  }
+#pragma unroll 1
+  for (int dct = 0; dct < 2; ++dct) {
+#pragma unroll
+    for (int i = 0; i < kPPT; ++i) {
+      int t, n;
+      where(i, t, n);
+      if constexpr (CHIRP) v[i] = fast::cmul<T>(v[i], cv[i]);
+      put<T, LOGM>(sm, t, n, v[i]);
+    }
+    __syncthreads();
+    fast::fft_ct<T, LOGM, 0>(sm, tw);
+    if constexpr (CHIRP) {
+      // x filter, inverse transform as conj FFT conj, x chirp: Y_n, n <= N
+#pragma unroll
+      for (int i = 0; i < kPPT; ++i) {
+        int t, n;
+        where(i, t, n);
+        put<T, LOGM>(sm, t, n, fast::conjg<T>(fast::cmul<T>(get<T, LOGM>(sm, t, n), fv[i])));
+      }
+      __syncthreads();
+      fast::fft_ct<T, LOGM, 0>(sm, tw);
+#pragma unroll
+      for (int i = 0; i < kPPT; ++i) {
+        int t, n;
+        where(i, t, n);
+        put<T, LOGM>(sm, t, n, fast::cmul<T>(fast::conjg<T>(get<T, LOGM>(sm, t, n)), cv[i]));
+      }
+      __syncthreads();
+    }
+    if (dct == 1) break;
+    // stencil: the thread's inputs of the second DCT, and the c^_0 sums (each Y_k, k <= N,
+    // once) of G consecutive entries, whatever the workgroup's size: a pair's result does
+    // not depend on the pairs it is launched with
+#pragma unroll
+    for (int i = 0; i < kPPT; ++i) {
+      int t, n;
+      where(i, t, n);
+      v[i] = fast::mk<T>(T(0), T(0));
+      double s0 = 0.0, s1 = 0.0;
+      if (t < tile.y) {
+        const PairDesc& d = pd[tile.x + t];
+        const int N = (int)d.N, L = 2 * N;
+        if (n < L) {
+          const int k = n <= N ? n : L - n;
+          const cplx<T> Ym = get<T, LOGM>(sm, t, k > 0 ? k - 1 : 0);
+          const cplx<T> Yp = get<T, LOGM>(sm, t, k < N ? k + 1 : N);
+          if (trans) {
+            v[i] = mid_tr<T>(k, N, get<T, LOGM>(sm, t, 0), Ym, Yp, T(1) / T(2 * N + 2));
+          } else {
+            if (k > 0) v[i] = mid_fwd<T>(k, N, Ym, Yp, T(1) / T(N), T(1) / T(4 * N + 4));
+            if (n <= N) {
+              const cplx<T> Y = get<T, LOGM>(sm, t, n);
+              const double w = c0_weight(n, N);
+              s0 = w * (double)Y.x;
+              s1 = w * (double)Y.y;
+            }
+          }
+        }
+      }
+      if (!trans) {
+        if constexpr (G == 64) {
+          s0 = wave_sum_last(s0);
+          s1 = wave_sum_last(s1);
+        } else {
+#pragma unroll
+          for (int off = G / 2; off > 0; off >>= 1) {
+            s0 += __shfl_xor(s0, off, 64);
+            s1 += __shfl_xor(s1, off, 64);
+          }
+        }
+        if ((tid & (G - 1)) == G - 1) {
+          double* r = red + 2 * ((tid + i * nthr) / G);
+          r[0] = s0;
+          r[1] = s1;
+        }
+      }
+    }
+    __syncthreads();
+  }
+  // out = Y / 2 + c^_0, or e_j Y_j / N
+  constexpr int per = M / G;   // partial sums per pair, consecutive
+  T ca = T(0), cb = T(0);
+  int tc = -1;
+#pragma unroll
+  for (int i = 0; i < kPPT; ++i) {
+    int t, n;
+    where(i, t, n);
+    if (t >= tile.y) continue;
+    const PairDesc& d = pd[tile.x + t];
+    const int N = (int)d.N;
+    if (n > N) continue;
+    cplx<T> Y = get<T, LOGM>(sm, t, n);
+    if (trans) {
+      const T sc = ((n == 0 || n == N) ? T(0.5) : T(1)) / T(N);
+      Y.x = Y.x * sc;
+      Y.y = Y.y * sc;
+    } else {
+      if (t != tc) {
+        // four chains, so that the reads do not wait for the adds
+        constexpr int U = per < 4 ? per : 4;
+        double s0[U], s1[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) s0[u] = s1[u] = 0.0;
+        for (int q = 0; q < per; q += U) {
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            s0[u] += red[2 * (t * per + q + u)];
+            s1[u] += red[2 * (t * per + q + u) + 1];
+          }
+        }
+#pragma unroll
+        for (int u = 1; u < U; ++u) {
+          s0[0] += s0[u];
+          s1[0] += s1[u];
+        }
+        ca = (T)(s0[0] / (double)N);
+        cb = (T)(s1[0] / (double)N);
+        tc = t;
+      }
+      Y.x = T(0.5) * Y.x + ca;
+      Y.y = T(0.5) * Y.y + cb;
+    }
+    T* o = out + d.src;
+    o[n] = Y.x;
+    if (d.has2) o[d.Nn + n] = Y.y;
+  }
+}
+
+template <typename T, bool CHIRP>
+__global__ __launch_bounds__(kLdsMax / kPPT) void k_lds_product(const T* __restrict__ x, T* __restrict__ out,
+                                                               const PairDesc* __restrict__ pd,
+                                                               const int2* __restrict__ tiles,
+                                                               const cplx<T>* __restrict__ tw, int trans) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ double red[2 * kPPT * 64];
+  T* sm = reinterpret_cast<T*>(smem_raw);
+  const int2 tile = tiles[blockIdx.x];
+  switch (pd[tile.x].logM) {
+#define BIRK_LDS_CASE(LG) \
+  case LG: lds_product<T, LG, CHIRP>(x, out, pd, tile, tw, trans, sm, red); break;
+    BIRK_LDS_CASE(3)
+    BIRK_LDS_CASE(4)
+    BIRK_LDS_CASE(5)
+    BIRK_LDS_CASE(6)
+    BIRK_LDS_CASE(7)
+    BIRK_LDS_CASE(8)
+    BIRK_LDS_CASE(9)
+    BIRK_LDS_CASE(10)
+    BIRK_LDS_CASE(11)
+    BIRK_LDS_CASE(12)
+#undef BIRK_LDS_CASE
+    default: break;
+  }
+}
+
+// Reals of LDS for transforms of length 2^logM in a workgroup of nthr threads.
+int lds_reals(int logM, int nthr) { return 2 * ((kPPT * nthr) >> logM) * fast::padded_ld(1 << logM); }
+
+template <typename T, bool CHIRP>
+hipError_t launch(birk_plan* p, const LdsSet& ls, const T* v, T* out, int transpose, hipStream_t s) {
+  if (ls.ntiles == 0) return hipSuccess;
+  const auto f = k_lds_product<T, CHIRP>;
+  const int bytes = ls.lds_reals * (int)sizeof(T);
+  (void)hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  hipLaunchKernelGGL(f, dim3(ls.ntiles), dim3(ls.threads), bytes, s, v, out, ls.dev, ls.tiles,
+                     (const cplx<T>*)p->lds_tw[prec_index<T>()], transpose);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t finalize_lds(birk_plan* p, LdsSet& ls) {
+  if (ls.host.empty()) return hipSuccess;
+  std::stable_sort(ls.host.begin(), ls.host.end(), [](const PairDesc& a, const PairDesc& b) { return a.logM < b.logM; });
+  ls.threads = std::max(64, (1 << ls.host.back().logM) / kPPT);
+  ls.lds_reals = 0;
+  std::vector<int2> tiles;
+  const int np = (int)ls.host.size();
+  for (int q = 0; q < np;) {
+    const int logM = ls.host[q].logM;
+    const int per = (kPPT * ls.threads) >> logM;
+    int cnt = 1;
+    while (q + cnt < np && cnt < per && ls.host[q + cnt].logM == logM) ++cnt;
+    tiles.push_back(make_int2(q, cnt));
+    ls.lds_reals = std::max(ls.lds_reals, lds_reals(logM, ls.threads));
+    q += cnt;
+  }
+  ls.ntiles = (int)tiles.size();
+  void* d = nullptr;
+  hipError_t e = upload_raw(p, ls.host.data(), ls.host.size() * sizeof(PairDesc), &d);
+  ls.dev = (PairDesc*)d;
+  if (e == hipSuccess) e = upload_raw(p, tiles.data(), tiles.size() * sizeof(int2), &d);
+  ls.tiles = (int2*)d;
+  return e;
+}
+
+template <typename T>
+hipError_t product_lds(birk_plan* p, const T* v, T* out, int transpose, hipStream_t s) {
+  const hipError_t e = launch<T, false>(p, p->lds[0], v, out, transpose, s);
+  return e == hipSuccess ? launch<T, true>(p, p->lds[1], v, out, transpose, s) : e;
+}
+
+template hipError_t product_lds<double>(birk_plan*, const double*, double*, int, hipStream_t);
+template hipError_t product_lds<float>(birk_plan*, const float*, float*, int, hipStream_t);
+template hipError_t product_lds<df32>(birk_plan*, const df32*, df32*, int, hipStream_t);
+
+}  // namespace birk

@@ -1,0 +1,86 @@
+// The coefficient stencil between the two DCT-I of a product, on packed component pairs,
+// for kernels that form it from the DFT values Y_k of the even extension (C v = Y / 2).
+//
+// Forward (eq:c_k=bydef with the alias of eq:chatk=): d_k = (-1)^k c^_k / e_k from the
+// Chebyshev coefficients a_k = (-1)^k e_k Y_k / N.  d_0 = 0 here: c^_0 adds a constant to
+// every output, and is a weighted sum of Y (c0_weight).
+// Transpose: q = S M^T S p with p = Y / 2.
+
+#pragma once
+
+#include "birk_fft.h"
+
+namespace birk {
+
+// Reciprocal of a positive integer-valued x: in double the hardware estimate refined by two
+// Newton steps (within an ulp of 1/x, several times cheaper than a division); a plain
+// division for the other storage types.
+template <typename T>
+__device__ __forceinline__ T recip_int(T x) {
+  return T(1) / x;
+}
+template <>
+__device__ __forceinline__ double recip_int<double>(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  double e = __builtin_fma(-x, r, 1.0);
+  r = __builtin_fma(r, e, r);
+  e = __builtin_fma(-x, r, 1.0);
+  return __builtin_fma(r, e, r);
+}
+
+// d_k for 1 <= k <= N from Y_{k-1} and Y_{k+1} (Yp is not used at k = N):
+// invN = 1/N, inv4N1 = 1/(4 (N + 1)).
+template <typename T>
+__device__ __forceinline__ cplx<T> mid_fwd(int k, int N, cplx<T> Ym, cplx<T> Yp, T invN, T inv4N1) {
+  const T i2k = recip_int<T>(T(2 * k));   // 1/(2k); at k = 1 also e_0 = 1/2
+  T cp = T(0);
+  if (k < N) cp = (k + 1 == N) ? T(0.5) * i2k - inv4N1 : i2k;
+  const T sc = (k == N) ? T(2) * invN : invN;
+  return fast::mk<T>((cp * Yp.x - i2k * Ym.x) * sc, (cp * Yp.y - i2k * Ym.y) * sc);
+}
+
+// N times the weight of Y_k in c^_0.
+__device__ __forceinline__ double c0_weight(int k, int N) {
+  if (k == 0) return 0.5;
+  if (k == 1) return 0.25;
+  const double r = -recip_int<double>(((double)k - 1.0) * ((double)k + 1.0));
+  return k == N ? 0.5 * r : r;
+}
+
+// q_j for 0 <= j <= N from Y_0, Y_{j-1}, Y_{j+1} (Yp is not used at j = N
+// nor Ym at j <= 1): inv2N1 = 1/(2 (N + 1)).
+template <typename T>
+__device__ __forceinline__ cplx<T> mid_tr(int j, int N, cplx<T> Y0, cplx<T> Ym, cplx<T> Yp, T inv2N1) {
+  const T h = T(0.5);
+  if (j == 0) return fast::mk<T>(h * (Y0.x - Yp.x), h * (Y0.y - Yp.y));
+  if (j == 1) return fast::mk<T>(T(0.125) * (Y0.x - Yp.x), T(0.125) * (Y0.y - Yp.y));
+  const T rm = recip_int<T>(T(j - 1)), rp = recip_int<T>(T(j + 1));
+  T cm = h * rm, cp = h * rp;
+  if (j == N) {
+    cm -= inv2N1;
+    cp = T(0);
+  }
+  const T c0 = rm * rp;
+  return fast::mk<T>(h * (cm * Ym.x - cp * Yp.x - c0 * Y0.x), h * (cm * Ym.y - cp * Yp.y - c0 * Y0.y));
+}
+
+// Sum of v over the wave, in its last lane: row_shr 1, 2, 4, 8 (DPP controls 0x110 + n) sum
+// each row of 16, row_bcast 15 and 31 (0x142, 0x143) carry the rows' sums up; a lane
+// without a source adds zero.  VALU moves, no LDS permutes.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double add_dpp(double v) {
+  const unsigned long long x = __builtin_bit_cast(unsigned long long, v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, ROWS, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, ROWS, 0xF, false);
+  return v + __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double wave_sum_last(double v) {
+  v = add_dpp<0x111, 0xF>(v);
+  v = add_dpp<0x112, 0xF>(v);
+  v = add_dpp<0x114, 0xF>(v);
+  v = add_dpp<0x118, 0xF>(v);
+  v = add_dpp<0x142, 0xA>(v);
+  return add_dpp<0x143, 0xC>(v);
+}
+
+}  // namespace birk

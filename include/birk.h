@@ -118,12 +118,14 @@ int64_t birk_plan_length(const birk_plan* plan);
  * default schedule stays unless a candidate is more than 2 % faster; the choice stays
  * with the plan for every later product.  The schedule changes only the
  * order of floating-point operations (results stay within the product tolerance).
- * Then the general path (N not a power of two: DCT-I by Bluestein's chirp convolution): for each
- * chirp-convolution length M = 2^m above 4096 in the plan, the two-step FFTs M = M1 M2 are
- * timed (whole products, same rounds) with every split 2^7 <= M1 <= 2^12, 2^6 <= M2 <= 2^12,
- * one length at a time, and the fastest kept (default M1 = 2^ceil(m/2), again kept unless
- * beaten by 2 %); the filter spectra of that length are moved into the new order and the
- * tile lists rebuilt (re-allocated: the only allocations of the call).
+ * Then the general path (N not a power of two, 3N > 4096: DCT-I by even chirp convolutions
+ * of length M = 1, 3 or 5 times a power of two, M >= 4N): for each class of pairs whose 3N
+ * lies under the same power of two 2^m (reported as M=2^m), the two-step FFTs M = M1 M2 are
+ * timed (whole products, same rounds) with every split that keeps 2^6 <= M2 <= 2^12 at a
+ * nominal M1 of 2^7 to 2^12 (a pair's own M1 is that, 3/4 or 5/8 of it), one class at a time,
+ * and the fastest kept (the default split again stays unless beaten by 2 %); the filter
+ * spectra of that class are formed again in the new order and the tile lists rebuilt
+ * (re-allocated: the only allocations of the call).
  * Inputs are the plan's own scratch vectors.  Blocks until done.
  * report: optional host buffer (NULL, or report_len > 0) that receives a NUL-terminated
  * summary of every timing and choice, truncated to report_len - 1 characters.

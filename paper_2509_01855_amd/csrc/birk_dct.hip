@@ -14,22 +14,19 @@
 //
 // The DCT-I of a length-(N+1) vector x is half the DFT of its even extension of
 // length L = 2N.  Two real vectors are packed into one complex sequence (the DFT of a
-// real even sequence is real, so real and imaginary parts separate).  L a power of
-// two: radix-4/2 Stockham FFTs in LDS, four-step above the LDS limit.  Any other L:
-// Bluestein's chirp-z identity with a power-of-two FFT of length M >= N + L = 3N.  Only
-// the N + 1 outputs k = 0..N are needed, so the lags k - n of the convolution lie in
-// [-(L - 1), N]: the filter holds lags 0..N at the start and -1..-(L - 1) at the end of
-// the circular buffer, which do not meet once M >= N + L.
+// real even sequence is real, so real and imaginary parts separate).  Which path takes it:
+//   * transforms that fit one workgroup (N <= 2048 a power of two, any N with 3N <= 4096):
+//     one launch (birk_lds.hip);
+//   * N a larger power of two: the three passes of birk_fast.hip, or with BIRK_FAST=0 the
+//     plain four-step FFTs of this file;
+//   * any other N: chirp convolutions on even sequences (birk_blu.hip).
+// This file lays the pairs of every path out, builds the tables and tunes the last one.
 //
-// Products whose transforms fit one workgroup (N <= 2048 a power of two, any N with
-// 3N <= 4096) run in one launch (birk_lds.hip); the rest of this file covers the others.
-//
-// Batching: the pairs of all instances of one kind (plain power of two, or Bluestein)
-// form a PairSet.  Each phase of the product (pack, FFT passes, filter, stencil, c^_0,
-// unpack) is ONE launch over the whole set, whatever the mix of sizes: the grid is a
-// list of (pair, block) tiles built at plan creation, and every block reads its pair's
-// sizes, offsets and tables from a descriptor.  A product of a batch of uneven
-// instances is therefore a fixed number of launches (at most 14 per set).
+// Batching: the pairs of all instances of one kind form a set.  Each phase of the product
+// is ONE launch over the whole set, whatever the mix of sizes: the grid is a list of
+// (pair, block) tiles built at plan creation, and every block reads its pair's sizes,
+// offsets and tables from a descriptor.  A product of a batch of uneven instances is
+// therefore a fixed number of launches.
 
 #include <hip/hip_runtime.h>
 
@@ -44,6 +41,7 @@
 
 #include "birk_fft.h"
 #include "birk_internal.h"
+#include "birk_mid.h"
 
 namespace birk {
 
@@ -271,28 +269,16 @@ __global__ __launch_bounds__(256) void k_pack(const T* __restrict__ x, cplx<T>* 
   const PairDesc& d = pd[tile.x];
   const int64_t n = (int64_t)tile.y * blockDim.x + threadIdx.x;
   if (n >= d.M) return;
-  cplx<T> val = mk<T>(T(0), T(0));
-  if (n < d.L) {
-    const int64_t N = d.N;
-    const int64_t k = n <= N ? n : d.L - n;
-    const T* xa = x + d.src;
-    T a = xa[k];
-    T b = d.has2 ? xa[d.Nn + k] : T(0);
-    if (ends2 && (k == 0 || k == N)) {
-      a = a + a;
-      b = b + b;
-    }
-    val = mk<T>(a, b);
+  const int64_t N = d.N;
+  const int64_t k = n <= N ? n : d.L - n;
+  const T* xa = x + d.src;
+  T a = xa[k];
+  T b = d.has2 ? xa[d.Nn + k] : T(0);
+  if (ends2 && (k == 0 || k == N)) {
+    a = a + a;
+    b = b + b;
   }
-  z[d.work + n] = val;
-}
-
-// DFT value Y_k (k in [0, N]) of the even extension from the FFT output.
-template <typename T>
-__device__ __forceinline__ cplx<T> dft_value(const cplx<T>* __restrict__ z, const cplx<T>* __restrict__ chirp,
-                                             int64_t k) {
-  cplx<T> v = z[k];
-  return chirp ? cmul<T>(v, chirp[k]) : v;
+  z[d.work + n] = mk<T>(a, b);
 }
 
 // Forward mid stage.  From Y = DFT(even ext of v) (so C v = Y/2), form the Chebyshev
@@ -305,61 +291,25 @@ __device__ __forceinline__ cplx<T> dft_value(const cplx<T>* __restrict__ z, cons
 template <typename T>
 __global__ __launch_bounds__(256) void k_mid_fwd(const cplx<T>* __restrict__ z, cplx<T>* __restrict__ z2,
                                                  const PairDesc* __restrict__ pd, const int2* __restrict__ tiles,
-                                                 double* __restrict__ part, int compact) {
-  constexpr int pi = prec_index<T>();
+                                                 double* __restrict__ part) {
   const int2 tile = tiles[blockIdx.x];
   const PairDesc& d = pd[tile.x];
-  const int64_t N = d.N, L = d.L, M = d.M;
-  // compact: z holds Y_k (chirp applied) and d_k, k <= N, goes to z2 as is
-  const cplx<T>* chirp = compact ? nullptr : (const cplx<T>*)d.chirp[pi];
+  const int N = (int)d.N, L = (int)d.L;
   const cplx<T>* zz = z + d.work;
   cplx<T>* z2p = z2 + d.work;
-  const int64_t k = (int64_t)tile.y * blockDim.x + threadIdx.x;
+  const int k = tile.y * (int)blockDim.x + (int)threadIdx.x;
   double s0 = 0.0, s1 = 0.0;
   if (k <= N) {
-    const T invN = T(1) / T(N);
-    cplx<T> Yk = dft_value<T>(zz, chirp, k);
-    const T ek = (k == 0 || k == N) ? T(0.5) : T(1);
-    {
-      double c;
-      if (k == 0) c = 0.5;
-      else if (k == 1) c = 0.25;
-      else c = -(k == N ? 0.5 : 1.0) / ((double)k * (double)k - 1.0);
-      s0 = c * (double)Yk.x;
-      s1 = c * (double)Yk.y;
-    }
+    const cplx<T> Yk = zz[k];
+    const double c = c0_weight(k, N);
+    s0 = c * (double)Yk.x;
+    s1 = c * (double)Yk.y;
     if (k >= 1) {
-      // (-1)^k c^_k = -lo_k e_{k-1} Y_{k-1}/N - hi_k e_{k+1} Y_{k+1}/N - [k = N-1] Y_N / (4 N (N+1))
-      const T lo = (k == 1) ? T(1) : T(1) / (T(2) * T(k));
-      const T em1 = (k - 1 == 0) ? T(0.5) : T(1);
-      cplx<T> Ym = dft_value<T>(zz, chirp, k - 1);
-      T rx = -lo * em1 * Ym.x;
-      T ry = -lo * em1 * Ym.y;
-      if (k < N) {
-        const T hi = -T(1) / (T(2) * T(k));
-        const T ep1 = (k + 1 == N) ? T(0.5) : T(1);
-        cplx<T> Yp = dft_value<T>(zz, chirp, k + 1);
-        rx -= hi * ep1 * Yp.x;
-        ry -= hi * ep1 * Yp.y;
-      }
-      if (k == N - 1) {
-        cplx<T> YN = dft_value<T>(zz, chirp, N);
-        const T f = T(1) / (T(4) * T(N + 1));
-        rx -= f * YN.x;
-        ry -= f * YN.y;
-      }
-      const T sc = invN / ek;
-      cplx<T> dv = mk<T>(rx * sc, ry * sc);
-      z2p[k] = chirp ? cmul<T>(dv, chirp[k]) : dv;
-      if (k < N && !compact) {
-        const int64_t m = L - k;
-        z2p[m] = chirp ? cmul<T>(dv, chirp[m]) : dv;
-      }
+      const cplx<T> dv = mid_fwd<T>(k, N, zz[k - 1], zz[min(k + 1, N)], T(1) / T(N), T(1) / T(4 * (int64_t)N + 4));
+      z2p[k] = dv;
+      if (k < N) z2p[L - k] = dv;
     }
   }
-  // zero fill of the Bluestein padding [L, M)
-  if (!compact)
-    for (int64_t m = L + k; m < M; m += (int64_t)d.nblk * blockDim.x) z2p[m] = mk<T>(T(0), T(0));
   // block reduction of the c^_0 partials, fixed order
   __shared__ double r0[256], r1[256];
   r0[threadIdx.x] = s0;
@@ -401,7 +351,6 @@ __global__ __launch_bounds__(256) void k_c0(const double* __restrict__ part, cpl
   }
   if (threadIdx.x == 0) {
     const double s = 2.0 / (double)d.N;
-    // the Bluestein chirp is 1 at index 0, so no pre-multiplication is needed here
     z2[d.work] = mk<T>((T)(ra[0] * s), (T)(rb[0] * s));
   }
 }
@@ -411,48 +360,18 @@ __global__ __launch_bounds__(256) void k_c0(const double* __restrict__ part, cpl
 //   q_j = -p_0/(j^2-1) + p_{j-1} (1/(2(j-1)) - [j = N]/(2(N+1))) - [j < N] p_{j+1}/(2(j+1)).
 template <typename T>
 __global__ __launch_bounds__(256) void k_mid_tr(const cplx<T>* __restrict__ z, cplx<T>* __restrict__ z2,
-                                                const PairDesc* __restrict__ pd, const int2* __restrict__ tiles,
-                                                int compact) {
-  constexpr int pi = prec_index<T>();
+                                                const PairDesc* __restrict__ pd, const int2* __restrict__ tiles) {
   const int2 tile = tiles[blockIdx.x];
   const PairDesc& d = pd[tile.x];
-  const int64_t N = d.N, L = d.L, M = d.M;
-  const cplx<T>* chirp = compact ? nullptr : (const cplx<T>*)d.chirp[pi];
+  const int N = (int)d.N, L = (int)d.L;
   const cplx<T>* zz = z + d.work;
   cplx<T>* z2p = z2 + d.work;
-  const int64_t j = (int64_t)tile.y * blockDim.x + threadIdx.x;
-  if (j <= N) {
-    cplx<T> p0 = dft_value<T>(zz, chirp, 0);
-    p0.x *= T(0.5);
-    p0.y *= T(0.5);
-    cplx<T> q;
-    if (j == 0) {
-      cplx<T> p1 = dft_value<T>(zz, chirp, 1);
-      q = mk<T>(p0.x - T(0.5) * p1.x, p0.y - T(0.5) * p1.y);
-    } else if (j == 1) {
-      cplx<T> p2 = dft_value<T>(zz, chirp, 2);
-      q = mk<T>(T(0.25) * (p0.x - T(0.5) * p2.x), T(0.25) * (p0.y - T(0.5) * p2.y));
-    } else {
-      const T jj = T(j);
-      const T c0 = -T(1) / (jj * jj - T(1));
-      T cm = T(1) / (T(2) * (jj - T(1)));
-      if (j == N) cm -= T(1) / (T(2) * T(N + 1));
-      cplx<T> pm = dft_value<T>(zz, chirp, j - 1);
-      T qx = c0 * p0.x + cm * T(0.5) * pm.x;
-      T qy = c0 * p0.y + cm * T(0.5) * pm.y;
-      if (j < N) {
-        const T cp = -T(1) / (T(2) * (jj + T(1)));
-        cplx<T> pp = dft_value<T>(zz, chirp, j + 1);
-        qx += cp * T(0.5) * pp.x;
-        qy += cp * T(0.5) * pp.y;
-      }
-      q = mk<T>(qx, qy);
-    }
-    z2p[j] = chirp ? cmul<T>(q, chirp[j]) : q;
-    if (j >= 1 && j < N && !compact) z2p[L - j] = chirp ? cmul<T>(q, chirp[L - j]) : q;
-  }
-  if (!compact)
-    for (int64_t m = L + j; m < M; m += (int64_t)d.nblk * blockDim.x) z2p[m] = mk<T>(T(0), T(0));
+  const int j = tile.y * (int)blockDim.x + (int)threadIdx.x;
+  if (j > N) return;
+  const cplx<T> q =
+      mid_tr<T>(j, N, zz[0], zz[max(j - 1, 0)], zz[min(j + 1, N)], T(1) / T(2 * (int64_t)N + 2));
+  z2p[j] = q;
+  if (j >= 1 && j < N) z2p[L - j] = q;
 }
 
 // Final stage: out_j = scale_j * Y_j for j in [0, N], unpacking the pair.
@@ -460,14 +379,13 @@ __global__ __launch_bounds__(256) void k_mid_tr(const cplx<T>* __restrict__ z, c
 template <typename T>
 __global__ __launch_bounds__(256) void k_final(const cplx<T>* __restrict__ z, T* __restrict__ out,
                                                const PairDesc* __restrict__ pd, const int2* __restrict__ tiles,
-                                               int transpose, int compact) {
-  constexpr int pi = prec_index<T>();
+                                               int transpose) {
   const int2 tile = tiles[blockIdx.x];
   const PairDesc& d = pd[tile.x];
   const int64_t N = d.N;
   const int64_t j = (int64_t)tile.y * blockDim.x + threadIdx.x;
   if (j > N) return;
-  const cplx<T> Y = dft_value<T>(z + d.work, compact ? nullptr : (const cplx<T>*)d.chirp[pi], j);
+  const cplx<T> Y = z[d.work + j];
   T sc;
   if (transpose) sc = ((j == 0 || j == N) ? T(0.5) : T(1)) / T(N);
   else sc = T(0.5);
@@ -488,345 +406,14 @@ static hipError_t product_set(birk_plan* p, const PairSet& ps, const T* v, T* ou
   hipError_t e = fft_set<T>(p, ps, z, tmp, 0, s);
   if (e != hipSuccess) return e;
   if (!transpose) {
-    hipLaunchKernelGGL(k_mid_fwd<T>, dim3(ps.n_n), dim3(256), 0, s, z, z2, ps.dev, ps.tiles_n, p->partials, 0);
+    hipLaunchKernelGGL(k_mid_fwd<T>, dim3(ps.n_n), dim3(256), 0, s, z, z2, ps.dev, ps.tiles_n, p->partials);
     hipLaunchKernelGGL(k_c0<T>, dim3((unsigned)ps.host.size()), dim3(256), 0, s, p->partials, z2, ps.dev);
   } else {
-    hipLaunchKernelGGL(k_mid_tr<T>, dim3(ps.n_n), dim3(256), 0, s, z, z2, ps.dev, ps.tiles_n, 0);
+    hipLaunchKernelGGL(k_mid_tr<T>, dim3(ps.n_n), dim3(256), 0, s, z, z2, ps.dev, ps.tiles_n);
   }
   e = fft_set<T>(p, ps, z2, tmp, 0, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_final<T>, dim3(ps.n_n), dim3(256), 0, s, z2, out, ps.dev, ps.tiles_n, transpose, 0);
-  return hipGetLastError();
-}
-
-// ----------------------------------------------------------------- fused Bluestein path
-// For 2N not a power of two each DCT-I is a Bluestein convolution of the chirped even
-// extension (length L = 2N, padded to M).  The fused path runs it in three passes over M
-// (two-step FFTs above the LDS limit, one kernel below it) instead of pack, FFT, filter,
-// inverse FFT as separate passes:
-//   columns:  even extension x chirp, column FFTs (length M1), twiddle    -> tmp
-//   rows:     row FFTs (M2), x filter spectrum, inverse row FFTs, inverse twiddle
-//   icolumns: inverse column FFTs, x chirp, only the N + 1 outputs Y_k are stored.
-// The inverse two-step transform takes its factors in the reverse order of the forward
-// one, so the rows pass sees the forward spectrum of a row, multiplies it by the filter,
-// and transforms it straight back.  Inputs: the pair's two components (first DCT,
-// optionally with doubled end points) or the compact stencil output d_k (second DCT);
-// outputs Y_k, k <= N, with the chirp applied.
-
-// Padded Bluestein input at position n: (even extension of the source) x chirp_n.
-template <typename T>
-__device__ __forceinline__ cplx<T> blu_in(const PairDesc& d, const T* __restrict__ x, const cplx<T>* __restrict__ dz,
-                                         int src_x, int ends2, const cplx<T>* __restrict__ chirp, int64_t n) {
-  if (n >= d.L) return mk<T>(T(0), T(0));
-  const int64_t k = n <= d.N ? n : d.L - n;
-  cplx<T> v;
-  if (src_x) {
-    const T* xa = x + d.src;
-    T a = xa[k];
-    T b = d.has2 ? xa[d.Nn + k] : T(0);
-    if (ends2 && (k == 0 || k == d.N)) {
-      a = a + a;
-      b = b + b;
-    }
-    v = mk<T>(a, b);
-  } else {
-    v = dz[d.work + k];
-  }
-  return cmul<T>(v, chirp[n]);
-}
-
-// ---- fused Bluestein passes on the compile-time FFTs of birk_fft.h ----
-// A block of kBluThreads threads transforms kLdsMax points: kLdsMax / 2^LOGL transforms
-// of length 2^LOGL in the split layout of fast::fft_ct (transform t: real parts in row
-// 2t, imaginary parts in row 2t + 1, rows padded_ld(2^LOGL) reals apart).  A pair's
-// length is known only at run time, so each kernel switches to the body compiled for
-// it.  The inverse transform is conj(FFT(conj(.))), unnormalised (the filter spectrum
-// carries 1/M).
-constexpr int kBluThreads = kLdsMax / fast::kPPT;
-
-__host__ __device__ constexpr int blu_lds_reals(int logL) {
-  return 2 * (kLdsMax >> logL) * fast::padded_ld(1 << logL);
-}
-constexpr int blu_lds_reals_max() {
-  int m = 0;
-  for (int l = 3; l <= kLdsMaxLog; ++l) m = blu_lds_reals(l) > m ? blu_lds_reals(l) : m;
-  return m;
-}
-constexpr int kBluLdsReals = blu_lds_reals_max();
-
-template <typename T>
-__device__ __forceinline__ cplx<T> cconj(cplx<T> a) {
-  return mk<T>(a.x, -a.y);
-}
-
-template <typename T, int LOGL>
-__device__ __forceinline__ void sput(T* sm, int t, int n, cplx<T> v) {
-  constexpr int LD = fast::padded_ld(1 << LOGL);
-  sm[2 * t * LD + fast::pad(n)] = v.x;
-  sm[(2 * t + 1) * LD + fast::pad(n)] = v.y;
-}
-
-template <typename T, int LOGL>
-__device__ __forceinline__ cplx<T> sget(const T* sm, int t, int n) {
-  constexpr int LD = fast::padded_ld(1 << LOGL);
-  return mk<T>(sm[2 * t * LD + fast::pad(n)], sm[(2 * t + 1) * LD + fast::pad(n)]);
-}
-
-#define BIRK_LOG_SWITCH(val, LO, CALL)                                         \
-  switch (val) {                                                               \
-    case 3: if constexpr (3 >= LO) { constexpr int LG = 3; CALL; } break;      \
-    case 4: if constexpr (4 >= LO) { constexpr int LG = 4; CALL; } break;      \
-    case 5: if constexpr (5 >= LO) { constexpr int LG = 5; CALL; } break;      \
-    case 6: if constexpr (6 >= LO) { constexpr int LG = 6; CALL; } break;      \
-    case 7: { constexpr int LG = 7; CALL; } break;                             \
-    case 8: { constexpr int LG = 8; CALL; } break;                             \
-    case 9: { constexpr int LG = 9; CALL; } break;                             \
-    case 10: { constexpr int LG = 10; CALL; } break;                           \
-    case 11: { constexpr int LG = 11; CALL; } break;                           \
-    case 12: { constexpr int LG = 12; CALL; } break;                           \
-    default: break;                                                            \
-  }
-
-// Columns pass: n = M2 n1 + n2; the W = kLdsMax / M1 columns [c0, c0 + W) of the padded
-// input, FFT over n1, twiddle W_M^(n2 k1), tmp[k1 M2 + n2].  tile = (pair, column block).
-template <typename T, int LOGM1>
-__device__ __forceinline__ void blu_cols_body(const T* __restrict__ x, const cplx<T>* __restrict__ dz,
-                                              cplx<T>* __restrict__ tmp, const PairDesc& d, int ty,
-                                              const cplx<T>* __restrict__ tw, int src_x, int ends2, T* sm) {
-  constexpr int pi = prec_index<T>();
-  constexpr int LOGW = kLdsMaxLog - LOGM1;
-  constexpr int W = 1 << LOGW;
-  const int logM2 = d.logM2;
-  const int c0 = ty << LOGW;
-  const cplx<T>* chirp = (const cplx<T>*)d.chirp[pi];
-  const cplx<T>* thi = (const cplx<T>*)d.thi[pi];
-  const cplx<T>* tlo = (const cplx<T>*)d.tlo[pi];
-  cplx<T>* ts = tmp + d.work;
-  if constexpr (std::is_floating_point<T>::value) {
-    // double and float: a thread's outputs k1 = k1_0 + i s (s = blockDim / W) share the
-    // column n2, so their twiddles W_M^(n2 k1) are W_M^(n2 k1_0) times powers of W_M^(n2 s):
-    // two reads of the double table issued with the inputs, the powers formed in double
-    // (at most seven rounded products per twiddle)
-    constexpr int PER = kLdsMax / kBluThreads;
-    constexpr int S = kBluThreads >> LOGW;
-    const int w = (int)threadIdx.x & (W - 1), k10 = (int)threadIdx.x >> LOGW;
-    const int n2 = c0 + w;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int n1 = k10 + i * S;
-      sput<T, LOGM1>(sm, w, n1, blu_in<T>(d, x, dz, src_x, ends2, chirp, ((int64_t)n1 << logM2) + n2));
-    }
-    const cplx<double>* thd = (const cplx<double>*)d.thi[0];
-    const cplx<double>* tld = (const cplx<double>*)d.tlo[0];
-    cplx<double> wv = tw4<double>(thd, tld, d.tw_shift, (int64_t)n2 * k10, 0);
-    const cplx<double> ws = tw4<double>(thd, tld, d.tw_shift, (int64_t)n2 * S, 0);
-    __syncthreads();
-    fast::fft_ct<T, LOGM1, W>(sm, tw);
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int k1 = k10 + i * S;
-      ts[((int64_t)k1 << logM2) + n2] = cmul<T>(sget<T, LOGM1>(sm, w, k1), mk<T>((T)wv.x, (T)wv.y));
-      wv = cmul<double>(wv, ws);
-    }
-  } else {
-    for (int e = threadIdx.x; e < kLdsMax; e += kBluThreads) {
-      const int w = e & (W - 1), n1 = e >> LOGW;
-      sput<T, LOGM1>(sm, w, n1, blu_in<T>(d, x, dz, src_x, ends2, chirp, ((int64_t)n1 << logM2) + c0 + w));
-    }
-    __syncthreads();
-    fast::fft_ct<T, LOGM1, W>(sm, tw);
-    for (int e = threadIdx.x; e < kLdsMax; e += kBluThreads) {
-      const int w = e & (W - 1), k1 = e >> LOGW;
-      const int64_t t = (int64_t)(c0 + w) * k1;
-      ts[((int64_t)k1 << logM2) + c0 + w] = cmul<T>(sget<T, LOGM1>(sm, w, k1), tw4<T>(thi, tlo, d.tw_shift, t, 0));
-    }
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBluThreads) void k_blu_cols(const T* __restrict__ x, const cplx<T>* __restrict__ dz,
-                                                         cplx<T>* __restrict__ tmp, const PairDesc* __restrict__ pd,
-                                                         const int2* __restrict__ tiles,
-                                                         const cplx<T>* __restrict__ tw, int src_x, int ends2) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  T* sm = reinterpret_cast<T*>(smem_raw);
-  const int2 tile = tiles[blockIdx.x];
-  const PairDesc& d = pd[tile.x];
-  BIRK_LOG_SWITCH(d.logM1, 7, (blu_cols_body<T, LG>(x, dz, tmp, d, tile.y, tw, src_x, ends2, sm)))
-}
-
-// Rows pass: the W = kLdsMax / M2 rows k1 in [r0, r0 + W) of tmp; FFT over n2 (frequency
-// k2 of k = k1 + M1 k2), times the filter spectrum (stored in this order), inverse FFT
-// back to n2, times W_M^(-n2 k1), in place.  tile = (pair, row block).
-template <typename T, int LOGM2>
-__device__ __forceinline__ void blu_rows_body(cplx<T>* __restrict__ tmp, const PairDesc& d, int ty,
-                                              const cplx<T>* __restrict__ tw, T* sm) {
-  constexpr int pi = prec_index<T>();
-  constexpr int M2 = 1 << LOGM2;
-  constexpr int LOGW = kLdsMaxLog - LOGM2;
-  constexpr int W = 1 << LOGW;
-  const int r0 = ty << LOGW;
-  cplx<T>* ts = tmp + d.work + ((int64_t)r0 << LOGM2);
-  const cplx<T>* filt = (const cplx<T>*)d.filt[pi] + ((int64_t)r0 << LOGM2);
-  constexpr int PER = kLdsMax / kBluThreads;
-  // the tile and its filter spectrum are read in one batch
-  cplx<T> v[PER], fv[PER];
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = (int)threadIdx.x + i * kBluThreads;
-    v[i] = ts[e];
-    fv[i] = filt[e];
-  }
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = (int)threadIdx.x + i * kBluThreads;
-    sput<T, LOGM2>(sm, e >> LOGM2, e & (M2 - 1), v[i]);
-  }
-  __syncthreads();
-  fast::fft_ct<T, LOGM2, W>(sm, tw);
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = (int)threadIdx.x + i * kBluThreads;
-    const int w = e >> LOGM2, k2 = e & (M2 - 1);
-    sput<T, LOGM2>(sm, w, k2, cconj<T>(cmul<T>(sget<T, LOGM2>(sm, w, k2), fv[i])));
-  }
-  __syncthreads();
-  const cplx<T>* thi = (const cplx<T>*)d.thi[pi];
-  const cplx<T>* tlo = (const cplx<T>*)d.tlo[pi];
-  if constexpr (std::is_floating_point<T>::value && LOGM2 <= 9) {
-    // double and float, rows of at most blockDim points: a thread's elements share n2 and
-    // step through rows w = w_0 + i s, so their twiddles W_M^(-n2 (r0 + w)) are powers of
-    // one step times a base (double table, read before the second transform; powers in
-    // double)
-    constexpr int S = kBluThreads >> LOGM2;
-    const int n2 = (int)threadIdx.x & (M2 - 1), w0 = (int)threadIdx.x >> LOGM2;
-    const cplx<double>* thd = (const cplx<double>*)d.thi[0];
-    const cplx<double>* tld = (const cplx<double>*)d.tlo[0];
-    cplx<double> wv = tw4<double>(thd, tld, d.tw_shift, (int64_t)n2 * (r0 + w0), 1);
-    const cplx<double> ws = tw4<double>(thd, tld, d.tw_shift, (int64_t)n2 * S, 1);
-    fast::fft_ct<T, LOGM2, W>(sm, tw);
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int w = w0 + i * S;
-      ts[(w << LOGM2) + n2] = cmul<T>(cconj<T>(sget<T, LOGM2>(sm, w, n2)), mk<T>((T)wv.x, (T)wv.y));
-      wv = cmul<double>(wv, ws);
-    }
-  } else {
-    fast::fft_ct<T, LOGM2, W>(sm, tw);
-    for (int e = threadIdx.x; e < kLdsMax; e += kBluThreads) {
-      const int w = e >> LOGM2, n2 = e & (M2 - 1);
-      ts[e] = cmul<T>(cconj<T>(sget<T, LOGM2>(sm, w, n2)), tw4<T>(thi, tlo, d.tw_shift, (int64_t)n2 * (r0 + w), 1));
-    }
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBluThreads) void k_blu_rows(cplx<T>* __restrict__ tmp, const PairDesc* __restrict__ pd,
-                                                         const int2* __restrict__ tiles,
-                                                         const cplx<T>* __restrict__ tw) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  T* sm = reinterpret_cast<T*>(smem_raw);
-  const int2 tile = tiles[blockIdx.x];
-  const PairDesc& d = pd[tile.x];
-  BIRK_LOG_SWITCH(d.logM2, 6, (blu_rows_body<T, LG>(tmp, d, tile.y, tw, sm)))
-}
-
-// Inverse columns pass: columns n2 in [c0, c0 + W) of tmp[k1 M2 + n2], inverse FFT over
-// k1 -> n1, output index n = M2 n1 + n2; Y_n = value x chirp_n for n <= N.
-// tile = (pair, column block).
-template <typename T, int LOGM1>
-__device__ __forceinline__ void blu_icols_body(const cplx<T>* __restrict__ tmp, cplx<T>* __restrict__ Y,
-                                               const PairDesc& d, int ty, const cplx<T>* __restrict__ tw, T* sm) {
-  constexpr int pi = prec_index<T>();
-  constexpr int LOGW = kLdsMaxLog - LOGM1;
-  constexpr int W = 1 << LOGW;
-  const int logM2 = d.logM2;
-  const int c0 = ty << LOGW;
-  const cplx<T>* ts = tmp + d.work;
-  const cplx<T>* chirp = (const cplx<T>*)d.chirp[pi];
-  constexpr int PER = kLdsMax / kBluThreads;
-  // the tile and the chirp of its outputs n = M2 n1 + n2 <= N are read in one batch
-  cplx<T> v[PER], cv[PER];
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = (int)threadIdx.x + i * kBluThreads;
-    const int w = e & (W - 1), k = e >> LOGW;
-    const int64_t idx = ((int64_t)k << logM2) + c0 + w;
-    v[i] = ts[idx];
-    cv[i] = idx <= d.N ? chirp[idx] : mk<T>(T(0), T(0));
-  }
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = (int)threadIdx.x + i * kBluThreads;
-    sput<T, LOGM1>(sm, e & (W - 1), e >> LOGW, cconj<T>(v[i]));
-  }
-  __syncthreads();
-  fast::fft_ct<T, LOGM1, W>(sm, tw);
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = (int)threadIdx.x + i * kBluThreads;
-    const int w = e & (W - 1), n1 = e >> LOGW;
-    const int64_t idx = ((int64_t)n1 << logM2) + c0 + w;
-    if (idx <= d.N) Y[d.work + idx] = cmul<T>(cconj<T>(sget<T, LOGM1>(sm, w, n1)), cv[i]);
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBluThreads) void k_blu_icols(const cplx<T>* __restrict__ tmp, cplx<T>* __restrict__ Y,
-                                                          const PairDesc* __restrict__ pd,
-                                                          const int2* __restrict__ tiles,
-                                                          const cplx<T>* __restrict__ tw) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  T* sm = reinterpret_cast<T*>(smem_raw);
-  const int2 tile = tiles[blockIdx.x];
-  const PairDesc& d = pd[tile.x];
-  BIRK_LOG_SWITCH(d.logM1, 7, (blu_icols_body<T, LG>(tmp, Y, d, tile.y, tw, sm)))
-}
-
-#undef BIRK_LOG_SWITCH
-
-// One DCT-I (= 2 C) of every pair of a Bluestein set by the fused passes; Y receives
-// Y_k, k <= N, at each pair's work offset.
-template <typename T>
-static hipError_t dct_blu(birk_plan* p, const PairSet& ps, const T* x, const cplx<T>* dz, cplx<T>* Y, int src_x,
-                          int ends2, hipStream_t s) {
-  const cplx<T>* tw = (const cplx<T>*)p->lds_tw[prec_index<T>()];
-  cplx<T>* tmp = (cplx<T>*)p->work[0];
-  const size_t lds = (size_t)kBluLdsReals * sizeof(T);
-  static const bool attr = [] {  // above the default dynamic LDS limit in double
-    constexpr int b = (int)(kBluLdsReals * sizeof(T));
-    (void)hipFuncSetAttribute((const void*)k_blu_cols<T>, hipFuncAttributeMaxDynamicSharedMemorySize, b);
-    (void)hipFuncSetAttribute((const void*)k_blu_rows<T>, hipFuncAttributeMaxDynamicSharedMemorySize, b);
-    (void)hipFuncSetAttribute((const void*)k_blu_icols<T>, hipFuncAttributeMaxDynamicSharedMemorySize, b);
-    return true;
-  }();
-  (void)attr;
-  if (ps.n_c4 > 0) {
-    hipLaunchKernelGGL(k_blu_cols<T>, dim3(ps.n_c4), dim3(kBluThreads), lds, s, x, dz, tmp, ps.dev, ps.tiles_c4, tw,
-                       src_x, ends2);
-    hipLaunchKernelGGL(k_blu_rows<T>, dim3(ps.n_r4), dim3(kBluThreads), lds, s, tmp, ps.dev, ps.tiles_r4, tw);
-    hipLaunchKernelGGL(k_blu_icols<T>, dim3(ps.n_c4), dim3(kBluThreads), lds, s, tmp, Y, ps.dev, ps.tiles_c4, tw);
-  }
-  return hipGetLastError();
-}
-
-// Product over a Bluestein set: DCT (fused) -> stencil and c^_0 -> DCT (fused) -> unpack.
-template <typename T>
-static hipError_t product_blu(birk_plan* p, const PairSet& ps, const T* v, T* out, int transpose, hipStream_t s) {
-  if (ps.host.empty()) return hipSuccess;
-  cplx<T>* Y = (cplx<T>*)p->work[1];
-  cplx<T>* dz = (cplx<T>*)p->work[2];
-  hipError_t e = dct_blu<T>(p, ps, v, nullptr, Y, 1, transpose, s);
-  if (e != hipSuccess) return e;
-  if (!transpose) {
-    hipLaunchKernelGGL(k_mid_fwd<T>, dim3(ps.n_n), dim3(256), 0, s, Y, dz, ps.dev, ps.tiles_n, p->partials, 1);
-    hipLaunchKernelGGL(k_c0<T>, dim3((unsigned)ps.host.size()), dim3(256), 0, s, p->partials, dz, ps.dev);
-  } else {
-    hipLaunchKernelGGL(k_mid_tr<T>, dim3(ps.n_n), dim3(256), 0, s, Y, dz, ps.dev, ps.tiles_n, 1);
-  }
-  e = dct_blu<T>(p, ps, nullptr, dz, Y, 0, 0, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_final<T>, dim3(ps.n_n), dim3(256), 0, s, Y, out, ps.dev, ps.tiles_n, transpose, 1);
+  hipLaunchKernelGGL(k_final<T>, dim3(ps.n_n), dim3(256), 0, s, z2, out, ps.dev, ps.tiles_n, transpose);
   return hipGetLastError();
 }
 
@@ -891,55 +478,38 @@ static hipError_t upload_cplx(birk_plan* p, const std::vector<double>& re, const
   return e;
 }
 
-// One table in all three precisions.
+// One table in double and in the plan's own precision.
 static hipError_t upload_all(birk_plan* p, const std::vector<double>& re, const std::vector<double>& im,
                              const void** dst) {
   hipError_t e = upload_cplx<double>(p, re, im, &dst[0]);
-  if (e == hipSuccess) e = upload_cplx<float>(p, re, im, &dst[1]);
-  if (e == hipSuccess) e = upload_cplx<df32>(p, re, im, &dst[2]);
+  if (e == hipSuccess && (p->prec == BIRK_F32 || p->prec == BIRK_F32_REFINE_F64))
+    e = upload_cplx<float>(p, re, im, &dst[1]);
+  if (e == hipSuccess && p->prec == BIRK_DF32) e = upload_cplx<df32>(p, re, im, &dst[2]);
   return e;
 }
 
-// Bluestein filter b_m = conj(chirp_|lag|) on the circular buffer of length M: lags
-// 0..N at m = lag, lags -1..-(L - 1) at m = M + lag, zero between.
+// Filter of the one-workgroup convolutions (length M >= 3N, see birk_lds.hip): conj(chirp)
+// at lags 0..N at m = lag, lags -1..-(L - 1) at m = M + lag, zero between; the chirp has
+// period L and is even, so its first N + 1 values give every lag.
 template <typename T>
 __global__ void k_build_filter(cplx<T>* __restrict__ b, const cplx<T>* __restrict__ chirp, int64_t L,
                                int64_t M) {
   const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= M) return;
   cplx<T> v = mk<T>(T(0), T(0));
-  if (m <= L / 2) {
-    v = chirp[m];
-    v.y = -v.y;
-  } else if (M - m < L) {
-    v = chirp[M - m];
+  const int64_t lag = m <= L / 2 ? m : M - m;
+  if (lag < L) {
+    v = chirp[lag <= L / 2 ? lag : L - lag];
     v.y = -v.y;
   }
   b[m] = v;
 }
 
-// dst = s src; with logM1 > 0 in the order of the two-step rows pass: dst[k1 M2 + k2] =
-// s src[k1 + M1 k2] (frequency k = k1 + M1 k2), so each row reads its filter contiguously.
+// dst = s src
 template <typename T>
-__global__ void k_scale_to(const cplx<double>* __restrict__ src, cplx<T>* __restrict__ dst, int64_t M,
-                           double s, int logM1, int logM2) {
+__global__ void k_scale_to(const cplx<double>* __restrict__ src, cplx<T>* __restrict__ dst, int64_t M, double s) {
   const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= M) return;
-  int64_t from = m;
-  if (logM1 > 0) from = (m >> logM2) + ((m & ((int64_t(1) << logM2) - 1)) << logM1);
-  dst[m] = mk<T>((T)(src[from].x * s), (T)(src[from].y * s));
-}
-
-// Filter spectrum moved from the rows-pass order of the split (a1, a2) of M to that of
-// (b1, b2): dst[k1 M2' + k2] = src at the position of frequency k1 + M1' k2 in the old order.
-template <typename T>
-__global__ void k_relayout(const cplx<T>* __restrict__ src, cplx<T>* __restrict__ dst, int64_t M, int a1, int a2,
-                           int b1, int b2) {
-  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= M) return;
-  const int64_t q = (m >> b2) + ((m & ((int64_t(1) << b2) - 1)) << b1);     // frequency
-  const int64_t from = ((q & ((int64_t(1) << a1) - 1)) << a2) + (q >> a1);  // its old position
-  dst[m] = src[from];
+  if (m < M) dst[m] = mk<T>((T)(src[m].x * s), (T)(src[m].y * s));
 }
 
 static int ilog2_ceil(int64_t x) {
@@ -948,7 +518,10 @@ static int ilog2_ceil(int64_t x) {
   return l;
 }
 
-static PairDesc make_pair(int64_t src, int64_t Nn, int has2, const int* split) {
+// Twiddle tables of length M (1, 3 or 5 times a power of two): W^t = hi[t >> shift] lo[...].
+static int tw_shift_of(int64_t M) { return std::min((ilog2_ceil(M) + 1) / 2, __builtin_ctzll(M)); }
+
+static PairDesc make_pair(int64_t src, int64_t Nn, int has2) {
   PairDesc d;
   d.src = src;
   d.Nn = Nn;
@@ -957,11 +530,18 @@ static PairDesc make_pair(int64_t src, int64_t Nn, int has2, const int* split) {
   const bool pow2 = (d.L & (d.L - 1)) == 0 && d.L >= 8;   // the shortest compiled transform
   d.M = pow2 ? d.L : (int64_t(1) << ilog2_ceil(d.N + d.L));
   d.logM = ilog2_ceil(d.M);
+  d.slot = d.L == 4 ? 4 : d.M;
+  d.cls = d.logM;
   if (d.logM > kLdsMaxLog) {
-    d.logM1 = (split && split[d.logM] > 0) ? split[d.logM] : (d.logM + 1) / 2;
-    d.logM2 = d.logM - d.logM1;
+    if (pow2) {
+      d.logM1 = (d.logM + 1) / 2;
+      d.logM2 = d.logM - d.logM1;
+    } else {
+      blu_length(d);
+      blu_set_split(d, blu_default_split(d));
+    }
+    d.tw_shift = tw_shift_of(d.M);
   }
-  d.tw_shift = (d.logM + 1) / 2;
   d.has2 = has2;
   d.nblk = (int)((Nn + 255) / 256);
   return d;
@@ -975,8 +555,8 @@ static void layout_set(PairSet& ps, int64_t& woff, int64_t& poff) {
   ps.parts = 0;
   for (PairDesc& d : ps.host) {
     d.work = woff;
-    woff += d.M;
-    ps.work += d.M;
+    woff += d.slot;
+    ps.work += d.slot;
     d.part = poff;
     poff += 2 * (int64_t)d.nblk;
     ps.parts += 2 * (int64_t)d.nblk;
@@ -1017,7 +597,7 @@ void plan_products(birk_plan* p) {
         for (; i < j; ++i)
           for (int q = 0; q < (p->inst[i].nx + 1) / 2; ++q)
             p->lds[0].host.push_back(make_pair(p->inst[i].off + 2 * (int64_t)q * in.Nn, in.Nn,
-                                               2 * q + 1 < p->inst[i].nx, p->blu_split));
+                                               2 * q + 1 < p->inst[i].nx));
         woff += fw;
         poff += fp;
         continue;
@@ -1032,17 +612,17 @@ void plan_products(birk_plan* p) {
     }
     const int np = (in.nx + 1) / 2;
     for (int q = 0; q < np; ++q) {
-      PairDesc d = make_pair(in.off + 2 * (int64_t)q * in.Nn, in.Nn, 2 * q + 1 < in.nx, p->blu_split);
-      const int chirp = d.L == d.M ? 0 : 1;
+      PairDesc d = make_pair(in.off + 2 * (int64_t)q * in.Nn, in.Nn, 2 * q + 1 < in.nx);
+      const int chirp = d.L == d.slot && d.L > 4 ? 0 : 1;
       p->noalloc_nbuf = 3;
-      if (d.logM > kLdsMaxLog) {
+      if (d.cls > kLdsMaxLog) {
         p->gen[chirp].host.push_back(d);
         continue;
       }
       // whole product in LDS: a work slot only for the filter's set-up at plan creation
       // (and in the plan's size)
       d.work = woff;
-      woff += d.L == 4 ? 4 : d.M;
+      woff += d.slot;
       poff += 2 * (int64_t)d.nblk;
       p->lds[chirp].host.push_back(d);
     }
@@ -1104,70 +684,31 @@ static hipError_t finalize_set(birk_plan* p, PairSet& ps) {
 }
 
 // ----------------------------------------------------------------- general-path tuner
-// Bluestein pairs with M above the LDS limit run their two-step FFTs with M = M1 M2; the
-// default M1 = 2^ceil(log2(M) / 2).  For each such size (2^logM) the tuner times the plan's
-// product with every split the compile-time kernels support (7 <= log2 M1 <= 12,
-// 6 <= log2 M2 <= 12), one size at a time with the others fixed, and keeps the fastest
-// (the current choice stays unless another is more than 2 % faster).  A change of split
-// moves the filter spectra of that size into the new rows-pass order and rebuilds the
-// four-step tile lists; the products change only in rounding order.
-
-// Split (log2 M1) of every pair of size 2^logM in the Bluestein set: descriptors,
-// filter tables (each distinct filter once) and the cols / rows tile lists.
-static hipError_t set_blu_split(birk_plan* p, int logM, int logM1, hipStream_t s) {
+// The chirp convolutions of birk_blu.hip run their two-step FFTs with M = M1 M2.  Pairs
+// whose 3N lies under the same power of two 2^m form a class (their M are 3/4, 1, 5/4 or
+// 3/2 times it) and share a nominal M1 = 2^x (a pair's own M1 is 2^x, 3/4 2^x or
+// 5/8 2^x).  For each class the tuner times the plan's product with every x the compiled
+// kernels support for all of its pairs, one class at a time with the others fixed, and
+// keeps the fastest (the current choice stays unless another is more than 2 % faster).  A
+// change of split rebuilds the class's filter spectra in the new rows-pass order and the
+// tile lists; the products change only in rounding order.
+static hipError_t set_blu_split(birk_plan* p, int cls, int x, hipStream_t s) {
   PairSet& ps = p->gen[1];
-  hipError_t e = hipSuccess;
-  std::vector<const void*> moved;
-  cplx<double>* tmp = (cplx<double>*)p->work[0];
+  hipError_t e = hipStreamSynchronize(s);   // the lists in use are freed
+  PairSet fs;
+  std::vector<int64_t> seen;
   for (PairDesc& d : ps.host) {
-    if (d.logM != logM || d.logM1 == logM1) continue;
-    const int a1 = d.logM1, a2 = d.logM2, b1 = logM1, b2 = logM - logM1;
-    if (std::find(moved.begin(), moved.end(), d.filt[0]) == moved.end()) {
-      moved.push_back(d.filt[0]);
-      const dim3 grid((unsigned)((d.M + 255) / 256));
-      // through work[0] (free between products), one precision at a time
-      hipLaunchKernelGGL(k_relayout<double>, grid, dim3(256), 0, s, (const cplx<double>*)d.filt[0], tmp, d.M, a1, a2,
-                         b1, b2);
-      e = hipMemcpyAsync((void*)d.filt[0], tmp, d.M * sizeof(cplx<double>), hipMemcpyDeviceToDevice, s);
-      hipLaunchKernelGGL(k_relayout<float>, grid, dim3(256), 0, s, (const cplx<float>*)d.filt[1], (cplx<float>*)tmp,
-                         d.M, a1, a2, b1, b2);
-      if (e == hipSuccess) e = hipMemcpyAsync((void*)d.filt[1], tmp, d.M * sizeof(cplx<float>), hipMemcpyDeviceToDevice, s);
-      hipLaunchKernelGGL(k_relayout<df32>, grid, dim3(256), 0, s, (const cplx<df32>*)d.filt[2], (cplx<df32>*)tmp,
-                         d.M, a1, a2, b1, b2);
-      if (e == hipSuccess) e = hipMemcpyAsync((void*)d.filt[2], tmp, d.M * sizeof(cplx<df32>), hipMemcpyDeviceToDevice, s);
-      if (e != hipSuccess) return e;
-    }
-    d.logM1 = b1;
-    d.logM2 = b2;
+    if (d.cls != cls) continue;
+    blu_set_split(d, x);
+    if (std::find(seen.begin(), seen.end(), d.N) != seen.end()) continue;
+    seen.push_back(d.N);
+    fs.host.push_back(d);
   }
-  p->blu_split[logM] = logM1;
-  // descriptors in place; cols / rows tile lists rebuilt (their lengths depend on the split)
-  e = hipMemcpyAsync(ps.dev, ps.host.data(), ps.host.size() * sizeof(PairDesc), hipMemcpyHostToDevice, s);
-  std::vector<int2> tc, tr;
-  for (int q = 0; q < (int)ps.host.size(); ++q) {
-    const PairDesc& d = ps.host[q];
-    if (d.logM <= kLdsMaxLog) continue;
-    const int logW1 = std::min(kLdsMaxLog - d.logM1, d.logM2);
-    const int logW2 = std::min(kLdsMaxLog - d.logM2, d.logM1);
-    for (int b = 0; b < (1 << (d.logM2 - logW1)); ++b) tc.push_back(make_int2(q, b));
-    for (int b = 0; b < (1 << (d.logM1 - logW2)); ++b) tr.push_back(make_int2(q, b));
-  }
-  auto replace = [&](const std::vector<int2>& v, int2** dst, int* cnt) {
-    if (e != hipSuccess) return;
-    if (*dst) {
-      e = hipStreamSynchronize(s);
-      auto it = std::find(p->allocs.begin(), p->allocs.end(), (void*)*dst);
-      if (it != p->allocs.end()) p->allocs.erase(it);
-      if (e == hipSuccess) e = hipFree(*dst);
-    }
-    void* x = nullptr;
-    if (e == hipSuccess) e = upload_raw(p, v.data(), v.size() * sizeof(int2), &x);
-    *dst = (int2*)x;
-    *cnt = (int)v.size();
-  };
-  replace(tc, &ps.tiles_c4, &ps.n_c4);
-  replace(tr, &ps.tiles_r4, &ps.n_r4);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  blu_free_lists(p, ps);
+  if (e == hipSuccess) e = blu_lists(p, fs);
+  if (e == hipSuccess) e = blu_filters(p, fs, s);
+  blu_free_lists(p, fs);
+  if (e == hipSuccess) e = blu_lists(p, ps);
   return e;
 }
 
@@ -1175,7 +716,7 @@ template <typename T>
 static hipError_t tune_general_t(birk_plan* p, hipStream_t s, std::string* report) {
   std::vector<int> sizes;
   for (const PairDesc& d : p->gen[1].host)
-    if (d.logM > kLdsMaxLog && std::find(sizes.begin(), sizes.end(), d.logM) == sizes.end()) sizes.push_back(d.logM);
+    if (std::find(sizes.begin(), sizes.end(), d.cls) == sizes.end()) sizes.push_back(d.cls);
   if (sizes.empty()) {
     *report += "general path: no Bluestein sizes above the LDS limit\n";
     return hipSuccess;
@@ -1204,30 +745,32 @@ static hipError_t tune_general_t(birk_plan* p, hipStream_t s, std::string* repor
   };
   std::sort(sizes.begin(), sizes.end());
   char line[160];
-  for (int logM : sizes) {
+  for (int cls : sizes) {
     if (e != hipSuccess) break;
-    int cur = 0;
+    const PairDesc* member = nullptr;
     for (const PairDesc& d : p->gen[1].host)
-      if (d.logM == logM) cur = d.logM1;
+      if (d.cls == cls) member = &d;
+    const int cur = blu_split(*member);
     float best_ms = 0.0f;
     if ((e = time_product(&best_ms)) != hipSuccess) break;
-    snprintf(line, sizeof line, "general path M=2^%d: [M1 2^%d] %.1f us;", logM, cur, 1000.0 * best_ms);
+    snprintf(line, sizeof line, "general path M=2^%d: [M1 2^%d] %.1f us;", cls, cur, 1000.0 * best_ms);
     *report += line;
     int best = cur;
-    const int lo = std::max(7, logM - kLdsMaxLog), hi = std::min(kLdsMaxLog, logM - 6);
-    for (int l1 = lo; l1 <= hi && e == hipSuccess; ++l1) {
-      if (l1 == cur) continue;
-      if ((e = set_blu_split(p, logM, l1, s)) != hipSuccess) break;
+    for (int x = 7; x <= kLdsMaxLog && e == hipSuccess; ++x) {
+      bool ok = x != cur;
+      for (const PairDesc& d : p->gen[1].host) ok = ok && (d.cls != cls || blu_split_ok(d, x));
+      if (!ok) continue;
+      if ((e = set_blu_split(p, cls, x, s)) != hipSuccess) break;
       float ms = 0.0f;
       if ((e = time_product(&ms)) != hipSuccess) break;
-      snprintf(line, sizeof line, " [M1 2^%d] %.1f us;", l1, 1000.0 * ms);
+      snprintf(line, sizeof line, " [M1 2^%d] %.1f us;", x, 1000.0 * ms);
       *report += line;
       if (ms < best_ms * (1.0f - 0.02f)) {
         best_ms = ms;
-        best = l1;
+        best = x;
       }
     }
-    if (e == hipSuccess) e = set_blu_split(p, logM, best, s);
+    if (e == hipSuccess) e = set_blu_split(p, cls, best, s);
     snprintf(line, sizeof line, " chosen [M1 2^%d]\n", best);
     *report += line;
   }
@@ -1258,8 +801,7 @@ hipError_t build_tables(birk_plan* p) {
       return hipSuccess;
     }
     TwiddleSet ts;
-    const int logM = ilog2_ceil(M);
-    ts.shift = (logM + 1) / 2;
+    ts.shift = tw_shift_of(M);
     const int64_t nlo = (int64_t)1 << ts.shift, nhi = M >> ts.shift;
     std::vector<double> re(nlo), im(nlo);
     for (int64_t t = 0; t < nlo; ++t) expi_pi(2 * t, M, &re[t], &im[t]);
@@ -1276,7 +818,7 @@ hipError_t build_tables(birk_plan* p) {
     if ((e = twiddles(2 * g.N, &g.tw)) != hipSuccess) return e;
   for (int k = 0; k < 2; ++k)
     for (PairDesc& d : p->gen[k].host)
-      if (d.logM > kLdsMaxLog) {
+      if (d.cls > kLdsMaxLog) {
         TwiddleSet ts;
         if ((e = twiddles(d.M, &ts)) != hipSuccess) return e;
         for (int pi = 0; pi < kNumPrec; ++pi) {
@@ -1284,85 +826,80 @@ hipError_t build_tables(birk_plan* p) {
           d.tlo[pi] = ts.lo[pi];
         }
       }
-  // Bluestein chirp and filter spectrum, one per distinct L
+  // chirp (N + 1 values) and filter spectrum, one per distinct N: the spectrum of the plain
+  // convolution for one-workgroup pairs, of the even one for the others
   struct Blue {
-    const void* chirp[kNumPrec];
-    const void* filt[kNumPrec];
+    const void* chirp[kNumPrec] = {nullptr, nullptr, nullptr};
+    void* filt[kNumPrec] = {nullptr, nullptr, nullptr};
   };
   std::map<int64_t, Blue> blue;
-  PairSet fs;  // one pair per distinct L: the filter FFTs
   std::vector<PairDesc*> chirped;
   for (PairDesc& d : p->gen[1].host) chirped.push_back(&d);
   for (PairDesc& d : p->lds[1].host) chirped.push_back(&d);
-  for (const PairDesc* dp : chirped) {
-    const PairDesc& d = *dp;
-    if (blue.count(d.L)) continue;
-    Blue b{};
-    std::vector<double> re(d.L), im(d.L);
-    for (int64_t n = 0; n < d.L; ++n) {
-      const int64_t m = (int64_t)(((__int128)n * n) % (2 * d.L));
-      expi_pi(m, d.L, &re[n], &im[n]);
-    }
-    if ((e = upload_all(p, re, im, b.chirp)) != hipSuccess) return e;
-    blue[d.L] = b;
-    PairDesc f = d;
-    fs.host.push_back(f);
-  }
-  if (!fs.host.empty()) {
-    int64_t woff = 0, poff = 0;
-    layout_set(fs, woff, poff);  // filter slots from the start of work[0] / work[2]
-    for (PairDesc& f : fs.host) {
-      if (f.logM > kLdsMaxLog) {
-        TwiddleSet ts;
-        if ((e = twiddles(f.M, &ts)) != hipSuccess) return e;
-        for (int pi = 0; pi < kNumPrec; ++pi) {
-          f.thi[pi] = ts.hi[pi];
-          f.tlo[pi] = ts.lo[pi];
-        }
+  PairSet small, large;  // one pair per distinct N
+  for (PairDesc* dp : chirped) {
+    PairDesc& d = *dp;
+    const bool is_large = d.cls > kLdsMaxLog;
+    auto it = blue.find(d.N);
+    if (it == blue.end()) {
+      Blue b;
+      std::vector<double> re(d.Nn), im(d.Nn);
+      for (int64_t n = 0; n <= d.N; ++n) expi_pi((int64_t)(((__int128)n * n) % (2 * d.L)), d.L, &re[n], &im[n]);
+      if ((e = upload_all(p, re, im, b.chirp)) != hipSuccess) return e;
+      // M/2 + M2 values at the longest row of any split
+      const int64_t len = is_large ? d.M / 2 + kLdsMax : d.M;
+      for (int pi = 0; pi < kNumPrec; ++pi) {
+        if (!b.chirp[pi]) continue;
+        const size_t bytes[kNumPrec] = {sizeof(cplx<double>), sizeof(cplx<float>), sizeof(cplx<df32>)};
+        if ((e = hipMalloc(&b.filt[pi], len * bytes[pi])) != hipSuccess) return e;
+        p->allocs.push_back(b.filt[pi]);
       }
-      cplx<double>* bw = (cplx<double>*)p->work[0] + f.work;
-      hipLaunchKernelGGL(k_build_filter<double>, dim3((unsigned)((f.M + 255) / 256)), dim3(256), 0, p->stream, bw,
-                         (const cplx<double>*)blue[f.L].chirp[0], f.L, f.M);
+      it = blue.emplace(d.N, b).first;
+      (is_large ? large : small).host.push_back(d);
     }
-    if ((e = finalize_set(p, fs)) != hipSuccess) return e;
-    e = fft_set<double>(p, fs, (cplx<double>*)p->work[0], (cplx<double>*)p->work[2], 0, p->stream);
+    for (int pi = 0; pi < kNumPrec; ++pi) {
+      d.chirp[pi] = it->second.chirp[pi];
+      d.filt[pi] = it->second.filt[pi];
+    }
+  }
+  for (PairSet* fs : {&small, &large})
+    for (PairDesc& f : fs->host)
+      for (int pi = 0; pi < kNumPrec; ++pi) {
+        f.chirp[pi] = blue[f.N].chirp[pi];
+        f.filt[pi] = blue[f.N].filt[pi];
+      }
+  if (!small.host.empty()) {
+    int64_t woff = 0, poff = 0;
+    for (PairDesc& f : small.host) f.slot = f.M;
+    layout_set(small, woff, poff);  // filter slots from the start of work[0]
+    for (const PairDesc& f : small.host)
+      hipLaunchKernelGGL(k_build_filter<double>, dim3((unsigned)((f.M + 255) / 256)), dim3(256), 0, p->stream,
+                         (cplx<double>*)p->work[0] + f.work, (const cplx<double>*)f.chirp[0], f.L, f.M);
+    if ((e = finalize_set(p, small)) != hipSuccess) return e;
+    e = fft_set<double>(p, small, (cplx<double>*)p->work[0], (cplx<double>*)p->work[2], 0, p->stream);
     if (e != hipSuccess) return e;
-    for (const PairDesc& f : fs.host) {
-      Blue& b = blue[f.L];
+    for (const PairDesc& f : small.host) {
       const cplx<double>* bw = (const cplx<double>*)p->work[0] + f.work;
       const double s = 1.0 / (double)f.M;
-      const dim3 grid((unsigned)((f.M + 255) / 256));
-      void* d0 = nullptr;
-      void* d1 = nullptr;
-      void* d2 = nullptr;
-      if ((e = hipMalloc(&d0, f.M * sizeof(cplx<double>))) != hipSuccess) return e;
-      p->allocs.push_back(d0);
-      if ((e = hipMalloc(&d1, f.M * sizeof(cplx<float>))) != hipSuccess) return e;
-      p->allocs.push_back(d1);
-      if ((e = hipMalloc(&d2, f.M * sizeof(cplx<df32>))) != hipSuccess) return e;
-      p->allocs.push_back(d2);
-      const int l1 = f.logM > kLdsMaxLog ? f.logM1 : 0;  // two-step rows pass order
-      const int l2 = f.logM2;
-      hipLaunchKernelGGL(k_scale_to<double>, grid, dim3(256), 0, p->stream, bw, (cplx<double>*)d0, f.M, s, l1, l2);
-      hipLaunchKernelGGL(k_scale_to<float>, grid, dim3(256), 0, p->stream, bw, (cplx<float>*)d1, f.M, s, l1, l2);
-      hipLaunchKernelGGL(k_scale_to<df32>, grid, dim3(256), 0, p->stream, bw, (cplx<df32>*)d2, f.M, s, l1, l2);
-      b.filt[0] = d0;
-      b.filt[1] = d1;
-      b.filt[2] = d2;
+      const dim3 grid((unsigned)((f.M + 255) / 256)), blk(256);
+      hipLaunchKernelGGL(k_scale_to<double>, grid, blk, 0, p->stream, bw, (cplx<double>*)f.filt[0], f.M, s);
+      if (f.filt[1])
+        hipLaunchKernelGGL(k_scale_to<float>, grid, blk, 0, p->stream, bw, (cplx<float>*)f.filt[1], f.M, s);
+      if (f.filt[2])
+        hipLaunchKernelGGL(k_scale_to<df32>, grid, blk, 0, p->stream, bw, (cplx<df32>*)f.filt[2], f.M, s);
     }
     if ((e = hipStreamSynchronize(p->stream)) != hipSuccess) return e;
-    for (PairDesc* d : chirped) {
-      const Blue& b = blue[d->L];
-      for (int pi = 0; pi < kNumPrec; ++pi) {
-        d->chirp[pi] = b.chirp[pi];
-        d->filt[pi] = b.filt[pi];
-      }
-    }
   }
+  if (!large.host.empty()) {
+    e = blu_lists(p, large);
+    if (e == hipSuccess) e = blu_filters(p, large, p->stream);
+    blu_free_lists(p, large);
+    if (e == hipSuccess) e = blu_lists(p, p->gen[1]);
+    if (e != hipSuccess) return e;
+  }
+  if (!p->gen[0].host.empty() && (e = finalize_set(p, p->gen[0])) != hipSuccess) return e;
   for (int k = 0; k < 2; ++k)
-    if ((!p->gen[k].host.empty() && (e = finalize_set(p, p->gen[k])) != hipSuccess) ||
-        (e = finalize_lds(p, p->lds[k])) != hipSuccess)
-      return e;
+    if ((e = finalize_lds(p, p->lds[k])) != hipSuccess) return e;
   return hipGetLastError();
 }
 

@@ -118,14 +118,15 @@ __device__ __forceinline__ void load_tw_stage(cplx<T> (&w)[3], int logL, int log
 }
 
 // ---- fixed-length transforms: COUNT transforms of length 2^LOGL, blockDim = COUNT 2^LOGL / 8 ----
-// (COUNT = 0: 8 blockDim / 2^LOGL of them, blockDim known at run time)
+// (COUNT = 0: 8 blockDim / 2^LOGL of them, blockDim known at run time; GUARD: the workgroup may
+// have further threads, which only keep the barriers)
 // Transform t has its real part in row 2t and its imaginary part in row 2t + 1 of a
 // split array with padded rows of padded_ld(2^LOGL) reals.  With the length known at
 // compile time every LDS address of a butterfly is the padded position of its first
 // element plus a constant: pad(j + r s) = pad(j) + r s + (r s) / 16 for s a power of two
 // (s divides 16 or 16 divides s), so a thread needs one address register per butterfly
 // and the element offsets become instruction immediates.
-template <typename T, int LOGL, int LOGNS, int R, int COUNT>
+template <typename T, int LOGL, int LOGNS, int R, int COUNT, bool GUARD = false>
 __device__ __forceinline__ void stage_ct(T* __restrict__ buf, const cplx<T> (&w)[3]) {
   constexpr int logR = (R == 8) ? 3 : (R == 4) ? 2 : 1;
   constexpr int NB = kPPT / R;             // butterflies per thread
@@ -136,71 +137,105 @@ __device__ __forceinline__ void stage_ct(T* __restrict__ buf, const cplx<T> (&w)
   constexpr int LD = padded_ld(1 << LOGL);
   T vr[NB][R], vi[NB][R];
   int pd[NB];
+  const bool on = !GUARD || (int)threadIdx.x < NTHR;
+  if (on) {
 #pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int b = (int)threadIdx.x + i * NTHR;
-    const int t = b >> LOGNBF;
-    const int j = b & (NBF - 1);
-    const int rowoff = 2 * t * LD;
-    const int pj = rowoff + j + (j >> 4);
+    for (int i = 0; i < NB; ++i) {
+      const int b = (int)threadIdx.x + i * NTHR;
+      const int t = b >> LOGNBF;
+      const int j = b & (NBF - 1);
+      const int rowoff = 2 * t * LD;
+      const int pj = rowoff + j + (j >> 4);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int off = r * NBF + ((r * NBF) >> 4);
-      vr[i][r] = buf[pj + off];
-      vi[i][r] = buf[pj + LD + off];
-    }
-    const int jm = j & (NS - 1);
-    if constexpr (R == 8 && LOGNS > 0) {
-      if (jm != 0) {
-        const cplx<T> w1 = w[0], w2 = w[1], w4 = w[2];
-        const cplx<T> w3 = fast::cmul<T>(w2, w1);
-        const cplx<T> w5 = fast::cmul<T>(w4, w1), w6 = fast::cmul<T>(w4, w2), w7 = fast::cmul<T>(w4, w3);
-        cmul_inplace<T>(vr[i][1], vi[i][1], w1.x, w1.y);
-        cmul_inplace<T>(vr[i][2], vi[i][2], w2.x, w2.y);
-        cmul_inplace<T>(vr[i][3], vi[i][3], w3.x, w3.y);
-        cmul_inplace<T>(vr[i][4], vi[i][4], w4.x, w4.y);
-        cmul_inplace<T>(vr[i][5], vi[i][5], w5.x, w5.y);
-        cmul_inplace<T>(vr[i][6], vi[i][6], w6.x, w6.y);
-        cmul_inplace<T>(vr[i][7], vi[i][7], w7.x, w7.y);
+      for (int r = 0; r < R; ++r) {
+        const int off = r * NBF + ((r * NBF) >> 4);
+        vr[i][r] = buf[pj + off];
+        vi[i][r] = buf[pj + LD + off];
       }
+      const int jm = j & (NS - 1);
+      if constexpr (R == 8 && LOGNS > 0) {
+        if (jm != 0) {
+          const cplx<T> w1 = w[0], w2 = w[1], w4 = w[2];
+          const cplx<T> w3 = fast::cmul<T>(w2, w1);
+          const cplx<T> w5 = fast::cmul<T>(w4, w1), w6 = fast::cmul<T>(w4, w2), w7 = fast::cmul<T>(w4, w3);
+          cmul_inplace<T>(vr[i][1], vi[i][1], w1.x, w1.y);
+          cmul_inplace<T>(vr[i][2], vi[i][2], w2.x, w2.y);
+          cmul_inplace<T>(vr[i][3], vi[i][3], w3.x, w3.y);
+          cmul_inplace<T>(vr[i][4], vi[i][4], w4.x, w4.y);
+          cmul_inplace<T>(vr[i][5], vi[i][5], w5.x, w5.y);
+          cmul_inplace<T>(vr[i][6], vi[i][6], w6.x, w6.y);
+          cmul_inplace<T>(vr[i][7], vi[i][7], w7.x, w7.y);
+        }
+      }
+      dft_reg<T, R>(vr[i], vi[i]);
+      const int dst = ((j >> LOGNS) << (LOGNS + logR)) + jm;
+      pd[i] = rowoff + dst + (dst >> 4);
     }
-    dft_reg<T, R>(vr[i], vi[i]);
-    const int dst = ((j >> LOGNS) << (LOGNS + logR)) + jm;
-    pd[i] = rowoff + dst + (dst >> 4);
   }
   __syncthreads();
+  if (on) {
 #pragma unroll
-  for (int i = 0; i < NB; ++i) {
+    for (int i = 0; i < NB; ++i) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int off = r * NS + ((r * NS) >> 4);
-      buf[pd[i] + off] = vr[i][r];
-      buf[pd[i] + LD + off] = vi[i][r];
+      for (int r = 0; r < R; ++r) {
+        const int off = r * NS + ((r * NS) >> 4);
+        buf[pd[i] + off] = vr[i][r];
+        buf[pd[i] + LD + off] = vi[i][r];
+      }
     }
   }
   __syncthreads();
 }
 
-template <typename T, int LOGL, int COUNT, int K>
+template <typename T, int LOGL, int COUNT, int K, bool GUARD>
 __device__ __forceinline__ void stages8_ct(T* __restrict__ buf, const cplx<T>* __restrict__ tw) {
   constexpr int BASE = (LOGL % 3) ? (LOGL % 3) : 3;
   constexpr int LOGNS = BASE + 3 * K;
   if constexpr (LOGNS < LOGL) {
     cplx<T> w[3];
     load_tw_stage<T>(w, LOGL, LOGNS, tw);
-    stage_ct<T, LOGL, LOGNS, 8, COUNT>(buf, w);
-    stages8_ct<T, LOGL, COUNT, K + 1>(buf, tw);
+    stage_ct<T, LOGL, LOGNS, 8, COUNT, GUARD>(buf, w);
+    stages8_ct<T, LOGL, COUNT, K + 1, GUARD>(buf, tw);
   }
 }
 
 // COUNT in-place transforms of length 2^LOGL (see stage_ct for the layout).
-template <typename T, int LOGL, int COUNT>
+template <typename T, int LOGL, int COUNT, bool GUARD = false>
 __device__ __forceinline__ void fft_ct(T* __restrict__ buf, const cplx<T>* __restrict__ tw) {
   cplx<T> w[3];
-  if constexpr (LOGL % 3 == 1) stage_ct<T, LOGL, 0, 2, COUNT>(buf, w);
-  else if constexpr (LOGL % 3 == 2) stage_ct<T, LOGL, 0, 4, COUNT>(buf, w);
-  else stage_ct<T, LOGL, 0, 8, COUNT>(buf, w);
-  stages8_ct<T, LOGL, COUNT, 0>(buf, tw);
+  if constexpr (LOGL % 3 == 1) stage_ct<T, LOGL, 0, 2, COUNT, GUARD>(buf, w);
+  else if constexpr (LOGL % 3 == 2) stage_ct<T, LOGL, 0, 4, COUNT, GUARD>(buf, w);
+  else stage_ct<T, LOGL, 0, 8, COUNT, GUARD>(buf, w);
+  stages8_ct<T, LOGL, COUNT, 0, GUARD>(buf, tw);
+}
+
+// The thread's twiddles of every radix-8 stage of a length 2^LOGL: read once with a kernel's
+// inputs and used by each of its transforms, so that no stage waits for a table read.
+template <typename T, int LOGL>
+struct StageTw {
+  static constexpr int BASE = (LOGL % 3) ? (LOGL % 3) : 3;
+  static constexpr int N = LOGL > BASE ? (LOGL - BASE + 2) / 3 : 0;
+  cplx<T> w[N > 0 ? N : 1][3];
+  __device__ __forceinline__ void load(const cplx<T>* __restrict__ tw) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) load_tw_stage<T>(w[k], LOGL, BASE + 3 * k, tw);
+  }
+};
+
+template <typename T, int LOGL, int COUNT, int K, bool GUARD>
+__device__ __forceinline__ void stages8_ct(T* __restrict__ buf, const StageTw<T, LOGL>& st) {
+  if constexpr (K < StageTw<T, LOGL>::N) {
+    stage_ct<T, LOGL, StageTw<T, LOGL>::BASE + 3 * K, 8, COUNT, GUARD>(buf, st.w[K]);
+    stages8_ct<T, LOGL, COUNT, K + 1, GUARD>(buf, st);
+  }
+}
+
+// fft_ct with the stages' twiddles in registers.
+template <typename T, int LOGL, int COUNT, bool GUARD = false>
+__device__ __forceinline__ void fft_ct(T* __restrict__ buf, const StageTw<T, LOGL>& st) {
+  constexpr int R = (LOGL % 3 == 1) ? 2 : (LOGL % 3 == 2) ? 4 : 8;
+  stage_ct<T, LOGL, 0, R, COUNT, GUARD>(buf, st.w[0]);
+  stages8_ct<T, LOGL, COUNT, 0, GUARD>(buf, st);
 }
 
 // ---- one transform of length 2^LOGL per workgroup (blockDim = 2^LOGL / 8) whose input

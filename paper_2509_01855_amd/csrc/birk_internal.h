@@ -106,8 +106,11 @@ struct FastGroup {
 struct PairDesc {
   int64_t src = 0;       // vector offset of component 2p
   int64_t Nn = 0, N = 0, L = 0, M = 0;
-  int64_t work = 0;      // complex offset of this pair's M-long slot in work[0..2]
+  int64_t work = 0;      // complex offset of this pair's slot in work[0..2]
   int64_t part = 0;      // offset of the pair's c^_0 partials (2 per block)
+  int64_t slot = 0;      // complex elements of its slot: the power of two >= 3N, or M = L
+  int R = 1;             // chirp convolutions: M = R 2^logM, M1 = R 2^logM1 (R = 1, 3, 5)
+  int cls = 0;           // log2 of the power of two >= 3N (or of L): the tuner's class
   int logM = 0, logM1 = 0, logM2 = 0, tw_shift = 0;
   int has2 = 0;          // component 2p + 1 exists
   int nblk = 0;          // 256-wide blocks over [0, N_n)
@@ -125,8 +128,10 @@ struct PairSet {
   int2* tiles_m = nullptr;    // (pair, block of 256 over [0, M))
   int2* tiles_n = nullptr;    // (pair, block of 256 over [0, N_n))
   int2* tiles_lds = nullptr;  // (first pair, count): whole transforms of M <= kLdsMax
-  int2* tiles_c4 = nullptr;   // (pair, column block) of the four-step first pass
-  int2* tiles_r4 = nullptr;   // (pair, row block) of the four-step second pass
+  int2* tiles_c4 = nullptr;   // (pair, column block) of the two-step FFTs' column passes
+  int2* tiles_r4 = nullptr;   // (pair, row block) of their row pass
+  int thr_c = 0, thr_r = 0;   // chirp convolutions: threads and LDS reals of a workgroup
+  int lds_c = 0, lds_r = 0;
   int n_m = 0, n_n = 0, n_lds = 0, n_c4 = 0, n_r4 = 0;
   int64_t work = 0;           // complex elements needed per work buffer
   int64_t parts = 0;          // doubles of partials needed
@@ -263,7 +268,6 @@ struct birk_plan {
   double* comp_val = nullptr;       // one double per component (last node, or a total)
   double* comp_part = nullptr;      // per-component reduction partials (CompDesc::part)
   int use_fast = 1;               // power-of-two N takes the three-pass path
-  int blu_split[40] = {};         // log2 M1 of the Bluestein two-step FFTs per log2 M (0: default)
   birk::FastKnobs fast_kn;        // default tile schedule of the three-pass groups
   // HIP graphs of the products (birk_plan_set_graphs), per (direction, input, output)
   struct GraphSlot {
@@ -306,6 +310,21 @@ hipError_t build_tables(birk_plan* p);
 
 // A device array of the plan (in p->allocs) holding a copy of `bytes` host bytes.
 hipError_t upload_raw(birk_plan* p, const void* h, size_t bytes, void** d);
+
+// ---- chirp convolutions beyond one workgroup (birk_blu.hip) ----
+// R and logM of the pair's convolution length; its two-step split from the nominal log2 M1
+// x (and back); whether the kernels cover x; the split a pair starts with.
+void blu_length(PairDesc& d);
+void blu_set_split(PairDesc& d, int x);
+int blu_split(const PairDesc& d);
+bool blu_split_ok(const PairDesc& d, int x);
+int blu_default_split(const PairDesc& d);
+// Tile lists, launch sizes and descriptors of a set on the device, and their release.
+hipError_t blu_lists(birk_plan* p, PairSet& ps);
+void blu_free_lists(birk_plan* p, PairSet& ps);
+hipError_t blu_filters(birk_plan* p, const PairSet& ps, hipStream_t s);
+template <typename T>
+hipError_t product_blu(birk_plan* p, const PairSet& ps, const T* v, T* out, int transpose, hipStream_t s);
 
 // ---- whole products in LDS (birk_lds.hip) ----
 // Sort the set's pairs by length and upload its descriptors and tile list.

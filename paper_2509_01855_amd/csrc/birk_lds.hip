@@ -46,125 +46,134 @@ __device__ __forceinline__ cplx<T> get(const T* sm, int t, int n) {
   return fast::mk<T>(sm[2 * t * LD + fast::pad(n)], sm[(2 * t + 1) * LD + fast::pad(n)]);
 }
 
-// The pairs [tile.x, tile.x + tile.y) of one length M = 2^LOGM; CHIRP: Bluestein.
-// sm: 8 blockDim complex values in split padded rows; red: the c^_0 partial sums.
+// The pairs [tile.x, tile.x + tile.y) of one length M = 2^LOGM: one pair from M = 512 on, up
+// to 512 / M below; CHIRP: Bluestein.  NT threads work, any others only keep the barriers.
+// sm: 8 NT complex values in split padded rows; red: the c^_0 partial sums.
 template <typename T, int LOGM, bool CHIRP>
 __device__ __forceinline__ void lds_product(const T* __restrict__ x, T* __restrict__ out,
                                             const PairDesc* __restrict__ pd, int2 tile,
                                             const cplx<T>* __restrict__ tw, int trans, T* sm, double* red) {
   constexpr int pi = prec_index<T>();
   constexpr int M = 1 << LOGM;
+  constexpr int NT = M / kPPT > 64 ? M / kPPT : 64;
+  constexpr int COUNT = kPPT * NT / M;
   constexpr int G = M < 64 ? M : 64;   // lanes of a wave that share a pair
-  const int tid = (int)threadIdx.x, nthr = (int)blockDim.x;
-  // element i of the thread: entry n of pair t (wave-uniform from M = 64 on)
+  const int tid = (int)threadIdx.x;
+  const bool on = tid < NT;
+  // element i of the thread: entry n of pair t (a missing pair t repeats the tile's last
+  // one; it is not stored)
   auto where = [&](int i, int& t, int& n) {
-    const int e = tid + i * nthr;
-    t = e >> LOGM;
-    if constexpr (LOGM >= 6) t = __builtin_amdgcn_readfirstlane(t);
+    const int e = tid + i * NT;
+    t = COUNT > 1 ? e >> LOGM : 0;
     n = e & (M - 1);
   };
+  auto desc = [&](int t) -> const PairDesc& { return pd[tile.x + (COUNT > 1 ? min(t, tile.y - 1) : 0)]; };
   cplx<T> v[kPPT], fv[CHIRP ? kPPT : 1], cv[CHIRP ? kPPT : 1];
-#pragma unroll
-  for (int i = 0; i < kPPT; ++i) {
-    int t, n;
-    where(i, t, n);
-    v[i] = fast::mk<T>(T(0), T(0));
-    if constexpr (CHIRP) fv[i] = cv[i] = v[i];
-    if (t >= tile.y) continue;
-    const PairDesc& d = pd[tile.x + t];
-    const int N = (int)d.N, L = 2 * N;
-    if constexpr (CHIRP) fv[i] = ((const cplx<T>*)d.filt[pi])[n];
-    if (n >= L) continue;
-    const int k = n <= N ? n : L - n;
-    const T* xa = x + d.src;
-    T a = xa[k];
-    T b = d.has2 ? xa[d.Nn + k] : T(0);
-    if (trans && (k == 0 || k == N)) {
-      a = a + a;
-      b = b + b;
-    }
-    v[i] = fast::mk<T>(a, b);
-    if constexpr (CHIRP) cv[i] = ((const cplx<T>*)d.chirp[pi])[k];
-  }
-#pragma unroll 1
-  for (int dct = 0; dct < 2; ++dct) {
+  if (on) {
+    // every load of the thread from a valid address, none behind a branch
+    T va[kPPT], vb[kPPT];
 #pragma unroll
     for (int i = 0; i < kPPT; ++i) {
       int t, n;
       where(i, t, n);
-      if constexpr (CHIRP) v[i] = fast::cmul<T>(v[i], cv[i]);
-      put<T, LOGM>(sm, t, n, v[i]);
+      const PairDesc& d = desc(t);
+      const int N = (int)d.N, L = 2 * N;
+      const int k = n <= N ? n : n < L ? L - n : 0;
+      const T* xa = x + d.src;
+      va[i] = xa[k];
+      vb[i] = xa[(d.has2 ? d.Nn : 0) + k];
+      if constexpr (CHIRP) {
+        cv[i] = ((const cplx<T>*)d.chirp[pi])[k];
+        fv[i] = ((const cplx<T>*)d.filt[pi])[n];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kPPT; ++i) {
+      int t, n;
+      where(i, t, n);
+      const PairDesc& d = desc(t);
+      const int N = (int)d.N, L = 2 * N;
+      const T e = (trans && (n == 0 || n == N)) ? T(2) : T(1);   // E^{-1}: ends doubled
+      v[i] = fast::mk<T>(n < L ? e * va[i] : T(0), n < L && d.has2 ? e * vb[i] : T(0));
+    }
+  }
+#pragma unroll 1
+  for (int dct = 0; dct < 2; ++dct) {
+    if (on) {
+#pragma unroll
+      for (int i = 0; i < kPPT; ++i) {
+        int t, n;
+        where(i, t, n);
+        if constexpr (CHIRP) v[i] = fast::cmul<T>(v[i], cv[i]);
+        put<T, LOGM>(sm, t, n, v[i]);
+      }
     }
     __syncthreads();
-    fast::fft_ct<T, LOGM, 0>(sm, tw);
+    fast::fft_ct<T, LOGM, COUNT, true>(sm, tw);
     if constexpr (CHIRP) {
       // x filter, inverse transform as conj FFT conj, x chirp: Y_n, n <= N
+      if (on) {
 #pragma unroll
-      for (int i = 0; i < kPPT; ++i) {
-        int t, n;
-        where(i, t, n);
-        put<T, LOGM>(sm, t, n, fast::conjg<T>(fast::cmul<T>(get<T, LOGM>(sm, t, n), fv[i])));
+        for (int i = 0; i < kPPT; ++i) {
+          int t, n;
+          where(i, t, n);
+          put<T, LOGM>(sm, t, n, fast::conjg<T>(fast::cmul<T>(get<T, LOGM>(sm, t, n), fv[i])));
+        }
       }
       __syncthreads();
-      fast::fft_ct<T, LOGM, 0>(sm, tw);
+      fast::fft_ct<T, LOGM, COUNT, true>(sm, tw);
+      if (on) {
 #pragma unroll
-      for (int i = 0; i < kPPT; ++i) {
-        int t, n;
-        where(i, t, n);
-        put<T, LOGM>(sm, t, n, fast::cmul<T>(fast::conjg<T>(get<T, LOGM>(sm, t, n)), cv[i]));
+        for (int i = 0; i < kPPT; ++i) {
+          int t, n;
+          where(i, t, n);
+          put<T, LOGM>(sm, t, n, fast::cmul<T>(fast::conjg<T>(get<T, LOGM>(sm, t, n)), cv[i]));
+        }
       }
       __syncthreads();
     }
     if (dct == 1) break;
     // stencil: the thread's inputs of the second DCT, and the c^_0 sums (each Y_k, k <= N,
-    // once) of G consecutive entries, whatever the workgroup's size: a pair's result does
-    // not depend on the pairs it is launched with
+    // once) of G consecutive entries
+    if (on) {
 #pragma unroll
-    for (int i = 0; i < kPPT; ++i) {
-      int t, n;
-      where(i, t, n);
-      v[i] = fast::mk<T>(T(0), T(0));
-      double s0 = 0.0, s1 = 0.0;
-      if (t < tile.y) {
-        const PairDesc& d = pd[tile.x + t];
-        const int N = (int)d.N, L = 2 * N;
-        if (n < L) {
-          const int k = n <= N ? n : L - n;
-          const cplx<T> Ym = get<T, LOGM>(sm, t, k > 0 ? k - 1 : 0);
-          const cplx<T> Yp = get<T, LOGM>(sm, t, k < N ? k + 1 : N);
-          if (trans) {
-            v[i] = mid_tr<T>(k, N, get<T, LOGM>(sm, t, 0), Ym, Yp, T(1) / T(2 * N + 2));
+      for (int i = 0; i < kPPT; ++i) {
+        int t, n;
+        where(i, t, n);
+        const int N = (int)desc(t).N, L = 2 * N;
+        const int k = n <= N ? n : n < L ? L - n : 0;
+        const cplx<T> Ym = get<T, LOGM>(sm, t, max(k - 1, 0));
+        const cplx<T> Yp = get<T, LOGM>(sm, t, min(k + 1, N));
+        cplx<T> r;
+        if (trans) {
+          r = mid_tr<T>(k, N, get<T, LOGM>(sm, t, 0), Ym, Yp, T(1) / T(2 * N + 2));
+        } else {
+          r = mid_fwd<T>(max(k, 1), N, Ym, Yp, T(1) / T(N), T(1) / T(4 * N + 4));
+          const cplx<T> Y = get<T, LOGM>(sm, t, k);
+          const double w = n <= N ? c0_weight(n, N) : 0.0;
+          double s0 = w * (double)Y.x, s1 = w * (double)Y.y;
+          if constexpr (G == 64) {
+            s0 = wave_sum_last(s0);
+            s1 = wave_sum_last(s1);
           } else {
-            if (k > 0) v[i] = mid_fwd<T>(k, N, Ym, Yp, T(1) / T(N), T(1) / T(4 * N + 4));
-            if (n <= N) {
-              const cplx<T> Y = get<T, LOGM>(sm, t, n);
-              const double w = c0_weight(n, N);
-              s0 = w * (double)Y.x;
-              s1 = w * (double)Y.y;
+#pragma unroll
+            for (int off = G / 2; off > 0; off >>= 1) {
+              s0 += __shfl_xor(s0, off, 64);
+              s1 += __shfl_xor(s1, off, 64);
             }
           }
-        }
-      }
-      if (!trans) {
-        if constexpr (G == 64) {
-          s0 = wave_sum_last(s0);
-          s1 = wave_sum_last(s1);
-        } else {
-#pragma unroll
-          for (int off = G / 2; off > 0; off >>= 1) {
-            s0 += __shfl_xor(s0, off, 64);
-            s1 += __shfl_xor(s1, off, 64);
+          if ((tid & (G - 1)) == G - 1) {
+            double* p = red + 2 * ((tid + i * NT) / G);
+            p[0] = s0;
+            p[1] = s1;
           }
         }
-        if ((tid & (G - 1)) == G - 1) {
-          double* r = red + 2 * ((tid + i * nthr) / G);
-          r[0] = s0;
-          r[1] = s1;
-        }
+        v[i] = (n < L && (trans || k > 0)) ? r : fast::mk<T>(T(0), T(0));
       }
     }
     __syncthreads();
   }
+  if (!on) return;
   // out = Y / 2 + c^_0, or e_j Y_j / N
   constexpr int per = M / G;   // partial sums per pair, consecutive
   T ca = T(0), cb = T(0);
@@ -173,8 +182,8 @@ __device__ __forceinline__ void lds_product(const T* __restrict__ x, T* __restri
   for (int i = 0; i < kPPT; ++i) {
     int t, n;
     where(i, t, n);
-    if (t >= tile.y) continue;
-    const PairDesc& d = pd[tile.x + t];
+    if (COUNT > 1 && t >= tile.y) continue;
+    const PairDesc& d = desc(t);
     const int N = (int)d.N;
     if (n > N) continue;
     cplx<T> Y = get<T, LOGM>(sm, t, n);
@@ -220,7 +229,7 @@ __global__ __launch_bounds__(kLdsMax / kPPT) void k_lds_product(const T* __restr
                                                                const int2* __restrict__ tiles,
                                                                const cplx<T>* __restrict__ tw, int trans) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ double red[2 * kPPT * 64];
+  __shared__ double red[2 * kLdsMax / 64];   // 64 lanes a sum from M = 64 on; 512 points below
   T* sm = reinterpret_cast<T*>(smem_raw);
   const int2 tile = tiles[blockIdx.x];
   switch (pd[tile.x].logM) {
@@ -241,8 +250,9 @@ __global__ __launch_bounds__(kLdsMax / kPPT) void k_lds_product(const T* __restr
   }
 }
 
-// Reals of LDS for transforms of length 2^logM in a workgroup of nthr threads.
-int lds_reals(int logM, int nthr) { return 2 * ((kPPT * nthr) >> logM) * fast::padded_ld(1 << logM); }
+// Pairs of length 2^logM in a workgroup, and the LDS (reals) they take.
+int lds_pairs(int logM) { return logM >= 9 ? 1 : 512 >> logM; }
+int lds_reals(int logM) { return 2 * lds_pairs(logM) * fast::padded_ld(1 << logM); }
 
 template <typename T, bool CHIRP>
 hipError_t launch(birk_plan* p, const LdsSet& ls, const T* v, T* out, int transpose, hipStream_t s) {
@@ -266,11 +276,11 @@ hipError_t finalize_lds(birk_plan* p, LdsSet& ls) {
   const int np = (int)ls.host.size();
   for (int q = 0; q < np;) {
     const int logM = ls.host[q].logM;
-    const int per = (kPPT * ls.threads) >> logM;
+    const int per = lds_pairs(logM);
     int cnt = 1;
     while (q + cnt < np && cnt < per && ls.host[q + cnt].logM == logM) ++cnt;
     tiles.push_back(make_int2(q, cnt));
-    ls.lds_reals = std::max(ls.lds_reals, lds_reals(logM, ls.threads));
+    ls.lds_reals = std::max(ls.lds_reals, lds_reals(logM));
     q += cnt;
   }
   ls.ntiles = (int)tiles.size();

@@ -141,9 +141,8 @@ birk_status birk_plan_tune(birk_plan* plan, char* report, int64_t report_len);
  * use.  In graph mode birk_krylov_solve also records each chunk of Arnoldi steps it runs
  * (the steps between two host reads of the convergence flags: single steps at first, then
  * 2 and 4 steps on plans shorter than 2^20 elements) the first time a (precision, first
- * step, chunk length, restart, Jacobian pointer and kind, preconditioner, P^{-1} formed on
- * the fly or from the per-node tables cached after the first application) chunk occurs,
- * and replays it afterwards; the Jacobian must stay allocated while such graphs exist
+ * step, chunk length, restart, Jacobian pointer and kind, preconditioner, P^{-1} formed from
+ * J or from a table of the solve) chunk occurs, and replays it afterwards; the Jacobian must stay allocated while such graphs exist
  * (at most 48, all dropped beyond that).  enable = 0
  * (the default) drops every recorded graph.  birk_plan_tune drops them too (they hold the
  * old schedule).  Requires a plan created on a non-null stream.  Other entry points are

@@ -267,7 +267,7 @@ birk_status birk_plan_create(birk_plan** out, int32_t batch, const int64_t* n_no
     jcoff += (int64_t)in.nx * in.nx;
     soff += pinv_scratch(in.Nn, in.nx) + (int64_t)in.nx * ((in.Nn + 1023) / 1024) + 64;
     in.jsw_off = jswoff;
-    jswoff += pinv_jsw_size(in.Nn, in.nx);
+    jswoff += pinv_jsw_size(in.Nn, in.nx, prec);
   }
   p->total_len = off;
   p->total_jnode = joff;
@@ -318,6 +318,7 @@ birk_status birk_plan_create(birk_plan** out, int32_t batch, const int64_t* n_no
   if (e == hipSuccess) e = plan_bform(p);
   if (e == hipSuccess) e = plan_instances(p);
   if (e == hipSuccess) e = plan_solve(p);
+  if (e == hipSuccess) e = plan_scan(p);
   if (e == hipSuccess) e = plan_kkt(p);
   if (e != hipSuccess) {
     free_plan(p);
@@ -514,7 +515,7 @@ birk_status birk_precond(birk_plan* p, birk_jac_kind jk, const double* J, const 
     return e == hipSuccess ? BIRK_OK : BIRK_ERR_DEVICE;
   }
   if (inverse) {
-    e = precond_prepare(p, jk, J, p->prec == BIRK_F64 ? 0 : 1, p->stream, kPrepLarge);
+    e = precond_prepare(p, jk, J, p->prec == BIRK_F64 ? 0 : 1, p->stream, 0);
     if (e != hipSuccess) return BIRK_ERR_DEVICE;
   }
   if (p->prec == BIRK_F64) {
@@ -707,7 +708,7 @@ static hipError_t arnoldi_chunk(birk_plan* p, int jk, const double* J, int j0, i
 template <typename TK>
 birk_status gmres_cycle(birk_plan* p, int jk, const double* J, const double* r, double* chi, double* jchi,
                         std::vector<InstState>& st, const std::vector<double>& tol_inner, int m, int use_precond,
-                        int& budget, int& pinv_state) {
+                        int& budget) {
   const int B = (int)p->inst.size();
   const int64_t n = p->total_len;
   hipStream_t s = p->stream;
@@ -746,15 +747,8 @@ birk_status gmres_cycle(birk_plan* p, int jk, const double* J, const double* r, 
   while (j < m && budget > 0) {
     const int want = (!small || checks < 3) ? 1 : checks < 4 ? 2 : 4;
     const int k = std::min(want, std::min(m - j, budget));
-    // the first P^{-1} of the solve forms K_k on the fly; per-node H_k are cached (one
-    // preparation pass, outside any recorded chunk) before the second
-    if (use_precond && pinv_state == 1) {
-      if (precond_prepare(p, jk, J, sizeof(TK) == 4 ? 1 : 0, s, kPrepCache) != hipSuccess) return BIRK_ERR_DEVICE;
-      pinv_state = 2;
-    }
-    e = arnoldi_chunk<TK>(p, jk, J, j, k, m, use_precond, Yb != nullptr, pinv_state == 2 ? 1 : 0);
+    e = arnoldi_chunk<TK>(p, jk, J, j, k, m, use_precond, Yb != nullptr, sizeof(TK) == 4 ? 1 : 0);
     if (e != hipSuccess) return BIRK_ERR_DEVICE;
-    if (pinv_state == 0) pinv_state = 1;
     j += k;
     budget -= k;
     ++checks;
@@ -826,11 +820,8 @@ extern "C" birk_status birk_krylov_solve(birk_plan* p, birk_jac_kind jk, const d
   hipError_t e = ensure_krylov(p, o.restart, mixed ? sizeof(float) : sizeof(double));
   if (e != hipSuccess) return dev_err(e);
   if (hipMemsetAsync(p->flag, 0, sizeof(int), s) != hipSuccess) return BIRK_ERR_DEVICE;
-  // P^{-1} applications so far: 0, 1, or 2 = several (per-node H_k cached).  Mixed plans
-  // cache the float H_k at once: their staged double J reads cost more than a float table.
-  int pinv_state = mixed ? 2 : 0;
-  if (o.use_precond && precond_prepare(p, jk, J, mixed ? 1 : 0, s, mixed ? kPrepLarge | kPrepCache : kPrepLarge) !=
-                           hipSuccess)
+  // mixed plans keep the float H_k: reading the double J costs more than a float table
+  if (o.use_precond && precond_prepare(p, jk, J, mixed ? 1 : 0, s, mixed ? 1 : 0) != hipSuccess)
     return BIRK_ERR_DEVICE;
   if (!o.use_x0 && hipMemsetAsync(chi, 0, n * sizeof(double), s) != hipSuccess) return BIRK_ERR_DEVICE;
 
@@ -903,10 +894,8 @@ extern "C" birk_status birk_krylov_solve(birk_plan* p, birk_jac_kind jk, const d
       st[i].breakdown_last = st[i].status == BIRK_ERR_BREAKDOWN;
       if (st[i].status == BIRK_ERR_BREAKDOWN) st[i].status = BIRK_OK;
     }
-    birk_status cs = mixed ? gmres_cycle<float>(p, jk, J, rcur, chi, nullptr, st, tol, o.restart, o.use_precond, budget,
-                                                pinv_state)
-                           : gmres_cycle<double>(p, jk, J, rcur, chi, jchi, st, tol, o.restart, o.use_precond, budget,
-                                                 pinv_state);
+    birk_status cs = mixed ? gmres_cycle<float>(p, jk, J, rcur, chi, nullptr, st, tol, o.restart, o.use_precond, budget)
+                           : gmres_cycle<double>(p, jk, J, rcur, chi, jchi, st, tol, o.restart, o.use_precond, budget);
     if (cs == BIRK_ERR_SINGULAR || cs == BIRK_ERR_DEVICE) {
       result = cs;
       for (int i = 0; i < B; ++i) st[i].done = true;

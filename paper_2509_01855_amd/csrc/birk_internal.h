@@ -159,10 +159,6 @@ struct PinvDesc {
   int64_t st[kPinvMaxLevels] = {};      // start-state offsets (doubles) per level
   int L = 0;                            // top level
   int nb0 = 0;                          // level-0 blocks of 64 groups
-  // wave-scan path (n_x <= kWaveNx): tiles of kTileNodes nodes
-  int64_t ntile = 0;                    // tiles of the instance
-  int64_t tagg = 0, tst = 0;            // tile aggregates and start states, [field][tile] (doubles)
-  int64_t tmap = 0;                     // inclusive chunk maps, [tile][field][thread] (doubles)
 };
 
 // Instances with one state count n_x: each scan phase is one launch over all of them.
@@ -178,8 +174,28 @@ struct PinvClass {
   int n_up[kPinvMaxLevels] = {};
   int2* t_nodes = nullptr;                   // (k, block of 256 nodes): J x
   int n_nodes = 0;
-  int2* t_tile = nullptr;                    // (k, tile) of the wave-scan path
-  int n_tile = 0;
+};
+
+// Wave scan of P^{-1} and P^{-T} (birk_scan.hip, n_x <= kScanNx): one instance of one n_x
+// class.
+constexpr int kScanNx = 8;
+struct ScanDesc {
+  int64_t Nn, off, joff, jcoff;
+  int64_t hoff;              // H_k kept in float (mixed solves), elements into jsw
+  int64_t cmap, tmap, gmap;  // chunk, tile and group maps in the scan scratch (doubles)
+  const double* w;           // CC weights
+  int rounds;                // nodes per tile / 64
+  int ntile;
+};
+struct ScanClass {
+  int nx = 0;
+  ScanDesc* dev = nullptr;
+  int2* tiles = nullptr;     // (instance, tile)
+  int2* groups = nullptr;    // (instance, group of 64 tiles)
+  int2* nodes = nullptr;     // (instance, block of 256 nodes)
+  int* small = nullptr;      // instances worked by one workgroup
+  int n_tile = 0, n_group = 0, n_nodes = 0, n_small = 0;
+  int small_waves = 0;       // waves of those workgroups
 };
 
 // Backward scan of P^{-T} (birk_kkt.hip): one instance of one n_x class.
@@ -220,6 +236,7 @@ struct birk_plan {
   birk::LdsSet lds[2];            // pairs that fit one workgroup: [0] 2N a power of two, [1] Bluestein
   int noalloc_nbuf = 3;           // work buffers that birk_apply_noalloc accounts for
   std::vector<birk::PinvClass> pclass;  // preconditioner scan schedule, one class per n_x
+  std::vector<birk::ScanClass> sclass;  // its wave scans, n_x <= kScanNx
   birk::SegSet seg;               // Krylov segmentation of the batch
   std::vector<void*> allocs;      // device tables owned by the plan
   int64_t total_len = 0;
@@ -231,7 +248,7 @@ struct birk_plan {
   void* work[3] = {nullptr, nullptr, nullptr};   // complex work buffers sized for double
   double* partials = nullptr;
   double* scan = nullptr;     // preconditioner scan scratch
-  double* jsw = nullptr;      // per-node Jacobians and weights in the scan's thread layout
+  double* jsw = nullptr;      // H_k tables of the scans (n_x > 8; n_x <= 8 of mixed plans)
   int64_t total_jsw = 0;
   const void* lds_tw[birk::kNumPrec] = {nullptr, nullptr, nullptr};  // exp(-2 pi i t / kLdsMax)
   void* tmp_vec[4] = {nullptr, nullptr, nullptr, nullptr};  // vectors of total_len doubles
@@ -372,28 +389,31 @@ hipError_t jac_times(birk_plan* p, int jac_kind, const double* J, const T* x, T*
 template <typename T>
 hipError_t precond_forward(birk_plan* p, int jac_kind, const double* J, const T* y, T* out,
                            hipStream_t s);
-// cached = 1: per-node H_k laid out by precond_prepare(..., kPrepCache) for this J.
+// cached = 1: H_k kept by precond_prepare(..., cache = 1) for this J (float, per-node J).
+// flag (or null): receives 1 where a node's pivot is singular (n_x <= 8).
 template <typename T>
 hipError_t precond_inverse(birk_plan* p, int jac_kind, const double* J, const T* y, T* out,
                            T* jout, hipStream_t s, int* flag, int cached);
-// P^{-T} y for the instances with n_x <= 8 (backward wave scan, double); the instances
-// with larger n_x are left untouched (birk_kkt.hip covers them).  cached = 1: per-node
-// H_k laid out by precond_prepare(..., kPrepCache) in double for this J (read transposed).
-hipError_t precond_inverse_t_wave(birk_plan* p, int jac_kind, const double* J, const double* y, double* out,
-                                  hipStream_t s, int cached);
 int64_t pinv_scratch(int64_t Nn, int nx);
-int64_t pinv_jsw_size(int64_t Nn, int nx);
+int64_t pinv_jsw_size(int64_t Nn, int nx, birk_precision prec);
 // Build the per-n_x scan classes and the Krylov segmentation (after scan_off, jsw_off
 // and the weights exist); allocations are recorded in p->allocs.
 hipError_t plan_solve(birk_plan* p);
 // Per-J preparation of the inverse scan; must precede precond_inverse whenever J changes.
-// kPrepLarge: n_x > 8 lay H_k out in the level-0 slots (always needed there).
-// kPrepCache: n_x <= 8 with per-node J lay H_k out in the tile layout, read by
-// precond_inverse with cached = 1 (worth it from the second application with one J).
-// single = 1 lays the data out in float (for precond_inverse<float>), else in double.
-constexpr int kPrepLarge = 1, kPrepCache = 2;
-hipError_t precond_prepare(birk_plan* p, int jac_kind, const double* J, int single, hipStream_t s,
-                           int what);
+// single = 1 lays the data of n_x > 8 out in float (for precond_inverse<float>), else in
+// double; cache = 1 (float): H_k of n_x <= 8 kept in float for per-node J.
+hipError_t precond_prepare(birk_plan* p, int jac_kind, const double* J, int single, hipStream_t s, int cache);
+
+// ---- wave scans of the preconditioner, n_x <= kScanNx (birk_scan.hip) ----
+hipError_t plan_scan(birk_plan* p);
+int64_t scan_scratch(int64_t Nn, int nx);
+int64_t scan_htab(int64_t Nn, int nx);
+hipError_t scan_prepare(birk_plan* p, const double* J, hipStream_t s);
+template <typename T>
+hipError_t scan_inverse(birk_plan* p, int jac_kind, const double* J, const T* y, T* out, T* jout, int cached,
+                        hipStream_t s, int* flag);
+// P^{-T} y of the instances with n_x <= kScanNx (the others are left untouched).
+hipError_t scan_inverse_t(birk_plan* p, int jac_kind, const double* J, const double* y, double* out, hipStream_t s);
 
 // Krylov BLAS-1 launchers (birk_solve.hip).  Reductions accumulate in double.
 constexpr int kKryMaxDots = 32;
@@ -445,10 +465,9 @@ void gm_running(const birk_plan* p, const double* st, double* flags, hipStream_t
 // ---- the KKT form and MINRES (birk_kkt.hip) ----
 // Build the P^{-T} scan classes (after the weights exist).
 hipError_t plan_kkt(birk_plan* p);
-// x = P^{-T} y in double (scr: the plan's KKT scan scratch).  cached = 1: the per-node
-// H_k tables of precond_prepare(..., kPrepCache) (double) hold this J.
+// x = P^{-T} y in double (scr: the plan's KKT scan scratch).
 hipError_t precond_inverse_t(birk_plan* p, int jac_kind, const double* J, const double* y, double* x, double* scr,
-                             hipStream_t s, int cached = 0);
+                             hipStream_t s);
 // y_k = J_k^T x_k per node, double.
 hipError_t jac_t_times(birk_plan* p, int jac_kind, const double* J, const double* x, double* y, hipStream_t s);
 // MINRES on [[H, A^T], [A, 0]] [chi; lambda] = [f; g] (h or f null: identity, zero).

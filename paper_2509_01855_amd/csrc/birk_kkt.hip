@@ -623,12 +623,12 @@ hipError_t plan_kkt(birk_plan* p) {
 }
 
 hipError_t precond_inverse_t(birk_plan* p, int jac_kind, const double* J, const double* y, double* x, double* scr,
-                             hipStream_t s, int cached) {
-  // n_x <= 8: the backward wave scan of birk_solve.hip; larger n_x: the chunked scan here
-  hipError_t e = precond_inverse_t_wave(p, jac_kind, J, y, x, s, cached);
+                             hipStream_t s) {
+  // n_x <= 8: the backward wave scan of birk_scan.hip; larger n_x: the chunked scan here
+  hipError_t e = scan_inverse_t(p, jac_kind, J, y, x, s);
   if (e != hipSuccess) return e;
   for (const BtClass& bc : p->btclass) {
-    if (bc.nx <= 8) continue;
+    if (bc.nx <= kScanNx) continue;
     BIRK_NX_SWITCH(bc.nx, (bt_class<NX>(bc, J, jac_kind == BIRK_J_PER_NODE, y, x, scr, s)))
   }
   return hipGetLastError();
@@ -719,15 +719,15 @@ static hipError_t kkt_apply(birk_plan* p, int jk, const double* J, const double*
 
 // M^{-1} [r1; r2] = [r1 / h; P^{-T}(h * P^{-1} r2)] (P^{-1} prepared for J)
 static hipError_t kkt_prec(birk_plan* p, int jk, const double* J, const double* h, const double* r, double* z,
-                           double* scr, int use_precond, int cached, hipStream_t s) {
+                           double* scr, int use_precond, hipStream_t s) {
   const int64_t n = p->total_len;
   if (!use_precond) return hipMemcpyAsync(z, r, 2 * n * sizeof(double), hipMemcpyDeviceToDevice, s);
   hipLaunchKernelGGL(k_hscale, dim3(nb256(n)), dim3(256), 0, s, r, h, z, n, 1);
   double* t0 = (double*)p->tmp_vec[0];
-  hipError_t e = precond_inverse<double>(p, jk, J, r + n, t0, nullptr, s, nullptr, cached);
+  hipError_t e = precond_inverse<double>(p, jk, J, r + n, t0, nullptr, s, nullptr, 0);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_hscale, dim3(nb256(n)), dim3(256), 0, s, t0, h, t0, n, 0);
-  return precond_inverse_t(p, jk, J, t0, z + n, scr, s, cached);
+  return precond_inverse_t(p, jk, J, t0, z + n, scr, s);
 }
 
 // MINRES on the KKT system for every instance of the batch (arguments checked by the
@@ -756,20 +756,9 @@ birk_status kkt_solve(birk_plan* p, int jk, const double* J, const double* h, co
   } else if (e == hipSuccess) {
     e = hipMemsetAsync(b.x, 0, 2 * n * sizeof(double), s);
   }
-  if (e == hipSuccess && o->use_precond) e = precond_prepare(p, jk, J, 0, s, kPrepLarge);
+  if (e == hipSuccess && o->use_precond) e = precond_prepare(p, jk, J, 0, s, 0);
   if (e != hipSuccess) return BIRK_ERR_DEVICE;
-  // the first preconditioner application forms K_k on the fly; per-node H_k are cached
-  // before the second
-  int napp = 0;
-  auto prec = [&](const double* r, double* z) -> hipError_t {
-    if (o->use_precond && napp == 1) {
-      const hipError_t ee = precond_prepare(p, jk, J, 0, s, kPrepCache);
-      if (ee != hipSuccess) return ee;
-    }
-    const int cached = napp >= 1 ? 1 : 0;
-    ++napp;
-    return kkt_prec(p, jk, J, h, r, z, p->bt_scr, o->use_precond, cached, s);
-  };
+  auto prec = [&](const double* r, double* z) { return kkt_prec(p, jk, J, h, r, z, p->bt_scr, o->use_precond, s); };
   std::vector<double> hst((size_t)B * kSt), bn(B), rn(B), tolv(B);
   std::vector<int> run(B, 1), status(B, BIRK_OK), inner(B, 0), outer(B, 0);
   std::vector<char> done(B, 0);

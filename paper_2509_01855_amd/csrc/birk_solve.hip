@@ -13,10 +13,8 @@
 //                 S_{k+1} = S_k + w_k J_k xi_k.
 //             As an affine map of the carried sum, S_{k+1} = G_k S_k + h_k with
 //             G_k = I + w_k J_k K_k^{-1} and h_k = w_k J_k K_k^{-1} y_k.  The chain is
-//             evaluated as a scan of affine maps S_out = A S_in + b.  n_x <= 8: each
-//             thread holds whole maps; a DPP scan across waves, tile aggregates and
-//             tile start states (three launches), each node's K_k formed from J and
-//             w_k and factored where it is used.  Larger n_x: chunks of kChunk nodes
+//             evaluated as a scan of affine maps S_out = A S_in + b.  n_x <= 8:
+//             birk_scan.hip.  Larger n_x, here: chunks of kChunk nodes
 //             worked by sixteen-lane groups, groups of kFan aggregates per level up to a
 //             sequential top, start states pushed back down.  Either way each chunk is
 //             replayed from its start state, emitting xi_k and J_k xi_k (the latter
@@ -28,32 +26,13 @@
 #include <cmath>
 #include <type_traits>
 
+#include "birk_dense.h"
 #include "birk_internal.h"
 
 namespace birk {
 
 constexpr int kChunk = 16;
 constexpr int kFan = 16;
-
-// Lane P of each row of sixteen lanes, broadcast across its row (DPP row_newbcast: a VALU
-// move, in place of an LDS permute), for a double.
-template <int P>
-__device__ __forceinline__ double row_bcast(double v) {
-  const unsigned long long x = __builtin_bit_cast(unsigned long long, v);
-  const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)x, (int)(unsigned)x, 0x150 + P, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(x >> 32), (int)(unsigned)(x >> 32), 0x150 + P, 0xF, 0xF,
-                                             false);
-  return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
-
-// f(std::integral_constant<int, P>) for P = B .. E - 1, in order (compile-time lane indices).
-template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
 
 // ------------------------------------------------------------------ P y (forward)
 constexpr int kScanItems = 4;
@@ -345,70 +324,7 @@ hipError_t precond_forward(birk_plan* p, int jac_kind, const double* J, const T*
 
 // ------------------------------------------------------------------ P^{-1} y (inverse)
 
-// 1 / x from the hardware estimate and two Newton steps (within an ulp of the quotient;
-// several times cheaper than a division).
-__device__ __forceinline__ double recip(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = __builtin_fma(-x, r, 1.0);
-  r = __builtin_fma(r, e, r);
-  e = __builtin_fma(-x, r, 1.0);
-  return __builtin_fma(r, e, r);
-}
-
-// Unpivoted LU of K = I - (w/2) Jk in place, with reciprocal pivots.  K is strongly
-// diagonally dominant on the configurations of interest (w_k <= ~pi/N).  A pivot that
-// is non-finite, or not above 1e-13 times the scale 1 + |w/2| max|J_k| of K, marks K as
-// numerically singular in *flag.
-template <int NX>
-__device__ __forceinline__ void lu_kmat(double (&K)[NX][NX], double (&rp)[NX], int* flag, double scale) {
-#pragma unroll
-  for (int p = 0; p < NX; ++p) {
-    const double piv = K[p][p];
-    if (flag && (!(fabs(piv) > 1e-13 * scale) || !isfinite(piv))) atomicOr(flag, 1);
-    rp[p] = recip(piv);
-#pragma unroll
-    for (int i = p + 1; i < NX; ++i) {
-      const double f = K[i][p] * rp[p];
-      K[i][p] = f;
-#pragma unroll
-      for (int j = p + 1; j < NX; ++j) K[i][j] -= f * K[p][j];
-    }
-  }
-}
-
-template <int NX>
-__device__ __forceinline__ void lu_solve(const double (&K)[NX][NX], const double (&rp)[NX], double (&x)[NX]) {
-#pragma unroll
-  for (int i = 1; i < NX; ++i) {
-#pragma unroll
-    for (int j = 0; j < i; ++j) x[i] -= K[i][j] * x[j];
-  }
-#pragma unroll
-  for (int i = NX - 1; i >= 0; --i) {
-#pragma unroll
-    for (int j = i + 1; j < NX; ++j) x[i] -= K[i][j] * x[j];
-    x[i] *= rp[i];
-  }
-}
-
-template <int NX>
-__device__ __forceinline__ void load_jk(const double* __restrict__ J, int per_node, int64_t Nn, int64_t k,
-                                        double (&Jk)[NX][NX]) {
-#pragma unroll
-  for (int r = 0; r < NX; ++r)
-#pragma unroll
-    for (int c = 0; c < NX; ++c) Jk[r][c] = per_node ? J[((int64_t)(r * NX + c)) * Nn + k] : J[r * NX + c];
-}
-
-template <int NX>
-__device__ __forceinline__ void form_k(const double (&Jk)[NX][NX], double wk, double (&K)[NX][NX]) {
-#pragma unroll
-  for (int r = 0; r < NX; ++r)
-#pragma unroll
-    for (int c = 0; c < NX; ++c) K[r][c] = (r == c ? 1.0 : 0.0) - 0.5 * wk * Jk[r][c];
-}
-
-// ---- hierarchical path (n_x > kWaveNx): level-0 layout ----
+// ---- hierarchical path (n_x > 8): level-0 layout ----
 // Chunks of kChunk consecutive nodes are the level-0 slots (each worked by a group of
 // sixteen lanes).  Chunk c is child i = c % kFan of level-1 group g = c / kFan.  Slot
 // indices tau are laid out so that the
@@ -782,844 +698,6 @@ __global__ __launch_bounds__(256) void k_pinv_down(double* __restrict__ scan, co
   }
 }
 
-// ---- wave-scan path (n_x <= kWaveNx) ----
-// A tile is kTileThreads threads of kTC consecutive nodes each: thread t of tile g owns
-// chunk c = g kTileThreads + t, nodes k = c kTC + j (j < kTC), so the lanes of a wave
-// hold consecutive chunks in node order.  Per-node fields (the n_x^2 entries of H_k, then
-// w_k) are stored as [g][j][e][t]: each access of a wave is 64 consecutive values.
-// Three launches per class:
-//   reduce  each thread composes its chunk's node maps; a DPP scan across the wave and a
-//           4-lane scan of the wave totals give every chunk the map from the start of its
-//           tile through its last node (stored), the last of them the tile aggregate;
-//   tiles   one workgroup per instance scans the tile aggregates into tile start states;
-//   apply   each chunk advances its tile's start state by the stored map of the chunk
-//           before it and replays its nodes (no scan, few registers).
-// Nodes past N_n carry H = 0 (identity maps) and are neither read from y nor written.
-constexpr int kWaveNx = 8;
-constexpr int kTileThreads = 256;
-constexpr int kTC = 4;
-constexpr int64_t kTileNodes = (int64_t)kTileThreads * kTC;
-// Where the scan kernels take K_k from: formed from one J per instance (uniform), formed
-// from per-node J staged through LDS, or H_k = w_k J_k K_k^{-1} laid out once per J by
-// precond_prepare (k_tmake_h) and read coalesced, for solves that apply P^{-1} repeatedly.
-constexpr int kFlyConst = 0, kFlyPerNode = 1, kCachedH = 2;
-
-template <int NX>
-struct Aff {
-  double A[NX][NX];
-  double b[NX];
-};
-
-template <int NX>
-__device__ __forceinline__ void aff_identity(Aff<NX>& m) {
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-    m.b[r] = 0.0;
-#pragma unroll
-    for (int q = 0; q < NX; ++q) m.A[r][q] = (r == q) ? 1.0 : 0.0;
-  }
-}
-
-// s <- m(s) = A s + b
-template <int NX>
-__device__ __forceinline__ void aff_apply(const Aff<NX>& m, double (&s)[NX]) {
-  double ns[NX];
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-    double acc = m.b[r];
-#pragma unroll
-    for (int q = 0; q < NX; ++q) acc += m.A[r][q] * s[q];
-    ns[r] = acc;
-  }
-#pragma unroll
-  for (int r = 0; r < NX; ++r) s[r] = ns[r];
-}
-
-// v of the lane that DPP control CTRL selects, in the rows that ROWMASK enables
-// (row_shr:n = 0x110 + n, row_bcast:15 = 0x142, row_bcast:31 = 0x143); a lane with no
-// source keeps its own v.
-template <int CTRL, int ROWMASK>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const unsigned long long x = __builtin_bit_cast(unsigned long long, v);
-  const int lo = (int)(unsigned)x, hi = (int)(unsigned)(x >> 32);
-  const int rlo = __builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWMASK, 0xF, false);
-  const int rhi = __builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWMASK, 0xF, false);
-  return __builtin_bit_cast(double, ((unsigned long long)(unsigned)rhi << 32) | (unsigned)(unsigned)rlo);
-}
-
-// Where take: m <- m o e, e = the map of the source lane (applied first):
-// (A_m A_e, A_m b_e + b_m).  e arrives one row at a time.
-template <int NX, int CTRL, int ROWMASK>
-__device__ __forceinline__ void scan_step(Aff<NX>& m, bool take) {
-  double nA[NX][NX], nb[NX];
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-    nb[r] = m.b[r];
-#pragma unroll
-    for (int c = 0; c < NX; ++c) nA[r][c] = 0.0;
-  }
-#pragma unroll
-  for (int q = 0; q < NX; ++q) {
-    double er[NX];
-#pragma unroll
-    for (int c = 0; c < NX; ++c) er[c] = dpp_f64<CTRL, ROWMASK>(m.A[q][c]);
-    const double eb = dpp_f64<CTRL, ROWMASK>(m.b[q]);
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      const double a = m.A[r][q];
-#pragma unroll
-      for (int c = 0; c < NX; ++c) nA[r][c] += a * er[c];
-      nb[r] += a * eb;
-    }
-  }
-  if (take) {
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      m.b[r] = nb[r];
-#pragma unroll
-      for (int c = 0; c < NX; ++c) m.A[r][c] = nA[r][c];
-    }
-  }
-}
-
-// Inclusive scan of the lanes' maps in lane order: lane l ends with m_l o ... o m_0.
-// Rows of 16 lanes scan by row_shr 1, 2, 4, 8; row_bcast:15 then row_bcast:31 carry the
-// totals of the earlier rows.
-template <int NX>
-__device__ __forceinline__ void wave_scan(Aff<NX>& m) {
-  const int l = (int)(threadIdx.x & 63), lr = l & 15;
-  scan_step<NX, 0x111, 0xF>(m, lr >= 1);
-  scan_step<NX, 0x112, 0xF>(m, lr >= 2);
-  scan_step<NX, 0x114, 0xF>(m, lr >= 4);
-  scan_step<NX, 0x118, 0xF>(m, lr >= 8);
-  scan_step<NX, 0x142, 0xA>(m, ((l >> 4) & 1) != 0);
-  scan_step<NX, 0x143, 0xC>(m, l >= 32);
-}
-
-// K_k = I - (w_k / 2) J_k of node k, factored in place by lu_kmat (pivot check into *flag
-// when flag is set); entry (r, q) of J_k at Jp[(r NX + q) js] (per node in global memory:
-// Jp = J + k, js = N_n; staged in LDS: js = 64; one J for the instance: js = 1).  With u
-// given, also ju = J_k u (J is read once, for both).  TRJ: the same with J_k^T in place
-// of J_k (K_k^T = I - (w_k / 2) J_k^T, ju = J_k^T u).
-template <int NX, bool TRJ, typename P>
-__device__ __forceinline__ void node_lu(P Jp, int64_t js, double wk, double (&K)[NX][NX], double (&rp)[NX],
-                                        int* flag, const double* u, double* ju) {
-  double jmax = 0.0;
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-    double acc = 0.0;
-#pragma unroll
-    for (int q = 0; q < NX; ++q) {
-      const double jv = Jp[(int64_t)(TRJ ? q * NX + r : r * NX + q) * js];
-      if (flag) jmax = fmax(jmax, fabs(jv));
-      if (u) acc += jv * u[q];
-      K[r][q] = (r == q ? 1.0 : 0.0) - 0.5 * wk * jv;
-    }
-    if (u) ju[r] = acc;
-  }
-  lu_kmat<NX>(K, rp, flag, 1.0 + 0.5 * fabs(wk) * jmax);
-}
-
-// Per-node J staged through LDS: the kTC nodes of a chunk are consecutive, so a lane's
-// direct reads of J would be 32 bytes apart across the wave.  Instead each of kTC rounds
-// stages 64 consecutive nodes of the wave's 4 * 64 (J entry e of node 64 j + l at
-// lds[e * 64 + l], coalesced global reads), and the 16 lanes whose chunks lie in them
-// (lanes 16 j .. 16 j + 15) then work their nodes from LDS.
-// BACK: scan positions run from the last node down (position p is node N_n - 1 - p).
-// The loads of a round go to registers first (fetch_j), so that the next round's loads
-// can be in flight while the current round is worked; put_j then writes them to LDS.
-template <int NX, bool BACK>
-__device__ __forceinline__ void fetch_j(double (&v)[NX * NX], const double* __restrict__ Jn, int64_t Nn, int64_t kl) {
-  const int64_t k = BACK ? Nn - 1 - kl : kl;
-#pragma unroll
-  for (int e = 0; e < NX * NX; ++e) v[e] = (kl < Nn) ? Jn[(int64_t)e * Nn + k] : 0.0;
-}
-template <int NX>
-__device__ __forceinline__ void put_j(double* __restrict__ jw, const double (&v)[NX * NX], int l) {
-#pragma unroll
-  for (int e = 0; e < NX * NX; ++e) jw[e * 64 + l] = v[e];
-}
-
-// The map of one chunk, composed node by node from A = I, b = 0.  Node k takes
-// S -> S + w_k J_k K_k^{-1} (y_k + S); since w_k J_k = 2 (I - K_k), that is
-// S -> C_k S + (C_k - I) y_k with C_k = 2 K_k^{-1} - I, so with x = K_k^{-1} v
-//     A <- C_k A:  each column a of A becomes a + 2 (K_k^{-1} a - a),
-//     b <- C_k b + (C_k - I) y_k = b + 2 (K_k^{-1} u - u),  u = b + y_k,
-// which needs only the factors of K_k (no J_k and no H_k kept).  BACK (P^{-T}, backward
-// substitution with P^T from the last node, T the sum of the later x): node k takes
-// T -> T + K_k^{-T} (y_k + w_k J_k^T T) = C'_k T + K_k^{-T} y_k with C'_k = 2 K_k^{-T} - I,
-// so A as above with K_k^T, and b <- K_k^{-T} (2 b + y_k) - b.  Positions p = k0 + j run
-// over the nodes (node p, or N_n - 1 - p with BACK); positions past N_n are identity maps.
-template <int NX, bool BACK, typename P, typename T>
-__device__ __forceinline__ void chunk_map(P Jp, int64_t jstep, int64_t js, const double* __restrict__ w,
-                                          const T* __restrict__ yi, int64_t Nn, int64_t k0, Aff<NX>& m, int* flag) {
-#pragma unroll 1
-  for (int j = 0; j < kTC; ++j) {
-    const int64_t pos = k0 + j;
-    if (pos >= Nn) break;
-    const int64_t k = BACK ? Nn - 1 - pos : pos;
-    const double wk = w[k];
-    double K[NX][NX], rp[NX];
-    node_lu<NX, BACK>(Jp + j * jstep, js, wk, K, rp, flag, nullptr, nullptr);
-    double u[NX], x[NX];
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      const double yv = (double)yi[(int64_t)r * Nn + k];
-      u[r] = BACK ? 2.0 * m.b[r] + yv : m.b[r] + yv;
-      x[r] = u[r];
-    }
-    lu_solve<NX>(K, rp, x);
-#pragma unroll
-    for (int r = 0; r < NX; ++r) m.b[r] = BACK ? x[r] - m.b[r] : m.b[r] + 2.0 * (x[r] - u[r]);
-#pragma unroll
-    for (int c = 0; c < NX; ++c) {
-#pragma unroll
-      for (int r = 0; r < NX; ++r) x[r] = m.A[r][c];
-      lu_solve<NX>(K, rp, x);
-#pragma unroll
-      for (int r = 0; r < NX; ++r) m.A[r][c] += 2.0 * (x[r] - m.A[r][c]);
-    }
-  }
-}
-
-// Replay of a chunk from state s (FastPinvY box): per node u = y_k + S,
-// xi_k = K_k^{-1} u, (J xi)_k = K_k^{-1} (J_k u) (J_k commutes with K_k^{-1}),
-// S <- S + w_k (J xi)_k.  BACK (P^{-T}, from the last node): x_k = K_k^{-T} (y_k +
-// w_k J_k^T T), T <- T + x_k; ji is not written.
-// LOUT (J_k staged in LDS, one column of 64-strided entries per node): xi_k and (J xi)_k
-// go to entries 0..NX-1 and NX..2NX-1 of the node's own column, whose J_k has been read
-// by then, and the caller stores them coalesced after the round.
-template <int NX, bool BACK, bool LOUT = false, typename P, typename T>
-__device__ __forceinline__ void chunk_replay(P Jp, int64_t jstep, int64_t js, const double* __restrict__ w,
-                                             const T* __restrict__ yi, T* __restrict__ oi, T* __restrict__ ji,
-                                             int64_t Nn, int64_t k0, double (&s)[NX]) {
-#pragma unroll 1
-  for (int j = 0; j < kTC; ++j) {
-    const int64_t pos = k0 + j;
-    if (pos >= Nn) break;
-    const int64_t k = BACK ? Nn - 1 - pos : pos;
-    const double wk = w[k];
-    double u[NX], ju[NX], K[NX][NX], rp[NX];
-    if constexpr (BACK) {
-      node_lu<NX, true>(Jp + j * jstep, js, wk, K, rp, nullptr, s, ju);
-#pragma unroll
-      for (int r = 0; r < NX; ++r) u[r] = (double)yi[(int64_t)r * Nn + k] + wk * ju[r];
-      lu_solve<NX>(K, rp, u);
-#pragma unroll
-      for (int r = 0; r < NX; ++r) {
-        s[r] += u[r];
-        if constexpr (LOUT) Jp[j * jstep + (int64_t)r * js] = u[r];
-        else oi[(int64_t)r * Nn + k] = (T)u[r];
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < NX; ++r) u[r] = s[r] + (double)yi[(int64_t)r * Nn + k];
-      node_lu<NX, false>(Jp + j * jstep, js, wk, K, rp, nullptr, u, ju);
-      lu_solve<NX>(K, rp, u);
-      lu_solve<NX>(K, rp, ju);
-#pragma unroll
-      for (int r = 0; r < NX; ++r) {
-        s[r] += wk * ju[r];
-        if constexpr (LOUT) {
-          Jp[j * jstep + (int64_t)r * js] = u[r];
-          Jp[j * jstep + (int64_t)(NX + r) * js] = ju[r];
-        } else {
-          oi[(int64_t)r * Nn + k] = (T)u[r];
-          if (ji) ji[(int64_t)r * Nn + k] = (T)ju[r];
-        }
-      }
-    }
-  }
-}
-
-// The same replay from LDS-staged J_k for a whole wave, in round j of the staging
-// (positions kw + 64 j + c, c < 64, of which lane c read y and w coalesced into yc, wc):
-// lanes 16 j .. 16 j + 15 (act) replay their chunks, the node at column
-// c = 4 (l mod 16) + jj taking y and w from lane c by a shuffle, which every lane of the
-// wave executes; the other lanes run the same instructions on column 0 and change
-// nothing.  Outputs as with LOUT.
-template <int NX, bool BACK>
-__device__ __forceinline__ void chunk_replay_wave(double* __restrict__ jcol, bool act, const double (&yc)[NX],
-                                                  double wc, int64_t Nn, int64_t k0, double (&s)[NX]) {
-  const int l = (int)(threadIdx.x & 63);
-#pragma unroll 1
-  for (int j = 0; j < kTC; ++j) {
-    const int src = 4 * (l & 15) + j;
-    double yv[NX];
-#pragma unroll
-    for (int r = 0; r < NX; ++r) yv[r] = __shfl(yc[r], src, 64);
-    const double wk = __shfl(wc, src, 64);
-    const bool live = act && k0 + j < Nn;
-    double* Jp = jcol + j;
-    double u[NX], ju[NX], K[NX][NX], rp[NX];
-    if constexpr (BACK) {
-      node_lu<NX, true>(Jp, int64_t(64), wk, K, rp, nullptr, s, ju);
-#pragma unroll
-      for (int r = 0; r < NX; ++r) u[r] = yv[r] + wk * ju[r];
-      lu_solve<NX>(K, rp, u);
-      if (live) {
-#pragma unroll
-        for (int r = 0; r < NX; ++r) {
-          s[r] += u[r];
-          Jp[r * 64] = u[r];
-        }
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < NX; ++r) u[r] = s[r] + yv[r];
-      node_lu<NX, false>(Jp, int64_t(64), wk, K, rp, nullptr, u, ju);
-      lu_solve<NX>(K, rp, u);
-      lu_solve<NX>(K, rp, ju);
-      if (live) {
-#pragma unroll
-        for (int r = 0; r < NX; ++r) {
-          s[r] += wk * ju[r];
-          Jp[r * 64] = u[r];
-          Jp[(NX + r) * 64] = ju[r];
-        }
-      }
-    }
-  }
-}
-
-// The map of one chunk: node k takes S -> (I + H_k) S + H_k y_k, so from A = I, b = 0 the
-// first node gives (I + H, H y) and each further node A <- A + H A, b <- b + H (b + y).
-// hs points at the thread's slot of field 0, node 0 of its tile.
-// y of node j of the chunk, component r, at yb[r ystride + j] (global: yb = y + k0,
-// ystride = N_n; staged in LDS: the tile's y component-major).
-template <int NX, typename T>
-__device__ __forceinline__ void chunk_map_h(const T* __restrict__ hs, const T* __restrict__ yb, int64_t ystride,
-                                          int64_t Nn, int64_t k0, Aff<NX>& m) {
-  constexpr int E = NX * NX + 1;
-#pragma unroll 1
-  for (int j = 0; j < kTC; ++j) {
-    const int64_t k = k0 + j;
-    const T* base = hs + (int64_t)j * E * kTileThreads;
-    double H[NX][NX], yv[NX];
-#pragma unroll
-    for (int r = 0; r < NX; ++r)
-#pragma unroll
-      for (int q = 0; q < NX; ++q) H[r][q] = (double)base[(r * NX + q) * kTileThreads];
-#pragma unroll
-    for (int r = 0; r < NX; ++r) yv[r] = (k < Nn) ? (double)yb[(int64_t)r * ystride + j] : 0.0;
-    if (j == 0) {
-#pragma unroll
-      for (int r = 0; r < NX; ++r) {
-        double acc = 0.0;
-#pragma unroll
-        for (int q = 0; q < NX; ++q) {
-          m.A[r][q] = H[r][q] + ((r == q) ? 1.0 : 0.0);
-          acc += H[r][q] * yv[q];
-        }
-        m.b[r] = acc;
-      }
-    } else {
-      double u[NX];
-#pragma unroll
-      for (int r = 0; r < NX; ++r) u[r] = m.b[r] + yv[r];
-#pragma unroll
-      for (int r = 0; r < NX; ++r) {
-        double acc = 0.0;
-#pragma unroll
-        for (int q = 0; q < NX; ++q) acc += H[r][q] * u[q];
-        m.b[r] += acc;
-      }
-#pragma unroll
-      for (int c = 0; c < NX; ++c) {
-        double t[NX];
-#pragma unroll
-        for (int r = 0; r < NX; ++r) {
-          double acc = 0.0;
-#pragma unroll
-          for (int q = 0; q < NX; ++q) acc += H[r][q] * m.A[q][c];
-          t[r] = acc;
-        }
-#pragma unroll
-        for (int r = 0; r < NX; ++r) m.A[r][c] += t[r];
-      }
-    }
-  }
-}
-
-// Backward (P^{-T}) counterparts reading the same cached tables: position p is node
-// k = N_n - 1 - p, whose H_k sits in its own tile slot (tile k / kTileNodes, thread
-// (k / kTC) mod kTileThreads, node k mod kTC); G_k = H_k^T.  Node map (K_k^{-T} = I + G/2
-// and w_k J_k^T K_k^{-T} = G): T -> (I + G) T + (I + G / 2) y_k, so A <- A + G A and
-// b <- b + y_k + G (b + y_k / 2); replay x_k = y_k + G (T + y_k / 2), T <- T + x_k.
-template <typename T>
-__device__ __forceinline__ const T* node_slot(const T* __restrict__ tab, int64_t k, int E) {
-  return tab + (k / kTileNodes) * kTC * E * kTileThreads + (k % kTC) * E * kTileThreads + (k / kTC) % kTileThreads;
-}
-
-// yp: y of the chunk's positions, component r of position k0 + j at yp[r kTileNodes + j]
-// (the tile's y staged in LDS in position order).
-template <int NX, typename T>
-__device__ __forceinline__ void chunk_map_ht(const T* __restrict__ tab, const T* __restrict__ yp, int64_t Nn,
-                                             int64_t k0, Aff<NX>& m) {
-  constexpr int E = NX * NX + 1;
-#pragma unroll 1
-  for (int j = 0; j < kTC; ++j) {
-    const int64_t pos = k0 + j;
-    if (pos >= Nn) break;
-    const int64_t k = Nn - 1 - pos;
-    const T* base = node_slot<T>(tab, k, E);
-    double G[NX][NX], yv[NX], u[NX];
-#pragma unroll
-    for (int r = 0; r < NX; ++r)
-#pragma unroll
-      for (int q = 0; q < NX; ++q) G[r][q] = (double)base[(q * NX + r) * kTileThreads];
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      yv[r] = (double)yp[r * kTileNodes + j];
-      u[r] = m.b[r] + 0.5 * yv[r];
-    }
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      double acc = 0.0;
-#pragma unroll
-      for (int q = 0; q < NX; ++q) acc += G[r][q] * u[q];
-      m.b[r] += yv[r] + acc;
-    }
-#pragma unroll
-    for (int c = 0; c < NX; ++c) {
-      double t[NX];
-#pragma unroll
-      for (int r = 0; r < NX; ++r) {
-        double acc = 0.0;
-#pragma unroll
-        for (int q = 0; q < NX; ++q) acc += G[r][q] * m.A[q][c];
-        t[r] = acc;
-      }
-#pragma unroll
-      for (int r = 0; r < NX; ++r) m.A[r][c] += t[r];
-    }
-  }
-}
-
-// yp as in chunk_map_ht; x_k replaces y_k there (the caller stores the tile).
-template <int NX, typename T>
-__device__ __forceinline__ void chunk_replay_ht(const T* __restrict__ tab, T* __restrict__ yp, int64_t Nn, int64_t k0,
-                                                double (&s)[NX]) {
-  constexpr int E = NX * NX + 1;
-#pragma unroll 1
-  for (int j = 0; j < kTC; ++j) {
-    const int64_t pos = k0 + j;
-    if (pos >= Nn) break;
-    const int64_t k = Nn - 1 - pos;
-    const T* base = node_slot<T>(tab, k, E);
-    double yv[NX], u[NX], x[NX];
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      yv[r] = (double)yp[r * kTileNodes + j];
-      u[r] = s[r] + 0.5 * yv[r];
-    }
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      double acc = 0.0;
-#pragma unroll
-      for (int q = 0; q < NX; ++q) acc += (double)base[(q * NX + r) * kTileThreads] * u[q];
-      x[r] = yv[r] + acc;
-      yp[r * kTileNodes + j] = (T)x[r];
-    }
-#pragma unroll
-    for (int r = 0; r < NX; ++r) s[r] += x[r];
-  }
-}
-
-template <int NX>
-__device__ __forceinline__ void aff_store(double* __restrict__ o, const Aff<NX>& m) {
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-#pragma unroll
-    for (int q = 0; q < NX; ++q) o[r * NX + q] = m.A[r][q];
-    o[NX * NX + r] = m.b[r];
-  }
-}
-
-template <int NX>
-__device__ __forceinline__ void aff_load(const double* __restrict__ o, Aff<NX>& m) {
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-#pragma unroll
-    for (int q = 0; q < NX; ++q) m.A[r][q] = o[r * NX + q];
-    m.b[r] = o[NX * NX + r];
-  }
-}
-
-// H_k and w_k of every node in the tile layout, straight from J (per node or constant)
-// and the weights: K = I - (w_k / 2) J_k by unpivoted LU (pivot check as lu_kmat), then
-// H_k = K^{-1} (w_k J_k) column by column.  Slots of nodes past N_n are zeroed.  Each
-// of the kTC rounds of the workgroup takes kTileThreads consecutive nodes (coalesced
-// reads of J and w) and writes each node to its chunk's slot.  tile = (k, g).
-template <int NX, typename JT>
-__global__ __launch_bounds__(kTileThreads, 2) void k_tmake_h(JT* __restrict__ jsw, const double* __restrict__ J,
-                                                            int per_node, const PinvDesc* __restrict__ pd,
-                                                            const int2* __restrict__ tiles, int* flag) {
-  const int2 t = tiles[blockIdx.x];
-  const PinvDesc& d = pd[t.x];
-  const int64_t g = t.y;
-  constexpr int E = NX * NX + 1;
-  const int64_t Nn = d.Nn;
-  JT* tb = jsw + d.jsw_off + g * kTC * E * kTileThreads;
-  const double* Jn = J + d.joff;
-  const double* Jc = J + d.jcoff;
-#pragma unroll 1
-  for (int j = 0; j < kTC; ++j) {
-    const int i = j * kTileThreads + (int)threadIdx.x;  // node within the tile
-    const int64_t k = g * kTileNodes + i;
-    JT* base = tb + (int64_t)(i % kTC) * E * kTileThreads + i / kTC;
-    if (k >= Nn) {
-#pragma unroll
-      for (int e = 0; e < E; ++e) base[e * kTileThreads] = (JT)0;
-      continue;
-    }
-    const double wk = d.w[k];
-    double Jk[NX][NX], K[NX][NX], rp[NX];
-    double jmax = 0.0;
-#pragma unroll
-    for (int r = 0; r < NX; ++r)
-#pragma unroll
-      for (int q = 0; q < NX; ++q) {
-        const double jv = per_node ? Jn[(int64_t)(r * NX + q) * Nn + k] : Jc[r * NX + q];
-        Jk[r][q] = jv;
-        jmax = fmax(jmax, fabs(jv));
-        K[r][q] = (r == q ? 1.0 : 0.0) - 0.5 * wk * jv;
-      }
-    lu_kmat<NX>(K, rp, flag, 1.0 + 0.5 * fabs(wk) * jmax);
-#pragma unroll
-    for (int cc = 0; cc < NX; ++cc) {
-      double x[NX];
-#pragma unroll
-      for (int r = 0; r < NX; ++r) x[r] = wk * Jk[r][cc];
-      lu_solve<NX>(K, rp, x);
-#pragma unroll
-      for (int r = 0; r < NX; ++r) base[(r * NX + cc) * kTileThreads] = (JT)x[r];
-    }
-    base[(E - 1) * kTileThreads] = (JT)wk;
-  }
-}
-
-// A tile's y in position order (node k = tb + i, or N_n - 1 - tb - i with BACK) into
-// buf[r kTileNodes + i], coalesced; zeros past the instance.  And the store of buf back
-// to out in the same order.
-template <int NX, bool BACK, typename T>
-__device__ __forceinline__ void stage_tile(T* __restrict__ buf, const T* __restrict__ yi, int64_t Nn, int64_t tb) {
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-#pragma unroll
-    for (int q = 0; q < kTC; ++q) {
-      const int i = (int)threadIdx.x + q * kTileThreads;
-      const int64_t pos = tb + i;
-      buf[r * kTileNodes + i] = pos < Nn ? yi[(int64_t)r * Nn + (BACK ? Nn - 1 - pos : pos)] : T(0);
-    }
-  }
-}
-template <int NX, bool BACK, typename T>
-__device__ __forceinline__ void store_tile(const T* __restrict__ buf, T* __restrict__ oi, int64_t Nn, int64_t tb) {
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-#pragma unroll
-    for (int q = 0; q < kTC; ++q) {
-      const int i = (int)threadIdx.x + q * kTileThreads;
-      const int64_t pos = tb + i;
-      if (pos < Nn) oi[(int64_t)r * Nn + (BACK ? Nn - 1 - pos : pos)] = buf[r * kTileNodes + i];
-    }
-  }
-}
-
-// Tile maps: each chunk's map composed from its node maps, scanned across the wave by
-// DPP, then composed with the maps of the tile's earlier waves (a 4-lane scan of the wave
-// totals gives their prefixes), so chunk t holds the map of nodes 0 .. 4t + 3 of its tile.
-// These inclusive maps are stored as [g][field][t] (scan[tmap + g F 256 + f 256 + t]) and
-// the last one is the tile aggregate, stored field-major (scan[tagg + f ntile + g]) so
-// that the one-workgroup tile scan reads it coalesced.  tile = (k, g).
-template <int NX, int MODE, bool BACK, typename T>
-__global__ __launch_bounds__(kTileThreads, 2) void k_tscan_reduce(const double* __restrict__ J, const T* __restrict__ jsw,
-                                                             const T* __restrict__ y,
-                                                             const PinvDesc* __restrict__ pd,
-                                                             const int2* __restrict__ tiles,
-                                                             double* __restrict__ scan, int* flag) {
-  constexpr int F = NX * NX + NX;
-  constexpr int NW = kTileThreads / 64;
-  __shared__ double tot[NW][F];
-  __shared__ double jl[MODE == kFlyPerNode ? NW * 64 * NX * NX : 1];
-  __shared__ T yl[MODE == kCachedH ? NX * kTileNodes : 1];
-  const int2 t = tiles[blockIdx.x];
-  const PinvDesc& d = pd[t.x];
-  const int64_t g = t.y;
-  const int64_t k0 = (g * kTileThreads + threadIdx.x) * kTC;
-  const int w = (int)(threadIdx.x >> 6), l = (int)(threadIdx.x & 63);
-  double* cm = scan + d.tmap + g * F * kTileThreads + threadIdx.x;
-  {
-    Aff<NX> m;
-    aff_identity<NX>(m);
-    if constexpr (MODE == kFlyPerNode) {
-      double* jw = jl + w * 64 * NX * NX;
-      const int64_t kw = g * kTileNodes + (int64_t)w * 64 * kTC;
-      double pre[NX * NX];
-      fetch_j<NX, BACK>(pre, J + d.joff, d.Nn, kw + l);
-      for (int j = 0; j < kTC; ++j) {
-        put_j<NX>(jw, pre, l);
-        __syncthreads();
-        if (j + 1 < kTC) fetch_j<NX, BACK>(pre, J + d.joff, d.Nn, kw + 64 * (j + 1) + l);
-        if ((l >> 4) == j)
-          chunk_map<NX, BACK>(jw + (4 * l - 64 * j), int64_t(1), int64_t(64), d.w, y + d.off, d.Nn, k0, m, flag);
-        __syncthreads();
-      }
-    } else if constexpr (MODE == kFlyConst) {
-      chunk_map<NX, BACK>(J + d.jcoff, int64_t(0), int64_t(1), d.w, y + d.off, d.Nn, k0, m, flag);
-    } else {
-      // the tile's y staged coalesced through LDS (component-major, position order)
-      stage_tile<NX, BACK, T>(yl, y + d.off, d.Nn, g * kTileNodes);
-      __syncthreads();
-      if constexpr (BACK) {
-        chunk_map_ht<NX, T>(jsw + d.jsw_off, yl + (int)threadIdx.x * kTC, d.Nn, k0, m);
-      } else {
-        constexpr int E = NX * NX + 1;
-        chunk_map_h<NX, T>(jsw + d.jsw_off + g * kTC * E * kTileThreads + threadIdx.x, yl + (int)threadIdx.x * kTC,
-                           int64_t(kTileNodes), d.Nn, k0, m);
-      }
-    }
-    wave_scan<NX>(m);
-    if (l == 63) aff_store<NX>(&tot[w][0], m);
-#pragma unroll
-    for (int f = 0; f < F; ++f) cm[f * kTileThreads] = (f < NX * NX) ? m.A[f / NX][f % NX] : m.b[f - NX * NX];
-  }
-  __syncthreads();
-  if (w == 0) {
-    // lanes 1..NW-1 of wave 0 turn the wave totals into the maps of waves 0..l-1; within
-    // the wave every lane reads tot before any lane writes it
-    Aff<NX> p;
-    if (l >= 1 && l < NW)
-      aff_load<NX>(&tot[l - 1][0], p);
-    else
-      aff_identity<NX>(p);
-    scan_step<NX, 0x111, 0xF>(p, l >= 2);
-    scan_step<NX, 0x112, 0xF>(p, l >= 3);
-    if (l >= 1 && l < NW) aff_store<NX>(&tot[l][0], p);
-  }
-  __syncthreads();
-  if (w > 0) {
-    // the wave's maps, stored above, <- map o (map of the earlier waves); row r of the
-    // product needs row r of the map only
-    Aff<NX> q;
-    aff_load<NX>(&tot[w][0], q);
-    double last[F];
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      double a[NX];
-#pragma unroll
-      for (int c = 0; c < NX; ++c) a[c] = cm[(r * NX + c) * kTileThreads];
-      double nb = cm[(NX * NX + r) * kTileThreads];
-#pragma unroll
-      for (int c = 0; c < NX; ++c) {
-        nb += a[c] * q.b[c];
-        double v = 0.0;
-#pragma unroll
-        for (int u = 0; u < NX; ++u) v += a[u] * q.A[u][c];
-        cm[(r * NX + c) * kTileThreads] = v;
-        last[r * NX + c] = v;
-      }
-      cm[(NX * NX + r) * kTileThreads] = nb;
-      last[NX * NX + r] = nb;
-    }
-    if (threadIdx.x == kTileThreads - 1) {
-#pragma unroll
-      for (int f = 0; f < F; ++f) scan[d.tagg + f * d.ntile + g] = last[f];
-    }
-  }
-}
-
-
-// Tile start states of one instance (S = 0 before node 0), one workgroup of
-// tiles_threads<NX>() per instance: thread t composes the aggregates of tiles
-// [t q, t q + q), the maps are scanned across the workgroup, and each thread then walks
-// its tiles from its start state.  Aggregates and start states are field-major
-// ([field][tile]), so a wave's loads and stores touch a few cache lines rather than one
-// per lane: the whole scan runs on one CU, whose request rate bounds it.  512 threads
-// (fewer tiles per thread) where a thread's map fits two waves per SIMD, 256 above
-// n_x = 6.
-template <int NX>
-constexpr int tiles_threads() { return NX <= 6 ? 512 : 256; }
-
-template <int NX>
-__global__ __launch_bounds__(tiles_threads<NX>()) void k_tscan_tiles(double* __restrict__ scan,
-                                                                     const PinvDesc* __restrict__ pd) {
-  constexpr int F = NX * NX + NX;
-  constexpr int NT = tiles_threads<NX>();
-  __shared__ double tot[NT / 64][F];
-  const PinvDesc& d = pd[blockIdx.x];
-  const int64_t nt = d.ntile;
-  const int64_t q = (nt + NT - 1) / NT;
-  const int64_t i0 = (int64_t)threadIdx.x * q;
-  const int64_t i1 = min(nt, i0 + q);
-  const double* agg = scan + d.tagg;
-  Aff<NX> m;
-  aff_identity<NX>(m);
-  for (int64_t i = i0; i < i1; ++i) compose<NX>(agg + i, nt, m.A, m.b);
-  wave_scan<NX>(m);
-  const int w = (int)(threadIdx.x >> 6), l = (int)(threadIdx.x & 63);
-  if (l == 63) aff_store<NX>(&tot[w][0], m);
-  __syncthreads();
-  double s[NX];
-#pragma unroll
-  for (int r = 0; r < NX; ++r) s[r] = 0.0;
-  for (int v = 0; v < w; ++v) advance<NX>(&tot[v][0], 1, s);
-  double x[NX];
-#pragma unroll
-  for (int r = 0; r < NX; ++r) x[r] = s[r];
-  aff_apply<NX>(m, x);
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-    const double up = __shfl_up(x[r], 1);
-    s[r] = (l == 0) ? s[r] : up;
-  }
-  double* st = scan + d.tst;
-  for (int64_t i = i0; i < i1; ++i) {
-#pragma unroll
-    for (int r = 0; r < NX; ++r) st[r * nt + i] = s[r];
-    advance<NX>(agg + i, nt, s);
-  }
-}
-
-// Replay of one tile: chunk t starts from the tile start state advanced by the inclusive
-// map of chunk t - 1 (k_tscan_reduce), then replays its nodes (chunk_replay); K_k is
-// formed and factored here again from J_k and w_k.  tile = (k, g).
-template <int NX, int MODE, bool BACK, typename T>
-__global__ __launch_bounds__(kTileThreads) void k_tscan_apply(const double* __restrict__ J, const T* __restrict__ jsw,
-                                                            const T* __restrict__ y,
-                                                            const PinvDesc* __restrict__ pd,
-                                                            const int2* __restrict__ tiles,
-                                                            const double* __restrict__ scan, T* __restrict__ out,
-                                                            T* __restrict__ jout) {
-  constexpr int F = NX * NX + NX;
-  constexpr int NW = kTileThreads / 64;
-  __shared__ double jl[MODE == kFlyPerNode ? NW * 64 * NX * NX : 1];
-  // cached H, forward: the tile's y (component-major, node i of the tile at io[r][i]) and
-  // then its xi, so that both move coalesced
-  __shared__ T io[MODE == kCachedH ? NX * kTileNodes : 1];
-  const int2 t = tiles[blockIdx.x];
-  const PinvDesc& d = pd[t.x];
-  const int64_t g = t.y;
-  const int64_t Nn = d.Nn;
-  const int64_t k0 = (g * kTileThreads + threadIdx.x) * kTC;
-  double s[NX];
-#pragma unroll
-  for (int r = 0; r < NX; ++r) s[r] = scan[d.tst + r * d.ntile + g];
-  if (threadIdx.x > 0 && k0 < Nn) {
-    const double* cm = scan + d.tmap + g * F * kTileThreads + (threadIdx.x - 1);
-    double ns[NX];
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      double acc = cm[(NX * NX + r) * kTileThreads];
-#pragma unroll
-      for (int c = 0; c < NX; ++c) acc += cm[(r * NX + c) * kTileThreads] * s[c];
-      ns[r] = acc;
-    }
-#pragma unroll
-    for (int r = 0; r < NX; ++r) s[r] = ns[r];
-  }
-  const T* yi = y + d.off;
-  T* oi = out + d.off;
-  T* ji = jout ? jout + d.off : nullptr;
-  if constexpr (MODE == kFlyPerNode) {
-    // every thread takes part in the staging rounds (no early exit before the barriers)
-    const int w = (int)(threadIdx.x >> 6), l = (int)(threadIdx.x & 63);
-    double* jw = jl + w * 64 * NX * NX;
-    const int64_t kw = g * kTileNodes + (int64_t)w * 64 * kTC;
-    double pre[NX * NX];
-    fetch_j<NX, BACK>(pre, J + d.joff, Nn, kw + l);
-    // the round's outputs come back through the LDS columns (xi in entries 0..NX-1, J xi in
-    // NX..2NX-1) and are stored coalesced, lane l taking node kw + 64 j + l; each lane then
-    // writes only its own column in the next put_j, so no barrier is needed between
-    // (n_x >= 2) y and w are read coalesced with the staged J, one round ahead, and handed
-    // to the replaying lanes by shuffles (chunk_replay_wave)
-    constexpr bool kLout = 2 * NX <= NX * NX;
-    double ypre[NX], wpre = 0.0;
-    if constexpr (kLout) {
-      const int64_t pos = kw + l;
-      const int64_t k = BACK ? Nn - 1 - pos : pos;
-#pragma unroll
-      for (int r = 0; r < NX; ++r) ypre[r] = pos < Nn ? (double)yi[(int64_t)r * Nn + k] : 0.0;
-      wpre = pos < Nn ? d.w[k] : 0.0;
-    }
-    for (int j = 0; j < kTC; ++j) {
-      put_j<NX>(jw, pre, l);
-      double ycur[NX];
-#pragma unroll
-      for (int r = 0; r < NX; ++r) ycur[r] = kLout ? ypre[r] : 0.0;
-      const double wcur = wpre;
-      __syncthreads();
-      if (j + 1 < kTC) {
-        fetch_j<NX, BACK>(pre, J + d.joff, Nn, kw + 64 * (j + 1) + l);
-        if constexpr (kLout) {
-          const int64_t pos = kw + 64 * (j + 1) + l;
-          const int64_t k = BACK ? Nn - 1 - pos : pos;
-#pragma unroll
-          for (int r = 0; r < NX; ++r) ypre[r] = pos < Nn ? (double)yi[(int64_t)r * Nn + k] : 0.0;
-          wpre = pos < Nn ? d.w[k] : 0.0;
-        }
-      }
-      const bool act = (l >> 4) == j;
-      if constexpr (kLout) {
-        chunk_replay_wave<NX, BACK>(jw + (act ? 4 * l - 64 * j : 0), act, ycur, wcur, Nn, k0, s);
-      } else if (act) {
-        chunk_replay<NX, BACK>(jw + (4 * l - 64 * j), int64_t(1), int64_t(64), d.w, yi, oi, ji, Nn, k0, s);
-      }
-      __syncthreads();
-      if constexpr (kLout) {
-        const int64_t pos = kw + 64 * j + l;
-        if (pos < Nn) {
-          const int64_t k = BACK ? Nn - 1 - pos : pos;
-#pragma unroll
-          for (int r = 0; r < NX; ++r) oi[(int64_t)r * Nn + k] = (T)jw[r * 64 + l];
-          if (!BACK && ji) {
-#pragma unroll
-            for (int r = 0; r < NX; ++r) ji[(int64_t)r * Nn + k] = (T)jw[(NX + r) * 64 + l];
-          }
-        }
-      }
-    }
-  } else if constexpr (MODE == kFlyConst) {
-    chunk_replay<NX, BACK>(J + d.jcoff, int64_t(0), int64_t(1), d.w, yi, oi, ji, Nn, k0, s);
-  } else {
-    // H_k from precond_prepare: v = H_k u, xi_k = u + v / 2, (J xi)_k = v / w_k, S <- S + v
-    const int64_t tb = g * kTileNodes;  // first position of the tile
-    stage_tile<NX, BACK, T>(io, yi, Nn, tb);
-    __syncthreads();
-    if constexpr (BACK) {
-      chunk_replay_ht<NX, T>(jsw + d.jsw_off, io + (int)threadIdx.x * kTC, Nn, k0, s);
-      __syncthreads();
-      store_tile<NX, true, T>(io, oi, Nn, tb);
-      return;
-    }
-    constexpr int E = NX * NX + 1;
-    const T* hs = jsw + d.jsw_off + g * kTC * E * kTileThreads + threadIdx.x;
-    const int i0 = (int)threadIdx.x * kTC;
-#pragma unroll 1
-    for (int j = 0; j < kTC; ++j) {
-      const int64_t k = k0 + j;
-      if (k >= Nn) break;
-      const T* base = hs + (int64_t)j * E * kTileThreads;
-      const double inv_w = 1.0 / (double)base[(E - 1) * kTileThreads];
-      double u[NX];
-#pragma unroll
-      for (int r = 0; r < NX; ++r) u[r] = s[r] + (double)io[r * kTileNodes + i0 + j];
-#pragma unroll
-      for (int r = 0; r < NX; ++r) {
-        double v = 0.0;
-#pragma unroll
-        for (int q = 0; q < NX; ++q) v += (double)base[(r * NX + q) * kTileThreads] * u[q];
-        s[r] += v;
-        io[r * kTileNodes + i0 + j] = (T)(u[r] + 0.5 * v);
-        if (ji) ji[(int64_t)r * Nn + k] = (T)(v * inv_w);
-      }
-    }
-    __syncthreads();
-    store_tile<NX, false, T>(io, oi, Nn, tb);
-  }
-}
-
 // Replay for n_x > 8, sixteen lanes per chunk: lane r < NX carries component r of the
 // state; per node u_r = y_r + S_r, v_r = (H_k u)_r with u gathered across the group,
 // xi_r = u_r + v_r / 2, (J xi)_r = v_r / w_k, S_r <- S_r + v_r, from the chunk's level-0
@@ -1749,10 +827,9 @@ static int64_t pinv_blocks0(int64_t nchunks) {
   return (groups + 63) / 64;
 }
 
-static int64_t pinv_tiles(int64_t Nn) { return (Nn + kTileNodes - 1) / kTileNodes; }
-
-int64_t pinv_jsw_size(int64_t Nn, int nx) {
-  if (nx <= kWaveNx) return pinv_tiles(Nn) * kTileNodes * ((int64_t)nx * nx + 1);
+int64_t pinv_jsw_size(int64_t Nn, int nx, birk_precision prec) {
+  if (nx > 12) return 0;   // no preconditioner
+  if (nx <= kScanNx) return prec == BIRK_F32_REFINE_F64 ? scan_htab(Nn, nx) : 0;
   int64_t cnt[kPinvMaxLevels];
   pinv_levels(Nn, cnt);
   return pinv_blocks0(cnt[0]) * 64 * kFan * kChunk * (((int64_t)nx * nx + 4) & ~int64_t(3));  // hrec<nx>()
@@ -1760,8 +837,9 @@ int64_t pinv_jsw_size(int64_t Nn, int nx) {
 
 // Scratch (doubles) the inverse scan needs for one instance (level 0 in whole blocks).
 int64_t pinv_scratch(int64_t Nn, int nx) {
+  if (nx > 12) return 0;
   const int64_t S = (int64_t)nx * nx + 2 * nx;
-  if (nx <= kWaveNx) return pinv_tiles(Nn) * (S + ((int64_t)nx * nx + nx) * kTileThreads);
+  if (nx <= kScanNx) return scan_scratch(Nn, nx);
   int64_t cnt[kPinvMaxLevels];
   const int L = pinv_levels(Nn, cnt);
   int64_t tot = pinv_blocks0(cnt[0]) * 64 * kFan * S;
@@ -1825,12 +903,7 @@ hipError_t plan_solve(birk_plan* p) {
       d.w = in.w;
       const int64_t S = (int64_t)nx * nx + nx;
       int64_t base = in.scan_off;
-      if (nx <= kWaveNx) {
-        // scratch: tile aggregates, tile start states, inclusive chunk maps per tile
-        d.ntile = pinv_tiles(in.Nn);
-        d.tagg = base;
-        d.tst = base + d.ntile * S;
-        d.tmap = d.tst + d.ntile * nx;
+      if (nx <= kScanNx) {   // J x only; P^{-1} is birk_scan.hip's
         pc.host.push_back(d);
         continue;
       }
@@ -1849,11 +922,10 @@ hipError_t plan_solve(birk_plan* p) {
     }
     if (pc.host.empty()) continue;
     pc.ninst = (int)pc.host.size();
-    std::vector<int2> t0, tn, tt, tup[kPinvMaxLevels];
+    std::vector<int2> t0, tn, tup[kPinvMaxLevels];
     for (int k = 0; k < pc.ninst; ++k) {
       const PinvDesc& d = pc.host[k];
-      if (nx <= kWaveNx) {
-        for (int64_t g = 0; g < d.ntile; ++g) tt.push_back(make_int2(k, (int)g));
+      if (nx <= kScanNx) {
         for (unsigned b = 0; b < nblocks(d.Nn, 256); ++b) tn.push_back(make_int2(k, (int)b));
         continue;
       }
@@ -1874,8 +946,6 @@ hipError_t plan_solve(birk_plan* p) {
     pc.n_node0 = (int)t0.size();
     if ((e = upload_tiles(p, tn, &pc.t_nodes)) != hipSuccess) return e;
     pc.n_nodes = (int)tn.size();
-    if ((e = upload_tiles(p, tt, &pc.t_tile)) != hipSuccess) return e;
-    pc.n_tile = (int)tt.size();
     for (int l = 0; l < pc.Lmax; ++l) {
       if ((e = upload_tiles(p, tup[l], &pc.t_up[l])) != hipSuccess) return e;
       pc.n_up[l] = (int)tup[l].size();
@@ -1914,15 +984,9 @@ hipError_t plan_solve(birk_plan* p) {
 }
 
 template <int NX, typename JT>
-static void make_h_class(birk_plan* p, const PinvClass& pc, const double* J, int pn, int what, hipStream_t s) {
-  if constexpr (NX <= kWaveNx) {
-    // per-node J applied repeatedly: H_k cached in the tile layout; otherwise the scan
-    // kernels form K_k from J and w_k themselves
-    if (pn && (what & kPrepCache))
-      hipLaunchKernelGGL((k_tmake_h<NX, JT>), dim3(pc.n_tile), dim3(kTileThreads), 0, s, (JT*)p->jsw, J, pn, pc.dev,
-                         pc.t_tile, p->flag);
-  } else {
-    if (!(what & kPrepLarge) || pc.n_node0 == 0) return;
+static void make_h_class(birk_plan* p, const PinvClass& pc, const double* J, int pn, hipStream_t s) {
+  if constexpr (NX > kScanNx) {
+    if (pc.n_node0 == 0) return;
     hipLaunchKernelGGL((k_make_h_rows<NX, JT>), dim3(pc.n_node0, 16), dim3(256), 0, s, (JT*)p->jsw, J, pn, pc.dev,
                        pc.t_node0, p->flag);
   }
@@ -1945,56 +1009,31 @@ static void make_h_class(birk_plan* p, const PinvClass& pc, const double* J, int
     default: return hipErrorInvalidValue;                              \
   }
 
-// Per-Jacobian preparation of the scan: n_x > kWaveNx lay J and w out in the level-0
-// slots and replace the J fields by H_k (k_make_h_rows), which their scan kernels read.
-// n_x <= kWaveNx with per-node J and kPrepCache (a solve, before its second application)
-// cache H_k in the tile layout (k_tmake_h: one pass that turns the later applications'
-// staged J reads and per-node factorisations into coalesced H_k reads); otherwise they
-// need nothing.  what: kPrepLarge, kPrepCache or both.
-hipError_t precond_prepare(birk_plan* p, int jac_kind, const double* J, int single, hipStream_t s, int what) {
+// Per-Jacobian preparation of the scan: n_x > 8 lay J and w out in the level-0 slots and
+// replace the J fields by H_k (k_make_h_rows), which their scan kernels read.  n_x <= 8 with
+// per-node J in float (a mixed solve) keep H_k in float, half the bytes of J; otherwise they
+// need nothing.
+hipError_t precond_prepare(birk_plan* p, int jac_kind, const double* J, int single, hipStream_t s, int cache) {
   const int pn = jac_kind == BIRK_J_PER_NODE ? 1 : 0;
   for (const PinvClass& pc : p->pclass) {
     if (single) {
-      BIRK_NX_SWITCH(pc.nx, (make_h_class<NXC, float>(p, pc, J, pn, what, s)))
+      BIRK_NX_SWITCH(pc.nx, (make_h_class<NXC, float>(p, pc, J, pn, s)))
     } else {
-      BIRK_NX_SWITCH(pc.nx, (make_h_class<NXC, double>(p, pc, J, pn, what, s)))
+      BIRK_NX_SWITCH(pc.nx, (make_h_class<NXC, double>(p, pc, J, pn, s)))
     }
+  }
+  if (cache && pn) {
+    const hipError_t e = scan_prepare(p, J, s);
+    if (e != hipSuccess) return e;
   }
   return hipGetLastError();
 }
 
 template <int NX, typename T>
-static void pinv_class(birk_plan* p, const PinvClass& pc, const double* J, int pn, int cached, const T* y, T* out,
-                       T* jout, hipStream_t s) {
-  const T* jsw = (const T*)p->jsw;
-  double* scan = p->scan;
-  if constexpr (NX <= kWaveNx) {
-    const dim3 grid(pc.n_tile), block(kTileThreads);
-    if (!pn) {
-      hipLaunchKernelGGL((k_tscan_reduce<NX, kFlyConst, false, T>), grid, block, 0, s, J, jsw, y, pc.dev, pc.t_tile, scan,
-                         p->flag);
-    } else if (cached) {
-      hipLaunchKernelGGL((k_tscan_reduce<NX, kCachedH, false, T>), grid, block, 0, s, J, jsw, y, pc.dev, pc.t_tile, scan,
-                         p->flag);
-    } else {
-      hipLaunchKernelGGL((k_tscan_reduce<NX, kFlyPerNode, false, T>), grid, block, 0, s, J, jsw, y, pc.dev, pc.t_tile, scan,
-                         p->flag);
-    }
-    hipLaunchKernelGGL((k_tscan_tiles<NX>), dim3(pc.ninst), dim3(tiles_threads<NX>()), 0, s, scan, pc.dev);
-    if (!pn) {
-      hipLaunchKernelGGL((k_tscan_apply<NX, kFlyConst, false, T>), grid, block, 0, s, J, jsw, y, pc.dev, pc.t_tile, scan, out,
-                         jout);
-    } else if (cached) {
-      hipLaunchKernelGGL((k_tscan_apply<NX, kCachedH, false, T>), grid, block, 0, s, J, jsw, y, pc.dev, pc.t_tile, scan, out,
-                         jout);
-    } else {
-      hipLaunchKernelGGL((k_tscan_apply<NX, kFlyPerNode, false, T>), grid, block, 0, s, J, jsw, y, pc.dev, pc.t_tile, scan,
-                         out, jout);
-    }
-  } else {
-    (void)J;
-    (void)pn;
-    (void)cached;
+static void pinv_class(birk_plan* p, const PinvClass& pc, const T* y, T* out, T* jout, hipStream_t s) {
+  if constexpr (NX > kScanNx) {
+    const T* jsw = (const T*)p->jsw;
+    double* scan = p->scan;
     hipLaunchKernelGGL((k_pinv_up0<NX, T>), dim3(pc.n_node0, 16), dim3(256), 0, s, jsw, y, pc.dev, pc.t_node0, scan);
     for (int l = 0; l < pc.Lmax; ++l)
       hipLaunchKernelGGL((k_pinv_up<NX>), dim3(pc.n_up[l], 16), dim3(256), 0, s, scan, pc.dev, pc.t_up[l], l);
@@ -2016,57 +1055,12 @@ template <typename T>
 hipError_t precond_inverse(birk_plan* p, int jac_kind, const double* J, const T* y, T* out, T* jout,
                            hipStream_t s, int* flag, int cached) {
   // n_x <= 8: K_k formed from J and factored inside the scan kernels (pivot checks into
-  // the plan's flag), or, per-node J with cached = 1, the H_k that precond_prepare laid
-  // out with kPrepCache; larger n_x read the H_k that precond_prepare laid out for this
-  // J with kPrepLarge (checking the pivots there)
-  (void)flag;
-  const int pn = jac_kind == BIRK_J_PER_NODE ? 1 : 0;
+  // *flag when given), or with cached = 1 the H_k that precond_prepare kept; larger n_x
+  // read the H_k that precond_prepare laid out for this J (checking the pivots there)
+  hipError_t e = scan_inverse<T>(p, jac_kind, J, y, out, jout, cached, s, flag);
+  if (e != hipSuccess) return e;
   for (const PinvClass& pc : p->pclass) {
-    BIRK_NX_SWITCH(pc.nx, (pinv_class<NXC, T>(p, pc, J, pn, cached, y, out, jout, s)))
-  }
-  return hipGetLastError();
-}
-
-// P^{-T} y for the classes with n_x <= kWaveNx: the same three launches run backwards over
-// the nodes with K_k^T (double only; the classes above are left to the caller).
-template <int NX>
-static void pinv_t_class(birk_plan* p, const PinvClass& pc, const double* J, int pn, int cached, const double* y,
-                         double* out, hipStream_t s) {
-  if constexpr (NX <= kWaveNx) {
-    const dim3 grid(pc.n_tile), block(kTileThreads);
-    const double* jsw = (const double*)p->jsw;
-    if (pn && cached) {
-      hipLaunchKernelGGL((k_tscan_reduce<NX, kCachedH, true, double>), grid, block, 0, s, J, jsw, y, pc.dev,
-                         pc.t_tile, p->scan, p->flag);
-    } else if (pn) {
-      hipLaunchKernelGGL((k_tscan_reduce<NX, kFlyPerNode, true, double>), grid, block, 0, s, J, jsw, y, pc.dev,
-                         pc.t_tile, p->scan, p->flag);
-    } else {
-      hipLaunchKernelGGL((k_tscan_reduce<NX, kFlyConst, true, double>), grid, block, 0, s, J, jsw, y, pc.dev,
-                         pc.t_tile, p->scan, p->flag);
-    }
-    hipLaunchKernelGGL((k_tscan_tiles<NX>), dim3(pc.ninst), dim3(tiles_threads<NX>()), 0, s, p->scan, pc.dev);
-    if (pn && cached) {
-      hipLaunchKernelGGL((k_tscan_apply<NX, kCachedH, true, double>), grid, block, 0, s, J, jsw, y, pc.dev,
-                         pc.t_tile, p->scan, out, nullptr);
-    } else if (pn) {
-      hipLaunchKernelGGL((k_tscan_apply<NX, kFlyPerNode, true, double>), grid, block, 0, s, J, jsw, y, pc.dev,
-                         pc.t_tile, p->scan, out, nullptr);
-    } else {
-      hipLaunchKernelGGL((k_tscan_apply<NX, kFlyConst, true, double>), grid, block, 0, s, J, jsw, y, pc.dev,
-                         pc.t_tile, p->scan, out, nullptr);
-    }
-  } else {
-    (void)p, (void)pc, (void)J, (void)pn, (void)cached, (void)y, (void)out, (void)s;
-  }
-}
-
-hipError_t precond_inverse_t_wave(birk_plan* p, int jac_kind, const double* J, const double* y, double* out,
-                                  hipStream_t s, int cached) {
-  const int pn = jac_kind == BIRK_J_PER_NODE ? 1 : 0;
-  for (const PinvClass& pc : p->pclass) {
-    if (pc.nx > kWaveNx) continue;
-    BIRK_NX_SWITCH(pc.nx, (pinv_t_class<NXC>(p, pc, J, pn, cached, y, out, s)))
+    BIRK_NX_SWITCH(pc.nx, (pinv_class<NXC, T>(p, pc, y, out, jout, s)))
   }
   return hipGetLastError();
 }

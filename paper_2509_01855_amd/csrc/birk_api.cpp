@@ -80,7 +80,7 @@ void free_plan(birk_plan* p) {
   for (void* q : p->tmp_vec) if (q) (void)hipFree(q);
   if (p->partials) (void)hipFree(p->partials);
   if (p->scan) (void)hipFree(p->scan);
-  if (p->jsw) (void)hipFree(p->jsw);
+  if (p->htab) (void)hipFree(p->htab);
   if (p->krylov_Q) (void)hipFree(p->krylov_Q);
   if (p->krylov_vec) (void)hipFree(p->krylov_vec);
   if (p->newton_buf) (void)hipFree(p->newton_buf);
@@ -252,7 +252,7 @@ birk_status birk_plan_create(birk_plan** out, int32_t batch, const int64_t* n_no
     if (st) p->fast_kn.streams = std::max(1, std::min(1 + birk_plan::kExtraStreams, std::atoi(st)));
   }
   p->inst.resize(batch);
-  int64_t off = 0, joff = 0, jcoff = 0, soff = 0, jswoff = 0;
+  int64_t off = 0, joff = 0, jcoff = 0, soff = 0, hoff = 0;
   for (int i = 0; i < batch; ++i) {
     Instance& in = p->inst[i];
     in.Nn = n_nodes_host[i];
@@ -265,15 +265,14 @@ birk_status birk_plan_create(birk_plan** out, int32_t batch, const int64_t* n_no
     off += in.Nn * in.nx;
     joff += in.Nn * in.nx * in.nx;
     jcoff += (int64_t)in.nx * in.nx;
-    soff += pinv_scratch(in.Nn, in.nx) + (int64_t)in.nx * ((in.Nn + 1023) / 1024) + 64;
-    in.jsw_off = jswoff;
-    jswoff += pinv_jsw_size(in.Nn, in.nx, prec);
+    soff += scan_scratch(in.Nn, in.nx) + (int64_t)in.nx * ((in.Nn + 1023) / 1024) + 64;
+    in.htab_off = hoff;
+    hoff += scan_htab(in.Nn, in.nx, prec);
   }
   p->total_len = off;
   p->total_jnode = joff;
   p->total_jconst = jcoff;
   p->total_scan = soff;
-  p->total_jsw = jswoff;
   // product schedule: three-pass groups and the general-path pair sets
   plan_products(p);
   const int64_t woff = std::max<int64_t>(p->total_work, 1), poff = p->total_part;
@@ -285,7 +284,7 @@ birk_status birk_plan_create(birk_plan** out, int32_t batch, const int64_t* n_no
   for (int b = 0; b < 4 && e == hipSuccess; ++b) e = hipMalloc(&p->tmp_vec[b], off * sizeof(double));
   if (e == hipSuccess) e = hipMalloc(&p->partials, std::max<int64_t>(poff, 1) * sizeof(double));
   if (e == hipSuccess) e = hipMalloc(&p->scan, std::max<int64_t>(soff, 1) * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&p->jsw, std::max<int64_t>(jswoff, 1) * sizeof(double));
+  if (e == hipSuccess) e = hipMalloc(&p->htab, std::max<int64_t>(hoff, 1) * sizeof(float));
   if (e == hipSuccess) e = hipMalloc(&p->flag, sizeof(int));
   // extra streams (default priority) for the multi-stream schedule of the three-pass groups
   if (e == hipSuccess && !p->fgroups.empty()) {
@@ -319,7 +318,6 @@ birk_status birk_plan_create(birk_plan** out, int32_t batch, const int64_t* n_no
   if (e == hipSuccess) e = plan_instances(p);
   if (e == hipSuccess) e = plan_solve(p);
   if (e == hipSuccess) e = plan_scan(p);
-  if (e == hipSuccess) e = plan_kkt(p);
   if (e != hipSuccess) {
     free_plan(p);
     return dev_err(e);
@@ -511,18 +509,14 @@ birk_status birk_precond(birk_plan* p, birk_jac_kind jk, const double* J, const 
   DeviceGuard g(p->device);
   hipError_t e;
   if (inverse == 2) {
-    e = precond_inverse_t(p, jk, J, (const double*)y, (double*)out, p->bt_scr, p->stream);
+    e = scan_inverse_t(p, jk, J, (const double*)y, (double*)out, p->stream);
     return e == hipSuccess ? BIRK_OK : BIRK_ERR_DEVICE;
   }
-  if (inverse) {
-    e = precond_prepare(p, jk, J, p->prec == BIRK_F64 ? 0 : 1, p->stream, 0);
-    if (e != hipSuccess) return BIRK_ERR_DEVICE;
-  }
   if (p->prec == BIRK_F64) {
-    e = inverse ? precond_inverse<double>(p, jk, J, (const double*)y, (double*)out, nullptr, p->stream, nullptr, 0)
+    e = inverse ? scan_inverse<double>(p, jk, J, (const double*)y, (double*)out, nullptr, 0, p->stream, nullptr)
                 : precond_forward<double>(p, jk, J, (const double*)y, (double*)out, p->stream);
   } else {
-    e = inverse ? precond_inverse<float>(p, jk, J, (const float*)y, (float*)out, nullptr, p->stream, nullptr, 0)
+    e = inverse ? scan_inverse<float>(p, jk, J, (const float*)y, (float*)out, nullptr, 0, p->stream, nullptr)
                 : precond_forward<float>(p, jk, J, (const float*)y, (float*)out, p->stream);
   }
   return e == hipSuccess ? BIRK_OK : BIRK_ERR_DEVICE;
@@ -643,7 +637,7 @@ static hipError_t arnoldi_step(birk_plan* p, int jk, const double* J, int j, int
   const TK* uz = qj;
   hipError_t e;
   if (use_precond) {
-    e = precond_inverse<TK>(p, jk, J, qj, z, y, s, p->flag, cached);
+    e = scan_inverse<TK>(p, jk, J, qj, z, y, cached, s, p->flag);
     uz = z;
   } else {
     e = jac_times<TK>(p, jk, J, qj, y, s);
@@ -821,8 +815,7 @@ extern "C" birk_status birk_krylov_solve(birk_plan* p, birk_jac_kind jk, const d
   if (e != hipSuccess) return dev_err(e);
   if (hipMemsetAsync(p->flag, 0, sizeof(int), s) != hipSuccess) return BIRK_ERR_DEVICE;
   // mixed plans keep the float H_k: reading the double J costs more than a float table
-  if (o.use_precond && precond_prepare(p, jk, J, mixed ? 1 : 0, s, mixed ? 1 : 0) != hipSuccess)
-    return BIRK_ERR_DEVICE;
+  if (o.use_precond && mixed && jk == BIRK_J_PER_NODE && scan_prepare(p, J, s) != hipSuccess) return BIRK_ERR_DEVICE;
   if (!o.use_x0 && hipMemsetAsync(chi, 0, n * sizeof(double), s) != hipSuccess) return BIRK_ERR_DEVICE;
 
   std::vector<InstState> st(B);

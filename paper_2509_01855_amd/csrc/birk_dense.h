@@ -14,11 +14,7 @@ namespace birk {
 // move, in place of an LDS permute), for a double.
 template <int P>
 __device__ __forceinline__ double row_bcast(double v) {
-  const unsigned long long x = __builtin_bit_cast(unsigned long long, v);
-  const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)x, (int)(unsigned)x, 0x150 + P, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(x >> 32), (int)(unsigned)(x >> 32), 0x150 + P, 0xF, 0xF,
-                                             false);
-  return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+  return __builtin_amdgcn_mov_dpp(v, 0x150 + P, 0xF, 0xF, true);
 }
 
 // f(std::integral_constant<int, P>) for P = B .. E - 1, in order (compile-time lane indices).
@@ -74,6 +70,28 @@ __device__ __forceinline__ void lu_solve(const double (&K)[NX][NX], const double
     for (int j = i + 1; j < NX; ++j) x[i] -= K[i][j] * x[j];
     x[i] *= rp[i];
   }
+}
+
+// LDS written by some lanes of a wave and read by others.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_wave_barrier();
+  __threadfence_block();
+  __builtin_amdgcn_wave_barrier();
+}
+
+// s <- A s + b for the map at m (element (r, c) of [A | b] at m[(c NX + r) fs]); component r
+// of the state in lane r of every row of sixteen.
+template <int NX>
+__device__ __forceinline__ double advance(const double* __restrict__ m, int64_t fs, double s) {
+  const int rr = min((int)(threadIdx.x & 15), NX - 1);
+  double row[NX], acc = m[(NX * NX + rr) * fs];
+#pragma unroll
+  for (int q = 0; q < NX; ++q) row[q] = m[(q * NX + rr) * fs];
+  static_for<0, NX>([&](auto qc) {
+    constexpr int q = decltype(qc)::value;
+    acc += row[q] * row_bcast<q>(s);
+  });
+  return acc;
 }
 
 template <int NX>

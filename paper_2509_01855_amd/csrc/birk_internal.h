@@ -40,7 +40,7 @@ struct Instance {
   int64_t joff = 0;     // per-node Jacobian offset (elements)
   int64_t jcoff = 0;    // constant Jacobian offset (elements)
   int64_t scan_off = 0; // offset into the preconditioner scan scratch (doubles)
-  int64_t jsw_off = 0;  // offset into the swizzled per-node Jacobian buffer (doubles)
+  int64_t htab_off = 0;  // offset into htab
   double* w = nullptr;  // CC weights on the device [Nn]
 };
 
@@ -148,70 +148,27 @@ struct LdsSet {
   int lds_reals = 0;  // dynamic LDS of a workgroup
 };
 
-// Inverse-preconditioner scan of one instance (birk_solve.hip): level sizes and the
-// offsets of its aggregates and start states in the plan's scan scratch.
-constexpr int kPinvMaxLevels = 8;
-struct PinvDesc {
-  int64_t Nn = 0, off = 0, joff = 0, jcoff = 0, jsw_off = 0;
-  const double* w = nullptr;            // CC weights
-  int64_t cnt[kPinvMaxLevels] = {};     // cnt[0] chunks of kChunk nodes, then groups of kFan
-  int64_t agg[kPinvMaxLevels] = {};     // aggregate offsets (doubles) per level
-  int64_t st[kPinvMaxLevels] = {};      // start-state offsets (doubles) per level
-  int L = 0;                            // top level
-  int nb0 = 0;                          // level-0 blocks of 64 groups
-};
-
-// Instances with one state count n_x: each scan phase is one launch over all of them.
-struct PinvClass {
-  int nx = 0;
-  int ninst = 0;
-  int Lmax = 0;
-  std::vector<PinvDesc> host;
-  PinvDesc* dev = nullptr;
-  int2* t_node0 = nullptr;                   // (k, block) over level-0 threads
-  int n_node0 = 0;
-  int2* t_up[kPinvMaxLevels] = {};           // (k, block) over cnt[l + 1] parents of level l
-  int n_up[kPinvMaxLevels] = {};
-  int2* t_nodes = nullptr;                   // (k, block of 256 nodes): J x
-  int n_nodes = 0;
-};
-
-// Wave scan of P^{-1} and P^{-T} (birk_scan.hip, n_x <= kScanNx): one instance of one n_x
-// class.
-constexpr int kScanNx = 8;
+// Scans of P^{-1} and P^{-T} (birk_scan.hip to n_x = kScanNx, birk_wide.hip to kWideNx): one
+// instance of one n_x class.
+constexpr int kScanNx = 8, kWideNx = 12;
+constexpr int kWideNodes = 16, kWideGroup = 32;   // above kScanNx: nodes per round, tiles per group
 struct ScanDesc {
   int64_t Nn, off, joff, jcoff;
-  int64_t hoff;              // H_k kept in float (mixed solves), elements into jsw
+  int64_t hoff;              // H_k kept in float (mixed solves), elements into htab
   int64_t cmap, tmap, gmap;  // chunk, tile and group maps in the scan scratch (doubles)
   const double* w;           // CC weights
-  int rounds;                // nodes per tile / 64
+  int rounds;                // nodes per tile / 64 (16 above kScanNx)
   int ntile;
 };
 struct ScanClass {
   int nx = 0;
   ScanDesc* dev = nullptr;
   int2* tiles = nullptr;     // (instance, tile)
-  int2* groups = nullptr;    // (instance, group of 64 tiles)
+  int2* groups = nullptr;    // (instance, group of 64 (32 above kScanNx) tiles)
   int2* nodes = nullptr;     // (instance, block of 256 nodes)
   int* small = nullptr;      // instances worked by one workgroup
   int n_tile = 0, n_group = 0, n_nodes = 0, n_small = 0;
   int small_waves = 0;       // waves of those workgroups
-};
-
-// Backward scan of P^{-T} (birk_kkt.hip): one instance of one n_x class.
-struct BtDesc {
-  int64_t Nn, off, joff, jcoff;
-  int64_t nblk;        // blocks of 1024 nodes
-  int64_t soff;        // offset of its block maps and entry states in the scan scratch (doubles)
-  const double* w;     // CC weights
-};
-struct BtClass {
-  int nx = 0, ninst = 0;
-  int nblk = 0;        // (instance, block) tiles over all instances
-  int nnode = 0;       // (instance, block of 256 nodes) tiles
-  BtDesc* dev = nullptr;
-  int2* tiles = nullptr;
-  int2* ntiles256 = nullptr;
 };
 
 // Krylov vector segmentation: tiles of kSegChunk elements, each inside one instance.
@@ -235,7 +192,6 @@ struct birk_plan {
   birk::PairSet gen[2];           // general-path pairs: [0] 2N a power of two, [1] Bluestein
   birk::LdsSet lds[2];            // pairs that fit one workgroup: [0] 2N a power of two, [1] Bluestein
   int noalloc_nbuf = 3;           // work buffers that birk_apply_noalloc accounts for
-  std::vector<birk::PinvClass> pclass;  // preconditioner scan schedule, one class per n_x
   std::vector<birk::ScanClass> sclass;  // its wave scans, n_x <= kScanNx
   birk::SegSet seg;               // Krylov segmentation of the batch
   std::vector<void*> allocs;      // device tables owned by the plan
@@ -248,8 +204,7 @@ struct birk_plan {
   void* work[3] = {nullptr, nullptr, nullptr};   // complex work buffers sized for double
   double* partials = nullptr;
   double* scan = nullptr;     // preconditioner scan scratch
-  double* jsw = nullptr;      // H_k tables of the scans (n_x > 8; n_x <= 8 of mixed plans)
-  int64_t total_jsw = 0;
+  float* htab = nullptr;      // H_k in float (per-node J, n_x <= 8; mixed plans)
   const void* lds_tw[birk::kNumPrec] = {nullptr, nullptr, nullptr};  // exp(-2 pi i t / kLdsMax)
   void* tmp_vec[4] = {nullptr, nullptr, nullptr, nullptr};  // vectors of total_len doubles
   // Krylov workspace, allocated by the first solve that needs it.
@@ -278,9 +233,6 @@ struct birk_plan {
   int pfwd_maxnx = 0;               // largest n_x of the plan
   int pfwd_unx = 0;                 // the n_x every instance shares, else 0
   void* newton_buf = nullptr;       // Newton workspace, allocated by the first Newton solve
-  std::vector<birk::BtClass> btclass;  // P^{-T} scan schedule, one class per n_x
-  int64_t total_bt = 0;             // doubles of P^{-T} scan scratch
-  double* bt_scr = nullptr;         // P^{-T} scan scratch (block maps and entry states)
   void* kkt_buf = nullptr;          // KKT / MINRES workspace, allocated by the first KKT solve
   double* comp_val = nullptr;       // one double per component (last node, or a total)
   double* comp_part = nullptr;      // per-component reduction partials (CompDesc::part)
@@ -389,31 +341,32 @@ hipError_t jac_times(birk_plan* p, int jac_kind, const double* J, const T* x, T*
 template <typename T>
 hipError_t precond_forward(birk_plan* p, int jac_kind, const double* J, const T* y, T* out,
                            hipStream_t s);
-// cached = 1: H_k kept by precond_prepare(..., cache = 1) for this J (float, per-node J).
-// flag (or null): receives 1 where a node's pivot is singular (n_x <= 8).
-template <typename T>
-hipError_t precond_inverse(birk_plan* p, int jac_kind, const double* J, const T* y, T* out,
-                           T* jout, hipStream_t s, int* flag, int cached);
-int64_t pinv_scratch(int64_t Nn, int nx);
-int64_t pinv_jsw_size(int64_t Nn, int nx, birk_precision prec);
-// Build the per-n_x scan classes and the Krylov segmentation (after scan_off, jsw_off
-// and the weights exist); allocations are recorded in p->allocs.
+// Build the P y work lists and the Krylov segmentation (after scan_off and the weights
+// exist); allocations are recorded in p->allocs.
 hipError_t plan_solve(birk_plan* p);
-// Per-J preparation of the inverse scan; must precede precond_inverse whenever J changes.
-// single = 1 lays the data of n_x > 8 out in float (for precond_inverse<float>), else in
-// double; cache = 1 (float): H_k of n_x <= 8 kept in float for per-node J.
-hipError_t precond_prepare(birk_plan* p, int jac_kind, const double* J, int single, hipStream_t s, int cache);
-
-// ---- wave scans of the preconditioner, n_x <= kScanNx (birk_scan.hip) ----
+// ---- P^{-1} and P^{-T}, n_x <= kWideNx (birk_scan.hip, birk_wide.hip) ----
+// Instances with more states get no class and are left untouched.
 hipError_t plan_scan(birk_plan* p);
-int64_t scan_scratch(int64_t Nn, int nx);
-int64_t scan_htab(int64_t Nn, int nx);
+int64_t scan_scratch(int64_t Nn, int nx);                         // doubles
+int64_t scan_htab(int64_t Nn, int nx, birk_precision prec);       // elements of the float H_k
+// Float plans, per-node J, n_x <= kScanNx: H_k of this J to the plan's table (pivots checked
+// into the plan's flag).
 hipError_t scan_prepare(birk_plan* p, const double* J, hipStream_t s);
+// out = P^{-1} y, jout (or null) = J out; cached = 1: from the H_k of scan_prepare where it
+// kept them, otherwise K_k is formed from J and factored in the kernels.  flag (or null)
+// receives 1 where a node's pivot is singular.
 template <typename T>
 hipError_t scan_inverse(birk_plan* p, int jac_kind, const double* J, const T* y, T* out, T* jout, int cached,
                         hipStream_t s, int* flag);
-// P^{-T} y of the instances with n_x <= kScanNx (the others are left untouched).
+// out = P^{-T} y
 hipError_t scan_inverse_t(birk_plan* p, int jac_kind, const double* J, const double* y, double* out, hipStream_t s);
+// the n_x > kScanNx classes of the two
+int wide_rounds(int64_t Nn);
+template <typename T>
+hipError_t wide_inverse(birk_plan* p, const ScanClass& sc, int per_node, const double* J, const T* y, T* out, T* jout,
+                        int* flag, hipStream_t s);
+hipError_t wide_inverse_t(birk_plan* p, const ScanClass& sc, int per_node, const double* J, const double* y,
+                          double* out, hipStream_t s);
 
 // Krylov BLAS-1 launchers (birk_solve.hip).  Reductions accumulate in double.
 constexpr int kKryMaxDots = 32;
@@ -463,11 +416,6 @@ void gm_running(const birk_plan* p, const double* st, double* flags, hipStream_t
 }  // namespace kry
 
 // ---- the KKT form and MINRES (birk_kkt.hip) ----
-// Build the P^{-T} scan classes (after the weights exist).
-hipError_t plan_kkt(birk_plan* p);
-// x = P^{-T} y in double (scr: the plan's KKT scan scratch).
-hipError_t precond_inverse_t(birk_plan* p, int jac_kind, const double* J, const double* y, double* x, double* scr,
-                             hipStream_t s);
 // y_k = J_k^T x_k per node, double.
 hipError_t jac_t_times(birk_plan* p, int jac_kind, const double* J, const double* x, double* y, hipStream_t s);
 // MINRES on [[H, A^T], [A, 0]] [chi; lambda] = [f; g] (h or f null: identity, zero).

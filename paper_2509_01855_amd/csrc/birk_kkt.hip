@@ -16,12 +16,8 @@
 // substitution),
 //     x_j = y_j + G_j (y_j / 2 + T_j),   T_{j-1} = T_j + x_j
 //         = (I + G_j) T_j + (I + G_j / 2) y_j,
-// an affine recurrence run from the last node down.  It is evaluated as a scan of affine
-// maps: each thread composes the maps of a chunk of kBtChunk consecutive nodes, a
-// one-wave block combines its 64 chunk maps into a block map, one wave per instance
-// carries the state across the blocks from the last one down, and each block replays
-// its chunks from their entry states.  H_j is formed from J in every pass (no stored
-// preparation).  All arithmetic in double.
+// an affine recurrence run from the last node down, evaluated as a scan of affine maps
+// (birk_scan.hip, birk_wide.hip).  All arithmetic in double.
 //
 // MINRES keeps its scalar recurrences (the Lanczos coefficients, the Givens rotations and
 // the step lengths) per instance in device memory, updated by one-thread-per-instance
@@ -37,266 +33,13 @@
 namespace birk {
 namespace kkt {
 
-constexpr int kBtChunk = 16;
-constexpr int kBtThreads = 64;
-constexpr int64_t kBtNodes = (int64_t)kBtChunk * kBtThreads;
-
-// ------------------------------------------------------------------ per-node matrices
-template <int NX>
-__device__ __forceinline__ void node_jac(const BtDesc& d, const double* __restrict__ J, int per_node, int64_t k,
-                                         double (&Jk)[NX][NX]) {
-#pragma unroll
-  for (int r = 0; r < NX; ++r)
-#pragma unroll
-    for (int c = 0; c < NX; ++c)
-      Jk[r][c] = per_node ? J[d.joff + (int64_t)(r * NX + c) * d.Nn + k] : J[d.jcoff + r * NX + c];
-}
-
-// G_k = H_k^T, H_k = w_k K^{-1} J_k, K = I - (w_k / 2) J_k (unpivoted LU: K is strongly
-// diagonally dominant for w_k <= ~pi/N; the solve's forward preparation checks pivots).
-template <int NX>
-__device__ __forceinline__ void node_g(const double (&Jk)[NX][NX], double wk, double (&G)[NX][NX]) {
-  double K[NX][NX], rp[NX];
-#pragma unroll
-  for (int r = 0; r < NX; ++r)
-#pragma unroll
-    for (int c = 0; c < NX; ++c) K[r][c] = (r == c ? 1.0 : 0.0) - 0.5 * wk * Jk[r][c];
-#pragma unroll
-  for (int p = 0; p < NX; ++p) {
-    rp[p] = 1.0 / K[p][p];
-#pragma unroll
-    for (int i = p + 1; i < NX; ++i) {
-      const double f = K[i][p] * rp[p];
-      K[i][p] = f;
-#pragma unroll
-      for (int j = p + 1; j < NX; ++j) K[i][j] -= f * K[p][j];
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < NX; ++c) {
-    double x[NX];
-#pragma unroll
-    for (int r = 0; r < NX; ++r) x[r] = wk * Jk[r][c];
-#pragma unroll
-    for (int i = 1; i < NX; ++i)
-#pragma unroll
-      for (int j = 0; j < i; ++j) x[i] -= K[i][j] * x[j];
-#pragma unroll
-    for (int i = NX - 1; i >= 0; --i) {
-#pragma unroll
-      for (int j = i + 1; j < NX; ++j) x[i] -= K[i][j] * x[j];
-      x[i] *= rp[i];
-    }
-#pragma unroll
-    for (int r = 0; r < NX; ++r) G[c][r] = x[r];   // column c of H is row c of G
-  }
-}
-
-// ------------------------------------------------------------------ P^{-T}: chunk maps
-// Map of the chunk [k0, k1): T_out = A T_in + c, with T_in the state after node k1 - 1
-// and T_out the state after node k0 (i.e. T_{k0 - 1}); the nodes are applied from the
-// last one down, each as T -> (I + G_k) T + (I + G_k / 2) y_k.
-template <int NX>
-__device__ __forceinline__ void chunk_map(const BtDesc& d, const double* __restrict__ J, int per_node,
-                                          const double* __restrict__ y, int64_t k0, int64_t k1,
-                                          double (&A)[NX][NX], double (&c)[NX]) {
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-    c[r] = 0.0;
-#pragma unroll
-    for (int q = 0; q < NX; ++q) A[r][q] = (r == q) ? 1.0 : 0.0;
-  }
-  for (int64_t k = k1 - 1; k >= k0; --k) {
-    double Jk[NX][NX], G[NX][NX], yk[NX];
-    node_jac<NX>(d, J, per_node, k, Jk);
-    node_g<NX>(Jk, d.w[k], G);
-#pragma unroll
-    for (int r = 0; r < NX; ++r) yk[r] = y[d.off + (int64_t)r * d.Nn + k];
-    double An[NX][NX], cn[NX];
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      double s = c[r], dy = yk[r];
-#pragma unroll
-      for (int q = 0; q < NX; ++q) {
-        s += G[r][q] * c[q];
-        dy += 0.5 * G[r][q] * yk[q];
-      }
-      cn[r] = s + dy;
-#pragma unroll
-      for (int q = 0; q < NX; ++q) {
-        double a = A[r][q];
-#pragma unroll
-        for (int m = 0; m < NX; ++m) a += G[r][m] * A[m][q];
-        An[r][q] = a;
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      c[r] = cn[r];
-#pragma unroll
-      for (int q = 0; q < NX; ++q) A[r][q] = An[r][q];
-    }
-  }
-}
-
-template <int NX>
-constexpr int map_len() { return NX * NX + NX; }
-
-// tile = (descriptor, block): chunk maps of the block's 64 threads combined into the block
-// map (thread t holds nodes [k0 + 16 t, k0 + 16 t + 16); the block map is
-// map_0 o map_1 o ... o map_63, thread 63 applied first).
-template <int NX>
-__global__ __launch_bounds__(kBtThreads) void k_bt_reduce(const double* __restrict__ J, int per_node,
-                                                          const double* __restrict__ y, double* __restrict__ scr,
-                                                          const BtDesc* __restrict__ dd,
-                                                          const int2* __restrict__ tiles) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  double* sm = reinterpret_cast<double*>(smem_raw);   // [64][map_len]
-  constexpr int ML = map_len<NX>();
-  const int2 tile = tiles[blockIdx.x];
-  const BtDesc& d = dd[tile.x];
-  const int t = (int)threadIdx.x;
-  const int64_t k0 = (int64_t)tile.y * kBtNodes + (int64_t)t * kBtChunk;
-  const int64_t k1 = min(k0 + kBtChunk, d.Nn);
-  double A[NX][NX], c[NX];
-  chunk_map<NX>(d, J, per_node, y, k0, k1 > k0 ? k1 : k0, A, c);
-  double* mine = sm + t * ML;
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-#pragma unroll
-    for (int q = 0; q < NX; ++q) mine[r * NX + q] = A[r][q];
-    mine[NX * NX + r] = c[r];
-  }
-  __syncthreads();
-  for (int s = 1; s < kBtThreads; s <<= 1) {
-    if ((t & (2 * s - 1)) == 0) {
-      // (A_t, c_t) o (A_{t+s}, c_{t+s}) = (A_t A_{t+s}, A_t c_{t+s} + c_t)
-      const double* hi = sm + (t + s) * ML;
-      double An[NX][NX], cn[NX];
-#pragma unroll
-      for (int r = 0; r < NX; ++r) {
-        double cc = mine[NX * NX + r];
-#pragma unroll
-        for (int q = 0; q < NX; ++q) {
-          double a = 0.0;
-#pragma unroll
-          for (int m = 0; m < NX; ++m) a += mine[r * NX + m] * hi[m * NX + q];
-          An[r][q] = a;
-          cc += mine[r * NX + q] * hi[NX * NX + q];
-        }
-        cn[r] = cc;
-      }
-#pragma unroll
-      for (int r = 0; r < NX; ++r) {
-#pragma unroll
-        for (int q = 0; q < NX; ++q) mine[r * NX + q] = An[r][q];
-        mine[NX * NX + r] = cn[r];
-      }
-    }
-    __syncthreads();
-  }
-  double* out = scr + d.soff + (int64_t)tile.y * ML;
-  for (int e = t; e < ML; e += kBtThreads) out[e] = sm[e];
-}
-
-// One wave per instance: entry states of the blocks, from the last block down
-// (T = 0 after node N); lane r < NX holds component r of the state.
-template <int NX>
-__global__ __launch_bounds__(kBtThreads) void k_bt_top(double* __restrict__ scr, const BtDesc* __restrict__ dd) {
-  constexpr int ML = map_len<NX>();
-  const BtDesc& d = dd[blockIdx.x];
-  const int lane = (int)threadIdx.x;
-  const double* maps = scr + d.soff;
-  double* tin = scr + d.soff + d.nblk * ML;
-  double T = 0.0;
-  for (int64_t b = d.nblk - 1; b >= 0; --b) {
-    if (lane < NX) tin[b * NX + lane] = T;
-    const double* m = maps + b * ML;
-    double s = lane < NX ? m[NX * NX + lane] : 0.0;
-#pragma unroll
-    for (int q = 0; q < NX; ++q) {
-      const double tq = __shfl(T, q, 64);
-      if (lane < NX) s += m[lane * NX + q] * tq;
-    }
-    T = s;
-  }
-}
-
-// tile = (descriptor, block): entry state of every chunk from the block's entry state,
-// then each chunk replayed from its last node down: x_k = y_k + G_k (y_k / 2 + T),
-// T += x_k.
-template <int NX>
-__global__ __launch_bounds__(kBtThreads) void k_bt_apply(const double* __restrict__ J, int per_node,
-                                                         const double* __restrict__ y, double* __restrict__ x,
-                                                         const double* __restrict__ scr,
-                                                         const BtDesc* __restrict__ dd,
-                                                         const int2* __restrict__ tiles) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  double* sm = reinterpret_cast<double*>(smem_raw);   // [64][map_len], then [64][NX] entry states
-  constexpr int ML = map_len<NX>();
-  const int2 tile = tiles[blockIdx.x];
-  const BtDesc& d = dd[tile.x];
-  const int t = (int)threadIdx.x;
-  const int64_t k0 = (int64_t)tile.y * kBtNodes + (int64_t)t * kBtChunk;
-  const int64_t k1 = min(k0 + kBtChunk, d.Nn);
-  {
-    double A[NX][NX], c[NX];
-    chunk_map<NX>(d, J, per_node, y, k0, k1 > k0 ? k1 : k0, A, c);
-    double* mine = sm + t * ML;
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-#pragma unroll
-      for (int q = 0; q < NX; ++q) mine[r * NX + q] = A[r][q];
-      mine[NX * NX + r] = c[r];
-    }
-  }
-  double* tst = sm + kBtThreads * ML;
-  __syncthreads();
-  // entry states: thread 63 enters with the block's state; thread s - 1 with map_s(T_s)
-  double T = t < NX ? scr[d.soff + d.nblk * ML + (int64_t)tile.y * NX + t] : 0.0;
-  for (int s = kBtThreads - 1; s >= 0; --s) {
-    if (t < NX) tst[s * NX + t] = T;
-    if (s == 0) break;
-    const double* m = sm + s * ML;
-    double v = t < NX ? m[NX * NX + t] : 0.0;
-#pragma unroll
-    for (int q = 0; q < NX; ++q) {
-      const double tq = __shfl(T, q, 64);
-      if (t < NX) v += m[t * NX + q] * tq;
-    }
-    T = v;
-  }
-  __syncthreads();
-  double Tv[NX];
-#pragma unroll
-  for (int r = 0; r < NX; ++r) Tv[r] = tst[t * NX + r];
-  for (int64_t k = k1 - 1; k >= k0; --k) {
-    double Jk[NX][NX], G[NX][NX], yk[NX], u[NX];
-    node_jac<NX>(d, J, per_node, k, Jk);
-    node_g<NX>(Jk, d.w[k], G);
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      yk[r] = y[d.off + (int64_t)r * d.Nn + k];
-      u[r] = 0.5 * yk[r] + Tv[r];
-    }
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      double v = yk[r];
-#pragma unroll
-      for (int q = 0; q < NX; ++q) v += G[r][q] * u[q];
-      x[d.off + (int64_t)r * d.Nn + k] = v;
-      Tv[r] += v;
-    }
-  }
-}
-
 // ------------------------------------------------------------------ J^T x per node
 template <int NX>
 __global__ __launch_bounds__(256) void k_jac_t(const double* __restrict__ J, int per_node,
                                                const double* __restrict__ x, double* __restrict__ yv,
-                                               const BtDesc* __restrict__ dd, const int2* __restrict__ tiles) {
+                                               const ScanDesc* __restrict__ dd, const int2* __restrict__ tiles) {
   const int2 tile = tiles[blockIdx.x];
-  const BtDesc& d = dd[tile.x];
+  const ScanDesc& d = dd[tile.x];
   const int64_t k = (int64_t)tile.y * 256 + threadIdx.x;
   if (k >= d.Nn) return;
   double xv[NX];
@@ -530,27 +273,8 @@ __global__ __launch_bounds__(256) void k_mr_update(const double* __restrict__ v,
 
 // ------------------------------------------------------------------ host side
 template <int NX>
-static void bt_class(const BtClass& bc, const double* J, int per_node, const double* y, double* x, double* scr,
-                     hipStream_t s) {
-  constexpr int ML = map_len<NX>();
-  constexpr int lds_r = kBtThreads * ML * (int)sizeof(double);
-  constexpr int lds_a = lds_r + kBtThreads * NX * (int)sizeof(double);
-  static const bool attr = [] {
-    (void)hipFuncSetAttribute((const void*)k_bt_reduce<NX>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_a);
-    (void)hipFuncSetAttribute((const void*)k_bt_apply<NX>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_a);
-    return true;
-  }();
-  (void)attr;
-  hipLaunchKernelGGL(k_bt_reduce<NX>, dim3(bc.nblk), dim3(kBtThreads), lds_r, s, J, per_node, y, scr, bc.dev,
-                     bc.tiles);
-  hipLaunchKernelGGL(k_bt_top<NX>, dim3(bc.ninst), dim3(kBtThreads), 0, s, scr, bc.dev);
-  hipLaunchKernelGGL(k_bt_apply<NX>, dim3(bc.nblk), dim3(kBtThreads), lds_a, s, J, per_node, y, x, scr, bc.dev,
-                     bc.tiles);
-}
-
-template <int NX>
-static void jt_class(const BtClass& bc, const double* J, int per_node, const double* x, double* y, hipStream_t s) {
-  hipLaunchKernelGGL(k_jac_t<NX>, dim3(bc.nnode), dim3(256), 0, s, J, per_node, x, y, bc.dev, bc.ntiles256);
+static void jt_class(const ScanClass& sc, const double* J, int per_node, const double* x, double* y, hipStream_t s) {
+  hipLaunchKernelGGL(k_jac_t<NX>, dim3(sc.n_nodes), dim3(256), 0, s, J, per_node, x, y, sc.dev, sc.nodes);
 }
 
 #define BIRK_NX_SWITCH(nx, CALL)                                      \
@@ -573,70 +297,9 @@ static void jt_class(const BtClass& bc, const double* J, int per_node, const dou
 
 using namespace kkt;
 
-hipError_t plan_kkt(birk_plan* p) {
-  // classes by n_x; descriptors, block and node tile lists; scan scratch offsets
-  // (the KKT preconditioner covers n_x <= 12; instances with more states get no class)
-  std::vector<std::vector<int>> by(13);
-  for (int i = 0; i < (int)p->inst.size(); ++i)
-    if (p->inst[i].nx <= 12) by[p->inst[i].nx].push_back(i);
-  int64_t soff = 0;
-  hipError_t e = hipSuccess;
-  for (int nx = 1; nx <= 12 && e == hipSuccess; ++nx) {
-    if (by[nx].empty()) continue;
-    BtClass bc;
-    bc.nx = nx;
-    bc.ninst = (int)by[nx].size();
-    std::vector<BtDesc> h;
-    std::vector<int2> tb, tn;
-    for (int k = 0; k < bc.ninst; ++k) {
-      const Instance& in = p->inst[by[nx][k]];
-      BtDesc d;
-      d.Nn = in.Nn;
-      d.off = in.off;
-      d.joff = in.joff;
-      d.jcoff = in.jcoff;
-      d.w = in.w;
-      d.nblk = (in.Nn + kBtNodes - 1) / kBtNodes;
-      d.soff = soff;
-      soff += d.nblk * (int64_t)(nx * nx + nx) + d.nblk * nx;
-      for (int64_t b = 0; b < d.nblk; ++b) tb.push_back(make_int2(k, (int)b));
-      for (int64_t b = 0; b < (in.Nn + 255) / 256; ++b) tn.push_back(make_int2(k, (int)b));
-      h.push_back(d);
-    }
-    bc.nblk = (int)tb.size();
-    bc.nnode = (int)tn.size();
-    e = hipMalloc((void**)&bc.dev, h.size() * sizeof(BtDesc));
-    if (e == hipSuccess) p->allocs.push_back(bc.dev);
-    if (e == hipSuccess) e = hipMemcpy(bc.dev, h.data(), h.size() * sizeof(BtDesc), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc((void**)&bc.tiles, tb.size() * sizeof(int2));
-    if (e == hipSuccess) p->allocs.push_back(bc.tiles);
-    if (e == hipSuccess) e = hipMemcpy(bc.tiles, tb.data(), tb.size() * sizeof(int2), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc((void**)&bc.ntiles256, tn.size() * sizeof(int2));
-    if (e == hipSuccess) p->allocs.push_back(bc.ntiles256);
-    if (e == hipSuccess) e = hipMemcpy(bc.ntiles256, tn.data(), tn.size() * sizeof(int2), hipMemcpyHostToDevice);
-    p->btclass.push_back(bc);
-  }
-  p->total_bt = std::max<int64_t>(soff, 1);
-  if (e == hipSuccess) e = hipMalloc((void**)&p->bt_scr, p->total_bt * sizeof(double));
-  if (e == hipSuccess) p->allocs.push_back(p->bt_scr);
-  return e;
-}
-
-hipError_t precond_inverse_t(birk_plan* p, int jac_kind, const double* J, const double* y, double* x, double* scr,
-                             hipStream_t s) {
-  // n_x <= 8: the backward wave scan of birk_scan.hip; larger n_x: the chunked scan here
-  hipError_t e = scan_inverse_t(p, jac_kind, J, y, x, s);
-  if (e != hipSuccess) return e;
-  for (const BtClass& bc : p->btclass) {
-    if (bc.nx <= kScanNx) continue;
-    BIRK_NX_SWITCH(bc.nx, (bt_class<NX>(bc, J, jac_kind == BIRK_J_PER_NODE, y, x, scr, s)))
-  }
-  return hipGetLastError();
-}
-
 hipError_t jac_t_times(birk_plan* p, int jac_kind, const double* J, const double* x, double* y, hipStream_t s) {
-  for (const BtClass& bc : p->btclass) {
-    BIRK_NX_SWITCH(bc.nx, (jt_class<NX>(bc, J, jac_kind == BIRK_J_PER_NODE, x, y, s)))
+  for (const ScanClass& sc : p->sclass) {
+    BIRK_NX_SWITCH(sc.nx, (jt_class<NX>(sc, J, jac_kind == BIRK_J_PER_NODE, x, y, s)))
   }
   return hipGetLastError();
 }
@@ -717,17 +380,17 @@ static hipError_t kkt_apply(birk_plan* p, int jk, const double* J, const double*
   return hipGetLastError();
 }
 
-// M^{-1} [r1; r2] = [r1 / h; P^{-T}(h * P^{-1} r2)] (P^{-1} prepared for J)
+// M^{-1} [r1; r2] = [r1 / h; P^{-T}(h * P^{-1} r2)]
 static hipError_t kkt_prec(birk_plan* p, int jk, const double* J, const double* h, const double* r, double* z,
-                           double* scr, int use_precond, hipStream_t s) {
+                           int use_precond, hipStream_t s) {
   const int64_t n = p->total_len;
   if (!use_precond) return hipMemcpyAsync(z, r, 2 * n * sizeof(double), hipMemcpyDeviceToDevice, s);
   hipLaunchKernelGGL(k_hscale, dim3(nb256(n)), dim3(256), 0, s, r, h, z, n, 1);
   double* t0 = (double*)p->tmp_vec[0];
-  hipError_t e = precond_inverse<double>(p, jk, J, r + n, t0, nullptr, s, nullptr, 0);
+  hipError_t e = scan_inverse<double>(p, jk, J, r + n, t0, nullptr, 0, s, nullptr);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_hscale, dim3(nb256(n)), dim3(256), 0, s, t0, h, t0, n, 0);
-  return precond_inverse_t(p, jk, J, t0, z + n, scr, s);
+  return scan_inverse_t(p, jk, J, t0, z + n, s);
 }
 
 // MINRES on the KKT system for every instance of the batch (arguments checked by the
@@ -756,9 +419,8 @@ birk_status kkt_solve(birk_plan* p, int jk, const double* J, const double* h, co
   } else if (e == hipSuccess) {
     e = hipMemsetAsync(b.x, 0, 2 * n * sizeof(double), s);
   }
-  if (e == hipSuccess && o->use_precond) e = precond_prepare(p, jk, J, 0, s, 0);
   if (e != hipSuccess) return BIRK_ERR_DEVICE;
-  auto prec = [&](const double* r, double* z) { return kkt_prec(p, jk, J, h, r, z, p->bt_scr, o->use_precond, s); };
+  auto prec = [&](const double* r, double* z) { return kkt_prec(p, jk, J, h, r, z, o->use_precond, s); };
   std::vector<double> hst((size_t)B * kSt), bn(B), rn(B), tolv(B);
   std::vector<int> run(B, 1), status(B, BIRK_OK), inner(B, 0), outer(B, 0);
   std::vector<char> done(B, 0);

@@ -46,7 +46,7 @@ namespace birk {
 namespace {
 
 // Where H_k comes from: one J per instance, J per node, or (float plans in a solve with
-// per-node J) H_k kept in float by precond_prepare, half the bytes of J.
+// per-node J) H_k kept in float by scan_prepare, half the bytes of J.
 constexpr int kConst = 0, kPerNode = 1, kCachedH = 2;
 
 constexpr int kG = 16;   // nodes of a chunk, and lanes that work it
@@ -60,13 +60,6 @@ struct Lay {
   static constexpr int REC = 64 * RL + 16;         // a wave's records: 16 bytes of skew per 8 nodes
   static constexpr int SIZE = REC + kC * F;        // and its chunk maps
 };
-
-// LDS written by some lanes of a wave and read by others.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_wave_barrier();
-  __threadfence_block();
-  __builtin_amdgcn_wave_barrier();
-}
 
 template <int NX>
 __device__ __forceinline__ double* record(double* sm, int n) {
@@ -263,21 +256,6 @@ __device__ __forceinline__ void scan_chunks(double* mp, const Col<NX>& a) {
     }
     wave_sync();
   }
-}
-
-// s <- A s + b for the map at m (element (r, c) of [A | b] at m[(c NX + r) fs]); component r
-// of the state in lane r of every row of sixteen.
-template <int NX>
-__device__ __forceinline__ double advance(const double* __restrict__ m, int64_t fs, double s) {
-  const int rr = min((int)(threadIdx.x & 15), NX - 1);
-  double row[NX], acc = m[(NX * NX + rr) * fs];
-#pragma unroll
-  for (int q = 0; q < NX; ++q) row[q] = m[(q * NX + rr) * fs];
-  static_for<0, NX>([&](auto qc) {
-    constexpr int q = decltype(qc)::value;
-    acc += row[q] * row_bcast<q>(s);
-  });
-  return acc;
 }
 
 // Replay of the round's nodes from the records (H, then y): row of lanes g replays chunk g
@@ -708,7 +686,7 @@ int small_waves() {   // waves whose records fit one workgroup
 
 template <int NX, int MODE, bool BACK, typename T>
 void launch(birk_plan* p, const ScanClass& sc, const double* J, const T* y, T* out, T* jout, int* flag, hipStream_t s) {
-  const float* ht = (const float*)p->jsw;
+  const float* ht = p->htab;
   if (sc.n_small > 0) {
     const auto f = k_scan_small<NX, MODE, BACK, T>;
     const int bytes = sc.small_waves * Lay<NX>::SIZE * (int)sizeof(double);
@@ -762,23 +740,32 @@ int scan_rounds(int64_t Nn, int nx) {
 }  // namespace
 
 int64_t scan_scratch(int64_t Nn, int nx) {
+  if (nx > kWideNx) return 0;   // no preconditioner
+  if (nx > kScanNx) {
+    const int64_t R = wide_rounds(Nn), nt = (Nn + kWideNodes * R - 1) / (kWideNodes * R);
+    return ((int64_t)nx * nx + nx) * (nt + (nt + kWideGroup - 1) / kWideGroup);
+  }
   const int64_t F = (int64_t)nx * nx + nx, R = scan_rounds(Nn, nx), nt = (Nn + 64 * R - 1) / (64 * R);
   return F * (nt * (kC * R + 1) + (nt + 63) / 64);
 }
 
-int64_t scan_htab(int64_t Nn, int nx) { return Nn * nx * nx; }
+int64_t scan_htab(int64_t Nn, int nx, birk_precision prec) {
+  return nx <= kScanNx && prec == BIRK_F32_REFINE_F64 ? Nn * nx * nx : 0;
+}
 
 hipError_t plan_scan(birk_plan* p) {
   hipError_t e = hipSuccess;
   p->sclass.clear();
-  for (int nx = 1; nx <= kScanNx; ++nx) {
+  for (int nx = 1; nx <= kWideNx; ++nx) {
+    const bool wide = nx > kScanNx;
+    const int per = wide ? kWideNodes : 64, group = wide ? kWideGroup : 64;
     ScanClass sc;
     sc.nx = nx;
     std::vector<ScanDesc> h;
     std::vector<int2> tt, tg, tn;
     std::vector<int> ts;
     int most = 0;
-    SCAN_NX_SWITCH(nx, most = small_waves<NXC>())
+    if (!wide) SCAN_NX_SWITCH(nx, most = small_waves<NXC>())
     for (const Instance& in : p->inst) {
       if (in.nx != nx) continue;
       const int k = (int)h.size();
@@ -787,13 +774,13 @@ hipError_t plan_scan(birk_plan* p) {
       d.off = in.off;
       d.joff = in.joff;
       d.jcoff = in.jcoff;
-      d.hoff = in.jsw_off;
+      d.hoff = in.htab_off;
       d.w = in.w;
-      d.rounds = scan_rounds(in.Nn, nx);
-      d.ntile = (int)((in.Nn + 64 * d.rounds - 1) / (64 * d.rounds));
+      d.rounds = wide ? wide_rounds(in.Nn) : scan_rounds(in.Nn, nx);
+      d.ntile = (int)((in.Nn + per * d.rounds - 1) / (per * d.rounds));
       const int64_t F = (int64_t)nx * nx + nx;
       d.cmap = in.scan_off;
-      d.tmap = d.cmap + F * kC * d.rounds * d.ntile;
+      d.tmap = d.cmap + (wide ? 0 : F * kC * d.rounds * d.ntile);
       d.gmap = d.tmap + F * d.ntile;
       h.push_back(d);
       for (int64_t b = 0; b * 256 < in.Nn; ++b) tn.push_back(make_int2(k, (int)b));
@@ -804,7 +791,7 @@ hipError_t plan_scan(birk_plan* p) {
       }
       for (int b = 0; b < d.ntile; ++b) tt.push_back(make_int2(k, b));
       if (d.ntile > 1)
-        for (int b = 0; b * 64 + 1 < d.ntile; ++b) tg.push_back(make_int2(k, b));
+        for (int b = 0; b * group + 1 < d.ntile; ++b) tg.push_back(make_int2(k, b));
     }
     if (h.empty()) continue;
     sc.n_tile = (int)tt.size();
@@ -829,7 +816,8 @@ hipError_t plan_scan(birk_plan* p) {
 
 hipError_t scan_prepare(birk_plan* p, const double* J, hipStream_t s) {
   for (const ScanClass& sc : p->sclass) {
-    SCAN_NX_SWITCH(sc.nx, hipLaunchKernelGGL(k_make_h<NXC>, dim3(sc.n_nodes), dim3(256), 0, s, J, (float*)p->jsw, sc.dev,
+    if (sc.nx > kScanNx) continue;
+    SCAN_NX_SWITCH(sc.nx, hipLaunchKernelGGL(k_make_h<NXC>, dim3(sc.n_nodes), dim3(256), 0, s, J, p->htab, sc.dev,
                                              sc.nodes, p->flag))
   }
   return hipGetLastError();
@@ -840,7 +828,10 @@ hipError_t scan_inverse(birk_plan* p, int jac_kind, const double* J, const T* y,
                         hipStream_t s, int* flag) {
   const bool pn = jac_kind == BIRK_J_PER_NODE;
   for (const ScanClass& sc : p->sclass) {
-    if (pn && cached && std::is_same<T, float>::value) {
+    if (sc.nx > kScanNx) {
+      const hipError_t e = wide_inverse<T>(p, sc, pn, J, y, out, jout, flag, s);
+      if (e != hipSuccess) return e;
+    } else if (pn && cached && std::is_same<T, float>::value) {
       if constexpr (std::is_same<T, float>::value) {
         SCAN_NX_SWITCH(sc.nx, (launch<NXC, kCachedH, false, T>(p, sc, J, y, out, jout, flag, s)))
       }
@@ -855,7 +846,10 @@ hipError_t scan_inverse(birk_plan* p, int jac_kind, const double* J, const T* y,
 
 hipError_t scan_inverse_t(birk_plan* p, int jac_kind, const double* J, const double* y, double* out, hipStream_t s) {
   for (const ScanClass& sc : p->sclass) {
-    if (jac_kind == BIRK_J_PER_NODE) {
+    if (sc.nx > kScanNx) {
+      const hipError_t e = wide_inverse_t(p, sc, jac_kind == BIRK_J_PER_NODE, J, y, out, s);
+      if (e != hipSuccess) return e;
+    } else if (jac_kind == BIRK_J_PER_NODE) {
       SCAN_NX_SWITCH(sc.nx, (launch<NXC, kPerNode, true, double>(p, sc, J, y, out, nullptr, nullptr, s)))
     } else {
       SCAN_NX_SWITCH(sc.nx, (launch<NXC, kConst, true, double>(p, sc, J, y, out, nullptr, nullptr, s)))

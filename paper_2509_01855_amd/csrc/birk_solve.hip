@@ -13,26 +13,17 @@
 //                 S_{k+1} = S_k + w_k J_k xi_k.
 //             As an affine map of the carried sum, S_{k+1} = G_k S_k + h_k with
 //             G_k = I + w_k J_k K_k^{-1} and h_k = w_k J_k K_k^{-1} y_k.  The chain is
-//             evaluated as a scan of affine maps S_out = A S_in + b.  n_x <= 8:
-//             birk_scan.hip.  Larger n_x, here: chunks of kChunk nodes
-//             worked by sixteen-lane groups, groups of kFan aggregates per level up to a
-//             sequential top, start states pushed back down.  Either way each chunk is
-//             replayed from its start state, emitting xi_k and J_k xi_k (the latter
-//             feeds FastAX).  All arithmetic in double; y, xi and J xi are stored in the
-//             plan type.
+//             evaluated as a scan of affine maps S_out = A S_in + b: birk_scan.hip to
+//             n_x = 8, birk_wide.hip to 12.
 
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <type_traits>
 
-#include "birk_dense.h"
 #include "birk_internal.h"
 
 namespace birk {
-
-constexpr int kChunk = 16;
-constexpr int kFan = 16;
 
 // ------------------------------------------------------------------ P y (forward)
 constexpr int kScanItems = 4;
@@ -322,472 +313,15 @@ hipError_t precond_forward(birk_plan* p, int jac_kind, const double* J, const T*
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ P^{-1} y (inverse)
-
-// ---- hierarchical path (n_x > 8): level-0 layout ----
-// Chunks of kChunk consecutive nodes are the level-0 slots (each worked by a group of
-// sixteen lanes).  Chunk c is child i = c % kFan of level-1 group g = c / kFan.  Slot
-// indices tau are laid out so that the
-// 64 slots of a block of 64 hold 64 consecutive groups g and the index of that block
-// within kFan of them is the child index i:  slot tau -> block B = tau / (64 kFan),
-// i = (tau / 64) % kFan, lane l = tau % 64, g = 64 B + l, c = kFan g + i.
-// Every per-chunk array (swizzled Jacobians, aggregates, start states) is stored as
-// [B][i][field][l]: neighbouring slots hold neighbouring values of a field.
-//
-// Batching: the instances of one n_x form a PinvClass; every phase below is one launch
-// over all of them, each block reading its instance from a (k, block) tile and the
-// instance's sizes and scratch offsets from a PinvDesc.
-__device__ __forceinline__ int64_t swz(int64_t B, int i, int field, int nfield, int l) {
-  return (((B * kFan + i) * nfield) + field) * 64 + l;
-}
-
-// Per-node tables of the level-0 kernels: node k -> chunk c = k / kChunk, j = k % kChunk;
-// g = c / kFan, i = c % kFan; B = g / 64, l = g % 64; slot sigma = (B kFan + i) 64 + l.
-// Node j of slot sigma keeps row-major H_k (NX^2 values) then w_k in a record of
-// hrec<NX>() values (a multiple of four, so that the rows start 16-byte aligned for
-// doubles with NX even and for floats with NX a multiple of four) at
-// jsw[(sigma kChunk + j) hrec].  A lane holding row r of a chunk's state reads the NX
-// contiguous values of row r of H_k; the sixteen lanes of a chunk read one record.
-template <int NX>
-__host__ __device__ constexpr int hrec() { return (NX * NX + 1 + 3) & ~3; }
-
-// Row r of H_k (NX values at p) into registers; 16-byte loads where every row is 16-byte
-// aligned (records are multiples of four values).
-template <int NX, typename T>
-__device__ __forceinline__ void load_row(const T* __restrict__ p, double (&h)[NX]) {
-  if constexpr (sizeof(T) == 8 && (NX % 2) == 0) {
-    typedef double v2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-    for (int q = 0; q < NX; q += 2) {
-      const v2 v = *reinterpret_cast<const v2*>(p + q);
-      h[q] = v.x;
-      h[q + 1] = v.y;
-    }
-  } else if constexpr (sizeof(T) == 4 && (NX % 4) == 0) {
-    typedef float v4 __attribute__((ext_vector_type(4)));
-#pragma unroll
-    for (int q = 0; q < NX; q += 4) {
-      const v4 v = *reinterpret_cast<const v4*>(p + q);
-      h[q] = v.x;
-      h[q + 1] = v.y;
-      h[q + 2] = v.z;
-      h[q + 3] = v.w;
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < NX; ++q) h[q] = (double)p[q];
-  }
-}
-
-// Per node, H_k = w_k J_k K_k^{-1} with K_k = I - w_k J_k / 2 (J_k commutes with K_k^{-1}).
-// Everything the scan needs follows from H_k:  K_k^{-1} = I + H_k / 2, so for
-// u = y_k + S_k
-//     xi_k = u + H_k u / 2,   J_k xi_k = H_k u / w_k,   S_{k+1} = S_k + H_k u,
-// and the affine map of the node is S -> (I + H_k) S + H_k y_k.  H_k and w_k go to the
-// node's record (J, per node or constant, and w are read where they are).
-// Sixteen lanes per chunk: lane r < NX holds row r of [K_k | w_k J_k] and Gauss-Jordan
-// elimination without pivoting, the pivot row broadcast across the sixteen lanes, turns
-// it into [I | K_k^{-1} w_k J_k]; its pivots are those of the unpivoted LU, and one that
-// is non-finite or not above 1e-13 (1 + |w_k / 2| max |J_k|) sets *flag.  A chunk's 16
-// nodes are taken in turn; the four chunks of a wave are neighbours in the slot layout.
-// grid = (tile (k, block of 256 level-0 threads), 16 groups of 16 chunks).
-template <int NX, typename JT>
-__global__ __launch_bounds__(256) void k_make_h_rows(JT* __restrict__ jsw, const double* __restrict__ J,
-                                                    int per_node, const PinvDesc* __restrict__ pd,
-                                                    const int2* __restrict__ tiles, int* flag) {
-  static_assert(NX <= 16, "one row per lane of a 16-lane group");
-  const int2 t = tiles[blockIdx.x];
-  const PinvDesc& d = pd[t.x];
-  const int64_t tau = (int64_t)t.y * 256 + blockIdx.y * 16 + (threadIdx.x >> 4);
-  const int r = (int)(threadIdx.x & 15);
-  const int64_t B = tau / (64 * kFan);
-  const int i = (int)((tau >> 6) % kFan);
-  const int l = (int)(tau & 63);
-  const int64_t c = (B * 64 + l) * kFan + i;
-  if (c >= d.cnt[0]) return;  // the whole group leaves together
-  constexpr int E = hrec<NX>();
-  const double* Jc = J + d.jcoff;
-  const double* Jn = J + d.joff;
-  JT* js = jsw + d.jsw_off + (((B * kFan + i) * 64 + l) * kChunk) * E;
-  const int jn = (int)min((int64_t)kChunk, d.Nn - c * kChunk);
-  const bool act = r < NX;
-  const int rr = act ? r : 0;
-#pragma unroll 1
-  for (int j = 0; j < jn; ++j) {
-    JT* base = js + (int64_t)j * E;
-    const int64_t k = c * kChunk + j;
-    const double wk = d.w[k];
-    double Kr[NX], Xr[NX];
-    double jm = 0.0;
-#pragma unroll
-    for (int q = 0; q < NX; ++q) {
-      const double jv = act ? (per_node ? Jn[(int64_t)(rr * NX + q) * d.Nn + k] : Jc[rr * NX + q]) : 0.0;
-      jm = fmax(jm, fabs(jv));
-      Xr[q] = wk * jv;
-      Kr[q] = (r == q ? 1.0 : 0.0) - 0.5 * wk * jv;
-    }
-#pragma unroll
-    for (int o = 8; o >= 1; o >>= 1) jm = fmax(jm, __shfl_xor(jm, o, 16));
-    const double scale = 1.0 + 0.5 * fabs(wk) * jm;
-    static_for<0, NX>([&](auto pc) {
-      constexpr int p = decltype(pc)::value;
-      double pk[NX], px[NX];
-#pragma unroll
-      for (int q = p; q < NX; ++q) pk[q] = row_bcast<p>(Kr[q]);
-#pragma unroll
-      for (int q = 0; q < NX; ++q) px[q] = row_bcast<p>(Xr[q]);
-      const double piv = pk[p];
-      if (r == 0 && flag && (!(fabs(piv) > 1e-13 * scale) || !isfinite(piv))) atomicOr(flag, 1);
-      const double rp = recip(piv);
-      if (r == p) {
-#pragma unroll
-        for (int q = p + 1; q < NX; ++q) Kr[q] *= rp;
-#pragma unroll
-        for (int q = 0; q < NX; ++q) Xr[q] *= rp;
-      } else {
-        const double f = Kr[p] * rp;
-#pragma unroll
-        for (int q = p + 1; q < NX; ++q) Kr[q] -= f * pk[q];
-#pragma unroll
-        for (int q = 0; q < NX; ++q) Xr[q] -= f * px[q];
-      }
-    });
-    if (act) {
-#pragma unroll
-      for (int q = 0; q < NX; ++q) base[r * NX + q] = (JT)Xr[q];
-    }
-    if (r == 0) base[NX * NX] = (JT)wk;
-  }
-}
-
-// Level-0 up-sweep: each chunk of kChunk nodes is reduced to (A, b) with
-// S_out = A S_in + b by the node maps S -> (I + H_k) S + H_k y_k, sixteen lanes per chunk
-// with lane r < NX holding row r of A and b: from A = I, b = 0 each node takes
-//     A <- A + H_k A,   b <- b + H_k (b + y_k),
-// row r of H_k read contiguously from the node's record and the rows of A and of
-// b + y_k broadcast across the sixteen lanes (DPP row_newbcast).
-// grid = (tile (k, block of 256 level-0 threads), 16 groups of 16 chunks).
-template <int NX, typename T>
-__global__ __launch_bounds__(256) void k_pinv_up0(const T* __restrict__ jsw, const T* __restrict__ y,
-                                                  const PinvDesc* __restrict__ pd, const int2* __restrict__ tiles,
-                                                  double* __restrict__ scan) {
-  static_assert(NX <= 16, "one row per lane of a 16-lane group");
-  constexpr int E = hrec<NX>();
-  constexpr int F = NX * NX + NX;
-  const int2 t = tiles[blockIdx.x];
-  const PinvDesc& d = pd[t.x];
-  const int64_t tau = (int64_t)t.y * 256 + blockIdx.y * 16 + (threadIdx.x >> 4);
-  const int r = (int)(threadIdx.x & 15);
-  const int64_t B = tau / (64 * kFan);
-  const int i = (int)((tau >> 6) % kFan);
-  const int l = (int)(tau & 63);
-  const int64_t ch = (B * 64 + l) * kFan + i;
-  if (ch >= d.cnt[0]) return;  // the whole group leaves together
-  const bool act = r < NX;
-  const int rr = act ? r : 0;
-  const int64_t Nn = d.Nn;
-  const T* hs = jsw + d.jsw_off + (((B * kFan + i) * 64 + l) * kChunk) * E + rr * NX;
-  const T* yi = y + d.off + (int64_t)rr * Nn;
-  double a[NX], b = 0.0;
-#pragma unroll
-  for (int c = 0; c < NX; ++c) a[c] = (act && c == r) ? 1.0 : 0.0;
-  const int64_t k0 = ch * kChunk;
-  const int jn = (int)min((int64_t)kChunk, Nn - k0);
-  double yv[kChunk];  // the chunk's run of y for component r, loaded together
-#pragma unroll
-  for (int j = 0; j < kChunk; ++j) yv[j] = (act && j < jn) ? (double)yi[k0 + j] : 0.0;
-#pragma unroll
-  for (int j = 0; j < kChunk; ++j) {
-    if (j >= jn) break;
-    double h[NX];
-    load_row<NX, T>(hs + (int64_t)j * E, h);  // lanes r >= NX read row 0 (in bounds), unused
-    const double u = b + yv[j];
-    double na[NX], nb = b;
-#pragma unroll
-    for (int c = 0; c < NX; ++c) na[c] = a[c];
-    static_for<0, NX>([&](auto qc) {
-      constexpr int q = decltype(qc)::value;
-      nb += h[q] * row_bcast<q>(u);
-#pragma unroll
-      for (int c = 0; c < NX; ++c) na[c] += h[q] * row_bcast<q>(a[c]);
-    });
-#pragma unroll
-    for (int c = 0; c < NX; ++c) a[c] = na[c];
-    b = nb;
-  }
-  if (act) {
-    double* agg = scan + d.agg[0];
-#pragma unroll
-    for (int c = 0; c < NX; ++c) agg[swz(B, i, r * NX + c, F, l)] = a[c];
-    agg[swz(B, i, NX * NX + r, F, l)] = b;
-  }
-}
-
-// (A, b) <- (a_A A, a_A b + a_b) for the NX x NX + NX fields of aggregate a (field f at
-// a[f * fs]).
-template <int NX>
-__device__ __forceinline__ void compose(const double* __restrict__ a, int64_t fs, double (&A)[NX][NX],
-                                        double (&b)[NX]) {
-  double nb[NX];
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-    double acc = a[(NX * NX + r) * fs];
-#pragma unroll
-    for (int q = 0; q < NX; ++q) acc += a[(r * NX + q) * fs] * b[q];
-    nb[r] = acc;
-  }
-#pragma unroll
-  for (int col = 0; col < NX; ++col) {
-    double ncol[NX];
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      double acc = 0.0;
-#pragma unroll
-      for (int q = 0; q < NX; ++q) acc += a[(r * NX + q) * fs] * A[q][col];
-      ncol[r] = acc;
-    }
-#pragma unroll
-    for (int r = 0; r < NX; ++r) A[r][col] = ncol[r];
-  }
-#pragma unroll
-  for (int r = 0; r < NX; ++r) b[r] = nb[r];
-}
-
-// s <- a_A s + a_b
-template <int NX>
-__device__ __forceinline__ void advance(const double* __restrict__ a, int64_t fs, double (&s)[NX]) {
-  double ns[NX];
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-    double acc = a[(NX * NX + r) * fs];
-#pragma unroll
-    for (int q = 0; q < NX; ++q) acc += a[(r * NX + q) * fs] * s[q];
-    ns[r] = acc;
-  }
-#pragma unroll
-  for (int r = 0; r < NX; ++r) s[r] = ns[r];
-}
-
-// Upper levels of the hierarchical scan, sixteen lanes per parent (lane r < NX holds row
-// r of a map or component r of a state; rows and states broadcast with DPP row_newbcast).
-// Child aggregate i of parent g: level 0 in the slot layout (field f at stride 64), upper
-// levels plain (F consecutive fields).  grid = (tile (k, block of 256 parents), 16 groups
-// of 16 parents).
-template <int NX>
-__device__ __forceinline__ const double* child_agg(const double* __restrict__ child, int lv, int64_t g, int i,
-                                                   int64_t& fs) {
-  constexpr int F = NX * NX + NX;
-  if (lv == 0) {
-    fs = 64;
-    return child + swz(g >> 6, i, 0, F, (int)(g & 63));
-  }
-  fs = 1;
-  return child + (g * kFan + i) * F;
-}
-
-// Up-sweep level lv -> lv + 1: each parent composes its kFan child aggregates in order,
-// (A, b) <- (a_A A, a_A b + a_b).
-template <int NX>
-__global__ __launch_bounds__(256) void k_pinv_up(double* __restrict__ scan, const PinvDesc* __restrict__ pd,
-                                                 const int2* __restrict__ tiles, int lv) {
-  const int2 t = tiles[blockIdx.x];
-  const PinvDesc& d = pd[t.x];
-  const int64_t g = (int64_t)t.y * 256 + blockIdx.y * 16 + (threadIdx.x >> 4);
-  if (g >= d.cnt[lv + 1]) return;  // the whole group leaves together
-  const int r = (int)(threadIdx.x & 15);
-  const bool act = r < NX;
-  const int rr = act ? r : 0;
-  constexpr int F = NX * NX + NX;
-  const double* child = scan + d.agg[lv];
-  double a[NX], b = 0.0;
-#pragma unroll
-  for (int c = 0; c < NX; ++c) a[c] = (act && c == r) ? 1.0 : 0.0;
-  const int nc = (int)min((int64_t)kFan, d.cnt[lv] - g * kFan);
-#pragma unroll 1
-  for (int i = 0; i < nc; ++i) {
-    int64_t fs;
-    const double* ca = child_agg<NX>(child, lv, g, i, fs);
-    double row[NX];
-#pragma unroll
-    for (int q = 0; q < NX; ++q) row[q] = ca[(rr * NX + q) * fs];
-    double na[NX], nb = ca[(NX * NX + rr) * fs];
-#pragma unroll
-    for (int c = 0; c < NX; ++c) na[c] = 0.0;
-    static_for<0, NX>([&](auto qc) {
-      constexpr int q = decltype(qc)::value;
-      nb += row[q] * row_bcast<q>(b);
-#pragma unroll
-      for (int c = 0; c < NX; ++c) na[c] += row[q] * row_bcast<q>(a[c]);
-    });
-#pragma unroll
-    for (int c = 0; c < NX; ++c) a[c] = na[c];
-    b = nb;
-  }
-  if (act) {
-    double* o = scan + d.agg[lv + 1] + g * F;
-#pragma unroll
-    for (int c = 0; c < NX; ++c) o[r * NX + c] = a[c];
-    o[NX * NX + r] = b;
-  }
-}
-
-// Top: sixteen lanes per instance (one workgroup of 64 threads, the first row working)
-// walk the top-level aggregates from S = 0 and write their start states (level 0 in the
-// slot layout when the instance has a single group).
-template <int NX>
-__global__ void k_pinv_top(double* __restrict__ scan, const PinvDesc* __restrict__ pd) {
-  if (threadIdx.x >= 16) return;
-  const int r = (int)threadIdx.x;
-  const bool act = r < NX;
-  const int rr = act ? r : 0;
-  const PinvDesc& d = pd[blockIdx.x];
-  constexpr int F = NX * NX + NX;
-  const int L = d.L;
-  const double* agg = scan + d.agg[L];
-  double* state = scan + d.st[L];
-  double s = 0.0;
-  for (int64_t i = 0; i < d.cnt[L]; ++i) {
-    const double* ca = (L == 0) ? agg + swz(0, (int)i, 0, F, 0) : agg + i * F;
-    const int64_t fs = (L == 0) ? 64 : 1;
-    if (act) {
-      if (L == 0) state[swz(0, (int)i, r, NX, 0)] = s;
-      else state[i * NX + r] = s;
-    }
-    double ns = ca[(NX * NX + rr) * fs];
-    static_for<0, NX>([&](auto qc) {
-      constexpr int q = decltype(qc)::value;
-      ns += ca[(rr * NX + q) * fs] * row_bcast<q>(s);
-    });
-    s = ns;
-  }
-}
-
-// Down-sweep level lv + 1 -> lv: each parent pushes its start state through its children
-// (level 0 written in the slot layout).
-template <int NX>
-__global__ __launch_bounds__(256) void k_pinv_down(double* __restrict__ scan, const PinvDesc* __restrict__ pd,
-                                                   const int2* __restrict__ tiles, int lv) {
-  const int2 t = tiles[blockIdx.x];
-  const PinvDesc& d = pd[t.x];
-  const int64_t g = (int64_t)t.y * 256 + blockIdx.y * 16 + (threadIdx.x >> 4);
-  if (g >= d.cnt[lv + 1]) return;  // the whole group leaves together
-  const int r = (int)(threadIdx.x & 15);
-  const bool act = r < NX;
-  const int rr = act ? r : 0;
-  const double* child = scan + d.agg[lv];
-  double* cstate = scan + d.st[lv];
-  double s = act ? scan[d.st[lv + 1] + g * NX + r] : 0.0;
-  const int nc = (int)min((int64_t)kFan, d.cnt[lv] - g * kFan);
-#pragma unroll 1
-  for (int i = 0; i < nc; ++i) {
-    if (act) {
-      if (lv == 0) cstate[swz(g >> 6, i, r, NX, (int)(g & 63))] = s;
-      else cstate[(g * kFan + i) * NX + r] = s;
-    }
-    int64_t fs;
-    const double* ca = child_agg<NX>(child, lv, g, i, fs);
-    double row[NX];
-#pragma unroll
-    for (int q = 0; q < NX; ++q) row[q] = ca[(rr * NX + q) * fs];
-    double ns = ca[(NX * NX + rr) * fs];
-    static_for<0, NX>([&](auto qc) {
-      constexpr int q = decltype(qc)::value;
-      ns += row[q] * row_bcast<q>(s);
-    });
-    s = ns;
-  }
-}
-
-// Replay for n_x > 8, sixteen lanes per chunk: lane r < NX carries component r of the
-// state; per node u_r = y_r + S_r, v_r = (H_k u)_r with u gathered across the group,
-// xi_r = u_r + v_r / 2, (J xi)_r = v_r / w_k, S_r <- S_r + v_r, from the chunk's level-0
-// start state.  grid = (tile (k, block of 256 level-0 threads), 16 groups of 16 chunks).
-template <int NX, typename T>
-__global__ __launch_bounds__(256) void k_pinv_final_lanes(const T* __restrict__ jsw, const T* __restrict__ y,
-                                                          const PinvDesc* __restrict__ pd,
-                                                          const int2* __restrict__ tiles,
-                                                          const double* __restrict__ scan, T* __restrict__ out,
-                                                          T* __restrict__ jout) {
-  static_assert(NX <= 16, "one state component per lane of a 16-lane group");
-  const int2 t = tiles[blockIdx.x];
-  const PinvDesc& d = pd[t.x];
-  const int64_t tau = (int64_t)t.y * 256 + blockIdx.y * 16 + (threadIdx.x >> 4);
-  const int r = (int)(threadIdx.x & 15);
-  const int64_t B = tau / (64 * kFan);
-  const int i = (int)((tau >> 6) % kFan);
-  const int l = (int)(tau & 63);
-  const int64_t c = (B * 64 + l) * kFan + i;
-  if (c >= d.cnt[0]) return;  // the whole group leaves together
-  constexpr int E = hrec<NX>();
-  const int64_t Nn = d.Nn;
-  const bool act = r < NX;
-  const int rr = act ? r : 0;
-  const T* js = jsw + d.jsw_off + (((B * kFan + i) * 64 + l) * kChunk) * E;
-  const T* yi = y + d.off;
-  T* oi = out + d.off;
-  T* ji = jout ? jout + d.off : nullptr;
-  double s = act ? scan[d.st[0] + swz(B, i, rr, NX, l)] : 0.0;
-  const int64_t k0 = c * kChunk;
-  const int jn = (int)min((int64_t)kChunk, Nn - k0);
-  // the chunk's kChunk values of y (one 128-byte run per component) are loaded together,
-  // and its outputs kept in registers and stored together at the end, so that each run
-  // is read and written back to back; row r of H_k and w_k of the next node are loaded
-  // while the current node is replayed (the replay itself waits on the carried state)
-  const T* yr = yi + (int64_t)rr * Nn + k0;
-  double yv[kChunk], xo[kChunk], jo[kChunk];
-#pragma unroll
-  for (int j = 0; j < kChunk; ++j) yv[j] = (act && j < jn) ? (double)yr[j] : 0.0;
-  double hn[NX], wn = 1.0;
-  auto fetch = [&](int j) {
-    const T* base = js + (int64_t)j * E;
-    load_row<NX, T>(base + rr * NX, hn);
-    if (!act) {
-#pragma unroll
-      for (int q = 0; q < NX; ++q) hn[q] = 0.0;
-    }
-    wn = (double)base[NX * NX];
-  };
-  if (jn > 0) fetch(0);
-#pragma unroll
-  for (int j = 0; j < kChunk; ++j) {
-    if (j < jn) {
-      double h[NX];
-#pragma unroll
-      for (int q = 0; q < NX; ++q) h[q] = hn[q];
-      const double wk = wn;
-      const double u = s + yv[j];
-      if (j + 1 < jn) fetch(j + 1);
-      double v = 0.0;
-      static_for<0, NX>([&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        v += h[q] * row_bcast<q>(u);
-      });
-      s += v;
-      xo[j] = u + 0.5 * v;
-      jo[j] = v * recip(wk);
-    }
-  }
-  if (act) {
-    T* orow = oi + (int64_t)r * Nn + k0;
-#pragma unroll
-    for (int j = 0; j < kChunk; ++j)
-      if (j < jn) orow[j] = (T)xo[j];
-    if (ji) {
-      T* jrow = ji + (int64_t)r * Nn + k0;
-#pragma unroll
-      for (int j = 0; j < kChunk; ++j)
-        if (j < jn) jrow[j] = (T)jo[j];
-    }
-  }
-}
+// ------------------------------------------------------------------ J x per node
 
 // y_k = J_k x_k per node for every instance of a class.  tile = (k, block of 256 nodes).
 template <int NX, typename T>
 __global__ __launch_bounds__(256) void k_jac_class(const double* __restrict__ J, int per_node,
                                                    const T* __restrict__ x, T* __restrict__ y,
-                                                   const PinvDesc* __restrict__ pd, const int2* __restrict__ tiles) {
+                                                   const ScanDesc* __restrict__ sd, const int2* __restrict__ tiles) {
   const int2 t = tiles[blockIdx.x];
-  const PinvDesc& d = pd[t.x];
+  const ScanDesc& d = sd[t.x];
   const int64_t k = (int64_t)t.y * blockDim.x + threadIdx.x;
   const int64_t Nn = d.Nn;
   if (k >= Nn) return;
@@ -809,43 +343,6 @@ __global__ __launch_bounds__(256) void k_jac_class(const double* __restrict__ J,
 }
 
 static inline unsigned nblocks(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
-
-// Level sizes of the scan for one instance: cnt[0] chunks, then groups of kFan.
-static int pinv_levels(int64_t Nn, int64_t* cnt) {
-  int L = 0;
-  cnt[0] = (Nn + kChunk - 1) / kChunk;
-  while (cnt[L] > kFan && L < kPinvMaxLevels - 1) {
-    cnt[L + 1] = (cnt[L] + kFan - 1) / kFan;
-    ++L;
-  }
-  return L;
-}
-
-// Level-0 threads (and swizzled slots) are allocated in blocks of 64 groups.
-static int64_t pinv_blocks0(int64_t nchunks) {
-  const int64_t groups = (nchunks + kFan - 1) / kFan;
-  return (groups + 63) / 64;
-}
-
-int64_t pinv_jsw_size(int64_t Nn, int nx, birk_precision prec) {
-  if (nx > 12) return 0;   // no preconditioner
-  if (nx <= kScanNx) return prec == BIRK_F32_REFINE_F64 ? scan_htab(Nn, nx) : 0;
-  int64_t cnt[kPinvMaxLevels];
-  pinv_levels(Nn, cnt);
-  return pinv_blocks0(cnt[0]) * 64 * kFan * kChunk * (((int64_t)nx * nx + 4) & ~int64_t(3));  // hrec<nx>()
-}
-
-// Scratch (doubles) the inverse scan needs for one instance (level 0 in whole blocks).
-int64_t pinv_scratch(int64_t Nn, int nx) {
-  if (nx > 12) return 0;
-  const int64_t S = (int64_t)nx * nx + 2 * nx;
-  if (nx <= kScanNx) return scan_scratch(Nn, nx);
-  int64_t cnt[kPinvMaxLevels];
-  const int L = pinv_levels(Nn, cnt);
-  int64_t tot = pinv_blocks0(cnt[0]) * 64 * kFan * S;
-  for (int l = 1; l <= L; ++l) tot += cnt[l] * S;
-  return tot;
-}
 
 static hipError_t upload_tiles(birk_plan* p, const std::vector<int2>& v, int2** dst) {
   void* d = nullptr;
@@ -888,70 +385,6 @@ hipError_t plan_solve(birk_plan* p) {
     if ((e = upload_tiles(p, bt, &p->pfwd_btiles)) != hipSuccess) return e;
     p->pfwd_nbtiles = (int)bt.size();
   }
-  p->pclass.clear();
-  for (int nx = 1; nx <= 12; ++nx) {
-    PinvClass pc;
-    pc.nx = nx;
-    for (const Instance& in : p->inst) {
-      if (in.nx != nx) continue;
-      PinvDesc d;
-      d.Nn = in.Nn;
-      d.off = in.off;
-      d.joff = in.joff;
-      d.jcoff = in.jcoff;
-      d.jsw_off = in.jsw_off;
-      d.w = in.w;
-      const int64_t S = (int64_t)nx * nx + nx;
-      int64_t base = in.scan_off;
-      if (nx <= kScanNx) {   // J x only; P^{-1} is birk_scan.hip's
-        pc.host.push_back(d);
-        continue;
-      }
-      d.L = pinv_levels(in.Nn, d.cnt);
-      d.nb0 = (int)pinv_blocks0(d.cnt[0]);
-      // scratch: for each level l: agg[slots * S] then state[slots * NX]; level 0 swizzled
-      for (int l = 0; l <= d.L; ++l) {
-        const int64_t slots = (l == 0) ? (int64_t)d.nb0 * 64 * kFan : d.cnt[l];
-        d.agg[l] = base;
-        base += slots * S;
-        d.st[l] = base;
-        base += slots * nx;
-      }
-      pc.host.push_back(d);
-      pc.Lmax = std::max(pc.Lmax, d.L);
-    }
-    if (pc.host.empty()) continue;
-    pc.ninst = (int)pc.host.size();
-    std::vector<int2> t0, tn, tup[kPinvMaxLevels];
-    for (int k = 0; k < pc.ninst; ++k) {
-      const PinvDesc& d = pc.host[k];
-      if (nx <= kScanNx) {
-        for (unsigned b = 0; b < nblocks(d.Nn, 256); ++b) tn.push_back(make_int2(k, (int)b));
-        continue;
-      }
-      const int64_t thr0 = (int64_t)d.nb0 * 64 * kFan;
-      for (unsigned b = 0; b < nblocks(thr0, 256); ++b) t0.push_back(make_int2(k, (int)b));
-      for (unsigned b = 0; b < nblocks(d.Nn, 256); ++b) tn.push_back(make_int2(k, (int)b));
-      for (int l = 0; l < d.L; ++l) {
-        for (unsigned b = 0; b < nblocks(d.cnt[l + 1], 256); ++b) tup[l].push_back(make_int2(k, (int)b));
-      }
-    }
-    void* dd = nullptr;
-    if ((e = hipMalloc(&dd, pc.host.size() * sizeof(PinvDesc))) != hipSuccess) return e;
-    p->allocs.push_back(dd);
-    pc.dev = (PinvDesc*)dd;
-    if ((e = hipMemcpy(dd, pc.host.data(), pc.host.size() * sizeof(PinvDesc), hipMemcpyHostToDevice)) != hipSuccess)
-      return e;
-    if ((e = upload_tiles(p, t0, &pc.t_node0)) != hipSuccess) return e;
-    pc.n_node0 = (int)t0.size();
-    if ((e = upload_tiles(p, tn, &pc.t_nodes)) != hipSuccess) return e;
-    pc.n_nodes = (int)tn.size();
-    for (int l = 0; l < pc.Lmax; ++l) {
-      if ((e = upload_tiles(p, tup[l], &pc.t_up[l])) != hipSuccess) return e;
-      pc.n_up[l] = (int)tup[l].size();
-    }
-    p->pclass.push_back(std::move(pc));
-  }
   // Krylov segmentation
   {
     const int B = (int)p->inst.size();
@@ -983,15 +416,6 @@ hipError_t plan_solve(birk_plan* p) {
   return hipSuccess;
 }
 
-template <int NX, typename JT>
-static void make_h_class(birk_plan* p, const PinvClass& pc, const double* J, int pn, hipStream_t s) {
-  if constexpr (NX > kScanNx) {
-    if (pc.n_node0 == 0) return;
-    hipLaunchKernelGGL((k_make_h_rows<NX, JT>), dim3(pc.n_node0, 16), dim3(256), 0, s, (JT*)p->jsw, J, pn, pc.dev,
-                       pc.t_node0, p->flag);
-  }
-}
-
 #define BIRK_NX_SWITCH(nx, CALL)                                       \
   switch (nx) {                                                        \
     case 1: { constexpr int NXC = 1; CALL; } break;                    \
@@ -1009,67 +433,16 @@ static void make_h_class(birk_plan* p, const PinvClass& pc, const double* J, int
     default: return hipErrorInvalidValue;                              \
   }
 
-// Per-Jacobian preparation of the scan: n_x > 8 lay J and w out in the level-0 slots and
-// replace the J fields by H_k (k_make_h_rows), which their scan kernels read.  n_x <= 8 with
-// per-node J in float (a mixed solve) keep H_k in float, half the bytes of J; otherwise they
-// need nothing.
-hipError_t precond_prepare(birk_plan* p, int jac_kind, const double* J, int single, hipStream_t s, int cache) {
-  const int pn = jac_kind == BIRK_J_PER_NODE ? 1 : 0;
-  for (const PinvClass& pc : p->pclass) {
-    if (single) {
-      BIRK_NX_SWITCH(pc.nx, (make_h_class<NXC, float>(p, pc, J, pn, s)))
-    } else {
-      BIRK_NX_SWITCH(pc.nx, (make_h_class<NXC, double>(p, pc, J, pn, s)))
-    }
-  }
-  if (cache && pn) {
-    const hipError_t e = scan_prepare(p, J, s);
-    if (e != hipSuccess) return e;
-  }
-  return hipGetLastError();
-}
-
 template <int NX, typename T>
-static void pinv_class(birk_plan* p, const PinvClass& pc, const T* y, T* out, T* jout, hipStream_t s) {
-  if constexpr (NX > kScanNx) {
-    const T* jsw = (const T*)p->jsw;
-    double* scan = p->scan;
-    hipLaunchKernelGGL((k_pinv_up0<NX, T>), dim3(pc.n_node0, 16), dim3(256), 0, s, jsw, y, pc.dev, pc.t_node0, scan);
-    for (int l = 0; l < pc.Lmax; ++l)
-      hipLaunchKernelGGL((k_pinv_up<NX>), dim3(pc.n_up[l], 16), dim3(256), 0, s, scan, pc.dev, pc.t_up[l], l);
-    hipLaunchKernelGGL((k_pinv_top<NX>), dim3(pc.ninst), dim3(64), 0, s, scan, pc.dev);
-    for (int l = pc.Lmax - 1; l >= 0; --l)
-      hipLaunchKernelGGL((k_pinv_down<NX>), dim3(pc.n_up[l], 16), dim3(256), 0, s, scan, pc.dev, pc.t_up[l], l);
-    hipLaunchKernelGGL((k_pinv_final_lanes<NX, T>), dim3(pc.n_node0, 16), dim3(256), 0, s, jsw, y, pc.dev,
-                       pc.t_node0, scan, out, jout);
-  }
-}
-
-template <int NX, typename T>
-static void jac_class(const PinvClass& pc, const double* J, int pn, const T* x, T* y, hipStream_t s) {
-  hipLaunchKernelGGL((k_jac_class<NX, T>), dim3(pc.n_nodes), dim3(256), 0, s, J, pn, x, y, pc.dev, pc.t_nodes);
-}
-
-
-template <typename T>
-hipError_t precond_inverse(birk_plan* p, int jac_kind, const double* J, const T* y, T* out, T* jout,
-                           hipStream_t s, int* flag, int cached) {
-  // n_x <= 8: K_k formed from J and factored inside the scan kernels (pivot checks into
-  // *flag when given), or with cached = 1 the H_k that precond_prepare kept; larger n_x
-  // read the H_k that precond_prepare laid out for this J (checking the pivots there)
-  hipError_t e = scan_inverse<T>(p, jac_kind, J, y, out, jout, cached, s, flag);
-  if (e != hipSuccess) return e;
-  for (const PinvClass& pc : p->pclass) {
-    BIRK_NX_SWITCH(pc.nx, (pinv_class<NXC, T>(p, pc, y, out, jout, s)))
-  }
-  return hipGetLastError();
+static void jac_class(const ScanClass& sc, const double* J, int pn, const T* x, T* y, hipStream_t s) {
+  hipLaunchKernelGGL((k_jac_class<NX, T>), dim3(sc.n_nodes), dim3(256), 0, s, J, pn, x, y, sc.dev, sc.nodes);
 }
 
 template <typename T>
 hipError_t jac_times(birk_plan* p, int jac_kind, const double* J, const T* x, T* y, hipStream_t s) {
   const int pn = jac_kind == BIRK_J_PER_NODE ? 1 : 0;
-  for (const PinvClass& pc : p->pclass) {
-    BIRK_NX_SWITCH(pc.nx, (jac_class<NXC, T>(pc, J, pn, x, y, s)))
+  for (const ScanClass& sc : p->sclass) {
+    BIRK_NX_SWITCH(sc.nx, (jac_class<NXC, T>(sc, J, pn, x, y, s)))
   }
   return hipGetLastError();
 }
@@ -1080,10 +453,6 @@ template hipError_t jac_times<double>(birk_plan*, int, const double*, const doub
 template hipError_t jac_times<float>(birk_plan*, int, const double*, const float*, float*, hipStream_t);
 template hipError_t precond_forward<double>(birk_plan*, int, const double*, const double*, double*, hipStream_t);
 template hipError_t precond_forward<float>(birk_plan*, int, const double*, const float*, float*, hipStream_t);
-template hipError_t precond_inverse<double>(birk_plan*, int, const double*, const double*, double*, double*,
-                                            hipStream_t, int*, int);
-template hipError_t precond_inverse<float>(birk_plan*, int, const double*, const float*, float*, float*,
-                                           hipStream_t, int*, int);
 
 // ------------------------------------------------------------------ Krylov BLAS-1
 // Krylov BLAS-1: at most kMaxDots basis vectors per call, reductions in double.

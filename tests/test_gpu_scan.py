@@ -1,6 +1,6 @@
-"""GPU parity of the n_x <= 8 scans behind P^{-1} and P^{-T} at the sizes where their split
+"""GPU parity of the scans behind P^{-1} and P^{-T} at the sizes where their split
 changes: around one chunk (16 nodes) and one wave (64), the last instance that one workgroup
-holds and the first that it does not, one and two groups of 64 tiles, one and two rounds per
+holds and the first that it does not, one and two groups of tiles, one and two rounds per
 tile; forward and transposed, one J and J per node, double and float; alone and side by side
 in one plan, whose launches then hold all kinds, bit for bit.  Reference: block substitution in
 NumPy.  Bars as in the preconditioner tests: 1e-12 (double), 2e-6 (float storage) of the
@@ -103,3 +103,12 @@ def test_rounds(B, nx, inverse):
     n = 64 * 256 * WAVES[nx]   # one round per tile up to here, two from the next node on
     for nn in (n, n + 1):
         _check(B, [(nn, nx)], inverse, "f64", nx == 6)
+
+
+@pytest.mark.parametrize("per_node", [False, True])
+@pytest.mark.parametrize("inverse,prec", [(1, "f64"), (1, "f32"), (2, "f64")])
+@pytest.mark.parametrize("nx", range(9, 13))
+def test_split_edges_wide(B, nx, inverse, prec, per_node):
+    # sixteen nodes a tile (two rounds from 16385 nodes), 32 tiles a group
+    sizes = (3, 15, 16, 17, 32, 33, 512, 513, 528, 529, 1025) + ((16384, 16385) if nx == 12 else ())
+    _check(B, [(n, nx) for n in sizes], inverse, prec, per_node)

@@ -403,7 +403,6 @@ birk_status kkt_solve(birk_plan* p, int jk, const double* J, const double* h, co
   const int64_t n = p->total_len;
   hipStream_t s = p->stream;
   hipError_t e = ensure_kkt(p);
-  if (e == hipSuccess) e = (p->krylov_part ? hipSuccess : hipMalloc(&p->krylov_part, sizeof(double)));
   if (e != hipSuccess) return e == hipErrorOutOfMemory ? BIRK_ERR_NOMEM : BIRK_ERR_DEVICE;
   KktBufs b = kkt_bufs(p);
   const Seg sg = make_seg(p);

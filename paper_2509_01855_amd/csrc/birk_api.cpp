@@ -601,10 +601,9 @@ hipError_t ensure_krylov(birk_plan* p, int m, size_t esize) {
   return e;
 }
 
-// Per-instance ||v_i||^2 for a double vector (one segmented launch); results into host array.
-hipError_t seg_norms(birk_plan* p, const double* v, std::vector<double>& out) {
+// Per-instance norms whose squares are in the norm slots of krylov_dots, into a host array.
+hipError_t read_norms(birk_plan* p, std::vector<double>& out) {
   const int B = (int)p->inst.size();
-  kry::sdots<double>(p, nullptr, 0, v, p->krylov_dots, 2 * kDotsStride, p->stream);
   const double* h = stage_dots(p);
   hipError_t e = hipMemcpyAsync(stage_dots(p), p->krylov_dots, (size_t)B * 2 * kDotsStride * sizeof(double),
                                 hipMemcpyDeviceToHost, p->stream);
@@ -618,9 +617,15 @@ hipError_t seg_norms(birk_plan* p, const double* v, std::vector<double>& out) {
   return e;
 }
 
+// Per-instance ||v_i|| of a double vector into a host array.
+hipError_t seg_norms(birk_plan* p, const double* v, std::vector<double>& out) {
+  kry::snorms(p, v, p->krylov_dots, 2 * kDotsStride, p->stream);
+  return read_norms(p, out);
+}
+
 // One Arnoldi step j of every instance (stopped instances are carried along; the device
-// state ignores their columns): z = P^{-1} q_j and y = J z (or y = J q_j without the
-// preconditioner), t = B^a y, u = z - t, CGS2 against q_0..q_j, q_{j+1} = u / ||u||, and
+// state ignores their columns): q_j = u / ||u|| (j > 0), z = P^{-1} q_j and y = J z (or
+// y = J q_j without the preconditioner), t = B^a y, u = z - t, CGS2 against q_0..q_j, and
 // the device update of the Hessenberg column, rotations and g.
 template <typename TK>
 static hipError_t arnoldi_step(birk_plan* p, int jk, const double* J, int j, int m, int use_precond, bool keep_jz,
@@ -632,6 +637,9 @@ static hipError_t arnoldi_step(birk_plan* p, int jk, const double* J, int j, int
   TK* u = (TK*)p->krylov_vec;
   TK* y = keep_jz ? Z + (size_t)m * n + (size_t)j * n : u + n;
   TK* t = u + 2 * n;
+  double* dots = p->krylov_dots;
+  const int64_t ds = 2 * kDotsStride;
+  if (j > 0) kry::next_vector<TK>(p, u, dots, ds, Q + (size_t)j * n, s);
   const TK* qj = Q + (size_t)j * n;
   TK* z = Z + (size_t)j * n;
   const TK* uz = qj;
@@ -644,14 +652,7 @@ static hipError_t arnoldi_step(birk_plan* p, int jk, const double* J, int j, int
   }
   if (e == hipSuccess) e = apply_product<TK>(p, y, t, 0, s);
   if (e != hipSuccess) return e;
-  double* d1 = p->krylov_dots;
-  double* d2 = d1 + kDotsStride;
-  const int64_t ds = 2 * kDotsStride;
-  kry::sub_sdots<TK>(p, Q, j + 1, uz, t, u, d1, ds, s);
-  kry::saxpys_dots<TK>(p, Q, j + 1, d1, ds, u, d2, ds, s);
-  kry::saxpys<TK>(p, Q, j + 1, d2, ds, u, d2, s);
-  kry::snormalize<TK>(p, u, d2 + kKryMaxDots, ds, Q + (size_t)(j + 1) * n, s);
-  kry::gm_column(p, j, p->krylov_dots, ds, p->krylov_gm, s);
+  kry::gram_schmidt<TK>(p, Q, j, uz, t, u, dots, ds, p->krylov_gm, p->krylov_prm + 3 * p->inst.size(), s);
   return hipGetLastError();
 }
 
@@ -695,14 +696,15 @@ static hipError_t arnoldi_chunk(birk_plan* p, int jk, const double* J, int j0, i
 
 // One right-preconditioned GMRES cycle in precision TK on A d = r / ||r||, for every
 // instance not yet done; chi += ||r|| d.  r: the current residual (double).  jchi
-// (double plans, else null): J chi, updated alongside chi from the kept J z_j.  The
+// (double plans, else null): J chi, updated alongside chi from the kept J z_j.  fresh: both
+// count as zero, and are written (cleared on return).  The
 // Hessenberg columns, rotations and the small least-squares solve run on the device; the
 // host reads the per-instance running flags after each of the first three steps, then
 // (plans shorter than 2^20 elements) after chunks of 2, then 4 steps.
 template <typename TK>
 birk_status gmres_cycle(birk_plan* p, int jk, const double* J, const double* r, double* chi, double* jchi,
                         std::vector<InstState>& st, const std::vector<double>& tol_inner, int m, int use_precond,
-                        int& budget) {
+                        int& budget, bool& fresh) {
   const int B = (int)p->inst.size();
   const int64_t n = p->total_len;
   hipStream_t s = p->stream;
@@ -746,7 +748,6 @@ birk_status gmres_cycle(birk_plan* p, int jk, const double* J, const double* r, 
     j += k;
     budget -= k;
     ++checks;
-    kry::gm_running(p, p->krylov_gm, p->krylov_prm + 3 * B, s);
     e = hipMemcpyAsync(flags, p->krylov_prm + 3 * B, B * sizeof(double), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess && !flag_checked) e = hipMemcpyAsync(stage_flag(p), p->flag, sizeof(int), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -765,9 +766,10 @@ birk_status gmres_cycle(birk_plan* p, int jk, const double* J, const double* r, 
   // y = R^{-1} g and chi += ||r|| Z y (Z = Q without preconditioning) on the device
   kry::gm_solve(p, p->krylov_gm, p->krylov_coef, kDotsStride, p->krylov_cnt, p->krylov_prm + 3 * B, s);
   const TK* basis = use_precond ? Z : Q;
-  kry::scombine<TK>(p, basis, p->krylov_coef, kDotsStride, p->krylov_cnt, chi, s);
   // J chi += ||r|| J Z y (J Q y without preconditioning) from the kept J z_j
-  if (Yb) kry::scombine<TK>(p, Yb, p->krylov_coef, kDotsStride, p->krylov_cnt, jchi, s);
+  kry::scombine<TK>(p, p->krylov_coef, kDotsStride, p->krylov_cnt, basis, fresh ? nullptr : chi, chi, Yb,
+                    fresh ? nullptr : jchi, jchi, s);
+  fresh = false;
   e = hipMemcpyAsync(flags, p->krylov_prm + 3 * B, 3 * B * sizeof(double), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return BIRK_ERR_DEVICE;
@@ -816,7 +818,7 @@ extern "C" birk_status birk_krylov_solve(birk_plan* p, birk_jac_kind jk, const d
   if (hipMemsetAsync(p->flag, 0, sizeof(int), s) != hipSuccess) return BIRK_ERR_DEVICE;
   // mixed plans keep the float H_k: reading the double J costs more than a float table
   if (o.use_precond && mixed && jk == BIRK_J_PER_NODE && scan_prepare(p, J, s) != hipSuccess) return BIRK_ERR_DEVICE;
-  if (!o.use_x0 && hipMemsetAsync(chi, 0, n * sizeof(double), s) != hipSuccess) return BIRK_ERR_DEVICE;
+  bool fresh = !o.use_x0;   // chi = 0, not yet written
 
   std::vector<InstState> st(B);
   std::vector<double> nb;
@@ -831,8 +833,8 @@ extern "C" birk_status birk_krylov_solve(birk_plan* p, birk_jac_kind jk, const d
   // double plans carry J chi (tmp_vec[2]) alongside chi, updated from the kept J z_j, so
   // the true residual needs no Jacobian product; mixed plans form J chi from chi in double
   double* jchi = mixed ? nullptr : (double*)p->tmp_vec[2];
-  if (jchi) {
-    e = o.use_x0 ? jac_times<double>(p, jk, J, chi, jchi, s) : hipMemsetAsync(jchi, 0, n * sizeof(double), s);
+  if (jchi && o.use_x0) {
+    e = jac_times<double>(p, jk, J, chi, jchi, s);
     if (e != hipSuccess) return BIRK_ERR_DEVICE;
   }
   for (int outer = 0;; ++outer) {
@@ -846,8 +848,8 @@ extern "C" birk_status birk_krylov_solve(birk_plan* p, birk_jac_kind jk, const d
     } else {
       e = jchi ? apply_product<double>(p, jchi, t, 0, s) : fast_ax_f64(p, jk, J, chi, t);
       if (e != hipSuccess) return BIRK_ERR_DEVICE;
-      kry::residual(beta, chi, t, r, n, s);
-      if (seg_norms(p, r, rn) != hipSuccess) return BIRK_ERR_DEVICE;
+      kry::residual(p, beta, chi, t, r, p->krylov_dots, 2 * kDotsStride, s);
+      if (read_norms(p, rn) != hipSuccess) return BIRK_ERR_DEVICE;
     }
     bool all_done = true;
     for (int i = 0; i < B; ++i) {
@@ -887,8 +889,8 @@ extern "C" birk_status birk_krylov_solve(birk_plan* p, birk_jac_kind jk, const d
       st[i].breakdown_last = st[i].status == BIRK_ERR_BREAKDOWN;
       if (st[i].status == BIRK_ERR_BREAKDOWN) st[i].status = BIRK_OK;
     }
-    birk_status cs = mixed ? gmres_cycle<float>(p, jk, J, rcur, chi, nullptr, st, tol, o.restart, o.use_precond, budget)
-                           : gmres_cycle<double>(p, jk, J, rcur, chi, jchi, st, tol, o.restart, o.use_precond, budget);
+    birk_status cs = mixed ? gmres_cycle<float>(p, jk, J, rcur, chi, nullptr, st, tol, o.restart, o.use_precond, budget, fresh)
+                           : gmres_cycle<double>(p, jk, J, rcur, chi, jchi, st, tol, o.restart, o.use_precond, budget, fresh);
     if (cs == BIRK_ERR_SINGULAR || cs == BIRK_ERR_DEVICE) {
       result = cs;
       for (int i = 0; i < B; ++i) st[i].done = true;
@@ -897,6 +899,7 @@ extern "C" birk_status birk_krylov_solve(birk_plan* p, birk_jac_kind jk, const d
     for (int i = 0; i < B; ++i)
       if (st[i].status == BIRK_ERR_NONFINITE) st[i].done = true;
   }
+  if (fresh && hipMemsetAsync(chi, 0, n * sizeof(double), s) != hipSuccess) return BIRK_ERR_DEVICE;
   for (int i = 0; i < B; ++i) {
     if (result == BIRK_OK && st[i].status != BIRK_OK) result = (birk_status)st[i].status;
     if (info) {
@@ -1108,11 +1111,7 @@ birk_status birk_newton_ivp(birk_plan* p, const birk_ivp_model* model, const dou
         result = BIRK_ERR_DEVICE;
         break;
       }
-      if (hipMemcpyAsync(b.Xt, X, p->total_len * sizeof(double), hipMemcpyDeviceToDevice, s) != hipSuccess) {
-        result = BIRK_ERR_DEVICE;
-        break;
-      }
-      kry::scombine<double>(p, b.D, b.lam, 1, b.cnt, b.Xt, s);
+      kry::scombine<double>(p, b.lam, 1, b.cnt, b.D, X, b.Xt, nullptr, nullptr, nullptr, s);
       result = newton_residual(p, *model, xa, b.Xt, b.F, b.Gt, gtn, xtn);
       if (result != BIRK_OK) break;
       bool again = false;

@@ -212,7 +212,7 @@ struct birk_plan {
   void* krylov_Q = nullptr;   // (2m + 1) vectors of the Krylov precision (Q and Z)
   void* krylov_vec = nullptr; // 4 vectors of the Krylov precision
   double* krylov_dots = nullptr;  // [batch][2][kKryMaxDots + 1]
-  double* krylov_part = nullptr;  // reduction partials [tiles][kKryMaxDots + 1]
+  double* krylov_part = nullptr;  // reduction partials [kKryMaxDots + 1][tiles]
   double* krylov_coef = nullptr;  // per instance: scale factors / combination coefficients,
                                   // followed by the counts krylov_cnt (one upload for both)
   int* krylov_cnt = nullptr;      // per instance: number of combined basis vectors
@@ -334,7 +334,7 @@ hipError_t two_body(birk_plan* p, double mu, double scale, const double* X, doub
 // G = X - xa - G per component (G holds B^a F on entry).
 hipError_t ivp_residual(birk_plan* p, const double* xa, const double* X, double* G, hipStream_t s);
 
-// ---- preconditioner, Jacobian products and Krylov kernels (birk_solve.hip) ----
+// ---- preconditioner and Jacobian products (birk_solve.hip) ----
 template <typename T>
 hipError_t jac_times(birk_plan* p, int jac_kind, const double* J, const T* x, T* y,
                      hipStream_t s);
@@ -368,7 +368,8 @@ hipError_t wide_inverse(birk_plan* p, const ScanClass& sc, int per_node, const d
 hipError_t wide_inverse_t(birk_plan* p, const ScanClass& sc, int per_node, const double* J, const double* y,
                           double* out, hipStream_t s);
 
-// Krylov BLAS-1 launchers (birk_solve.hip).  Reductions accumulate in double.
+// ---- Krylov passes (birk_krylov.hip) ----
+// Reductions accumulate in double.
 constexpr int kKryMaxDots = 32;
 // Device-side GMRES state per instance (doubles): rotated Hessenberg columns R
 // (column-major, kGmLd rows per column), g, cos, sin, then the scalars of GM_*.
@@ -383,36 +384,32 @@ constexpr int kGmStride = kGmMisc + kGmMiscLen + 1;
 namespace kry {
 template <typename T>
 void sub(const T* a, const T* b, T* z, int64_t n, hipStream_t s);
-void residual(const double* beta, const double* x, const double* t, double* r, int64_t n, hipStream_t s);
-// Segmented forms over every instance of the batch at once (ld = plan length; per
-// instance i results at out + i * ostride).
+// Segmented forms over every instance of the batch at once (basis vectors Q_k a plan length
+// apart; per instance i results at out + i * ostride).
+// norm slot of out: ||v||^2
+void snorms(const birk_plan* p, const double* v, double* out, int64_t ostride, hipStream_t s);
+// r = beta - x + t, norm slot of out: ||r||^2
+void residual(const birk_plan* p, const double* beta, const double* x, const double* t, double* r, double* out,
+              int64_t ostride, hipStream_t s);
+// Step j of GMRES from u = a - b: two Gram-Schmidt passes against q_0 .. q_j (coefficients and
+// ||u||^2 in dots: two blocks of kGmLd per instance), the Hessenberg column into st, and
+// whether the instance runs on into flags.  q_{j+1} = u / ||u|| follows from next_vector,
+// which a next step starts with.
 template <typename T>
-void sdots(const birk_plan* p, const T* Q, int nq, const T* u, double* out, int64_t ostride, hipStream_t s);
-// u = a - b, then the dots of sdots, in one pass
+void gram_schmidt(const birk_plan* p, T* Q, int j, const T* a, const T* b, T* u, double* dots, int64_t dstride,
+                  double* st, double* flags, hipStream_t s);
 template <typename T>
-void sub_sdots(const birk_plan* p, const T* Q, int nq, const T* a, const T* b, T* u, double* out, int64_t ostride,
-               hipStream_t s);
-template <typename T>
-void saxpys(const birk_plan* p, const T* Q, int nq, const double* h, int64_t hstride, T* u, double* nrm_out,
-            hipStream_t s);
-// u -= sum_k h_k Q_k, then out = (Q_k . u for k < nq, ||u||^2 in the norm slot): the
-// update and the next Gram-Schmidt dot products in one pass
-template <typename T>
-void saxpys_dots(const birk_plan* p, const T* Q, int nq, const double* h, int64_t hstride, T* u, double* out,
-                 int64_t ostride, hipStream_t s);
-template <typename T>
-void snormalize(const birk_plan* p, const T* u, const double* nrm2, int64_t stride, T* q, hipStream_t s);
+void next_vector(const birk_plan* p, const T* u, const double* dots, int64_t dstride, T* q, hipStream_t s);
 template <typename TI, typename TO>
 void sscale_conv(const birk_plan* p, const TI* x, TO* y, const double* alpha, hipStream_t s);
-// x += sum_{k < cnt[i]} c[i][k] Q_k (x double, the sum in double)
+// x = x0 + sum_{k < cnt[i]} c[i][k] Q0_k, and with Q1 y = y0 + the same of Q1 (x, y double, the
+// sums in double; x0, y0 null: zero; x0 may be x, y0 y)
 template <typename T>
-void scombine(const birk_plan* p, const T* Q, const double* c, int64_t cstride, const int* cnt, double* x,
-              hipStream_t s);
+void scombine(const birk_plan* p, const double* c, int64_t cstride, const int* cnt, const T* Q0, const double* x0,
+              double* x, const T* Q1, const double* y0, double* y, hipStream_t s);
 // device-side GMRES scalars: prm = (active, tolerance, ||r||) per instance
 void gm_init(const birk_plan* p, const double* prm, double* st, hipStream_t s);
-void gm_column(const birk_plan* p, int j, const double* dots, int64_t dstride, double* st, hipStream_t s);
 void gm_solve(const birk_plan* p, double* st, double* coef, int64_t cstride, int* cnt, double* flags, hipStream_t s);
-void gm_running(const birk_plan* p, const double* st, double* flags, hipStream_t s);
 }  // namespace kry
 
 // ---- the KKT form and MINRES (birk_kkt.hip) ----

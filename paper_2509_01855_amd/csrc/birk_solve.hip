@@ -454,405 +454,4 @@ template hipError_t jac_times<float>(birk_plan*, int, const double*, const float
 template hipError_t precond_forward<double>(birk_plan*, int, const double*, const double*, double*, hipStream_t);
 template hipError_t precond_forward<float>(birk_plan*, int, const double*, const float*, float*, hipStream_t);
 
-// ------------------------------------------------------------------ Krylov BLAS-1
-// Krylov BLAS-1: at most kMaxDots basis vectors per call, reductions in double.
-constexpr int kMaxDots = 32;
-
-// z = a - b  (FastAX step 3)
-template <typename T>
-__global__ void k_sub(const T* __restrict__ a, const T* __restrict__ b, T* __restrict__ z, int64_t n) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  z[e] = a[e] - b[e];
-}
-
-// r = beta - (x - t) = beta - x + t, in double
-__global__ void k_residual(const double* __restrict__ beta, const double* __restrict__ x,
-                           const double* __restrict__ t, double* __restrict__ r, int64_t n) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  r[e] = beta[e] - x[e] + t[e];
-}
-
-
-// ---- segmented forms: one launch over every instance of the batch ----
-// A tile is kSegChunk consecutive elements of one instance; partial results go to
-// part[tile][kMaxDots + 1] and are summed per instance over its tile range in a fixed
-// order.
-
-// MAXQ >= nq bounds the per-thread accumulators (registers) at compile time.  SUB = 1
-// first forms u = a - b (in T, as k_sub does) and stores it, in the same pass.
-template <typename T, int MAXQ, int SUB>
-__global__ __launch_bounds__(256) void k_sdots(const T* __restrict__ Q, int64_t ld, int nq, const T* u_in,
-                                               const T* __restrict__ a, const T* __restrict__ b, T* u_out,
-                                               SegSet sg, double* __restrict__ part) {
-  const int2 t = sg.tiles[blockIdx.x];
-  const int64_t base = sg.ioff[t.x] + (int64_t)t.y * kSegChunk;
-  const int64_t end = sg.ioff[t.x] + min((int64_t)(t.y + 1) * kSegChunk, sg.ilen[t.x]);
-  double acc[MAXQ], nrm = 0.0;
-#pragma unroll
-  for (int i = 0; i < MAXQ; ++i) acc[i] = 0.0;
-  for (int64_t e = base + threadIdx.x; e < end; e += blockDim.x) {
-    double ue;
-    if (SUB) {
-      const T d = a[e] - b[e];
-      u_out[e] = d;
-      ue = (double)d;
-    } else {
-      ue = (double)u_in[e];
-    }
-#pragma unroll
-    for (int i = 0; i < MAXQ; ++i)
-      if (i < nq) acc[i] += (double)Q[(int64_t)i * ld + e] * ue;
-    nrm += ue * ue;
-  }
-  __shared__ double sh[256];
-#pragma unroll
-  for (int i = 0; i < MAXQ; ++i) {
-    if (i < nq) {
-      const double v = block_sum256(acc[i], sh);
-      if (threadIdx.x == 0) part[(int64_t)blockIdx.x * (kMaxDots + 1) + i] = v;
-    }
-  }
-  const double v = block_sum256(nrm, sh);
-  if (threadIdx.x == 0) part[(int64_t)blockIdx.x * (kMaxDots + 1) + kMaxDots] = v;
-}
-
-// Smallest accumulator bound of the Krylov kernels that covers nq basis vectors.
-#define BIRK_MAXQ_SWITCH(nq, CALL)                         \
-  if ((nq) <= 2) { constexpr int MQ = 2; CALL; }           \
-  else if ((nq) <= 8) { constexpr int MQ = 8; CALL; }      \
-  else { constexpr int MQ = kMaxDots; CALL; }
-
-// grid = (nq + 1, instances): block (x, i) sums output x (x == nq: the norm slot) of
-// instance i over its tiles into out[i * ostride + slot].
-__global__ __launch_bounds__(256) void k_sreduce(const double* __restrict__ part, SegSet sg, int nq,
-                                                 double* __restrict__ out, int64_t ostride) {
-  __shared__ double sh[256];
-  const int i = blockIdx.y;
-  const int slot = (blockIdx.x < (unsigned)nq) ? (int)blockIdx.x : kMaxDots;
-  const int2 r = sg.ranges[i];
-  double s = 0.0;
-  for (int b = r.x + threadIdx.x; b < r.y; b += blockDim.x) s += part[(int64_t)b * (kMaxDots + 1) + slot];
-  const double tot = block_sum256(s, sh);
-  if (threadIdx.x == 0) out[(int64_t)i * ostride + slot] = tot;
-}
-
-// u -= sum_k h[i][k] Q_k on instance i's tiles; part <- tile sums of ||u||^2 when asked,
-// and with DOTS also of Q_k . u (the updated u), the first half of the next Gram-Schmidt
-// pass fused into this one.
-template <typename T, bool DOTS, int MAXQ>
-__global__ __launch_bounds__(256) void k_saxpys(const T* __restrict__ Q, int64_t ld, int nq,
-                                                const double* __restrict__ h, int64_t hstride, T* __restrict__ u,
-                                                SegSet sg, double* __restrict__ part) {
-  const int2 t = sg.tiles[blockIdx.x];
-  __shared__ double hs[kMaxDots];
-  if (threadIdx.x < kMaxDots) hs[threadIdx.x] = (int)threadIdx.x < nq ? h[(int64_t)t.x * hstride + threadIdx.x] : 0.0;
-  __syncthreads();
-  const int64_t base = sg.ioff[t.x] + (int64_t)t.y * kSegChunk;
-  const int64_t end = sg.ioff[t.x] + min((int64_t)(t.y + 1) * kSegChunk, sg.ilen[t.x]);
-  constexpr int ND = DOTS ? MAXQ : 1;
-  double acc[ND];
-#pragma unroll
-  for (int i = 0; i < ND; ++i) acc[i] = 0.0;
-  double nrm = 0.0;
-  for (int64_t e = base + threadIdx.x; e < end; e += blockDim.x) {
-    double ue = (double)u[e];
-    double qv[ND];
-#pragma unroll
-    for (int i = 0; i < MAXQ; ++i)
-      if (i < nq) {
-        const double q = (double)Q[(int64_t)i * ld + e];
-        if constexpr (DOTS) qv[i] = q;
-        ue -= hs[i] * q;
-      }
-    const T us = (T)ue;
-    u[e] = us;
-    const double un = (double)us;
-    nrm += un * un;
-    if constexpr (DOTS) {
-#pragma unroll
-      for (int i = 0; i < MAXQ; ++i)
-        if (i < nq) acc[i] += qv[i] * un;
-    }
-  }
-  if (part) {
-    __shared__ double sh[256];
-    if constexpr (DOTS) {
-#pragma unroll
-      for (int i = 0; i < MAXQ; ++i) {
-        if (i < nq) {
-          const double v = block_sum256(acc[i], sh);
-          if (threadIdx.x == 0) part[(int64_t)blockIdx.x * (kMaxDots + 1) + i] = v;
-        }
-      }
-    }
-    const double v = block_sum256(nrm, sh);
-    if (threadIdx.x == 0) part[(int64_t)blockIdx.x * (kMaxDots + 1) + kMaxDots] = v;
-  }
-}
-
-// q = u / sqrt(nrm2[i]) on instance i's tiles; a zero or non-finite norm writes zeros
-// (the instance has stopped; its later basis vectors are never combined).
-template <typename T>
-__global__ __launch_bounds__(256) void k_snormalize(const T* __restrict__ u, const double* __restrict__ nrm2,
-                                                    int64_t stride, T* __restrict__ q, SegSet sg) {
-  const int2 t = sg.tiles[blockIdx.x];
-  const double n2 = nrm2[(int64_t)t.x * stride];
-  const double inv = (n2 > 0.0 && isfinite(n2)) ? 1.0 / sqrt(n2) : 0.0;
-  const int64_t base = sg.ioff[t.x] + (int64_t)t.y * kSegChunk;
-  const int64_t end = sg.ioff[t.x] + min((int64_t)(t.y + 1) * kSegChunk, sg.ilen[t.x]);
-  for (int64_t e = base + threadIdx.x; e < end; e += blockDim.x) q[e] = (T)(inv == 0.0 ? 0.0 : (double)u[e] * inv);
-}
-
-// y = alpha[i] x on instance i's tiles
-template <typename TI, typename TO>
-__global__ __launch_bounds__(256) void k_sscale_conv(const TI* __restrict__ x, TO* __restrict__ y,
-                                                     const double* __restrict__ alpha, SegSet sg) {
-  const int2 t = sg.tiles[blockIdx.x];
-  const double a = alpha[t.x];
-  const int64_t base = sg.ioff[t.x] + (int64_t)t.y * kSegChunk;
-  const int64_t end = sg.ioff[t.x] + min((int64_t)(t.y + 1) * kSegChunk, sg.ilen[t.x]);
-  for (int64_t e = base + threadIdx.x; e < end; e += blockDim.x) y[e] = (TO)(a == 0.0 ? 0.0 : a * (double)x[e]);
-}
-
-// x += sum_{k < cnt[i]} c[i][k] Q_k on instance i's tiles (x double, sum in double)
-template <typename T>
-__global__ __launch_bounds__(256) void k_scombine(const T* __restrict__ Q, int64_t ld, const double* __restrict__ c,
-                                                  int64_t cstride, const int* __restrict__ cnt,
-                                                  double* __restrict__ x, SegSet sg) {
-  const int2 t = sg.tiles[blockIdx.x];
-  const int nq = cnt[t.x];
-  __shared__ double cs[kMaxDots];
-  if (threadIdx.x < kMaxDots) cs[threadIdx.x] = (int)threadIdx.x < nq ? c[(int64_t)t.x * cstride + threadIdx.x] : 0.0;
-  __syncthreads();
-  const int64_t base = sg.ioff[t.x] + (int64_t)t.y * kSegChunk;
-  const int64_t end = sg.ioff[t.x] + min((int64_t)(t.y + 1) * kSegChunk, sg.ilen[t.x]);
-  for (int64_t e = base + threadIdx.x; e < end; e += blockDim.x) {
-    double acc = 0.0;
-#pragma unroll
-    for (int i = 0; i < kMaxDots; ++i)
-      if (i < nq) acc += cs[i] * (double)Q[(int64_t)i * ld + e];
-    x[e] += acc;
-  }
-}
-
-// ---- GMRES scalars on the device: per instance the rotated Hessenberg columns R, the
-// right-hand side g of the small least-squares problem, the Givens rotations, and
-// (running, columns kept, iterations, status, tolerance, ||r||); one thread per instance.
-__global__ void k_gm_init(const double* __restrict__ prm, double* __restrict__ st, int ninst) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= ninst) return;
-  double* s = st + (int64_t)i * kGmStride;
-  for (int k = 0; k < kGmLd; ++k) s[kGmG + k] = 0.0;
-  s[kGmG] = 1.0;
-  s[kGmMisc + GM_RUN] = prm[3 * i];
-  s[kGmMisc + GM_ACTIVE] = prm[3 * i];
-  s[kGmMisc + GM_JEND] = 0.0;
-  s[kGmMisc + GM_INNER] = 0.0;
-  s[kGmMisc + GM_STATUS] = 0.0;
-  s[kGmMisc + GM_TOL] = prm[3 * i + 1];
-  s[kGmMisc + GM_RNORM] = prm[3 * i + 2];
-}
-
-// Arnoldi column j of every running instance from the CGS2 dot products (d1 + d2 = the
-// coefficients, the norm slot of d2 = ||u||^2): earlier rotations, a new rotation that
-// annihilates h_{j+1,j}, the update of g; the instance stops when |g_{j+1}| <= tol, on a
-// lucky breakdown, on breakdown (no column kept) or on a non-finite value.
-__global__ void k_gm_column(int j, const double* __restrict__ dots, int64_t dstride, double* __restrict__ st,
-                            int ninst) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= ninst) return;
-  double* s = st + (int64_t)i * kGmStride;
-  double* misc = s + kGmMisc;
-  if (misc[GM_RUN] == 0.0) return;
-  misc[GM_INNER] += 1.0;
-  const double* d1 = dots + (int64_t)i * dstride;
-  const double* d2 = d1 + kGmLd;
-  double* col = s + kGmR + (int64_t)j * kGmLd;
-  double* cs = s + kGmCs;
-  double* sn = s + kGmSn;
-  double* g = s + kGmG;
-  const double hn2 = d2[kMaxDots];
-  const double hn = isfinite(hn2) ? sqrt(hn2 > 0.0 ? hn2 : 0.0) : NAN;
-  bool finite = isfinite(hn);
-  for (int k = 0; k <= j; ++k) {
-    col[k] = d1[k] + d2[k];
-    finite = finite && isfinite(col[k]);
-  }
-  if (!finite) {
-    misc[GM_STATUS] = (double)BIRK_ERR_NONFINITE;
-    misc[GM_RUN] = 0.0;
-    misc[GM_JEND] = (double)j;
-    return;
-  }
-  double below = hn;
-  for (int k = 0; k < j; ++k) {
-    const double a = cs[k] * col[k] + sn[k] * col[k + 1];
-    col[k + 1] = -sn[k] * col[k] + cs[k] * col[k + 1];
-    col[k] = a;
-  }
-  const double den = hypot(col[j], below);
-  if (den == 0.0) {
-    misc[GM_STATUS] = (double)BIRK_ERR_BREAKDOWN;
-    misc[GM_RUN] = 0.0;
-    misc[GM_JEND] = (double)j;
-    return;
-  }
-  cs[j] = col[j] / den;
-  sn[j] = below / den;
-  col[j] = den;
-  g[j + 1] = -sn[j] * g[j];
-  g[j] = cs[j] * g[j];
-  misc[GM_JEND] = (double)(j + 1);
-  const bool lucky = hn <= 1e-14 * den;
-  if (fabs(g[j + 1]) <= misc[GM_TOL] || lucky) misc[GM_RUN] = 0.0;
-}
-
-// End of a cycle: y = R^{-1} g on the kept columns, coefficients ||r|| y and their count
-// for the combination chi += sum_k c_k z_k; (running, iterations, status) per instance
-// into flags[3 i ...] for the host.
-__global__ void k_gm_solve(double* __restrict__ st, double* __restrict__ coef, int64_t cstride, int* __restrict__ cnt,
-                           double* __restrict__ flags, int ninst) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= ninst) return;
-  double* s = st + (int64_t)i * kGmStride;
-  const double* misc = s + kGmMisc;
-  double* c = coef + (int64_t)i * cstride;
-  const int k = misc[GM_ACTIVE] != 0.0 ? (int)misc[GM_JEND] : 0;
-  const double* R = s + kGmR;
-  const double* g = s + kGmG;
-  double y[kMaxDots];
-  for (int a = k - 1; a >= 0; --a) {
-    double acc = g[a];
-    for (int b = a + 1; b < k; ++b) acc -= R[(int64_t)b * kGmLd + a] * y[b];
-    y[a] = acc / R[(int64_t)a * kGmLd + a];
-  }
-  for (int a = 0; a < k; ++a) c[a] = y[a] * misc[GM_RNORM];
-  cnt[i] = k;
-  flags[3 * i] = misc[GM_RUN];
-  flags[3 * i + 1] = misc[GM_INNER];
-  flags[3 * i + 2] = misc[GM_STATUS];
-}
-
-// running flag per instance into flags[i] (read by the host between chunks)
-__global__ void k_gm_running(const double* __restrict__ st, double* __restrict__ flags, int ninst) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= ninst) return;
-  flags[i] = st[(int64_t)i * kGmStride + kGmMisc + GM_RUN];
-}
-
-// Host-side launch helpers used by the GMRES driver.
-namespace kry {
-
-template <typename T>
-void sub(const T* a, const T* b, T* z, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_sub<T>, dim3(nblocks(n, 256)), dim3(256), 0, s, a, b, z, n);
-}
-
-void residual(const double* beta, const double* x, const double* t, double* r, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_residual, dim3(nblocks(n, 256)), dim3(256), 0, s, beta, x, t, r, n);
-}
-
-
-template <typename T>
-void sdots(const birk_plan* p, const T* Q, int nq, const T* u, double* out, int64_t ostride, hipStream_t s) {
-  const SegSet& sg = p->seg;
-  BIRK_MAXQ_SWITCH(nq, hipLaunchKernelGGL((k_sdots<T, MQ, 0>), dim3(sg.ntiles), dim3(256), 0, s, Q, p->total_len, nq,
-                                           u, (const T*)nullptr, (const T*)nullptr, (T*)nullptr, sg, p->krylov_part))
-  hipLaunchKernelGGL(k_sreduce, dim3(nq + 1, (unsigned)p->inst.size()), dim3(256), 0, s, p->krylov_part, sg, nq, out,
-                     ostride);
-}
-
-template <typename T>
-void sub_sdots(const birk_plan* p, const T* Q, int nq, const T* a, const T* b, T* u, double* out, int64_t ostride,
-               hipStream_t s) {
-  const SegSet& sg = p->seg;
-  BIRK_MAXQ_SWITCH(nq, hipLaunchKernelGGL((k_sdots<T, MQ, 1>), dim3(sg.ntiles), dim3(256), 0, s, Q, p->total_len, nq,
-                                           (const T*)nullptr, a, b, u, sg, p->krylov_part))
-  hipLaunchKernelGGL(k_sreduce, dim3(nq + 1, (unsigned)p->inst.size()), dim3(256), 0, s, p->krylov_part, sg, nq, out,
-                     ostride);
-}
-
-template <typename T>
-void saxpys(const birk_plan* p, const T* Q, int nq, const double* h, int64_t hstride, T* u, double* nrm_out,
-            hipStream_t s) {
-  const SegSet& sg = p->seg;
-  BIRK_MAXQ_SWITCH(nq, hipLaunchKernelGGL((k_saxpys<T, false, MQ>), dim3(sg.ntiles), dim3(256), 0, s, Q,
-                                           p->total_len, nq, h, hstride, u, sg, nrm_out ? p->krylov_part : nullptr))
-  if (nrm_out)
-    hipLaunchKernelGGL(k_sreduce, dim3(1, (unsigned)p->inst.size()), dim3(256), 0, s, p->krylov_part, sg, 0, nrm_out,
-                       hstride);
-}
-
-template <typename T>
-void saxpys_dots(const birk_plan* p, const T* Q, int nq, const double* h, int64_t hstride, T* u, double* out,
-                 int64_t ostride, hipStream_t s) {
-  const SegSet& sg = p->seg;
-  BIRK_MAXQ_SWITCH(nq, hipLaunchKernelGGL((k_saxpys<T, true, MQ>), dim3(sg.ntiles), dim3(256), 0, s, Q,
-                                           p->total_len, nq, h, hstride, u, sg, p->krylov_part))
-  hipLaunchKernelGGL(k_sreduce, dim3(nq + 1, (unsigned)p->inst.size()), dim3(256), 0, s, p->krylov_part, sg, nq, out,
-                     ostride);
-}
-
-template <typename T>
-void snormalize(const birk_plan* p, const T* u, const double* nrm2, int64_t stride, T* q, hipStream_t s) {
-  hipLaunchKernelGGL(k_snormalize<T>, dim3(p->seg.ntiles), dim3(256), 0, s, u, nrm2, stride, q, p->seg);
-}
-
-template <typename TI, typename TO>
-void sscale_conv(const birk_plan* p, const TI* x, TO* y, const double* alpha, hipStream_t s) {
-  hipLaunchKernelGGL((k_sscale_conv<TI, TO>), dim3(p->seg.ntiles), dim3(256), 0, s, x, y, alpha, p->seg);
-}
-
-template <typename T>
-void scombine(const birk_plan* p, const T* Q, const double* c, int64_t cstride, const int* cnt, double* x,
-              hipStream_t s) {
-  hipLaunchKernelGGL(k_scombine<T>, dim3(p->seg.ntiles), dim3(256), 0, s, Q, p->total_len, c, cstride, cnt, x,
-                     p->seg);
-}
-
-void gm_init(const birk_plan* p, const double* prm, double* st, hipStream_t s) {
-  const int B = (int)p->inst.size();
-  hipLaunchKernelGGL(k_gm_init, dim3(nblocks(B, 64)), dim3(64), 0, s, prm, st, B);
-}
-void gm_column(const birk_plan* p, int j, const double* dots, int64_t dstride, double* st, hipStream_t s) {
-  const int B = (int)p->inst.size();
-  hipLaunchKernelGGL(k_gm_column, dim3(nblocks(B, 64)), dim3(64), 0, s, j, dots, dstride, st, B);
-}
-void gm_solve(const birk_plan* p, double* st, double* coef, int64_t cstride, int* cnt, double* flags, hipStream_t s) {
-  const int B = (int)p->inst.size();
-  hipLaunchKernelGGL(k_gm_solve, dim3(nblocks(B, 64)), dim3(64), 0, s, st, coef, cstride, cnt, flags, B);
-}
-void gm_running(const birk_plan* p, const double* st, double* flags, hipStream_t s) {
-  const int B = (int)p->inst.size();
-  hipLaunchKernelGGL(k_gm_running, dim3(nblocks(B, 64)), dim3(64), 0, s, st, flags, B);
-}
-
-template void sdots<double>(const birk_plan*, const double*, int, const double*, double*, int64_t, hipStream_t);
-template void sdots<float>(const birk_plan*, const float*, int, const float*, double*, int64_t, hipStream_t);
-template void sub_sdots<double>(const birk_plan*, const double*, int, const double*, const double*, double*, double*,
-                                int64_t, hipStream_t);
-template void sub_sdots<float>(const birk_plan*, const float*, int, const float*, const float*, float*, double*,
-                               int64_t, hipStream_t);
-template void saxpys_dots<double>(const birk_plan*, const double*, int, const double*, int64_t, double*, double*,
-                                  int64_t, hipStream_t);
-template void saxpys_dots<float>(const birk_plan*, const float*, int, const double*, int64_t, float*, double*,
-                                 int64_t, hipStream_t);
-template void saxpys<double>(const birk_plan*, const double*, int, const double*, int64_t, double*, double*,
-                             hipStream_t);
-template void saxpys<float>(const birk_plan*, const float*, int, const double*, int64_t, float*, double*,
-                            hipStream_t);
-template void snormalize<double>(const birk_plan*, const double*, const double*, int64_t, double*, hipStream_t);
-template void snormalize<float>(const birk_plan*, const float*, const double*, int64_t, float*, hipStream_t);
-template void sscale_conv<double, double>(const birk_plan*, const double*, double*, const double*, hipStream_t);
-template void sscale_conv<double, float>(const birk_plan*, const double*, float*, const double*, hipStream_t);
-template void scombine<double>(const birk_plan*, const double*, const double*, int64_t, const int*, double*,
-                               hipStream_t);
-template void scombine<float>(const birk_plan*, const float*, const double*, int64_t, const int*, double*,
-                              hipStream_t);
-
-template void sub<double>(const double*, const double*, double*, int64_t, hipStream_t);
-template void sub<float>(const float*, const float*, float*, int64_t, hipStream_t);
-}  // namespace kry
 }  // namespace birk

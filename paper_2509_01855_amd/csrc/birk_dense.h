@@ -1,5 +1,5 @@
-// Small dense helpers of the preconditioner scans: lane broadcasts, the node blocks' LU, and
-// affine maps scanned across a wave.
+// Wave helpers: lane broadcasts, the node blocks' LU and affine maps of the preconditioner
+// scans, sums.
 
 #pragma once
 
@@ -159,6 +159,33 @@ __device__ __forceinline__ void wave_scan(Aff<NX>& m) {
   scan_step<NX, 0x118, 0xF>(m, lr >= 8);
   scan_step<NX, 0x142, 0xA>(m, ((l >> 4) & 1) != 0);
   scan_step<NX, 0x143, 0xC>(m, l >= 32);
+}
+
+// Sum of v over the wave, in its last lane: row_shr 1, 2, 4, 8 (DPP controls 0x110 + n) sum
+// each row of 16, row_bcast 15 and 31 (0x142, 0x143) carry the rows' sums up; a lane
+// without a source adds zero.  VALU moves, no LDS permutes.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double add_dpp(double v) {
+  const unsigned long long x = __builtin_bit_cast(unsigned long long, v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, ROWS, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, ROWS, 0xF, false);
+  return v + __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double wave_sum_last(double v) {
+  v = add_dpp<0x111, 0xF>(v);
+  v = add_dpp<0x112, 0xF>(v);
+  v = add_dpp<0x114, 0xF>(v);
+  v = add_dpp<0x118, 0xF>(v);
+  v = add_dpp<0x142, 0xA>(v);
+  return add_dpp<0x143, 0xC>(v);
+}
+
+// v of the wave's last lane, in all.
+__device__ __forceinline__ double lane63(double v) {
+  const unsigned long long x = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, 63);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(x >> 32), 63);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
 }  // namespace birk

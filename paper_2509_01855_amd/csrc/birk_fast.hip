@@ -1167,7 +1167,6 @@ __global__ __launch_bounds__((1 << LOGW) << (LOGL1 - 4)) void k_fastC2(
   constexpr int NP = W / 2;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* U = reinterpret_cast<T*>(smem_raw);  // W real rows of L1
-  __shared__ double red[16];
   int comp, tile;
   xcd_tile(nt, nc, xcd_order, comp, tile);
   const int L2 = 1 << logL2;
@@ -1197,9 +1196,17 @@ __global__ __launch_bounds__((1 << LOGW) << (LOGL1 - 4)) void k_fastC2(
   }
   T c0hat = T(0);
   if (!TRANS) {
+    // every wave sums alike, so that the total does not depend on the tile width
     double acc = 0.0;
-    for (int i = t; i < ntB; i += NTHR) acc += part[(int64_t)comp * ntB + i];
-    c0hat = (T)(block_sum(acc, red) / (double)N);
+    for (int i = t & 63; i < ntB; i += 256) {
+      double v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = part[(int64_t)comp * ntB + min(i + 64 * k, ntB - 1)];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc += i + 64 * k < ntB ? v[k] : 0.0;
+    }
+    acc = lane63(wave_sum_last(acc));
+    c0hat = (T)(acc / (double)N);
   }
 #pragma unroll
   for (int u = 0; u < NI; ++u) {
@@ -1304,8 +1311,15 @@ static int fast_tiles_b(const FastKnobs& kn, int64_t N) {
 
 // Passes A and C take the compile-time-length kernels for L1 = 2^8..2^11 (tiles of 8
 // columns, 4 at 2^11); returns log2 of the tile width, or 0 for the general kernels.
-static int fixed_logw(const FastKnobs& kn, int logL1) {
+// Floats in tiles of 8 columns move 32-byte runs; where nc components give four workgroups a
+// CU or more they take 16 (192 components of 2^18 + 1 nodes 476 -> 431 us, of 2^16 + 1 102 ->
+// 95); fewer workgroups leave CUs idle (6 components of 2^16 + 1 nodes 19.2 -> 20.1), 32
+// columns are slower again (447), and at L1 = 2^10 the workgroups of 1024 threads are (24
+// components of 2^20 + 1 nodes 215 -> 228).
+template <typename T>
+static int fixed_logw(const FastKnobs& kn, int logL1, int logL2, int nc) {
   if (!kn.b2 || logL1 < 8 || logL1 > 11) return 0;
+  if (sizeof(T) == 4 && !kn.narrow && logL1 <= 9 && (int64_t)((1 << logL2) / 32 + 1) * nc >= 1024) return 4;
   if (kn.narrow && (logL1 == 9 || logL1 == 10)) return 2;
   return logL1 == 11 ? 2 : 3;
 }
@@ -1359,7 +1373,7 @@ static hipError_t fast_passes(birk_plan* p, const FastGroup& g, const T* v, T* o
   const cplx<double>* thd = (const cplx<double>*)g.tw.hi[0];
   const cplx<double>* tld = (const cplx<double>*)g.tw.lo[0];
   const int nc = g.nc;
-  const int lw = fixed_logw(kn, logL1);
+  const int lw = fixed_logw<T>(kn, logL1, logL2, nc);
   if (lw > 0) {
     // compile-time lengths: one tile of W = 2^lw columns per workgroup
     const int W = 1 << lw;
@@ -1367,8 +1381,18 @@ static hipError_t fast_passes(birk_plan* p, const FastGroup& g, const T* v, T* o
     const int lds = W * ld1 * (int)sizeof(T);
     auto f = fast::k_fastA2<T, 10, 3>;
     switch (logL1) {
-      case 8: f = fast::k_fastA2<T, 8, 3>; break;
-      case 9: f = lw == 2 ? fast::k_fastA2<T, 9, 2> : fast::k_fastA2<T, 9, 3>; break;
+      case 8:
+        f = fast::k_fastA2<T, 8, 3>;
+        if constexpr (sizeof(T) == 4) f = lw == 4 ? fast::k_fastA2<T, 8, 4> : f;
+        break;
+      case 9:
+        if constexpr (sizeof(T) == 4) {
+          if (lw == 4) {
+            f = fast::k_fastA2<T, 9, 4>;
+            break;
+          }
+        }
+        f = lw == 2 ? fast::k_fastA2<T, 9, 2> : fast::k_fastA2<T, 9, 3>; break;
       case 10: f = lw == 2 ? fast::k_fastA2<T, 10, 2> : fast::k_fastA2<T, 10, 3>; break;
       default: f = fast::k_fastA2<T, 11, 2>; break;
     }
@@ -1459,7 +1483,15 @@ static hipError_t fast_passes(birk_plan* p, const FastGroup& g, const T* v, T* o
     const int lds = W * ld1 * (int)sizeof(T);
     T* o = out + g.off;
     auto f = fast::k_fastC2<T, 0, 10, 3>;
-    switch (logL1 * 2 + (transpose ? 1 : 0)) {
+    bool wide = false;
+    if constexpr (sizeof(T) == 4) {
+      if (lw == 4) {
+        wide = true;
+        f = logL1 == 8 ? (transpose ? fast::k_fastC2<T, 1, 8, 4> : fast::k_fastC2<T, 0, 8, 4>)
+                       : (transpose ? fast::k_fastC2<T, 1, 9, 4> : fast::k_fastC2<T, 0, 9, 4>);
+      }
+    }
+    if (!wide) switch (logL1 * 2 + (transpose ? 1 : 0)) {
       case 16: f = fast::k_fastC2<T, 0, 8, 3>; break;
       case 17: f = fast::k_fastC2<T, 1, 8, 3>; break;
       case 18: f = lw == 2 ? fast::k_fastC2<T, 0, 9, 2> : fast::k_fastC2<T, 0, 9, 3>; break;
@@ -1510,7 +1542,7 @@ static std::vector<FastKnobs> tune_candidates(const FastKnobs& base, int64_t N) 
             FastKnobs k0 = k;
             k0.narrow = 0;
             const int l1 = log_l1(k, N);
-            if (nw && fixed_logw(k, l1) == fixed_logw(k0, l1)) continue;   // no effect at this size
+            if (nw && fixed_logw<double>(k, l1, 0, 0) == fixed_logw<double>(k0, l1, 0, 0)) continue;   // no effect at this size
             if (k.split != base.split || k.tb != base.tb || k.xcd != base.xcd || k.streams != base.streams ||
                 k.narrow != base.narrow)
               c.push_back(k);

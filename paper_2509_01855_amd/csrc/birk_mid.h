@@ -8,6 +8,7 @@
 
 #pragma once
 
+#include "birk_dense.h"
 #include "birk_fft.h"
 
 namespace birk {
@@ -62,25 +63,6 @@ __device__ __forceinline__ cplx<T> mid_tr(int j, int N, cplx<T> Y0, cplx<T> Ym, 
   }
   const T c0 = rm * rp;
   return fast::mk<T>(h * (cm * Ym.x - cp * Yp.x - c0 * Y0.x), h * (cm * Ym.y - cp * Yp.y - c0 * Y0.y));
-}
-
-// Sum of v over the wave, in its last lane: row_shr 1, 2, 4, 8 (DPP controls 0x110 + n) sum
-// each row of 16, row_bcast 15 and 31 (0x142, 0x143) carry the rows' sums up; a lane
-// without a source adds zero.  VALU moves, no LDS permutes.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double add_dpp(double v) {
-  const unsigned long long x = __builtin_bit_cast(unsigned long long, v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, ROWS, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, ROWS, 0xF, false);
-  return v + __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
-__device__ __forceinline__ double wave_sum_last(double v) {
-  v = add_dpp<0x111, 0xF>(v);
-  v = add_dpp<0x112, 0xF>(v);
-  v = add_dpp<0x114, 0xF>(v);
-  v = add_dpp<0x118, 0xF>(v);
-  v = add_dpp<0x142, 0xA>(v);
-  return add_dpp<0x143, 0xC>(v);
 }
 
 }  // namespace birk

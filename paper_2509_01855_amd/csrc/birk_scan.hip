@@ -480,13 +480,6 @@ __device__ __forceinline__ void node_map(const Node<NX, MODE>& nd, const double*
   wave_scan<NX>(m);
 }
 
-__device__ __forceinline__ double lane63(double v) {
-  const unsigned long long x = __builtin_bit_cast(unsigned long long, v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, 63);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(x >> 32), 63);
-  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-
 template <int NX, int MODE, bool BACK, typename T>
 __global__ __launch_bounds__(64) void k_lane_reduce(const double* __restrict__ J, const float* __restrict__ htab,
                                                     const T* __restrict__ y, const ScanDesc* __restrict__ sd,

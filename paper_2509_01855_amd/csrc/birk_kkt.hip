@@ -28,6 +28,7 @@
 
 #include <cmath>
 
+#include "birk_dense.h"
 #include "birk_internal.h"
 
 namespace birk {
@@ -58,32 +59,49 @@ __global__ __launch_bounds__(256) void k_jac_t(const double* __restrict__ J, int
 }
 
 // ------------------------------------------------------------------ segmented vector passes
-// The KKT vectors are pairs [top (n); bottom (n)]; a launch covers both halves: block b
-// of 2 ntiles works half b / ntiles on the plan's segment tile b % ntiles.
+// The KKT vectors are pairs [top (n); bottom (n)].  A launch covers both halves: block b works
+// half b % 2 of the plan's segment tile b / 2, kPer elements of each half per thread, all
+// loads of a pass before its stores.  Partial dot products: part[b], an instance's side by side.
+//
+// Bound: launches and latency up to some 1e5 nodes, memory beyond.  Each dot product is taken
+// where its second factor is formed, the scalars follow in the reduction's launch, and the
+// first residual of a solve from zero is the right-hand side.  Five iterations at 65537 nodes,
+// n_x = 6: 1244 us with a launch for each operation (27 an iteration), 1045 with 20.
 struct Seg {
   const int2* tiles;
   const int64_t* ioff;
   const int64_t* ilen;
+  const int2* ranges;
   int ntiles;
   int64_t n;
 };
+constexpr int kPer = kSegChunk / 512;
 
-__device__ __forceinline__ void seg_range(const Seg& sg, int blk, int* inst, int64_t* base, int64_t* end) {
-  const int half = blk >= sg.ntiles;
-  const int2 t = sg.tiles[blk - half * sg.ntiles];
-  *inst = t.x;
-  *base = sg.ioff[t.x] + (int64_t)t.y * kSegChunk + half * sg.n;
-  *end = sg.ioff[t.x] + min((int64_t)(t.y + 1) * kSegChunk, sg.ilen[t.x]) + half * sg.n;
+struct Elems {
+  int inst;
+  int64_t e[kPer];   // clamped into the block's range
+  bool in[kPer];
+};
+__device__ __forceinline__ Elems elems_of(const Seg& sg, int blk) {
+  const int2 t = sg.tiles[blk >> 1];
+  const int64_t o = (int64_t)t.y * kSegChunk, left = sg.ilen[t.x] - o;
+  Elems r;
+  r.inst = t.x;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int i = (blk & 1) * (kSegChunk / 2) + (int)threadIdx.x + 256 * k;
+    r.in[k] = i < left;
+    r.e[k] = sg.ioff[t.x] + o + (r.in[k] ? i : 0);
+  }
+  return r;
 }
 
-__device__ __forceinline__ double wave_block_sum(double v, double* sh) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+// Sum over the workgroup (256 threads), in thread 0.
+__device__ __forceinline__ double group_sum(double v, double* sh) {
+  v = wave_sum_last(v);
+  if ((threadIdx.x & 63) == 63) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  double s = 0.0;
-  for (int i = 0; i < (int)(blockDim.x >> 6); ++i) s += sh[i];
-  __syncthreads();
-  return s;
+  return threadIdx.x ? 0.0 : ((sh[0] + sh[1]) + sh[2]) + sh[3];
 }
 
 // Per-instance state of MINRES (doubles, kSt per instance).
@@ -92,69 +110,103 @@ enum {
   S_A1, S_A2, S_PHI, S_THR, S_ITERS, S_IT0, kSt
 };
 
-// z = a[i] x + b[i] y (+ c[i] z when ADDZ) on both halves; DOT: per-tile partial of q . z
-// (x and z may be the same vector.)  ia / ib / ic: state slot of the coefficient, -1 for
-// 1 (a) or 0 (b, c); a negative slot - 2 - k takes minus the coefficient in slot k.
-template <bool ADDZ, bool DOT>
-__global__ __launch_bounds__(256) void k_kv_lin(const double* x, const double* __restrict__ yv, double* z,
-                                                const double* __restrict__ st, int ia, int ib, int ic,
-                                                const double* __restrict__ q, double* __restrict__ part, Seg sg) {
-  int inst;
-  int64_t base, end;
-  seg_range(sg, blockIdx.x, &inst, &base, &end);
-  const double* s = st + (int64_t)inst * kSt;
-  auto coef = [s](int slot, double dflt) { return slot >= 0 ? s[slot] : slot <= -2 ? -s[-2 - slot] : dflt; };
-  const double a = coef(ia, 1.0), b = coef(ib, 0.0), c = coef(ic, 0.0);
-  double acc = 0.0;
-  for (int64_t e = base + threadIdx.x; e < end; e += blockDim.x) {
-    double v = a * x[e];
-    if (yv) v += b * yv[e];
-    if (ADDZ) v += c * z[e];
-    z[e] = v;
-    if (DOT) acc += q[e] * v;
-  }
-  if (DOT) {
-    __shared__ double sh[4];
-    const double tot = wave_block_sum(acc, sh);
-    if (threadIdx.x == 0) part[blockIdx.x] = tot;
-  }
-}
-
-// per-tile partial of a . b over both halves
+// per-block partial of a . b over both halves
 __global__ __launch_bounds__(256) void k_kv_dot(const double* __restrict__ a, const double* __restrict__ b,
                                                 double* __restrict__ part, Seg sg) {
-  int inst;
-  int64_t base, end;
-  seg_range(sg, blockIdx.x, &inst, &base, &end);
-  double acc = 0.0;
-  for (int64_t e = base + threadIdx.x; e < end; e += blockDim.x) acc += a[e] * b[e];
   __shared__ double sh[4];
-  const double tot = wave_block_sum(acc, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = tot;
+  const Elems x = elems_of(sg, blockIdx.x);
+  double acc = 0.0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const double v = a[x.e[k]] * b[x.e[k]] + a[sg.n + x.e[k]] * b[sg.n + x.e[k]];
+    acc += x.in[k] ? v : 0.0;
+  }
+  acc = group_sum(acc, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = acc;
 }
 
-// out[i] = sum of instance i's partials (both halves, tiles in order)
-__global__ __launch_bounds__(64) void k_kv_reduce(const double* __restrict__ part, const int2* __restrict__ ranges,
-                                                  int ntiles, double* __restrict__ out) {
-  const int i = blockIdx.x;
-  const int2 r = ranges[i];
+// Sum of instance i's partials, in thread 0 (256 threads).
+__device__ __forceinline__ double inst_sum(const double* __restrict__ part, const Seg& sg, int i, double* sh) {
+  const int2 r = sg.ranges[i];
   double s = 0.0;
-  for (int b = r.x + (int)threadIdx.x; b < r.y; b += 64) s += part[b] + part[ntiles + b];
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  if (threadIdx.x == 0) out[i] = s;
+#pragma unroll 4
+  for (int b = 2 * r.x + (int)threadIdx.x; b < 2 * r.y; b += 256) s += part[b];
+  return group_sum(s, sh);
+}
+
+// out[i] = sum of instance i's partials
+__global__ __launch_bounds__(256) void k_kv_reduce(const double* __restrict__ part, Seg sg, double* __restrict__ out) {
+  __shared__ double sh[4];
+  const double s = inst_sum(part, sg, blockIdx.x, sh);
+  if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
 // ------------------------------------------------------------------ KKT operator pieces
-// top = h * u + l - t (t = J^T B^aT l), bottom = u - s (s = B^a J u); h == null: H = I
-__global__ __launch_bounds__(256) void k_kkt_combine(const double* __restrict__ u, const double* __restrict__ l,
-                                                     const double* __restrict__ t, const double* __restrict__ s,
-                                                     const double* __restrict__ h, double* __restrict__ top,
-                                                     double* __restrict__ bot, int64_t n) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  const double hu = h ? h[e] * u[e] : u[e];
-  top[e] = hu + l[e] - t[e];
-  bot[e] = u[e] - s[e];
+// K z from its parts: top = h * u + l - t (t = J^T B^aT l), bottom = u - s (s = B^a J u);
+// z = [u; l], h == null: H = I.
+//   RESID: out = out2 = rhs - K z (the true residual), partials of out . out
+//   else:  out = K z - C1[i] r1 (r1 in rhs), partials of z . out
+template <bool RESID>
+__global__ __launch_bounds__(256) void k_kkt_out(const double* __restrict__ z, const double* __restrict__ t,
+                                                 const double* __restrict__ s, const double* __restrict__ h,
+                                                 const double* __restrict__ rhs, const double* __restrict__ st,
+                                                 double* __restrict__ out, double* __restrict__ out2,
+                                                 double* __restrict__ part, Seg sg) {
+  __shared__ double sh[4];
+  const Elems x = elems_of(sg, blockIdx.x);
+  const double c1 = RESID ? 0.0 : st[(int64_t)x.inst * kSt + S_C1];
+  const double *zl = z + sg.n, *rl = rhs + sg.n;
+  double top[kPer], bot[kPer], acc = 0.0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int64_t e = x.e[k];
+    const double u = z[e], l = zl[e];
+    const double kt = (h ? h[e] * u : u) + l - t[e], kb = u - s[e];
+    if (RESID) {
+      top[k] = rhs[e] - kt;
+      bot[k] = rl[e] - kb;
+    } else {
+      top[k] = kt - c1 * rhs[e];
+      bot[k] = kb - c1 * rl[e];
+    }
+    const double d = RESID ? top[k] * top[k] + bot[k] * bot[k] : u * top[k] + l * bot[k];
+    acc += x.in[k] ? d : 0.0;
+  }
+#pragma unroll
+  for (int k = 0; k < kPer; ++k)
+    if (x.in[k]) {
+      out[x.e[k]] = top[k];
+      out[sg.n + x.e[k]] = bot[k];
+      if (RESID) {
+        out2[x.e[k]] = top[k];
+        out2[sg.n + x.e[k]] = bot[k];
+      }
+    }
+  acc = group_sum(acc, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = acc;
+}
+
+// y -= C2[i] r2; ztop (when given) = y's top half / h: the first half of M^{-1} y
+__global__ __launch_bounds__(256) void k_kkt_orth(double* __restrict__ y, const double* __restrict__ r2,
+                                                  const double* __restrict__ h, const double* __restrict__ st,
+                                                  double* __restrict__ ztop, Seg sg) {
+  const Elems x = elems_of(sg, blockIdx.x);
+  const double c2 = st[(int64_t)x.inst * kSt + S_C2];
+  double top[kPer], bot[kPer], zt[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int64_t e = x.e[k];
+    top[k] = y[e] - c2 * r2[e];
+    bot[k] = y[sg.n + e] - c2 * r2[sg.n + e];
+    zt[k] = h ? top[k] / h[e] : top[k];
+  }
+#pragma unroll
+  for (int k = 0; k < kPer; ++k)
+    if (x.in[k]) {
+      y[x.e[k]] = top[k];
+      y[sg.n + x.e[k]] = bot[k];
+      if (ztop) ztop[x.e[k]] = zt[k];
+    }
 }
 
 // z = a / h (or a), z = h * a (or a)
@@ -165,65 +217,42 @@ __global__ __launch_bounds__(256) void k_hscale(const double* __restrict__ a, co
   z[e] = h ? (divide ? a[e] / h[e] : a[e] * h[e]) : a[e];
 }
 
-// r = b - k (the true residual), both halves at once (length 2n)
-__global__ __launch_bounds__(256) void k_sub2(const double* __restrict__ b, const double* __restrict__ k,
-                                              double* __restrict__ r, int64_t n2) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n2) return;
-  r[e] = b[e] - k[e];
-}
-
 // ------------------------------------------------------------------ MINRES scalar recurrences
 // Cycle start: beta1 = sqrt(r1 . M^{-1} r1) from dot; thr = tol[i] beta1.
-__global__ void k_mr_init(double* __restrict__ st, const double* __restrict__ dot, const double* __restrict__ tol,
-                          const int* __restrict__ run, int ninst) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= ninst) return;
-  double* s = st + (int64_t)i * kSt;
-  const double b2 = dot[i];
+__device__ __forceinline__ void mr_init(double* __restrict__ s, double b2, double tol, int run) {
   const double b = (b2 > 0.0 && isfinite(b2)) ? sqrt(b2) : 0.0;
   for (int k = 0; k < kSt; ++k) s[k] = 0.0;
   s[S_BETA1] = b;
   s[S_BETA] = b;
   s[S_PHIBAR] = b;
   s[S_CS] = -1.0;
-  s[S_THR] = tol[i] * b;
-  s[S_ACTIVE] = (run[i] && b > 0.0) ? 1.0 : 0.0;
+  s[S_THR] = tol * b;
+  s[S_ACTIVE] = (run && b > 0.0) ? 1.0 : 0.0;
   s[S_IT0] = 1.0;
 }
 
 // Before an iteration: v = y / beta, and the coefficient of r1 in y = K v - (beta / oldb) r1.
-__global__ void k_mr_pre(double* __restrict__ st, int ninst) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= ninst) return;
-  double* s = st + (int64_t)i * kSt;
+__device__ __forceinline__ void mr_pre(double* __restrict__ s) {
   const bool on = s[S_ACTIVE] != 0.0;
   s[S_SV] = on ? 1.0 / s[S_BETA] : 0.0;
   s[S_C1] = (on && s[S_IT0] == 0.0) ? s[S_BETA] / s[S_OLDB] : 0.0;
 }
 
 // alpha = v . y; coefficient of r2 in y -= (alpha / beta) r2.
-__global__ void k_mr_alpha(double* __restrict__ st, const double* __restrict__ dot, int ninst) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= ninst) return;
-  double* s = st + (int64_t)i * kSt;
+__device__ __forceinline__ void mr_alpha(double* __restrict__ s, double dot) {
   const bool on = s[S_ACTIVE] != 0.0;
-  s[S_ALPHA] = on ? dot[i] : 0.0;
-  s[S_C2] = on ? dot[i] / s[S_BETA] : 0.0;
+  s[S_ALPHA] = on ? dot : 0.0;
+  s[S_C2] = on ? dot / s[S_BETA] : 0.0;
 }
 
 // beta_{k+1} = sqrt(r2 . M^{-1} r2), the new Givens rotation, the step phi and the
 // coefficients of w_k = (v - eps_{k-1} w_{k-2} - delta w_{k-1}) / gamma; stop when
 // |phibar| <= thr, on breakdown, or on a non-finite value.
-__global__ void k_mr_givens(double* __restrict__ st, const double* __restrict__ dot, int ninst) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= ninst) return;
-  double* s = st + (int64_t)i * kSt;
+__device__ __forceinline__ void mr_givens(double* __restrict__ s, double b2) {
   if (s[S_ACTIVE] == 0.0) {
     s[S_PHI] = s[S_AV] = s[S_A1] = s[S_A2] = 0.0;
     return;
   }
-  const double b2 = dot[i];
   const double beta = (b2 > 0.0 && isfinite(b2)) ? sqrt(b2) : (b2 == 0.0 ? 0.0 : NAN);
   const double oldeps = s[S_EPS];
   const double cs = s[S_CS], sn = s[S_SN], dbar = s[S_DBAR], alpha = s[S_ALPHA];
@@ -254,20 +283,66 @@ __global__ void k_mr_givens(double* __restrict__ st, const double* __restrict__ 
   if (fabs(s[S_PHIBAR]) <= s[S_THR] || beta == 0.0) s[S_ACTIVE] = 0.0;
 }
 
-// w_new = av v + a1 w1 + a2 w2 (into w1's buffer), x += phi w_new
-__global__ __launch_bounds__(256) void k_mr_update(const double* __restrict__ v, double* __restrict__ w1,
-                                                   const double* __restrict__ w2, double* __restrict__ x,
-                                                   const double* __restrict__ st, Seg sg) {
-  int inst;
-  int64_t base, end;
-  seg_range(sg, blockIdx.x, &inst, &base, &end);
-  const double* s = st + (int64_t)inst * kSt;
-  const double av = s[S_AV], a1 = s[S_A1], a2 = s[S_A2], phi = s[S_PHI];
-  if (phi == 0.0 && av == 0.0) return;
-  for (int64_t e = base + threadIdx.x; e < end; e += blockDim.x) {
-    const double wn = av * v[e] + a1 * w1[e] + a2 * w2[e];
-    w1[e] = wn;
-    x[e] += phi * wn;
+// A dot product from its partials and the scalars that follow from it, one workgroup per
+// instance (a launch each for the sum, the step and the next iteration's coefficients otherwise).
+enum { MR_INIT, MR_ALPHA, MR_GIVENS };
+template <int OP>
+__global__ __launch_bounds__(256) void k_mr_scalars(double* __restrict__ st, const double* __restrict__ part,
+                                                    const double* __restrict__ tol, const int* __restrict__ run,
+                                                    Seg sg) {
+  __shared__ double sh[4];
+  const int i = blockIdx.x;
+  const double dot = inst_sum(part, sg, i, sh);
+  if (threadIdx.x) return;
+  double* s = st + (int64_t)i * kSt;
+  if (OP == MR_INIT) mr_init(s, dot, tol[i], run[i]);
+  if (OP == MR_ALPHA) mr_alpha(s, dot);
+  if (OP == MR_GIVENS) mr_givens(s, dot);
+  if (OP != MR_ALPHA) mr_pre(s);
+}
+
+// w_new = av v + a1 w1 + a2 w2 (into w1's buffer), x += phi w_new; and the next v = SV[i] y.
+// A coefficient of zero leaves its vector unread (w1 and w2 hold nothing before the third and
+// second iteration).  FIRST: only v.
+template <bool FIRST>
+__global__ __launch_bounds__(256) void k_mr_update(double* __restrict__ v, const double* __restrict__ y,
+                                                   double* __restrict__ w1, const double* __restrict__ w2,
+                                                   double* __restrict__ x, const double* __restrict__ st, Seg sg) {
+  const Elems b = elems_of(sg, blockIdx.x);
+  const double* s = st + (int64_t)b.inst * kSt;
+  const double sv = s[S_SV];
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    const int64_t o = half * sg.n;
+    double wn[kPer], xn[kPer], vn[kPer];
+    if (!FIRST) {
+      const double av = s[S_AV], a1 = s[S_A1], a2 = s[S_A2], phi = s[S_PHI];
+      if (phi != 0.0 || av != 0.0) {
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) wn[k] = av * v[o + b.e[k]];
+        if (a1 != 0.0) {
+#pragma unroll
+          for (int k = 0; k < kPer; ++k) wn[k] += a1 * w1[o + b.e[k]];
+        }
+        if (a2 != 0.0) {
+#pragma unroll
+          for (int k = 0; k < kPer; ++k) wn[k] += a2 * w2[o + b.e[k]];
+        }
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) xn[k] = x[o + b.e[k]] + phi * wn[k];
+#pragma unroll
+        for (int k = 0; k < kPer; ++k)
+          if (b.in[k]) {
+            w1[o + b.e[k]] = wn[k];
+            x[o + b.e[k]] = xn[k];
+          }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) vn[k] = sv * y[o + b.e[k]];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k)
+      if (b.in[k]) v[o + b.e[k]] = vn[k];
   }
 }
 
@@ -312,7 +387,7 @@ namespace {
 static inline unsigned nb256(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 struct KktBufs {
-  double *x, *v, *y, *r1, *r2, *w, *w1, *rhs, *tmp;   // pair vectors (2n each)
+  double *x, *v, *y, *r1, *r2, *w, *w1, *rhs;   // pair vectors (2n each)
   double *st, *part, *dot, *tol;
   int* run;
 };
@@ -322,6 +397,7 @@ Seg make_seg(const birk_plan* p) {
   sg.tiles = p->seg.tiles;
   sg.ioff = p->seg.ioff;
   sg.ilen = p->seg.ilen;
+  sg.ranges = p->seg.ranges;
   sg.ntiles = p->seg.ntiles;
   sg.n = p->total_len;
   return sg;
@@ -333,7 +409,7 @@ hipError_t ensure_kkt(birk_plan* p) {
   if (p->kkt_buf) return hipSuccess;
   const size_t n = (size_t)p->total_len, B = p->inst.size();
   const size_t nt = 2 * (size_t)std::max(p->seg.ntiles, 1);
-  const size_t doubles = 9 * 2 * n + B * kSt + nt + 2 * B;
+  const size_t doubles = 8 * 2 * n + B * kSt + nt + 2 * B;
   hipError_t e = hipMalloc(&p->kkt_buf, doubles * sizeof(double) + B * sizeof(int));
   return e;
 }
@@ -344,7 +420,7 @@ static KktBufs kkt_bufs(birk_plan* p) {
   const size_t nt = 2 * (size_t)std::max(p->seg.ntiles, 1);
   double* q = (double*)p->kkt_buf;
   KktBufs b;
-  double** vecs[] = {&b.x, &b.v, &b.y, &b.r1, &b.r2, &b.w, &b.w1, &b.rhs, &b.tmp};
+  double** vecs[] = {&b.x, &b.v, &b.y, &b.r1, &b.r2, &b.w, &b.w1, &b.rhs};
   for (double** v : vecs) {
     *v = q;
     q += n2;
@@ -361,12 +437,10 @@ static KktBufs kkt_bufs(birk_plan* p) {
   return b;
 }
 
-// K [u; l] -> [top; bottom] (pair vectors); uses tmp_vec[0..3]
-static hipError_t kkt_apply(birk_plan* p, int jk, const double* J, const double* h, const double* z, double* out,
-                            hipStream_t s) {
-  const int64_t n = p->total_len;
+// The parts of K [u; l]: B^a J u in tmp_vec[1], J^T B^aT l in tmp_vec[3] (tmp_vec[0], [2] used).
+static hipError_t kkt_parts(birk_plan* p, int jk, const double* J, const double* z, hipStream_t s) {
   const double* u = z;
-  const double* l = z + n;
+  const double* l = z + p->total_len;
   double* t0 = (double*)p->tmp_vec[0];
   double* t1 = (double*)p->tmp_vec[1];
   double* t2 = (double*)p->tmp_vec[2];
@@ -375,21 +449,19 @@ static hipError_t kkt_apply(birk_plan* p, int jk, const double* J, const double*
   if (e == hipSuccess) e = apply_product<double>(p, t0, t1, 0, s);       // B^a J u
   if (e == hipSuccess) e = apply_product<double>(p, l, t2, 1, s);        // B^aT l
   if (e == hipSuccess) e = jac_t_times(p, jk, J, t2, t3, s);             // J^T B^aT l
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_kkt_combine, dim3(nb256(n)), dim3(256), 0, s, u, l, t3, t1, h, out, out + n, n);
-  return hipGetLastError();
+  return e;
 }
 
-// M^{-1} [r1; r2] = [r1 / h; P^{-T}(h * P^{-1} r2)]
+// M^{-1} [r1; r2] = [r1 / h; P^{-T}(h * P^{-1} r2)]; top_done: z's top half is there already
 static hipError_t kkt_prec(birk_plan* p, int jk, const double* J, const double* h, const double* r, double* z,
-                           int use_precond, hipStream_t s) {
+                           int use_precond, bool top_done, hipStream_t s) {
   const int64_t n = p->total_len;
   if (!use_precond) return hipMemcpyAsync(z, r, 2 * n * sizeof(double), hipMemcpyDeviceToDevice, s);
-  hipLaunchKernelGGL(k_hscale, dim3(nb256(n)), dim3(256), 0, s, r, h, z, n, 1);
+  if (!top_done) hipLaunchKernelGGL(k_hscale, dim3(nb256(n)), dim3(256), 0, s, r, h, z, n, 1);
   double* t0 = (double*)p->tmp_vec[0];
   hipError_t e = scan_inverse<double>(p, jk, J, r + n, t0, nullptr, 0, s, nullptr);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_hscale, dim3(nb256(n)), dim3(256), 0, s, t0, h, t0, n, 0);
+  if (h) hipLaunchKernelGGL(k_hscale, dim3(nb256(n)), dim3(256), 0, s, t0, h, t0, n, 0);
   return scan_inverse_t(p, jk, J, t0, z + n, s);
 }
 
@@ -407,7 +479,6 @@ birk_status kkt_solve(birk_plan* p, int jk, const double* J, const double* h, co
   KktBufs b = kkt_bufs(p);
   const Seg sg = make_seg(p);
   const unsigned nt2 = 2u * (unsigned)sg.ntiles;
-  const unsigned ib = (unsigned)((B + 63) / 64);
   // rhs = [f; g]; x = [chi; lam] (zero unless use_x0)
   if (f) e = hipMemcpyAsync(b.rhs, f, n * sizeof(double), hipMemcpyDeviceToDevice, s);
   else e = hipMemsetAsync(b.rhs, 0, n * sizeof(double), s);
@@ -419,19 +490,20 @@ birk_status kkt_solve(birk_plan* p, int jk, const double* J, const double* h, co
     e = hipMemsetAsync(b.x, 0, 2 * n * sizeof(double), s);
   }
   if (e != hipSuccess) return BIRK_ERR_DEVICE;
-  auto prec = [&](const double* r, double* z) { return kkt_prec(p, jk, J, h, r, z, o->use_precond, s); };
+  const double* t1 = (const double*)p->tmp_vec[1];
+  const double* t3 = (const double*)p->tmp_vec[3];
   std::vector<double> hst((size_t)B * kSt), bn(B), rn(B), tolv(B);
   std::vector<int> run(B, 1), status(B, BIRK_OK), inner(B, 0), outer(B, 0);
   std::vector<char> done(B, 0);
-  auto norms = [&](const double* vec, std::vector<double>& out) -> hipError_t {
-    hipLaunchKernelGGL(k_kv_dot, dim3(nt2), dim3(256), 0, s, vec, vec, b.part, sg);
-    hipLaunchKernelGGL(k_kv_reduce, dim3(B), dim3(64), 0, s, b.part, p->seg.ranges, sg.ntiles, b.dot);
+  auto read_norms = [&](std::vector<double>& out) -> hipError_t {   // from the squares' partials
+    hipLaunchKernelGGL(k_kv_reduce, dim3(B), dim3(256), 0, s, b.part, sg, b.dot);
     hipError_t ee = hipMemcpyAsync(hst.data(), b.dot, B * sizeof(double), hipMemcpyDeviceToHost, s);
     if (ee == hipSuccess) ee = hipStreamSynchronize(s);
     for (int i = 0; i < B; ++i) out[i] = std::isfinite(hst[i]) ? std::sqrt(std::max(hst[i], 0.0)) : NAN;
     return ee;
   };
-  if (norms(b.rhs, bn) != hipSuccess) return BIRK_ERR_DEVICE;
+  hipLaunchKernelGGL(k_kv_dot, dim3(nt2), dim3(256), 0, s, b.rhs, b.rhs, b.part, sg);
+  if (read_norms(bn) != hipSuccess) return BIRK_ERR_DEVICE;
   int budget = o->max_iter;
   // iterations between host reads of the convergence state: 2, 2, 4, then 8 per cycle
   // (the preconditioned counts are small, and an iteration past convergence costs a
@@ -439,11 +511,18 @@ birk_status kkt_solve(birk_plan* p, int jk, const double* J, const double* h, co
   constexpr int kChunkIts = 8;
   birk_status result = BIRK_OK;
   for (int cycle = 0;; ++cycle) {
-    // true residual r = rhs - K x in double
-    e = kkt_apply(p, jk, J, h, b.x, b.tmp, s);
-    if (e != hipSuccess) return BIRK_ERR_DEVICE;
-    hipLaunchKernelGGL(k_sub2, dim3(nb256(2 * n)), dim3(256), 0, s, b.rhs, b.tmp, b.r1, 2 * n);
-    if (norms(b.r1, rn) != hipSuccess) return BIRK_ERR_DEVICE;
+    // true residual r = rhs - K x in double, into r1 and r2 (x = 0 at first without x0)
+    if (cycle == 0 && !o->use_x0) {
+      e = hipMemcpyAsync(b.r1, b.rhs, 2 * n * sizeof(double), hipMemcpyDeviceToDevice, s);
+      if (e == hipSuccess) e = hipMemcpyAsync(b.r2, b.rhs, 2 * n * sizeof(double), hipMemcpyDeviceToDevice, s);
+      if (e != hipSuccess) return BIRK_ERR_DEVICE;
+      rn = bn;
+    } else {
+      if (kkt_parts(p, jk, J, b.x, s) != hipSuccess) return BIRK_ERR_DEVICE;
+      hipLaunchKernelGGL(k_kkt_out<true>, dim3(nt2), dim3(256), 0, s, b.x, t3, t1, h, b.rhs, b.st, b.r1, b.r2, b.part,
+                         sg);
+      if (read_norms(rn) != hipSuccess) return BIRK_ERR_DEVICE;
+    }
     bool all = true;
     for (int i = 0; i < B; ++i) {
       run[i] = 0;
@@ -465,17 +544,15 @@ birk_status kkt_solve(birk_plan* p, int jk, const double* J, const double* h, co
       }
     }
     if (all) break;
-    // cycle start: r2 = r1, y = M^{-1} r1, beta1; w = w2 = 0
-    e = hipMemcpyAsync(b.r2, b.r1, 2 * n * sizeof(double), hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess) e = hipMemsetAsync(b.w, 0, 2 * n * sizeof(double), s);
-    if (e == hipSuccess) e = hipMemsetAsync(b.w1, 0, 2 * n * sizeof(double), s);
-    if (e == hipSuccess) e = hipMemcpyAsync(b.tol, tolv.data(), B * sizeof(double), hipMemcpyHostToDevice, s);
+    // cycle start: y = M^{-1} r1, beta1, v = y / beta1
+    e = hipMemcpyAsync(b.tol, tolv.data(), B * sizeof(double), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(b.run, run.data(), B * sizeof(int), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = prec(b.r1, b.y);
+    if (e == hipSuccess) e = kkt_prec(p, jk, J, h, b.r1, b.y, o->use_precond, false, s);
     if (e != hipSuccess) return BIRK_ERR_DEVICE;
     hipLaunchKernelGGL(k_kv_dot, dim3(nt2), dim3(256), 0, s, b.r1, b.y, b.part, sg);
-    hipLaunchKernelGGL(k_kv_reduce, dim3(B), dim3(64), 0, s, b.part, p->seg.ranges, sg.ntiles, b.dot);
-    hipLaunchKernelGGL(k_mr_init, dim3(ib), dim3(64), 0, s, b.st, b.dot, b.tol, b.run, B);
+    hipLaunchKernelGGL(k_mr_scalars<MR_INIT>, dim3(B), dim3(256), 0, s, b.st, b.part, b.tol, b.run, sg);
+    hipLaunchKernelGGL(k_mr_update<true>, dim3(nt2), dim3(256), 0, s, b.v, b.y, (double*)nullptr,
+                       (const double*)nullptr, (double*)nullptr, b.st, sg);
     // w: w_{k-1}, w1: w_{k-2}
     double *r1 = b.r1, *r2 = b.r2, *y = b.y, *w = b.w, *w1 = b.w1;
     bool cycle_done = false;
@@ -485,30 +562,23 @@ birk_status kkt_solve(birk_plan* p, int jk, const double* J, const double* h, co
       ++chunk_no;
       const int its = std::min(want, budget);
       for (int k = 0; k < its; ++k) {
-        hipLaunchKernelGGL(k_mr_pre, dim3(ib), dim3(64), 0, s, b.st, B);
-        // v = y / beta
-        hipLaunchKernelGGL((k_kv_lin<false, false>), dim3(nt2), dim3(256), 0, s, y, (const double*)nullptr, b.v,
-                           b.st, (int)S_SV, -1, -1, (const double*)nullptr, (double*)nullptr, sg);
         // y = K v - (beta / oldb) r1; alpha = v . y
-        if (kkt_apply(p, jk, J, h, b.v, y, s) != hipSuccess) return BIRK_ERR_DEVICE;
-        hipLaunchKernelGGL((k_kv_lin<false, true>), dim3(nt2), dim3(256), 0, s, y, r1, y, b.st, -1, -2 - S_C1, -1,
-                           b.v, b.part, sg);
-        hipLaunchKernelGGL(k_kv_reduce, dim3(B), dim3(64), 0, s, b.part, p->seg.ranges, sg.ntiles, b.dot);
-        hipLaunchKernelGGL(k_mr_alpha, dim3(ib), dim3(64), 0, s, b.st, b.dot, B);
-        // y -= (alpha / beta) r2; then r1 <- r2, r2 <- y
-        hipLaunchKernelGGL((k_kv_lin<false, false>), dim3(nt2), dim3(256), 0, s, y, r2, y, b.st, -1, -2 - S_C2, -1,
-                           (const double*)nullptr, (double*)nullptr, sg);
+        if (kkt_parts(p, jk, J, b.v, s) != hipSuccess) return BIRK_ERR_DEVICE;
+        hipLaunchKernelGGL(k_kkt_out<false>, dim3(nt2), dim3(256), 0, s, b.v, t3, t1, h, r1, b.st, y, (double*)nullptr,
+                           b.part, sg);
+        hipLaunchKernelGGL(k_mr_scalars<MR_ALPHA>, dim3(B), dim3(256), 0, s, b.st, b.part, b.tol, b.run, sg);
+        // y -= (alpha / beta) r2; then r1 <- r2, r2 <- y, and y = M^{-1} r2 in the buffer of r1
+        hipLaunchKernelGGL(k_kkt_orth, dim3(nt2), dim3(256), 0, s, y, r2, h, b.st, o->use_precond ? r1 : nullptr, sg);
         double* t = r1;
         r1 = r2;
         r2 = y;
         y = t;
-        // y = M^{-1} r2; beta = sqrt(r2 . y)
-        if (prec(r2, y) != hipSuccess) return BIRK_ERR_DEVICE;
+        if (kkt_prec(p, jk, J, h, r2, y, o->use_precond, true, s) != hipSuccess) return BIRK_ERR_DEVICE;
+        // beta = sqrt(r2 . y)
         hipLaunchKernelGGL(k_kv_dot, dim3(nt2), dim3(256), 0, s, r2, y, b.part, sg);
-        hipLaunchKernelGGL(k_kv_reduce, dim3(B), dim3(64), 0, s, b.part, p->seg.ranges, sg.ntiles, b.dot);
-        hipLaunchKernelGGL(k_mr_givens, dim3(ib), dim3(64), 0, s, b.st, b.dot, B);
-        // w_new = (v - eps w1 - delta w2) / gamma into w1's buffer; x += phi w_new
-        hipLaunchKernelGGL(k_mr_update, dim3(nt2), dim3(256), 0, s, b.v, w1, w, b.x, b.st, sg);
+        hipLaunchKernelGGL(k_mr_scalars<MR_GIVENS>, dim3(B), dim3(256), 0, s, b.st, b.part, b.tol, b.run, sg);
+        // w_new = (v - eps w1 - delta w2) / gamma into w1's buffer; x += phi w_new; v = y / beta
+        hipLaunchKernelGGL(k_mr_update<false>, dim3(nt2), dim3(256), 0, s, b.v, y, w1, w, b.x, b.st, sg);
         double* wn = w1;
         w1 = w;
         w = wn;

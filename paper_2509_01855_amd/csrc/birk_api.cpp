@@ -559,13 +559,14 @@ struct InstState {
 };
 
 // Pinned host staging of the Krylov driver: [dots: B x 2 x kDotsStride doubles][flag: one
-// double slot][coefficients: B x kDotsStride doubles][counts: B ints], the last two laid
-// out like krylov_coef on the device so one copy uploads both.
-size_t stage_bytes(size_t B) { return (B * 3 * kDotsStride + 1) * sizeof(double) + B * sizeof(int); }
+// double slot][coefficients: B x kDotsStride doubles][counts: B ints, padded][end of a cycle: 3 B
+// doubles].
+size_t stage_bytes(size_t B) { return (B * 3 * kDotsStride + 1 + B + 3 * B) * sizeof(double); }
 double* stage_dots(birk_plan* p) { return (double*)p->krylov_stage; }
 int* stage_flag(birk_plan* p) { return (int*)(stage_dots(p) + p->inst.size() * 2 * kDotsStride); }
 double* stage_coef(birk_plan* p) { return stage_dots(p) + p->inst.size() * 2 * kDotsStride + 1; }
 int* stage_cnt(birk_plan* p) { return (int*)(stage_coef(p) + p->inst.size() * kDotsStride); }
+double* stage_end(birk_plan* p) { return stage_coef(p) + p->inst.size() * (kDotsStride + 1); }
 
 hipError_t ensure_krylov(birk_plan* p, int m, size_t esize) {
   hipError_t e = hipSuccess;
@@ -601,18 +602,23 @@ hipError_t ensure_krylov(birk_plan* p, int m, size_t esize) {
   return e;
 }
 
-// Per-instance norms whose squares are in the norm slots of krylov_dots, into a host array.
-hipError_t read_norms(birk_plan* p, std::vector<double>& out) {
+// Per-instance norms whose squares are in the norm slots of krylov_dots (and in slot 0, when
+// asked for), into host arrays.
+hipError_t read_norms(birk_plan* p, std::vector<double>& out, std::vector<double>* slot0 = nullptr) {
   const int B = (int)p->inst.size();
   const double* h = stage_dots(p);
   hipError_t e = hipMemcpyAsync(stage_dots(p), p->krylov_dots, (size_t)B * 2 * kDotsStride * sizeof(double),
                                 hipMemcpyDeviceToHost, p->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
-  out.resize(B);
-  for (int i = 0; i < B; ++i) {
-    const double v = h[(size_t)i * 2 * kDotsStride + kKryMaxDots];
+  auto root = [](double v) {
     // NaN must survive: std::max(0.0, NaN) would return 0
-    out[i] = std::isfinite(v) ? std::sqrt(v > 0.0 ? v : 0.0) : std::numeric_limits<double>::quiet_NaN();
+    return std::isfinite(v) ? std::sqrt(v > 0.0 ? v : 0.0) : std::numeric_limits<double>::quiet_NaN();
+  };
+  out.resize(B);
+  if (slot0) slot0->resize(B);
+  for (int i = 0; i < B; ++i) {
+    out[i] = root(h[(size_t)i * 2 * kDotsStride + kKryMaxDots]);
+    if (slot0) (*slot0)[i] = root(h[(size_t)i * 2 * kDotsStride]);
   }
   return e;
 }
@@ -704,7 +710,7 @@ static hipError_t arnoldi_chunk(birk_plan* p, int jk, const double* J, int j0, i
 template <typename TK>
 birk_status gmres_cycle(birk_plan* p, int jk, const double* J, const double* r, double* chi, double* jchi,
                         std::vector<InstState>& st, const std::vector<double>& tol_inner, int m, int use_precond,
-                        int& budget, bool& fresh) {
+                        int& budget, bool& fresh, std::vector<char>& active) {
   const int B = (int)p->inst.size();
   const int64_t n = p->total_len;
   hipStream_t s = p->stream;
@@ -713,7 +719,6 @@ birk_status gmres_cycle(birk_plan* p, int jk, const double* J, const double* r, 
   TK* Yb = jchi ? Z + (size_t)m * n : nullptr;  // J z_j, j < m
   hipError_t e = hipSuccess;
 
-  std::vector<char> active(B, 0);
   for (int i = 0; i < B; ++i) active[i] = !st[i].done;
   // q_0 = r / ||r|| (zero for inactive instances), and the device state (active,
   // tolerance, ||r||); the pinned staging is rewritten only after the synchronisations
@@ -770,16 +775,22 @@ birk_status gmres_cycle(birk_plan* p, int jk, const double* J, const double* r, 
   kry::scombine<TK>(p, p->krylov_coef, kDotsStride, p->krylov_cnt, basis, fresh ? nullptr : chi, chi, Yb,
                     fresh ? nullptr : jchi, jchi, s);
   fresh = false;
-  e = hipMemcpyAsync(flags, p->krylov_prm + 3 * B, 3 * B * sizeof(double), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  // iterations and status, read after the caller's next synchronisation (cycle_end)
+  e = hipMemcpyAsync(stage_end(p), p->krylov_prm + 3 * B, 3 * B * sizeof(double), hipMemcpyDeviceToHost, s);
   if (e != hipSuccess) return BIRK_ERR_DEVICE;
-  for (int i = 0; i < B; ++i) {
+  return BIRK_OK;
+}
+
+// What gmres_cycle left of the instances it ran, once the stream has been synchronised.
+void cycle_end(birk_plan* p, const std::vector<char>& active, std::vector<InstState>& st) {
+  const double* flags = stage_end(p);
+  for (size_t i = 0; i < active.size(); ++i) {
     if (!active[i]) continue;
     st[i].inner += (int)flags[3 * i + 1];
     const int stat = (int)flags[3 * i + 2];
     if (stat != 0) st[i].status = stat;
+    if (st[i].status == BIRK_ERR_NONFINITE) st[i].done = true;
   }
-  return BIRK_OK;
 }
 
 }  // namespace
@@ -837,6 +848,7 @@ extern "C" birk_status birk_krylov_solve(birk_plan* p, birk_jac_kind jk, const d
     e = jac_times<double>(p, jk, J, chi, jchi, s);
     if (e != hipSuccess) return BIRK_ERR_DEVICE;
   }
+  std::vector<char> active(B, 0);
   for (int outer = 0;; ++outer) {
     // true residual r = beta - A chi = beta - chi + B^a (J chi) in double (chi = 0 on the
     // first step without x0: r = beta, whose norms are known)
@@ -850,6 +862,7 @@ extern "C" birk_status birk_krylov_solve(birk_plan* p, birk_jac_kind jk, const d
       if (e != hipSuccess) return BIRK_ERR_DEVICE;
       kry::residual(p, beta, chi, t, r, p->krylov_dots, 2 * kDotsStride, s);
       if (read_norms(p, rn) != hipSuccess) return BIRK_ERR_DEVICE;
+      if (outer > 0) cycle_end(p, active, st);
     }
     bool all_done = true;
     for (int i = 0; i < B; ++i) {
@@ -889,15 +902,13 @@ extern "C" birk_status birk_krylov_solve(birk_plan* p, birk_jac_kind jk, const d
       st[i].breakdown_last = st[i].status == BIRK_ERR_BREAKDOWN;
       if (st[i].status == BIRK_ERR_BREAKDOWN) st[i].status = BIRK_OK;
     }
-    birk_status cs = mixed ? gmres_cycle<float>(p, jk, J, rcur, chi, nullptr, st, tol, o.restart, o.use_precond, budget, fresh)
-                           : gmres_cycle<double>(p, jk, J, rcur, chi, jchi, st, tol, o.restart, o.use_precond, budget, fresh);
+    birk_status cs = mixed ? gmres_cycle<float>(p, jk, J, rcur, chi, nullptr, st, tol, o.restart, o.use_precond, budget, fresh, active)
+                           : gmres_cycle<double>(p, jk, J, rcur, chi, jchi, st, tol, o.restart, o.use_precond, budget, fresh, active);
     if (cs == BIRK_ERR_SINGULAR || cs == BIRK_ERR_DEVICE) {
       result = cs;
       for (int i = 0; i < B; ++i) st[i].done = true;
       break;
     }
-    for (int i = 0; i < B; ++i)
-      if (st[i].status == BIRK_ERR_NONFINITE) st[i].done = true;
   }
   if (fresh && hipMemsetAsync(chi, 0, n * sizeof(double), s) != hipSuccess) return BIRK_ERR_DEVICE;
   for (int i = 0; i < B; ++i) {
@@ -985,14 +996,8 @@ birk_status newton_residual(birk_plan* p, const birk_ivp_model& m, const double*
   birk_status st = eval_model(p, m, X, F, nullptr);
   if (st != BIRK_OK) return st;
   if (apply_product<double>(p, F, G, 0, p->stream) != hipSuccess) return BIRK_ERR_DEVICE;
-  if (ivp_residual(p, xa, X, G, p->stream) != hipSuccess) return BIRK_ERR_DEVICE;
-  if (seg_norms(p, G, gn) != hipSuccess || seg_norms(p, X, xn) != hipSuccess) return BIRK_ERR_DEVICE;
-  return BIRK_OK;
-}
-
-hipError_t upload(double* dst, const std::vector<double>& h, hipStream_t s) {
-  hipError_t e = hipMemcpyAsync(dst, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice, s);
-  return e == hipSuccess ? hipStreamSynchronize(s) : e;
+  kry::ivp_residual(p, xa, X, G, p->krylov_dots, 2 * kDotsStride, p->stream);
+  return read_norms(p, gn, &xn) == hipSuccess ? BIRK_OK : BIRK_ERR_DEVICE;
 }
 
 }  // namespace
@@ -1070,9 +1075,10 @@ birk_status birk_newton_ivp(birk_plan* p, const birk_ivp_model* model, const dou
     // right-hand side, hence D = 0, for the others)
     result = eval_model(p, *model, X, b.F, b.J);
     if (result != BIRK_OK) break;
-    std::vector<double> alpha(B);
+    // (the staging is rewritten only after the solve's first synchronisation)
+    double* alpha = stage_coef(p);
     for (int i = 0; i < B; ++i) alpha[i] = done[i] ? 0.0 : -1.0;
-    if (upload(b.alpha, alpha, s) != hipSuccess) {
+    if (hipMemcpyAsync(b.alpha, alpha, B * sizeof(double), hipMemcpyHostToDevice, s) != hipSuccess) {
       result = BIRK_ERR_DEVICE;
       break;
     }
@@ -1104,10 +1110,16 @@ birk_status birk_newton_ivp(birk_plan* p, const birk_ivp_model* model, const dou
     }
     for (;;) {
       // lam_i = 0 takes instance i out of the update (its D may not be finite)
-      std::vector<int> cnt(B);
-      for (int i = 0; i < B; ++i) cnt[i] = lam[i] > 0.0 ? 1 : 0;
-      e = hipMemcpyAsync(b.cnt, cnt.data(), B * sizeof(int), hipMemcpyHostToDevice, s);
-      if (e != hipSuccess || upload(b.lam, lam, s) != hipSuccess) {
+      // (the staging is rewritten only after the synchronisation in newton_residual)
+      int* cnt = stage_cnt(p);
+      for (int i = 0; i < B; ++i) {
+        cnt[i] = lam[i] > 0.0 ? 1 : 0;
+        stage_coef(p)[i] = lam[i];
+      }
+      e = hipMemcpyAsync(b.cnt, cnt, B * sizeof(int), hipMemcpyHostToDevice, s);
+      if (e == hipSuccess)
+        e = hipMemcpyAsync(b.lam, stage_coef(p), B * sizeof(double), hipMemcpyHostToDevice, s);
+      if (e != hipSuccess) {
         result = BIRK_ERR_DEVICE;
         break;
       }

@@ -179,6 +179,7 @@ struct SegSet {
   int2* ranges = nullptr;   // per instance [first tile, end tile)
   int64_t* ioff = nullptr;  // per instance vector offset
   int64_t* ilen = nullptr;  // per instance length n_x N_n
+  int64_t* icol = nullptr;  // per instance first component (of the plan's)
 };
 
 }  // namespace birk
@@ -331,8 +332,6 @@ hipError_t endpoint(birk_plan* p, const double* xa, const T* v, double* xb, hipS
 hipError_t plan_instances(birk_plan* p);
 // Two-body right-hand side F and per-node Jacobian J (either may be null), n_x = 6.
 hipError_t two_body(birk_plan* p, double mu, double scale, const double* X, double* F, double* J, hipStream_t s);
-// G = X - xa - G per component (G holds B^a F on entry).
-hipError_t ivp_residual(birk_plan* p, const double* xa, const double* X, double* G, hipStream_t s);
 
 // ---- preconditioner and Jacobian products (birk_solve.hip) ----
 template <typename T>
@@ -391,6 +390,9 @@ void snorms(const birk_plan* p, const double* v, double* out, int64_t ostride, h
 // r = beta - x + t, norm slot of out: ||r||^2
 void residual(const birk_plan* p, const double* beta, const double* x, const double* t, double* r, double* out,
               int64_t ostride, hipStream_t s);
+// G = X - xa - G per component (G holds B^a F on entry); norm slot of out: ||G||^2, slot 0: ||X||^2
+void ivp_residual(const birk_plan* p, const double* xa, const double* X, double* G, double* out, int64_t ostride,
+                  hipStream_t s);
 // Step j of GMRES from u = a - b: two Gram-Schmidt passes against q_0 .. q_j (coefficients and
 // ||u||^2 in dots: two blocks of kGmLd per instance), the Hessenberg column into st, and
 // whether the instance runs on into flags.  q_{j+1} = u / ||u|| follows from next_vector,

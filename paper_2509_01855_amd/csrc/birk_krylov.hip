@@ -237,6 +237,36 @@ __global__ __launch_bounds__(256) void k_sresidual(const double* __restrict__ be
   if (threadIdx.x == 0) part[(int64_t)kMaxDots * sg.ntiles + blockIdx.x] = s;
 }
 
+// G = X - xa - G, component by component; part <- tile sums of ||G||^2 (norm slot) and ||X||^2
+// (slot 0), in the pass that has both at hand.
+__global__ __launch_bounds__(256) void k_sivp(const InstDesc* __restrict__ idesc, const double* __restrict__ xa,
+                                              const double* __restrict__ X, double* __restrict__ G, SegSet sg,
+                                              double* __restrict__ part) {
+  __shared__ double sh[8];
+  const Tile t = tile_of(sg, blockIdx.x);
+  const int64_t Nn = idesc[t.inst].Nn, rel = t.base - sg.ioff[t.inst] + threadIdx.x;
+  const double* xc = xa + sg.icol[t.inst];
+  int64_t c = rel / Nn, r = rel - c * Nn;   // component and node of the thread's element
+  double acc[2] = {0.0, 0.0};
+#pragma unroll 4
+  for (int k = 0; k < kItems; ++k) {
+    const int64_t i = (int64_t)threadIdx.x + 256 * k;
+    if (i < t.n) {
+      const double x = X[t.base + i], g = x - xc[c] - G[t.base + i];
+      G[t.base + i] = g;
+      acc[0] = fma(x, x, acc[0]);
+      acc[1] = fma(g, g, acc[1]);
+    }
+    r += 256;
+    while (r >= Nn) {
+      r -= Nn;
+      ++c;
+    }
+  }
+  const double s = group_sums<2>(acc, 2, sh);
+  if (threadIdx.x < 2) part[(int64_t)(threadIdx.x ? kMaxDots : 0) * sg.ntiles + blockIdx.x] = s;
+}
+
 // q = u / sqrt(nrm2[i]) on instance i's tiles; a zero or non-finite norm writes zeros
 // (the instance has stopped; its later basis vectors are never combined).
 __device__ __forceinline__ double inv_norm(double n2) { return (n2 > 0.0 && isfinite(n2)) ? 1.0 / sqrt(n2) : 0.0; }
@@ -508,6 +538,12 @@ void residual(const birk_plan* p, const double* beta, const double* x, const dou
               int64_t ostride, hipStream_t s) {
   hipLaunchKernelGGL(k_sresidual, dim3(p->seg.ntiles), dim3(256), 0, s, beta, x, t, r, p->seg, p->krylov_part);
   sreduce(p, 0, out, ostride, s);
+}
+
+void ivp_residual(const birk_plan* p, const double* xa, const double* X, double* G, double* out, int64_t ostride,
+                  hipStream_t s) {
+  hipLaunchKernelGGL(k_sivp, dim3(p->seg.ntiles), dim3(256), 0, s, p->idesc, xa, X, G, p->seg, p->krylov_part);
+  sreduce(p, 1, out, ostride, s);
 }
 
 template <typename T>

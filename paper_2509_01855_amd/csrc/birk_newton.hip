@@ -60,18 +60,6 @@ __global__ __launch_bounds__(kThreads) void k_two_body(const InstDesc* __restric
   }
 }
 
-// G[c][k] = X[c][k] - xa[c] - G[c][k] for every component c (G holds B^a F on entry).
-__global__ __launch_bounds__(kThreads) void k_ivp_residual(const CompDesc* __restrict__ cd, int64_t ncomp,
-                                                           const double* __restrict__ xa,
-                                                           const double* __restrict__ X, double* __restrict__ G) {
-  for (int64_t c = blockIdx.y; c < ncomp; c += gridDim.y) {
-    const CompDesc d = cd[c];
-    const double a = xa[c];
-    for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k < d.Nn; k += (int64_t)gridDim.x * kThreads)
-      G[d.off + k] = X[d.off + k] - a - G[d.off + k];
-  }
-}
-
 inline unsigned node_tiles(const birk_plan* p) {
   const int64_t t = (p->max_nn + kThreads * 4 - 1) / (kThreads * 4);
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>(t, 2048));
@@ -98,12 +86,6 @@ hipError_t two_body(birk_plan* p, double mu, double scale, const double* X, doub
   const int64_t ninst = (int64_t)p->inst.size();
   hipLaunchKernelGGL(k_two_body, dim3(node_tiles(p), (unsigned)std::min<int64_t>(ninst, kMaxGridY)), dim3(kThreads),
                      0, s, p->idesc, ninst, mu, scale, X, F, J);
-  return hipGetLastError();
-}
-
-hipError_t ivp_residual(birk_plan* p, const double* xa, const double* X, double* G, hipStream_t s) {
-  hipLaunchKernelGGL(k_ivp_residual, dim3(node_tiles(p), (unsigned)std::min<int64_t>(p->ncomp, kMaxGridY)),
-                     dim3(kThreads), 0, s, p->comps, p->ncomp, xa, X, G);
   return hipGetLastError();
 }
 

@@ -389,11 +389,14 @@ hipError_t plan_solve(birk_plan* p) {
   {
     const int B = (int)p->inst.size();
     std::vector<int2> tiles, ranges(B);
-    std::vector<int64_t> ioff(B), ilen(B);
+    std::vector<int64_t> ioff(B), ilen(B), icol(B);
+    int64_t ncol = 0;
     for (int i = 0; i < B; ++i) {
       const Instance& in = p->inst[i];
       ioff[i] = in.off;
       ilen[i] = in.Nn * in.nx;
+      icol[i] = ncol;
+      ncol += in.nx;
       ranges[i].x = (int)tiles.size();
       for (int64_t c = 0; c * kSegChunk < ilen[i]; ++c) tiles.push_back(make_int2(i, (int)c));
       ranges[i].y = (int)tiles.size();
@@ -402,16 +405,11 @@ hipError_t plan_solve(birk_plan* p) {
     sg.ntiles = (int)tiles.size();
     if ((e = upload_tiles(p, tiles, &sg.tiles)) != hipSuccess) return e;
     if ((e = upload_tiles(p, ranges, &sg.ranges)) != hipSuccess) return e;
-    void* d1 = nullptr;
-    void* d2 = nullptr;
-    if ((e = hipMalloc(&d1, B * sizeof(int64_t))) != hipSuccess) return e;
-    p->allocs.push_back(d1);
-    if ((e = hipMalloc(&d2, B * sizeof(int64_t))) != hipSuccess) return e;
-    p->allocs.push_back(d2);
-    sg.ioff = (int64_t*)d1;
-    sg.ilen = (int64_t*)d2;
-    if ((e = hipMemcpy(d1, ioff.data(), B * sizeof(int64_t), hipMemcpyHostToDevice)) != hipSuccess) return e;
-    if ((e = hipMemcpy(d2, ilen.data(), B * sizeof(int64_t), hipMemcpyHostToDevice)) != hipSuccess) return e;
+    for (auto [src, dst] : {std::pair{&ioff, &sg.ioff}, std::pair{&ilen, &sg.ilen}, std::pair{&icol, &sg.icol}}) {
+      void* d = nullptr;
+      if ((e = upload_raw(p, src->data(), B * sizeof(int64_t), &d)) != hipSuccess) return e;
+      *dst = (int64_t*)d;
+    }
   }
   return hipSuccess;
 }

@@ -689,17 +689,19 @@ static hipError_t finalize_set(birk_plan* p, PairSet& ps) {
 // 3/2 times it) and share a nominal M1 = 2^x (a pair's own M1 is 2^x, 3/4 2^x or
 // 5/8 2^x).  For each class the tuner times the plan's product with every x the compiled
 // kernels support for all of its pairs, one class at a time with the others fixed, and
-// keeps the fastest (the current choice stays unless another is more than 2 % faster).  A
-// change of split rebuilds the class's filter spectra in the new rows-pass order and the
+// keeps the fastest (the current choice stays unless another is more than 2 % faster; it may
+// differ between the pairs of a class, whose lengths do not all allow every x).  A change of
+// split rebuilds the class's filter spectra in the new rows-pass order and the
 // tile lists; the products change only in rounding order.
-static hipError_t set_blu_split(birk_plan* p, int cls, int x, hipStream_t s) {
+static hipError_t set_blu_split(birk_plan* p, int cls, const std::vector<int>& xs, hipStream_t s) {
   PairSet& ps = p->gen[1];
   hipError_t e = hipStreamSynchronize(s);   // the lists in use are freed
   PairSet fs;
   std::vector<int64_t> seen;
-  for (PairDesc& d : ps.host) {
+  for (size_t q = 0; q < ps.host.size(); ++q) {
+    PairDesc& d = ps.host[q];
     if (d.cls != cls) continue;
-    blu_set_split(d, x);
+    blu_set_split(d, xs[q]);
     if (std::find(seen.begin(), seen.end(), d.N) != seen.end()) continue;
     seen.push_back(d.N);
     fs.host.push_back(d);
@@ -747,20 +749,29 @@ static hipError_t tune_general_t(birk_plan* p, hipStream_t s, std::string* repor
   char line[160];
   for (int cls : sizes) {
     if (e != hipSuccess) break;
-    const PairDesc* member = nullptr;
-    for (const PairDesc& d : p->gen[1].host)
-      if (d.cls == cls) member = &d;
-    const int cur = blu_split(*member);
+    const size_t np = p->gen[1].host.size();
+    std::vector<int> keep(np);   // every pair's split (those of the class are used)
+    int cur = 0;                 // the class's last
+    for (size_t q = 0; q < np; ++q) {
+      keep[q] = blu_split(p->gen[1].host[q]);
+      if (p->gen[1].host[q].cls == cls) cur = keep[q];
+    }
+    std::vector<int> chosen = keep;
     float best_ms = 0.0f;
     if ((e = time_product(&best_ms)) != hipSuccess) break;
     snprintf(line, sizeof line, "general path M=2^%d: [M1 2^%d] %.1f us;", cls, cur, 1000.0 * best_ms);
     *report += line;
     int best = cur;
     for (int x = 7; x <= kLdsMaxLog && e == hipSuccess; ++x) {
-      bool ok = x != cur;
-      for (const PairDesc& d : p->gen[1].host) ok = ok && (d.cls != cls || blu_split_ok(d, x));
-      if (!ok) continue;
-      if ((e = set_blu_split(p, cls, x, s)) != hipSuccess) break;
+      bool ok = true, same = true;
+      for (const PairDesc& d : p->gen[1].host) {
+        if (d.cls != cls) continue;
+        ok = ok && blu_split_ok(d, x);
+        same = same && keep[&d - p->gen[1].host.data()] == x;
+      }
+      if (!ok || same) continue;
+      const std::vector<int> all(np, x);
+      if ((e = set_blu_split(p, cls, all, s)) != hipSuccess) break;
       float ms = 0.0f;
       if ((e = time_product(&ms)) != hipSuccess) break;
       snprintf(line, sizeof line, " [M1 2^%d] %.1f us;", x, 1000.0 * ms);
@@ -768,9 +779,10 @@ static hipError_t tune_general_t(birk_plan* p, hipStream_t s, std::string* repor
       if (ms < best_ms * (1.0f - 0.02f)) {
         best_ms = ms;
         best = x;
+        chosen = all;
       }
     }
-    if (e == hipSuccess) e = set_blu_split(p, cls, best, s);
+    if (e == hipSuccess) e = set_blu_split(p, cls, chosen, s);
     snprintf(line, sizeof line, " chosen [M1 2^%d]\n", best);
     *report += line;
   }

@@ -724,19 +724,15 @@ birk_status gmres_cycle(birk_plan* p, int jk, const double* J, const double* r, 
   // tolerance, ||r||); the pinned staging is rewritten only after the synchronisations
   // that follow these copies
   {
-    double* sc = stage_coef(p);
-    double* prm = sc + B;
+    double* prm = stage_coef(p);
     for (int i = 0; i < B; ++i) {
-      sc[i] = active[i] && st[i].rnorm > 0 ? 1.0 / st[i].rnorm : 0.0;
       prm[3 * i] = active[i] ? 1.0 : 0.0;
       prm[3 * i + 1] = tol_inner[i];
       prm[3 * i + 2] = st[i].rnorm;
     }
-    e = hipMemcpyAsync(p->krylov_coef, sc, B * sizeof(double), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(p->krylov_prm, prm, 3 * B * sizeof(double), hipMemcpyHostToDevice, s);
+    e = hipMemcpyAsync(p->krylov_prm, prm, 3 * B * sizeof(double), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return BIRK_ERR_DEVICE;
-    kry::sscale_conv<double, TK>(p, r, Q, p->krylov_coef, s);
-    kry::gm_init(p, p->krylov_prm, p->krylov_gm, s);
+    kry::gm_start<TK>(p, r, Q, p->krylov_prm, p->krylov_gm, s);
   }
   double* flags = stage_dots(p);
   int j = 0, checks = 0;
@@ -1082,7 +1078,7 @@ birk_status birk_newton_ivp(birk_plan* p, const birk_ivp_model* model, const dou
       result = BIRK_ERR_DEVICE;
       break;
     }
-    kry::sscale_conv<double, double>(p, b.G, b.beta, b.alpha, s);
+    kry::sscale(p, b.G, b.beta, b.alpha, s);
     std::fill(lst.begin(), lst.end(), BIRK_OK);
     std::fill(lin_it.begin(), lin_it.end(), 0);
     const birk_status ls = birk_krylov_solve(p, BIRK_J_PER_NODE, b.J, b.beta, b.D, &lo, &li);

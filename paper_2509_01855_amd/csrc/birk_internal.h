@@ -402,15 +402,17 @@ void gram_schmidt(const birk_plan* p, T* Q, int j, const T* a, const T* b, T* u,
                   double* st, double* flags, hipStream_t s);
 template <typename T>
 void next_vector(const birk_plan* p, const T* u, const double* dots, int64_t dstride, T* q, hipStream_t s);
-template <typename TI, typename TO>
-void sscale_conv(const birk_plan* p, const TI* x, TO* y, const double* alpha, hipStream_t s);
+// y = alpha[i] x
+void sscale(const birk_plan* p, const double* x, double* y, const double* alpha, hipStream_t s);
 // x = x0 + sum_{k < cnt[i]} c[i][k] Q0_k, and with Q1 y = y0 + the same of Q1 (x, y double, the
 // sums in double; x0, y0 null: zero; x0 may be x, y0 y)
 template <typename T>
 void scombine(const birk_plan* p, const double* c, int64_t cstride, const int* cnt, const T* Q0, const double* x0,
               double* x, const T* Q1, const double* y0, double* y, hipStream_t s);
-// device-side GMRES scalars: prm = (active, tolerance, ||r||) per instance
-void gm_init(const birk_plan* p, const double* prm, double* st, hipStream_t s);
+// Start of a GMRES cycle: q = r / ||r|| and the states, prm = (active, tolerance, ||r||) per
+// instance; its end: the coefficients and their count, and what the host reads.
+template <typename T>
+void gm_start(const birk_plan* p, const double* r, T* q, const double* prm, double* st, hipStream_t s);
 void gm_solve(const birk_plan* p, double* st, double* coef, int64_t cstride, int* cnt, double* flags, hipStream_t s);
 }  // namespace kry
 

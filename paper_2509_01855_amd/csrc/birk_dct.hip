@@ -563,11 +563,12 @@ static void layout_set(PairSet& ps, int64_t& woff, int64_t& poff) {
   }
 }
 
-// Longest power-of-two N whose products run in one workgroup's LDS (2N <= kLdsMax).  Up to
-// there one launch that reads v and writes out once beats the three passes and their two
-// intermediate arrays at every batch size (double, N = 512 / 1024 / 2048: 24 / 26 / 30 us in
-// three passes, 12.6 / 15.2 / 20.5 us here at six components, and 25 / 28 / 32 against
-// 12.8 / 15.4 / 21 us at 192; double-float at 192 and N = 2048 65 against 46 us).
+// Longest power-of-two N whose products run in one workgroup's LDS, a component each
+// (birk_lds.hip).  Up to there one launch that reads v and writes out once beats the three
+// passes and their two intermediate arrays at every batch size (N = 512 / 1024 / 2048, three
+// passes against one launch: 25 / 26 / 30 us against 6.9 / 8.7 / 10.4 at six components in
+// double, 379 / 528 / 854 against 140 / 167 / 353 at 16386; double-float at 2048 62 against 36
+// and 1520 against 1197).
 constexpr int64_t kLdsMaxN = kLdsMax / 2;
 
 void plan_products(birk_plan* p) {
@@ -576,6 +577,7 @@ void plan_products(birk_plan* p) {
     p->gen[k] = PairSet();
     p->lds[k] = LdsSet();
   }
+  p->lds_even = LdsSet();
   p->noalloc_nbuf = 2;
   int64_t woff = 0, poff = 0;
   const int B = (int)p->inst.size();
@@ -594,10 +596,15 @@ void plan_products(birk_plan* p) {
       if (g.N <= kLdsMaxN) {
         // no workspace used; the plan's size (what birk_apply_noalloc accepts) counts it
         // as for the three-pass groups
-        for (; i < j; ++i)
-          for (int q = 0; q < (p->inst[i].nx + 1) / 2; ++q)
-            p->lds[0].host.push_back(make_pair(p->inst[i].off + 2 * (int64_t)q * in.Nn, in.Nn,
-                                               2 * q + 1 < p->inst[i].nx));
+        PairDesc d;
+        d.Nn = g.Nn;
+        d.N = g.N;
+        d.logM = ilog2_ceil(g.N);
+        for (int c = 0; c < g.nc; ++c) {
+          d.src = g.off + (int64_t)c * g.Nn;
+          p->lds_even.host.push_back(d);
+        }
+        i = j;
         woff += fw;
         poff += fp;
         continue;
@@ -912,6 +919,7 @@ hipError_t build_tables(birk_plan* p) {
   if (!p->gen[0].host.empty() && (e = finalize_set(p, p->gen[0])) != hipSuccess) return e;
   for (int k = 0; k < 2; ++k)
     if ((e = finalize_lds(p, p->lds[k])) != hipSuccess) return e;
+  if ((e = finalize_lds_even(p, p->lds_even)) != hipSuccess) return e;
   return hipGetLastError();
 }
 

@@ -137,8 +137,8 @@ struct PairSet {
   int64_t parts = 0;          // doubles of partials needed
 };
 
-// Pairs whose whole product runs in one workgroup's LDS (birk_lds.hip): one launch over the
-// tiles (first pair, count) of pairs of one length.
+// Components whose whole product runs in one workgroup's LDS (birk_lds.hip): one launch over the
+// tiles (first pair, count) of pairs of one length, or over single components.
 struct LdsSet {
   std::vector<PairDesc> host;
   PairDesc* dev = nullptr;
@@ -192,6 +192,7 @@ struct birk_plan {
   std::vector<birk::FastGroup> fgroups;
   birk::PairSet gen[2];           // general-path pairs: [0] 2N a power of two, [1] Bluestein
   birk::LdsSet lds[2];            // pairs that fit one workgroup: [0] 2N a power of two, [1] Bluestein
+  birk::LdsSet lds_even;          // single components, N = 512, 1024, 2048 (logM = log2 N)
   int noalloc_nbuf = 3;           // work buffers that birk_apply_noalloc accounts for
   std::vector<birk::ScanClass> sclass;  // its wave scans, n_x <= kScanNx
   birk::SegSet seg;               // Krylov segmentation of the batch
@@ -299,6 +300,7 @@ hipError_t product_blu(birk_plan* p, const PairSet& ps, const T* v, T* out, int 
 // ---- whole products in LDS (birk_lds.hip) ----
 // Sort the set's pairs by length and upload its descriptors and tile list.
 hipError_t finalize_lds(birk_plan* p, LdsSet& ls);
+hipError_t finalize_lds_even(birk_plan* p, LdsSet& ls);
 template <typename T>
 hipError_t product_lds(birk_plan* p, const T* v, T* out, int transpose, hipStream_t s);
 

@@ -1,8 +1,13 @@
 // Products whose transforms fit one workgroup (gfx950): N <= 2048 a power of two, or any N
-// with 3N <= 4096.  One launch takes a pair of components from v to out: DCT-I, the
+// with 3N <= 4096.  One launch takes a component or a pair of them from v to out: DCT-I, the
 // coefficient stencil with c^_0, DCT-I, all in LDS, so that a product reads v and writes
 // out once and a small product is one launch instead of five (Bluestein) to seven (pack,
 // transform, stencil, c^_0, transform, unpack).
+//
+// k_lds_product: a pair of components as one complex vector, N < 512 and the chirp lengths.
+// k_lds_even: one component, N = 512, 1024, 2048.  There, as in the three passes of longer
+// powers of two, no component may meet another's rounding or infinities (states are often
+// in units 10^3 apart), so a pair must not share a complex vector.
 //
 // A DCT-I is half the DFT of the even extension, of length L = 2N (see birk_dct.hip): L a
 // power of two is transformed as it is, any other L by Bluestein's convolution in a
@@ -14,10 +19,9 @@
 // four stages at M = 1024); with many pairs LDS bandwidth.  A pair of components per
 // workgroup (M / 8 threads) keeps the chain short and uses as many CUs as there are pairs;
 // plans whose largest M is below 512 put 512 / M pairs in one wave.  Measured per product,
-// six components in double, before (five to seven launches, or three passes from N = 512)
-// and after: N = 255 (M = 1024) 36.6 -> 16.5 us, 256 28.4 -> 11.2, 999 (M = 4096)
-// 36.1 -> 29.7, 1024 26.0 -> 15.2, 2048 29.8 -> 20.5; 192 components: N = 256
-// 46.2 -> 11.5 us, 2048 32.1 -> 21.
+// six components in double, before (five to seven launches) and after: N = 255 (M = 1024)
+// 36.6 -> 16.5 us, 256 28.4 -> 11.2, 999 (M = 4096) 36.1 -> 29.7; 192 components: N = 256
+// 46.2 -> 11.5 us.
 
 #include <hip/hip_runtime.h>
 
@@ -250,6 +254,154 @@ __global__ __launch_bounds__(kLdsMax / kPPT) void k_lds_product(const T* __restr
   }
 }
 
+// One component of N = 2^LOGN per workgroup, N / 8 threads.  The even extension y_m,
+// m < 2N, goes through a complex transform of half its length, z_n = y_2n + i y_(2n+1).  Both
+// halves are symmetric (y_2n in n -> N - n, y_(2n+1) in n -> N - 1 - n), so that with
+// c - i s = W_2N^k, a = (Im Z_k + Im Z_(N-k)) / 2 and b = (Re Z_(N-k) - Re Z_k) / 2
+//     E = (Re Z_k + Re Z_(N-k)) / 2,  R = c a + s b,  Y_k = E + R,  Y_(N-k) = E - R
+// are the DFT values, all of them real.  Thread t holds k = t + i N/8, i < 4, and N - k;
+// Y_(N/2) is Re Z_(N/2) as it stands.  Bound: as above, the chain of LDS stages, then LDS
+// bandwidth.  Six components in double at N = 512, 1024, 2048: 6.9, 8.7, 10.4 us; pairs of
+// components in transforms of 2N points took 10.5, 12.5, 18.6 (16386 components at N = 2048:
+// 353 against 668), a lone component with a zero partner the same and twice as much per
+// component once the chip is full.
+template <typename T, int LOGN>
+__device__ __forceinline__ void lds_even(const T* __restrict__ x, T* __restrict__ out, const PairDesc& d,
+                                         const cplx<T>* __restrict__ tw, int trans, T* sm, double* red) {
+  constexpr int N = 1 << LOGN, NT = N / kPPT, H = kPPT / 2, LD = fast::padded_ld(N);
+  const int t = (int)threadIdx.x;
+  const bool on = t < NT;
+  T* re = sm;        // N + 1 places: also row Y_0 .. Y_N between the transforms
+  T* im = sm + LD;
+  T ve[H], vo[H], last = T(0);
+  // element 2n (and its mirror) or 2n + 1 of the extension
+  auto put_even = [&](int n, T v) {
+    re[fast::pad(n)] = v;
+    if (n > 0 && n < N / 2) re[fast::pad(N - n)] = v;
+  };
+  auto put_odd = [&](int n, T v) {
+    im[fast::pad(n)] = v;
+    im[fast::pad(N - 1 - n)] = v;
+  };
+  // Y_k and Y_(N-k) of the thread's i-th k
+  auto values = [&](int i, T& lo, T& hi) {
+    const int k = t + i * NT, m = (N - k) & (N - 1);
+    const T zr = re[fast::pad(k)], zi = im[fast::pad(k)], wr = re[fast::pad(m)], wi = im[fast::pad(m)];
+    const cplx<T> w = tw[k << (kLdsMaxLog - 1 - LOGN)];   // c - i s
+    const T E = T(0.5) * (zr + wr);
+    const T R = T(0.5) * (w.x * (zi + wi) - w.y * (wr - zr));
+    lo = E + R;
+    hi = E - R;
+  };
+  if (on) {
+    const T* xa = x + d.src;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const int n = t + i * NT;
+      ve[i] = xa[2 * n];
+      vo[i] = xa[2 * n + 1];
+    }
+    if (t == 0) last = xa[N];
+    const T e = trans ? T(2) : T(1);   // E^{-1} of the transpose: ends doubled
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const int n = t + i * NT;
+      put_even(n, n == 0 ? e * ve[i] : ve[i]);
+      put_odd(n, vo[i]);
+    }
+    if (t == 0) put_even(N / 2, e * last);
+  }
+  __syncthreads();
+  fast::fft_ct<T, LOGN, 1, true>(sm, tw);
+  // Y in place of the real row (a k and its mirror are read and written by one thread), and
+  // the c^_0 sums
+  if (on) {
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const int k = t + i * NT;
+      T lo, hi;
+      values(i, lo, hi);
+      re[fast::pad(k)] = lo;
+      re[fast::pad(N - k)] = hi;
+      if (!trans) s += c0_weight(k, N) * (double)lo + c0_weight(N - k, N) * (double)hi;
+    }
+    if (!trans) {
+      if (t == 0) s += c0_weight(N / 2, N) * (double)re[fast::pad(N / 2)];   // W_2N^(N/2) = -i: Y = E = Re Z
+      s = wave_sum_last(s);
+      if ((t & 63) == 63) red[t >> 6] = s;
+    }
+  }
+  __syncthreads();
+  // stencil: the inputs of the second DCT from Y, all read before any is written
+  if (on) {
+    const T invN = T(1) / T(N), inv4N1 = T(1) / T(4 * N + 4), inv2N1 = T(1) / T(2 * N + 2);
+    const T Y0 = re[0];
+    auto stencil = [&](int k) {
+      const T Ym = re[fast::pad(max(k - 1, 0))], Yp = re[fast::pad(min(k + 1, N))];
+      if (trans) return TrStencil<T>(k, N, inv2N1)(Y0, Ym, Yp);
+      return FwdStencil<T>(max(k, 1), N, invN, inv4N1)(Ym, Yp);
+    };
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const int n = t + i * NT;
+      const T v = stencil(2 * n);
+      ve[i] = (trans || n > 0) ? v : T(0);   // d_0 is c^_0, added at the end
+      vo[i] = stencil(2 * n + 1);
+    }
+    if (t == 0) last = stencil(N);
+  }
+  __syncthreads();
+  if (on) {
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      put_even(t + i * NT, ve[i]);
+      put_odd(t + i * NT, vo[i]);
+    }
+    if (t == 0) put_even(N / 2, last);
+  }
+  __syncthreads();
+  fast::fft_ct<T, LOGN, 1, true>(sm, tw);
+  if (!on) return;
+  // out = Y / 2 + c^_0, or e_j Y_j / N
+  T sc = T(0.5), c0 = T(0);
+  if (trans) {
+    sc = T(1) / T(N);
+  } else {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < (NT + 63) / 64; ++w) s += red[w];
+    c0 = (T)(s / (double)N);
+  }
+  T* o = out + d.src;
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    const int k = t + i * NT;
+    T lo, hi;
+    values(i, lo, hi);
+    const T f = (trans && k == 0) ? T(0.5) * sc : sc;
+    o[k] = f * lo + c0;
+    o[N - k] = f * hi + c0;
+  }
+  if (t == 0) o[N / 2] = sc * re[fast::pad(N / 2)] + c0;
+}
+
+template <typename T>
+__global__ __launch_bounds__(kLdsMax / 2 / kPPT) void k_lds_even(const T* __restrict__ x, T* __restrict__ out,
+                                                                const PairDesc* __restrict__ pd,
+                                                                const cplx<T>* __restrict__ tw, int trans) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ double red[kLdsMax / 2 / kPPT / 64];
+  T* sm = reinterpret_cast<T*>(smem_raw);
+  const PairDesc& d = pd[blockIdx.x];
+  switch (d.logM) {
+    case 9: lds_even<T, 9>(x, out, d, tw, trans, sm, red); break;
+    case 10: lds_even<T, 10>(x, out, d, tw, trans, sm, red); break;
+    case 11: lds_even<T, 11>(x, out, d, tw, trans, sm, red); break;
+    default: break;
+  }
+}
+
 // Pairs of length 2^logM in a workgroup, and the LDS (reals) they take.
 int lds_pairs(int logM) { return logM >= 9 ? 1 : 512 >> logM; }
 int lds_reals(int logM) { return 2 * lds_pairs(logM) * fast::padded_ld(1 << logM); }
@@ -292,8 +444,29 @@ hipError_t finalize_lds(birk_plan* p, LdsSet& ls) {
   return e;
 }
 
+// Components by length, and their descriptors.
+hipError_t finalize_lds_even(birk_plan* p, LdsSet& ls) {
+  if (ls.host.empty()) return hipSuccess;
+  std::stable_sort(ls.host.begin(), ls.host.end(), [](const PairDesc& a, const PairDesc& b) { return a.logM < b.logM; });
+  const int longest = ls.host.back().logM;
+  ls.threads = (1 << longest) / kPPT;
+  ls.lds_reals = 2 * fast::padded_ld(1 << longest);
+  ls.ntiles = (int)ls.host.size();
+  void* d = nullptr;
+  const hipError_t e = upload_raw(p, ls.host.data(), ls.host.size() * sizeof(PairDesc), &d);
+  ls.dev = (PairDesc*)d;
+  return e;
+}
+
 template <typename T>
 hipError_t product_lds(birk_plan* p, const T* v, T* out, int transpose, hipStream_t s) {
+  const LdsSet& le = p->lds_even;
+  if (le.ntiles > 0) {
+    const int bytes = le.lds_reals * (int)sizeof(T);
+    (void)hipFuncSetAttribute((const void*)k_lds_even<T>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    hipLaunchKernelGGL(k_lds_even<T>, dim3(le.ntiles), dim3(le.threads), bytes, s, v, out, le.dev,
+                       (const cplx<T>*)p->lds_tw[prec_index<T>()], transpose);
+  }
   const hipError_t e = launch<T, false>(p, p->lds[0], v, out, transpose, s);
   return e == hipSuccess ? launch<T, true>(p, p->lds[1], v, out, transpose, s) : e;
 }

@@ -30,14 +30,22 @@ __device__ __forceinline__ double recip_int<double>(double x) {
 }
 
 // d_k for 1 <= k <= N from Y_{k-1} and Y_{k+1} (Yp is not used at k = N):
-// invN = 1/N, inv4N1 = 1/(4 (N + 1)).
+// invN = 1/N, inv4N1 = 1/(4 (N + 1)).  One component, then a pair.
+template <typename T>
+struct FwdStencil {
+  T i2k, cp, sc;
+  __device__ __forceinline__ FwdStencil(int k, int N, T invN, T inv4N1) {
+    i2k = recip_int<T>(T(2 * k));   // 1/(2k); at k = 1 also e_0 = 1/2
+    cp = T(0);
+    if (k < N) cp = (k + 1 == N) ? T(0.5) * i2k - inv4N1 : i2k;
+    sc = (k == N) ? T(2) * invN : invN;
+  }
+  __device__ __forceinline__ T operator()(T Ym, T Yp) const { return (cp * Yp - i2k * Ym) * sc; }
+};
 template <typename T>
 __device__ __forceinline__ cplx<T> mid_fwd(int k, int N, cplx<T> Ym, cplx<T> Yp, T invN, T inv4N1) {
-  const T i2k = recip_int<T>(T(2 * k));   // 1/(2k); at k = 1 also e_0 = 1/2
-  T cp = T(0);
-  if (k < N) cp = (k + 1 == N) ? T(0.5) * i2k - inv4N1 : i2k;
-  const T sc = (k == N) ? T(2) * invN : invN;
-  return fast::mk<T>((cp * Yp.x - i2k * Ym.x) * sc, (cp * Yp.y - i2k * Ym.y) * sc);
+  const FwdStencil<T> f(k, N, invN, inv4N1);
+  return fast::mk<T>(f(Ym.x, Yp.x), f(Ym.y, Yp.y));
 }
 
 // N times the weight of Y_k in c^_0.
@@ -51,18 +59,31 @@ __device__ __forceinline__ double c0_weight(int k, int N) {
 // q_j for 0 <= j <= N from Y_0, Y_{j-1}, Y_{j+1} (Yp is not used at j = N
 // nor Ym at j <= 1): inv2N1 = 1/(2 (N + 1)).
 template <typename T>
-__device__ __forceinline__ cplx<T> mid_tr(int j, int N, cplx<T> Y0, cplx<T> Ym, cplx<T> Yp, T inv2N1) {
-  const T h = T(0.5);
-  if (j == 0) return fast::mk<T>(h * (Y0.x - Yp.x), h * (Y0.y - Yp.y));
-  if (j == 1) return fast::mk<T>(T(0.125) * (Y0.x - Yp.x), T(0.125) * (Y0.y - Yp.y));
-  const T rm = recip_int<T>(T(j - 1)), rp = recip_int<T>(T(j + 1));
-  T cm = h * rm, cp = h * rp;
-  if (j == N) {
-    cm -= inv2N1;
-    cp = T(0);
+struct TrStencil {
+  T cm, cp, c0;
+  int j;
+  __device__ __forceinline__ TrStencil(int j_, int N, T inv2N1) : j(j_) {
+    const T h = T(0.5);
+    const T rm = recip_int<T>(T(max(j, 2) - 1)), rp = recip_int<T>(T(j + 1));
+    cm = h * rm;
+    cp = h * rp;
+    if (j == N) {
+      cm -= inv2N1;
+      cp = T(0);
+    }
+    c0 = rm * rp;
   }
-  const T c0 = rm * rp;
-  return fast::mk<T>(h * (cm * Ym.x - cp * Yp.x - c0 * Y0.x), h * (cm * Ym.y - cp * Yp.y - c0 * Y0.y));
+  __device__ __forceinline__ T operator()(T Y0, T Ym, T Yp) const {
+    const T h = T(0.5);
+    if (j == 0) return h * (Y0 - Yp);
+    if (j == 1) return T(0.125) * (Y0 - Yp);
+    return h * (cm * Ym - cp * Yp - c0 * Y0);
+  }
+};
+template <typename T>
+__device__ __forceinline__ cplx<T> mid_tr(int j, int N, cplx<T> Y0, cplx<T> Ym, cplx<T> Yp, T inv2N1) {
+  const TrStencil<T> f(j, N, inv2N1);
+  return fast::mk<T>(f(Y0.x, Ym.x, Yp.x), f(Y0.y, Ym.y, Yp.y));
 }
 
 }  // namespace birk

@@ -906,7 +906,10 @@ extern "C" birk_status birk_krylov_solve(birk_plan* p, birk_jac_kind jk, const d
       break;
     }
   }
-  if (fresh && hipMemsetAsync(chi, 0, n * sizeof(double), s) != hipSuccess) return BIRK_ERR_DEVICE;
+  // no cycle wrote chi (zero or non-finite beta, a singular pivot): cleared, and waited for, since
+  // the call returns with its stream idle
+  if (fresh && (hipMemsetAsync(chi, 0, n * sizeof(double), s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess))
+    return BIRK_ERR_DEVICE;
   for (int i = 0; i < B; ++i) {
     if (result == BIRK_OK && st[i].status != BIRK_OK) result = (birk_status)st[i].status;
     if (info) {

@@ -229,7 +229,8 @@ birk_status birk_precond(birk_plan* plan, birk_jac_kind jac_kind, const double* 
                          const void* y, void* out, int32_t inverse);
 
 /* out = A x = x - (I (x) B^a)(J x)  (FastAX box, eq:Achibetadef), double in and out
- * regardless of the plan precision (the product runs in double).  Errors as above. */
+ * regardless of the plan precision (the product runs in double); any n_x.  Errors:
+ * BIRK_ERR_ARG, BIRK_ERR_DEVICE. */
 birk_status birk_fast_ax(birk_plan* plan, birk_jac_kind jac_kind, const double* J,
                          const double* x, double* out);
 

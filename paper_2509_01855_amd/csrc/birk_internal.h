@@ -339,6 +339,9 @@ hipError_t two_body(birk_plan* p, double mu, double scale, const double* X, doub
 template <typename T>
 hipError_t jac_times(birk_plan* p, int jac_kind, const double* J, const T* x, T* y,
                      hipStream_t s);
+// J x, or J^T x, of the instances with n_x > kWideNx (part of jac_times and jac_t_times).
+template <typename T, bool TRANS>
+hipError_t jac_many(birk_plan* p, int jac_kind, const double* J, const T* x, T* y, hipStream_t s);
 template <typename T>
 hipError_t precond_forward(birk_plan* p, int jac_kind, const double* J, const T* y, T* out,
                            hipStream_t s);

@@ -376,7 +376,7 @@ hipError_t jac_t_times(birk_plan* p, int jac_kind, const double* J, const double
   for (const ScanClass& sc : p->sclass) {
     BIRK_NX_SWITCH(sc.nx, (jt_class<NX>(sc, J, jac_kind == BIRK_J_PER_NODE, x, y, s)))
   }
-  return hipGetLastError();
+  return jac_many<double, true>(p, jac_kind, J, x, y, s);
 }
 
 #undef BIRK_NX_SWITCH

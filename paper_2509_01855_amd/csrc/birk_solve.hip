@@ -342,7 +342,42 @@ __global__ __launch_bounds__(256) void k_jac_class(const double* __restrict__ J,
   }
 }
 
-static inline unsigned nblocks(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
+// The same, or y_k = J_k^T x_k, for the instances with more states than there are classes for
+// (n_x > kWideNx; the others' tiles return at once).  tile = (instance, component * tiles + tile),
+// as in the P y passes.  Bound: J per node from memory; x and one J per instance from the caches.
+template <typename T, bool TRANS>
+__global__ __launch_bounds__(256) void k_jac_many(const int2* __restrict__ tiles, const InstDesc* __restrict__ idesc,
+                                                  const double* __restrict__ J, int per_node,
+                                                  const T* __restrict__ x, T* __restrict__ y) {
+  const int2 t = tiles[blockIdx.x];
+  const InstDesc d = idesc[t.x];
+  if (d.nx <= kWideNx) return;
+  const int nt = pfwd_ntiles(d.Nn), r = t.y / nt, nx = (int)d.nx;
+  const int64_t Nn = d.Nn, base = (int64_t)(t.y - r * nt) * kScanBlock;
+  const double* Ji = J + (per_node ? d.joff : d.jcoff);
+  const T* xi = x + d.off;
+#pragma unroll
+  for (int i = 0; i < kScanItems; ++i) {
+    const int64_t k = base + i * 256 + threadIdx.x;
+    if (k >= Nn) break;
+    double acc = 0.0;
+    for (int c = 0; c < nx; ++c) {
+      const int64_t e = TRANS ? (int64_t)c * nx + r : (int64_t)r * nx + c;
+      acc += (per_node ? Ji[e * Nn + k] : Ji[e]) * (double)xi[(int64_t)c * Nn + k];
+    }
+    y[d.off + (int64_t)r * Nn + k] = (T)acc;
+  }
+}
+
+template <typename T, bool TRANS>
+hipError_t jac_many(birk_plan* p, int jac_kind, const double* J, const T* x, T* y, hipStream_t s) {
+  if (p->pfwd_maxnx <= kWideNx) return hipSuccess;
+  hipLaunchKernelGGL((k_jac_many<T, TRANS>), dim3(p->pfwd_ntiles), dim3(256), 0, s, p->pfwd_tiles, p->idesc, J,
+                     jac_kind == BIRK_J_PER_NODE ? 1 : 0, x, y);
+  return hipGetLastError();
+}
+template hipError_t jac_many<double, true>(birk_plan*, int, const double*, const double*, double*, hipStream_t);
+
 
 static hipError_t upload_tiles(birk_plan* p, const std::vector<int2>& v, int2** dst) {
   void* d = nullptr;
@@ -442,7 +477,7 @@ hipError_t jac_times(birk_plan* p, int jac_kind, const double* J, const T* x, T*
   for (const ScanClass& sc : p->sclass) {
     BIRK_NX_SWITCH(sc.nx, (jac_class<NXC, T>(sc, J, pn, x, y, s)))
   }
-  return hipGetLastError();
+  return jac_many<T, false>(p, jac_kind, J, x, y, s);
 }
 
 #undef BIRK_NX_SWITCH

@@ -649,9 +649,21 @@ __global__ void k_convert(const cplx<double>* __restrict__ src, cplx<T>* __restr
   if (m < n) dst[m] = fast::mk<T>((T)src[m].x, (T)src[m].y);
 }
 
-template <typename F>
-void lds_attr(F f, size_t bytes) {
-  (void)hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+// LDS reals of a column tile (2^A R points a column) and of a row tile.
+constexpr int lds_cols(int R, int A) { return 2 * R * (1 << (log_sub(R, A) - A)) * fast::padded_ld(1 << A); }
+constexpr int lds_rows(int B) { return 2 * (1 << (std::max(B, kLogRows) - B)) * fast::padded_ld(1 << B); }
+// The most of them over the lengths that the kernels cover.
+constexpr int lds_cols_most() {
+  int m = 0;
+  for (int A = 7; A <= kLdsMaxLog; ++A) m = std::max(m, lds_cols(1, A));
+  for (int A = 5; A <= kLdsMaxLog - 2; ++A) m = std::max(m, lds_cols(3, A));
+  for (int A = 4; A <= kLdsMaxLog - 3; ++A) m = std::max(m, lds_cols(5, A));
+  return m;
+}
+constexpr int lds_rows_most() {
+  int m = 0;
+  for (int B = 6; B <= kLdsMaxLog; ++B) m = std::max(m, lds_rows(B));
+  return m;
 }
 
 }  // namespace
@@ -710,8 +722,8 @@ hipError_t blu_lists(birk_plan* p, PairSet& ps) {
     for (int b = 0; b < (nrows + Wr - 1) / Wr; ++b) tr.push_back(make_int2(q, b));
     ps.thr_c = std::max(ps.thr_c, (d.R << ls) / kPPT);
     ps.thr_r = std::max(ps.thr_r, (1 << lp) / kPPT);
-    ps.lds_c = std::max(ps.lds_c, 2 * d.R * W * fast::padded_ld(1 << d.logM1));
-    ps.lds_r = std::max(ps.lds_r, 2 * Wr * fast::padded_ld(1 << d.logM2));
+    ps.lds_c = std::max(ps.lds_c, lds_cols(d.R, d.logM1));
+    ps.lds_r = std::max(ps.lds_r, lds_rows(d.logM2));
   }
   ps.n_c4 = (int)tc.size();
   ps.n_r4 = (int)tr.size();
@@ -744,8 +756,8 @@ hipError_t blu_filters(birk_plan* p, const PairSet& ps, hipStream_t s) {
   cplx<double>* G = (cplx<double>*)p->work[0];
   cplx<double>* Y = (cplx<double>*)p->work[1];
   const cplx<double>* tw = (const cplx<double>*)p->lds_tw[0];
-  lds_attr(k_blu_cols<double>, ps.lds_c * sizeof(double));
-  lds_attr(k_blu_rows<double, true>, ps.lds_r * sizeof(double));
+  lds_limit(k_blu_cols<double>, lds_cols_most() * (int)sizeof(double));
+  lds_limit(k_blu_rows<double, true>, lds_rows_most() * (int)sizeof(double));
   hipLaunchKernelGGL(k_blu_cols<double>, dim3(ps.n_c4), dim3(ps.thr_c), ps.lds_c * sizeof(double), s, nullptr, Y, G,
                      ps.dev, ps.tiles_c4, tw, (int)kSrcFilter);
   hipLaunchKernelGGL((k_blu_rows<double, true>), dim3(ps.n_r4), dim3(ps.thr_r), ps.lds_r * sizeof(double), s, G,
@@ -768,10 +780,11 @@ hipError_t product_blu(birk_plan* p, const PairSet& ps, const T* v, T* out, int 
   cplx<T>* Y = (cplx<T>*)p->work[1];
   const cplx<T>* tw = (const cplx<T>*)p->lds_tw[prec_index<T>()];
   const size_t lc = ps.lds_c * sizeof(T), lr = ps.lds_r * sizeof(T);
-  lds_attr(k_blu_cols<T>, lc);
-  lds_attr(k_blu_rows<T, false>, lr);
-  lds_attr(k_blu_icols<T, false>, lc);
-  lds_attr(k_blu_icols<T, true>, lc);
+  constexpr int mc = lds_cols_most() * (int)sizeof(T), mr = lds_rows_most() * (int)sizeof(T);
+  lds_limit(k_blu_cols<T>, mc);
+  lds_limit(k_blu_rows<T, false>, mr);
+  lds_limit(k_blu_icols<T, false>, mc);
+  lds_limit(k_blu_icols<T, true>, mc);
   const dim3 gc(ps.n_c4), gr(ps.n_r4), bc(ps.thr_c), br(ps.thr_r);
   hipLaunchKernelGGL(k_blu_cols<T>, gc, bc, lc, s, v, Y, G, ps.dev, ps.tiles_c4, tw,
                      (int)(transpose ? kSrcVT : kSrcV));

@@ -1337,17 +1337,16 @@ static int threads_for(int complex_points) {
   return std::max(64, std::min(512, t));
 }
 
-template <typename F>
-static void lds_attr(F f, int bytes) {
-  (void)hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-}
+// Most dynamic LDS of the runtime-length kernels: 16 rows of 2^10, 8 of 2^11 or 4 of 2^12 points
+// in pass B, 139 KB in double (the others take the same at every launch).
+constexpr int kRuntimeLds = 140 * 1024;
 
 template <typename T, int TB, int TRANS>
 static void launch_B(int xcd, int nt, int nc, int thr, int lds, hipStream_t s, const cplx<T>* G, int64_t gcomp, int64_t sg,
                      cplx<T>* G2, int64_t g2comp, int64_t sg2, int64_t N, int logL1, int logL2, const cplx<T>* tw,
                      const cplx<T>* thi, const cplx<T>* tlo, int tsh, double* part) {
   auto f = fast::k_fastB<T, TB, TRANS>;
-  lds_attr(f, lds);
+  lds_limit(f, kRuntimeLds);
   hipLaunchKernelGGL(f, dim3(nt * nc), dim3(thr), lds, s, G, gcomp, sg, G2, g2comp, sg2, N, logL1, logL2, tw, thi,
                      tlo, tsh, part, nt, nc, xcd);
 }
@@ -1396,14 +1395,14 @@ static hipError_t fast_passes(birk_plan* p, const FastGroup& g, const T* v, T* o
       case 10: f = lw == 2 ? fast::k_fastA2<T, 10, 2> : fast::k_fastA2<T, 10, 3>; break;
       default: f = fast::k_fastA2<T, 11, 2>; break;
     }
-    lds_attr(f, lds);
+    lds_limit(f, lds);
     hipLaunchKernelGGL(f, dim3(ntA * nc), dim3(W * L1 / 16), lds, s, v + g.off, g.Nn, logL2, G, gcomp, sg, tw, thi,
                        tlo, tsh, thd, tld, transpose ? 1 : 0, ntA, nc, kn.xcd);
   } else {
     const int ntA = (L2 / 2 + 1 + WA - 1) / WA;
     const int lds = WA * ld1 * (int)sizeof(T);
     auto f = fast::k_fastA<T>;
-    lds_attr(f, lds);
+    lds_limit(f, kRuntimeLds);
     hipLaunchKernelGGL(f, dim3(ntA * nc), dim3(threads_for(WA * L1 / 2)), lds, s, v + g.off, g.Nn, logL1, logL2,
                        ilog2i(WA), G, gcomp, sg, tw, thi, tlo, tsh, transpose ? 1 : 0, ntA, nc, kn.xcd);
   }
@@ -1427,7 +1426,7 @@ static hipError_t fast_passes(birk_plan* p, const FastGroup& g, const T* v, T* o
       case 46: f = fast::k_fastB3<T, 1, 11, 2>; break;
       default: f = fast::k_fastB3<T, 1, 11, 4>; break;
     }
-    lds_attr(f, lds);
+    lds_limit(f, lds);
     hipLaunchKernelGGL(f, dim3(ntB * nc), dim3(thr), lds, s, G, gcomp, sg, G2, g2comp, sg2, g.N, logL1, tw, thi, tlo,
                        tsh, thd, tld, part, ntB, nc, kn.xcd);
   } else if (use_b2(kn, logL2)) {
@@ -1449,7 +1448,7 @@ static hipError_t fast_passes(birk_plan* p, const FastGroup& g, const T* v, T* o
       case 46: f = fast::k_fastB2<T, 1, 11, 2>; break;
       default: f = fast::k_fastB2<T, 1, 11, 4>; break;
     }
-    lds_attr(f, lds);
+    lds_limit(f, lds);
     hipLaunchKernelGGL(f, dim3(ntB * nc), dim3(thr), lds, s, G, gcomp, sg, G2, g2comp, sg2, g.N, logL1, tw, thi, tlo,
                        tsh, part, ntB, nc, kn.xcd);
   } else {
@@ -1501,7 +1500,7 @@ static hipError_t fast_passes(birk_plan* p, const FastGroup& g, const T* v, T* o
       case 22: f = fast::k_fastC2<T, 0, 11, 2>; break;
       default: f = fast::k_fastC2<T, 1, 11, 2>; break;
     }
-    lds_attr(f, lds);
+    lds_limit(f, lds);
     hipLaunchKernelGGL(f, dim3(ntC * nc), dim3(W * L1 / 16), lds, s, G2, g2comp, sg2, o, g.Nn, logL2, tw, part, ntB,
                        ntC, nc, kn.xcd);
   } else {
@@ -1510,7 +1509,7 @@ static hipError_t fast_passes(birk_plan* p, const FastGroup& g, const T* v, T* o
     const int thr = threads_for(WC * L1 / 2);
     T* o = out + g.off;
     auto f = transpose ? fast::k_fastC<T, 1> : fast::k_fastC<T, 0>;
-    lds_attr(f, lds);
+    lds_limit(f, kRuntimeLds);
     hipLaunchKernelGGL(f, dim3(ntC * nc), dim3(thr), lds, s, G2, g2comp, sg2, o, g.Nn, logL1, logL2, ilog2i(WC), tw,
                        part, ntB, ntC, nc, kn.xcd);
   }

@@ -32,6 +32,14 @@ constexpr int prec_index() {
 }
 constexpr int kNumPrec = 3;
 
+// Dynamic LDS a kernel may be launched with.  The limit belongs to the kernel, not to a plan: it is
+// always set to the most that any plan launches it with, so that plans on other threads cannot
+// find it lowered between their own setting and launch.
+template <typename F>
+inline void lds_limit(F f, int most) {
+  (void)hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+}
+
 // Per-instance data of the preconditioner and the solve.
 struct Instance {
   int64_t Nn = 0, N = 0;

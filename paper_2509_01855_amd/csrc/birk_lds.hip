@@ -411,7 +411,7 @@ hipError_t launch(birk_plan* p, const LdsSet& ls, const T* v, T* out, int transp
   if (ls.ntiles == 0) return hipSuccess;
   const auto f = k_lds_product<T, CHIRP>;
   const int bytes = ls.lds_reals * (int)sizeof(T);
-  (void)hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  lds_limit(f, lds_reals(kLdsMaxLog) * (int)sizeof(T));
   hipLaunchKernelGGL(f, dim3(ls.ntiles), dim3(ls.threads), bytes, s, v, out, ls.dev, ls.tiles,
                      (const cplx<T>*)p->lds_tw[prec_index<T>()], transpose);
   return hipGetLastError();
@@ -463,7 +463,7 @@ hipError_t product_lds(birk_plan* p, const T* v, T* out, int transpose, hipStrea
   const LdsSet& le = p->lds_even;
   if (le.ntiles > 0) {
     const int bytes = le.lds_reals * (int)sizeof(T);
-    (void)hipFuncSetAttribute((const void*)k_lds_even<T>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    lds_limit(k_lds_even<T>, 2 * fast::padded_ld(kLdsMax / 2) * (int)sizeof(T));
     hipLaunchKernelGGL(k_lds_even<T>, dim3(le.ntiles), dim3(le.threads), bytes, s, v, out, le.dev,
                        (const cplx<T>*)p->lds_tw[prec_index<T>()], transpose);
   }

@@ -683,7 +683,7 @@ void launch(birk_plan* p, const ScanClass& sc, const double* J, const T* y, T* o
   if (sc.n_small > 0) {
     const auto f = k_scan_small<NX, MODE, BACK, T>;
     const int bytes = sc.small_waves * Lay<NX>::SIZE * (int)sizeof(double);
-    (void)hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    lds_limit(f, small_waves<NX>() * Lay<NX>::SIZE * (int)sizeof(double));
     hipLaunchKernelGGL(f, dim3(sc.n_small), dim3(64 * sc.small_waves), bytes, s, J, ht, y, sc.dev, sc.small, out, jout,
                        flag);
   }

@@ -108,8 +108,9 @@ int64_t birk_plan_length(const birk_plan* plan);
 /* Autotuner of the product schedules.  Power-of-two path (N = 2^p >= 4096): for each group of
  * same-length components it times B^a (FastBV box) in the plan's precision over a
  * fixed set of tile schedules: both splits 2N = L1 L2 of the two-step DCTs, two or four
- * rows per middle-pass tile, the plain or XCD-grouped tile order, four- or eight-column
- * tiles in the first and last passes where their transforms are 512 or 1024 points long,
+ * rows per middle-pass tile, the plain or XCD-grouped tile order, wide or narrow tiles in
+ * the first and last passes (eight or four columns where their transforms are 512 or 1024
+ * points long; sixteen or fewer for large groups of floats up to 512 points),
  * and the components on one stream or in two or three parts on as many streams (forked
  * from and joined back into the plan's stream by events; same kernels per component).
  * In each of two interleaved rounds a candidate runs once to warm up, then four times

@@ -1351,9 +1351,11 @@ static void launch_B(int xcd, int nt, int nc, int thr, int lds, hipStream_t s, c
                      tlo, tsh, part, nt, nc, xcd);
 }
 
-// The three passes for the components of g (a whole group or a contiguous part of one).
+// The three passes for the components of g (a whole group of ncg, or a contiguous part of one,
+// whose tiles are those of the group).
 template <typename T>
-static hipError_t fast_passes(birk_plan* p, const FastGroup& g, const T* v, T* out, int transpose, hipStream_t s) {
+static hipError_t fast_passes(birk_plan* p, const FastGroup& g, int ncg, const T* v, T* out, int transpose,
+                              hipStream_t s) {
   constexpr int pi = prec_index<T>();
   int logL1, logL2, WA, TB, WC;
   const FastKnobs& kn = g.kn;
@@ -1372,7 +1374,7 @@ static hipError_t fast_passes(birk_plan* p, const FastGroup& g, const T* v, T* o
   const cplx<double>* thd = (const cplx<double>*)g.tw.hi[0];
   const cplx<double>* tld = (const cplx<double>*)g.tw.lo[0];
   const int nc = g.nc;
-  const int lw = fixed_logw<T>(kn, logL1, logL2, nc);
+  const int lw = fixed_logw<T>(kn, logL1, logL2, ncg);
   if (lw > 0) {
     // compile-time lengths: one tile of W = 2^lw columns per workgroup
     const int W = 1 << lw;
@@ -1516,16 +1518,19 @@ static hipError_t fast_passes(birk_plan* p, const FastGroup& g, const T* v, T* o
   return hipGetLastError();
 }
 
-// Tile schedules the autotuner tries for a group: the defaults first, then both splits of
-// 2N = L1 L2, two or four rows per pass-B tile, both tile orders, one to three streams,
-// and, where L1 is 2^9 or 2^10, tiles of four or eight columns in passes A and C.
-static int log_l1(const FastKnobs& kn, int64_t N) {
+// Tile schedules the autotuner tries for a group of nc components: the defaults first, then both
+// splits of 2N = L1 L2, two or four rows per pass-B tile, both tile orders, one to three streams,
+// and the narrow tiles of passes A and C where they differ from the wide ones.
+static int log_l1(const FastKnobs& kn, int64_t N, int* logL2) {
   int s = 0;
   while ((int64_t(1) << s) < 2 * N) ++s;
-  return kn.split == 0 ? s - (s + 1) / 2 : (s + 1) / 2;
+  const int l1 = kn.split == 0 ? s - (s + 1) / 2 : (s + 1) / 2;
+  *logL2 = s - l1;
+  return l1;
 }
 
-static std::vector<FastKnobs> tune_candidates(const FastKnobs& base, int64_t N) {
+template <typename T>
+static std::vector<FastKnobs> tune_candidates(const FastKnobs& base, int64_t N, int nc) {
   std::vector<FastKnobs> c{base};
   for (int split = 0; split < 2; ++split)
     for (int tb = 2; tb <= 4; tb += 2)
@@ -1540,8 +1545,9 @@ static std::vector<FastKnobs> tune_candidates(const FastKnobs& base, int64_t N) 
             k.narrow = nw;
             FastKnobs k0 = k;
             k0.narrow = 0;
-            const int l1 = log_l1(k, N);
-            if (nw && fixed_logw<double>(k, l1, 0, 0) == fixed_logw<double>(k0, l1, 0, 0)) continue;   // no effect at this size
+            int l2;
+            const int l1 = log_l1(k, N, &l2);
+            if (nw && fixed_logw<T>(k, l1, l2, nc) == fixed_logw<T>(k0, l1, l2, nc)) continue;   // no effect here
             if (k.split != base.split || k.tb != base.tb || k.xcd != base.xcd || k.streams != base.streams ||
                 k.narrow != base.narrow)
               c.push_back(k);
@@ -1557,7 +1563,7 @@ static std::vector<FastKnobs> tune_candidates(const FastKnobs& base, int64_t N) 
 template <typename T>
 hipError_t fast_product(birk_plan* p, const FastGroup& g, const T* v, T* out, int transpose, hipStream_t s) {
   const int S = std::min(std::min(g.kn.streams, g.nc), 1 + birk_plan::kExtraStreams);
-  if (S < 2 || !p->xstream[0]) return fast_passes<T>(p, g, v, out, transpose, s);
+  if (S < 2 || !p->xstream[0]) return fast_passes<T>(p, g, g.nc, v, out, transpose, s);
   int logL1, logL2, WA, TB, WC;
   fast_shape<T>(g.kn, g.N, logL1, logL2, WA, TB, WC);
   const int64_t gcomp = (int64_t)((1 << logL1) / 2 + 1) * ((1 << logL2) / 2 + 1);
@@ -1572,11 +1578,11 @@ hipError_t fast_product(birk_plan* p, const FastGroup& g, const T* v, T* out, in
     part.work_off = g.work_off + (int64_t)c0 * gcomp;
     part.part_off = g.part_off + (int64_t)c0 * ntB;
     if (k == 0) {
-      e = fast_passes<T>(p, part, v, out, transpose, s);
+      e = fast_passes<T>(p, part, g.nc, v, out, transpose, s);
     } else {
       hipStream_t x = p->xstream[k - 1];
       e = hipStreamWaitEvent(x, p->ev_fork, 0);
-      if (e == hipSuccess) e = fast_passes<T>(p, part, v, out, transpose, x);
+      if (e == hipSuccess) e = fast_passes<T>(p, part, g.nc, v, out, transpose, x);
       if (e == hipSuccess) e = hipEventRecord(p->ev_join[k - 1], x);
     }
     c0 = c1;
@@ -1590,7 +1596,7 @@ hipError_t fast_product(birk_plan* p, const FastGroup& g, const T* v, T* out, in
 // autotuner may choose.
 void fast_sizes(const birk_plan* p, int64_t N, int nc, int64_t* work, int64_t* part) {
   int64_t w = 0, ntB = 0;
-  for (const FastKnobs& kn : tune_candidates(p->fast_kn, N)) {
+  for (const FastKnobs& kn : tune_candidates<double>(p->fast_kn, N, nc)) {   // (narrow tiles need no more)
     int l1, l2, wa, tb, wc;
     fast_shape<double>(kn, N, l1, l2, wa, tb, wc);
     w = std::max(w, (int64_t)nc * ((int64_t(1) << l1) / 2 + 1) * ((int64_t(1) << l2) / 2 + 1));
@@ -1623,7 +1629,7 @@ static hipError_t tune_groups(birk_plan* p, hipStream_t s, std::string* report) 
   char line[160];
   for (FastGroup& g : p->fgroups) {
     if (e != hipSuccess) break;
-    const std::vector<FastKnobs> cand = tune_candidates(p->fast_kn, g.N);
+    const std::vector<FastKnobs> cand = tune_candidates<T>(p->fast_kn, g.N, g.nc);
     std::vector<float> best_of(cand.size(), 0.0f);
     for (int round = 0; round < kTuneRounds && e == hipSuccess; ++round) {
       for (size_t ci = 0; ci < cand.size() && e == hipSuccess; ++ci) {

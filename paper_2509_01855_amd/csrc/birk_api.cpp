@@ -248,6 +248,9 @@ birk_status birk_plan_create(birk_plan** out, int32_t batch, const int64_t* n_no
     if (nw) p->fast_kn.narrow = std::atoi(nw) ? 1 : 0;
     const char* b3 = std::getenv("BIRK_FAST_B3");
     if (b3) p->fast_kn.b3 = std::atoi(b3) ? 1 : 0;
+    // two-step split of the chirp convolutions whose lengths allow it (testing aid)
+    const char* bs = std::getenv("BIRK_BLU_SPLIT");
+    if (bs) p->blu_split = std::max(0, std::min(kLdsMaxLog, std::atoi(bs)));
     const char* st = std::getenv("BIRK_FAST_STREAMS");
     if (st) p->fast_kn.streams = std::max(1, std::min(1 + birk_plan::kExtraStreams, std::atoi(st)));
   }

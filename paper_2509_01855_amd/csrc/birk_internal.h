@@ -248,6 +248,7 @@ struct birk_plan {
   double* comp_part = nullptr;      // per-component reduction partials (CompDesc::part)
   int use_fast = 1;               // power-of-two N takes the three-pass path
   birk::FastKnobs fast_kn;        // default tile schedule of the three-pass groups
+  int blu_split = 0;              // nominal log2 M1 of the chirp convolutions (0: by length)
   // HIP graphs of the products (birk_plan_set_graphs), per (direction, input, output)
   struct GraphSlot {
     int transpose;

@@ -703,23 +703,32 @@ static hipError_t finalize_set(birk_plan* p, PairSet& ps) {
 // tile lists; the products change only in rounding order.
 static hipError_t set_blu_split(birk_plan* p, int cls, const std::vector<int>& xs, hipStream_t s) {
   PairSet& ps = p->gen[1];
-  hipError_t e = hipStreamSynchronize(s);   // the lists in use are freed
-  PairSet fs;
+  hipError_t e = hipStreamSynchronize(s);   // the lists in use are freed below
+  if (e != hipSuccess) return e;
+  // the new lists are built next to the old ones, which stay if an allocation fails
+  PairSet next = ps, fs;
+  next.dev = nullptr;
+  next.tiles_c4 = next.tiles_r4 = nullptr;
   std::vector<int64_t> seen;
-  for (size_t q = 0; q < ps.host.size(); ++q) {
-    PairDesc& d = ps.host[q];
+  for (size_t q = 0; q < next.host.size(); ++q) {
+    PairDesc& d = next.host[q];
     if (d.cls != cls) continue;
     blu_set_split(d, xs[q]);
     if (std::find(seen.begin(), seen.end(), d.N) != seen.end()) continue;
     seen.push_back(d.N);
     fs.host.push_back(d);
   }
-  blu_free_lists(p, ps);
+  e = blu_lists(p, next);
   if (e == hipSuccess) e = blu_lists(p, fs);
   if (e == hipSuccess) e = blu_filters(p, fs, s);
   blu_free_lists(p, fs);
-  if (e == hipSuccess) e = blu_lists(p, ps);
-  return e;
+  if (e != hipSuccess) {
+    blu_free_lists(p, next);
+    return e;
+  }
+  blu_free_lists(p, ps);
+  ps = next;
+  return hipSuccess;
 }
 
 template <typename T>

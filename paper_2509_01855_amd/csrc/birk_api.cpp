@@ -585,7 +585,7 @@ hipError_t ensure_krylov(birk_plan* p, int m, size_t esize) {
   if (e == hipSuccess && !p->krylov_gm) e = hipMalloc(&p->krylov_gm, B * kGmStride * sizeof(double));
   if (e == hipSuccess && !p->krylov_prm) e = hipMalloc(&p->krylov_prm, 6 * B * sizeof(double));
   if (e != hipSuccess) return e;
-  if (p->krylov_Q && p->krylov_m >= m) return hipSuccess;
+  if (p->krylov_m >= m) return hipSuccess;
   // recorded Arnoldi chunks hold the old buffers' addresses
   for (auto& g : p->kgraphs)
     if (g.exec) (void)hipGraphExecDestroy(g.exec);
@@ -593,6 +593,7 @@ hipError_t ensure_krylov(birk_plan* p, int m, size_t esize) {
   if (p->krylov_Q) (void)hipFree(p->krylov_Q);
   if (p->krylov_vec) (void)hipFree(p->krylov_vec);
   p->krylov_Q = p->krylov_vec = nullptr;
+  p->krylov_m = 0;   // nothing held until both allocations have succeeded
   // sized for double so that one allocation serves either Krylov precision
   (void)esize;
   // Q: m + 1 basis vectors; Z: m preconditioned vectors z_j = P^{-1} q_j (kept so the

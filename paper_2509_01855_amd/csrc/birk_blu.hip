@@ -14,7 +14,7 @@
 //
 // M is the smallest of 4, 5, 6, 8 times a power of two that is >= 4N: M1 = R 2^A with
 // R = 1, 3, 5, the factor R taken as R interleaved transforms of length 2^A and one
-// butterfly at the output.
+// butterfly at the output (short double-float convolutions leave R = 5 out, see blu_length).
 //
 //   columns:   even input (components, or the stencil of the first DCT's Y) x chirp,
 //              FFT over n1, twiddle                                   -> G
@@ -85,27 +85,31 @@ __device__ __forceinline__ cplx<T> get(const T* sm, int t, int n) {
   return fast::mk<T>(sm[2 * t * LD + fast::pad(n)], sm[(2 * t + 1) * LD + fast::pad(n)]);
 }
 
-// X_j = sum_s g_s exp(-2 pi i s j / R) in place.
+// X_j = sum_s g_s exp(-2 pi i s j / R) in place.  R = 5: cos(2 pi / 5), cos(4 pi / 5) =
+// -1/4 +- sqrt(5)/4.
 template <typename T, int R>
 __device__ __forceinline__ void dft_odd(cplx<T> (&g)[R]) {
   auto add = [](cplx<T> a, cplx<T> b) { return fast::mk<T>(a.x + b.x, a.y + b.y); };
   auto sub = [](cplx<T> a, cplx<T> b) { return fast::mk<T>(a.x - b.x, a.y - b.y); };
   if constexpr (R == 3) {
-    const T h = T(0.5), s = T(0.86602540378443864676);
+    const T s = T(0.86602540378443864676);
     const cplx<T> t = add(g[1], g[2]), u = sub(g[1], g[2]);
-    const cplx<T> m = fast::mk<T>(g[0].x - h * t.x, g[0].y - h * t.y);
+    const cplx<T> m = fast::mk<T>(g[0].x - pow2_times(0.5f, t.x), g[0].y - pow2_times(0.5f, t.y));
+    const cplx<T> su = fast::mk<T>(s * u.x, s * u.y);
     g[0] = add(g[0], t);
-    g[1] = fast::mk<T>(m.x + s * u.y, m.y - s * u.x);
-    g[2] = fast::mk<T>(m.x - s * u.y, m.y + s * u.x);
+    g[1] = fast::mk<T>(m.x + su.y, m.y - su.x);
+    g[2] = fast::mk<T>(m.x - su.y, m.y + su.x);
   } else if constexpr (R == 5) {
-    const T c1 = T(0.30901699437494742410), c2 = T(-0.80901699437494742410);
+    const T q = T(0.55901699437494742410);   // sqrt(5)/4
     const T s1 = T(0.95105651629515357212), s2 = T(0.58778525229247312917);
     const cplx<T> t1 = add(g[1], g[4]), t2 = add(g[2], g[3]), u1 = sub(g[1], g[4]), u2 = sub(g[2], g[3]);
-    const cplx<T> m1 = fast::mk<T>(g[0].x + c1 * t1.x + c2 * t2.x, g[0].y + c1 * t1.y + c2 * t2.y);
-    const cplx<T> m2 = fast::mk<T>(g[0].x + c2 * t1.x + c1 * t2.x, g[0].y + c2 * t1.y + c1 * t2.y);
+    const cplx<T> t = add(t1, t2), v = sub(t1, t2);
+    const cplx<T> m = fast::mk<T>(g[0].x - pow2_times(0.25f, t.x), g[0].y - pow2_times(0.25f, t.y));
+    const cplx<T> qv = fast::mk<T>(q * v.x, q * v.y);
+    const cplx<T> m1 = add(m, qv), m2 = sub(m, qv);
     const cplx<T> n1 = fast::mk<T>(s1 * u1.x + s2 * u2.x, s1 * u1.y + s2 * u2.y);
     const cplx<T> n2 = fast::mk<T>(s2 * u1.x - s1 * u2.x, s2 * u1.y - s1 * u2.y);
-    g[0] = add(g[0], add(t1, t2));
+    g[0] = add(g[0], t);
     g[1] = fast::mk<T>(m1.x + n1.y, m1.y - n1.x);
     g[4] = fast::mk<T>(m1.x - n1.y, m1.y + n1.x);
     g[2] = fast::mk<T>(m2.x + n2.y, m2.y - n2.x);
@@ -153,8 +157,8 @@ __device__ __forceinline__ void load_cols(const PairDesc& d, const T* __restrict
   };
   // x chirp, half weight at n = +-N (both are in the sum), zero outside
   auto finish = [&](int k, cplx<T> v, cplx<T> c) {
-    const T h = k == N ? T(0.5) : T(1);
-    const cplx<T> r = fast::cmul<T>(fast::mk<T>(v.x * h, v.y * h), c);
+    const float h = k == N ? 0.5f : 1.0f;
+    const cplx<T> r = fast::cmul<T>(fast::mk<T>(pow2_times(h, v.x), pow2_times(h, v.y)), c);
     return k >= 0 ? r : fast::mk<T>(T(0), T(0));
   };
   if (src <= kSrcVT) {
@@ -173,8 +177,8 @@ __device__ __forceinline__ void load_cols(const PairDesc& d, const T* __restrict
     for (int i = 0; i < kPPT; ++i) {
       const int k = entry(i);
       // E^{-1} of the transpose: ends doubled
-      const T e = (src == kSrcVT && (k == 0 || k == N)) ? T(2) : T(1);
-      store(i, finish(k, fast::mk<T>(e * va[i], d.has2 ? e * vb[i] : T(0)), c[i]));
+      const float e = (src == kSrcVT && (k == 0 || k == N)) ? 2.0f : 1.0f;
+      store(i, finish(k, fast::mk<T>(pow2_times(e, va[i]), d.has2 ? pow2_times(e, vb[i]) : T(0)), c[i]));
     }
   } else if (src != kSrcFilter) {
     constexpr int HB = kPPT / 2;
@@ -216,16 +220,26 @@ __device__ __forceinline__ void load_cols(const PairDesc& d, const T* __restrict
   }
 }
 
+// Twiddles are stepped in double (a tenth of the operations of a double-float product) and
+// rounded to T where they are used; the powers that join the residues are formed in T, or in
+// double for double-floats.
+template <typename T>
+using Pow = std::conditional_t<std::is_floating_point<T>::value, T, double>;
+template <typename T, typename C>
+__device__ __forceinline__ cplx<T> to(C a) {
+  return fast::mk<T>((T)a.x, (T)a.y);
+}
+
 // The R outputs k + j 2^A of item (w, k): residues x W_M1^(s k), one R-point butterfly.
 template <typename T, int R, int A>
-__device__ __forceinline__ void join_residues(const T* sm, int w, int k, cplx<T> q, cplx<T> (&g)[R]) {
-  cplx<T> p = q;
+__device__ __forceinline__ void join_residues(const T* sm, int w, int k, cplx<Pow<T>> q, cplx<T> (&g)[R]) {
+  cplx<Pow<T>> p = q;
 #pragma unroll
   for (int s = 0; s < R; ++s) {
     g[s] = get<T, A>(sm, w * R + s, k);
     if (s > 0) {
-      g[s] = fast::cmul<T>(g[s], p);
-      if (s + 1 < R) p = fast::cmul<T>(p, q);
+      g[s] = fast::cmul<T>(g[s], to<T>(p));
+      if (s + 1 < R) p = fast::cmul<Pow<T>>(p, q);
     }
   }
   if constexpr (R > 1) dft_odd<T, R>(g);
@@ -235,10 +249,8 @@ __device__ __forceinline__ void join_residues(const T* sm, int w, int k, cplx<T>
 template <typename T, int R, int A>
 __device__ __forceinline__ void cols_body(const T* __restrict__ x, const cplx<T>* __restrict__ Y, cplx<T>* __restrict__ G, const PairDesc& d, int ty, int src,
                                           const cplx<T>* __restrict__ tw, T* sm) {
-  constexpr int pi = prec_index<T>();
   constexpr int LOGW = log_sub(R, A) - A, W = 1 << LOGW, NT = (R << log_sub(R, A)) / kPPT;
   constexpr int M1 = R << A, NI = ((1 << log_sub(R, A)) + NT - 1) / NT, S = NT >> LOGW;
-  constexpr bool kStep = std::is_floating_point<T>::value;   // twiddles stepped in double
   const int t = (int)threadIdx.x;
   const bool on = t < NT;
   const int b = d.logM2, h = 1 << (b - 1);
@@ -248,23 +260,20 @@ __device__ __forceinline__ void cols_body(const T* __restrict__ x, const cplx<T>
   const int w = t & (W - 1), k0 = t >> LOGW, n2 = c0 + w;
   // phase = W_M^(n2 k), stepped from item to item; stp = W_M^(n2 2^A); wrap = W_M2^(-n2)
   // (k1 - M1 for k1); q = W_M1^k
-  using P = std::conditional_t<kStep, double, T>;
-  constexpr int pp = prec_index<P>();
-  const cplx<P>* thi = (const cplx<P>*)d.thi[pp];
-  const cplx<P>* tlo = (const cplx<P>*)d.tlo[pp];
+  using P = double;
+  const cplx<P>* thi = (const cplx<P>*)d.thi[0];
+  const cplx<P>* tlo = (const cplx<P>*)d.tlo[0];
   const int sh = d.tw_shift;
   cplx<P> phase, dphase, stp, wrap, q, dq;
   if (on) {
     load_cols<T, R, A>(d, x, Y, src, c0, nw, sm);
-    if constexpr (kStep) {
-      phase = tw_at<P>(thi, tlo, sh, (int64_t)n2 * k0, false);
-      dphase = tw_at<P>(thi, tlo, sh, (int64_t)n2 * S, false);
-      wrap = tw_at<P>(thi, tlo, sh, (int64_t)n2 * M1, true);
-      if constexpr (R > 1) {
-        stp = tw_at<P>(thi, tlo, sh, (int64_t)n2 << A, false);
-        q = tw_at<P>(thi, tlo, sh, (int64_t)k0 << b, false);
-        dq = tw_at<P>(thi, tlo, sh, (int64_t)S << b, false);
-      }
+    phase = tw_at<P>(thi, tlo, sh, (int64_t)n2 * k0, false);
+    dphase = tw_at<P>(thi, tlo, sh, (int64_t)n2 * S, false);
+    wrap = tw_at<P>(thi, tlo, sh, (int64_t)n2 * M1, true);
+    if constexpr (R > 1) {
+      stp = tw_at<P>(thi, tlo, sh, (int64_t)n2 << A, false);
+      q = tw_at<P>(thi, tlo, sh, (int64_t)k0 << b, false);
+      dq = tw_at<P>(thi, tlo, sh, (int64_t)S << b, false);
     }
   }
   __syncthreads();
@@ -276,30 +285,20 @@ __device__ __forceinline__ void cols_body(const T* __restrict__ x, const cplx<T>
     const int k = k0 + it * S;
     if (k < (1 << A) && w < nw) {
       cplx<T> g[R];
-      cplx<T> qt = fast::mk<T>(T(0), T(0));
-      if constexpr (R > 1) {
-        if constexpr (kStep) qt = fast::mk<T>((T)q.x, (T)q.y);
-        else qt = tw_at<T>(thi, tlo, sh, (int64_t)k << b, false);
-      }
+      cplx<Pow<T>> qt = to<Pow<T>>(fast::mk<P>(0.0, 0.0));
+      if constexpr (R > 1) qt = to<Pow<T>>(q);
       join_residues<T, R, A>(sm, w, k, qt, g);
       cplx<P> p = phase;
 #pragma unroll
       for (int j = 0; j < R; ++j) {
         const int k1 = k + (j << A);
-        const bool up = 2 * k1 > M1;
-        if constexpr (kStep) {
-          const cplx<P> f = up ? fast::cmul<P>(p, wrap) : p;
-          store(k1, fast::cmul<T>(g[j], fast::mk<T>((T)f.x, (T)f.y)));
-          if (j + 1 < R) p = fast::cmul<P>(p, stp);
-        } else {
-          store(k1, fast::cmul<T>(g[j], tw_at<T>(thi, tlo, sh, (int64_t)n2 * (up ? M1 - k1 : k1), up)));
-        }
+        const cplx<P> f = 2 * k1 > M1 ? fast::cmul<P>(p, wrap) : p;
+        store(k1, fast::cmul<T>(g[j], to<T>(f)));
+        if (j + 1 < R) p = fast::cmul<P>(p, stp);
       }
     }
-    if constexpr (kStep) {
-      phase = fast::cmul<P>(phase, dphase);
-      if constexpr (R > 1) q = fast::cmul<P>(q, dq);
-    }
+    phase = fast::cmul<P>(phase, dphase);
+    if constexpr (R > 1) q = fast::cmul<P>(q, dq);
   }
 }
 
@@ -314,7 +313,6 @@ __device__ __forceinline__ void icols_body(const cplx<T>* __restrict__ G,
   constexpr int pi = prec_index<T>();
   constexpr int LOGW = log_sub(R, A) - A, W = 1 << LOGW, NT = (R << log_sub(R, A)) / kPPT;
   constexpr int NI = ((1 << log_sub(R, A)) + NT - 1) / NT, S = NT >> LOGW;
-  constexpr bool kStep = std::is_floating_point<T>::value;
   const int t = (int)threadIdx.x;
   const bool on = t < NT;
   const int N = (int)d.N, M = (int)d.M, b = d.logM2, h = 1 << (b - 1);
@@ -323,10 +321,9 @@ __device__ __forceinline__ void icols_body(const cplx<T>* __restrict__ G,
   const int nw = last ? 1 : min(W, h - c0);
   const int w = t & (W - 1), k0 = t >> LOGW, n2 = c0 + w;
   const cplx<T>* chirp = (const cplx<T>*)d.chirp[pi];
-  using P = std::conditional_t<kStep, double, T>;
-  constexpr int pp = prec_index<P>();
-  const cplx<P>* thi = (const cplx<P>*)d.thi[pp];
-  const cplx<P>* tlo = (const cplx<P>*)d.tlo[pp];
+  using P = double;
+  const cplx<P>* thi = (const cplx<P>*)d.thi[0];
+  const cplx<P>* tlo = (const cplx<P>*)d.tlo[0];
   const int sh = d.tw_shift;
   cplx<P> q, dq;
   auto index = [&](int n1) {   // output k of position n1, or -1
@@ -348,7 +345,7 @@ __device__ __forceinline__ void icols_body(const cplx<T>* __restrict__ G,
         const int k = k0 + it * S;
         cv[it * R + j] = chirp[k < (1 << A) ? max(index(k + (j << A)), 0) : 0];
       }
-    if constexpr (R > 1 && kStep) {
+    if constexpr (R > 1) {
       q = tw_at<P>(thi, tlo, sh, (int64_t)k0 << b, false);
       dq = tw_at<P>(thi, tlo, sh, (int64_t)S << b, false);
     }
@@ -394,11 +391,8 @@ __device__ __forceinline__ void icols_body(const cplx<T>* __restrict__ G,
       const int k = k0 + it * S;
       if (k < (1 << A) && w < nw) {
         cplx<T> g[R];
-        cplx<T> qt = fast::mk<T>(T(0), T(0));
-        if constexpr (R > 1) {
-          if constexpr (kStep) qt = fast::mk<T>((T)q.x, (T)q.y);
-          else qt = tw_at<T>(thi, tlo, sh, (int64_t)k << b, false);
-        }
+        cplx<Pow<T>> qt = to<Pow<T>>(fast::mk<P>(0.0, 0.0));
+        if constexpr (R > 1) qt = to<Pow<T>>(q);
         join_residues<T, R, A>(sm, w, k, qt, g);
 #pragma unroll
         for (int j = 0; j < R; ++j) {
@@ -419,7 +413,7 @@ __device__ __forceinline__ void icols_body(const cplx<T>* __restrict__ G,
           }
         }
       }
-      if constexpr (R > 1 && kStep) q = fast::cmul<P>(q, dq);
+      if constexpr (R > 1) q = fast::cmul<P>(q, dq);
     }
   }
   if (!FIN && !trans) {
@@ -451,7 +445,6 @@ __device__ __forceinline__ void rows_body(cplx<T>* __restrict__ G, cplx<T>* __re
   constexpr int pi = prec_index<T>();
   constexpr int LOGP = B > kLogRows ? B : kLogRows;
   constexpr int M2 = 1 << B, h = M2 / 2, hs = row_stride(h), W = 1 << (LOGP - B), NT = (1 << LOGP) / kPPT;
-  constexpr bool kStep = std::is_floating_point<T>::value;
   const int t = (int)threadIdx.x;
   const bool on = t < NT;
   const int M1 = (int)d.M >> B, h1 = M1 / 2, r0 = ty * W;
@@ -496,10 +489,9 @@ __device__ __forceinline__ void rows_body(cplx<T>* __restrict__ G, cplx<T>* __re
   // twiddles W_M^(mu k1) of the outputs, mu = -n2 up to M2/2 and M2 - n2 above: a thread's
   // outputs step through k1 (rows of at most NT points) or through n2 (longer rows: a base
   // for each half)
-  using P = std::conditional_t<kStep, double, T>;
-  constexpr int pp = prec_index<P>();
-  const cplx<P>* thi = (const cplx<P>*)d.thi[pp];
-  const cplx<P>* tlo = (const cplx<P>*)d.tlo[pp];
+  using P = double;
+  const cplx<P>* thi = (const cplx<P>*)d.thi[0];
+  const cplx<P>* tlo = (const cplx<P>*)d.tlo[0];
   const int sh = d.tw_shift;
   auto twid = [&](int64_t mu, int64_t k1) {
     const int64_t p = mu * k1;
@@ -519,22 +511,15 @@ __device__ __forceinline__ void rows_body(cplx<T>* __restrict__ G, cplx<T>* __re
   // row k1 up to M2/2; row -k1 from there on, and its column 0
   auto store = [&](int k1, int n2, cplx<P> f) {
     const cplx<T> z = fast::conjg<T>(get<T, B>(sm, k1 - r0, n2));
-    const cplx<T> r = fast::cmul<T>(z, fast::mk<T>((T)f.x, (T)f.y));
+    const cplx<T> r = fast::cmul<T>(z, to<T>(f));
     const bool twin = k1 > 0 && k1 < h1;
     if (n2 <= h) G[k1 * hs + n2] = r;
     if (!twin) return;
     if (n2 > h) G[(M1 - k1) * hs + (M2 - n2)] = r;
-    else if (n2 == h) G[(M1 - k1) * hs + h] = fast::cmul<T>(z, fast::mk<T>((T)f.x, -(T)f.y));
+    else if (n2 == h) G[(M1 - k1) * hs + h] = fast::cmul<T>(z, to<T>(fast::conjg<P>(f)));
     else if (n2 == 0) G[(M1 - k1) * hs] = r;   // no twiddle
   };
-  if constexpr (!kStep) {
-#pragma unroll
-    for (int i = 0; i < kPPT; ++i) {
-      const int e = t + i * NT;
-      const int k1 = r0 + (e >> B), n2 = e & (M2 - 1);
-      if (k1 <= h1) store(k1, n2, twid(n2 <= h ? -n2 : M2 - n2, k1));
-    }
-  } else if constexpr (M2 <= NT) {
+  if constexpr (M2 <= NT) {
     constexpr int S = NT / M2;   // rows between a thread's elements
     const int n2 = t & (M2 - 1), w0 = t >> B;
     const int mu = n2 <= h ? -n2 : M2 - n2;
@@ -668,11 +653,16 @@ constexpr int lds_rows_most() {
 
 }  // namespace
 
-// Length and default split of a pair: M = R 2^m, M1 = R 2^A, M2 = 2^(m - A).
-void blu_length(PairDesc& d) {
+// Length of a pair: M = R 2^m, M1 = R 2^A, M2 = 2^(m - A).  Double-float plans leave R = 5 out up
+// to N = 2^14: their five-point butterflies cost more there than the longer M (N = 2499, one,
+// 32 and 128 instances of six components: 128, 185 and 385 us with R = 5, 121, 134 and 370 with
+// R = 3; N = 9999: one 140 against 116, eight 130 against 138, 32 372 against 335; but N = 39999,
+// four 197 against 237, and N = 299999, two 744 against 838).
+void blu_length(PairDesc& d, birk_precision prec) {
   const int64_t need = 4 * d.N;
   int64_t best = 0;
   for (int R : {1, 3, 5}) {
+    if (R == 5 && prec == BIRK_DF32 && d.N <= (1 << 14)) continue;
     int m = 0;
     while (((int64_t)R << m) < need) ++m;
     if (best == 0 || ((int64_t)R << m) < best) {

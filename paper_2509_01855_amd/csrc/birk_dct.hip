@@ -521,8 +521,7 @@ static int ilog2_ceil(int64_t x) {
 // Twiddle tables of length M (1, 3 or 5 times a power of two): W^t = hi[t >> shift] lo[...].
 static int tw_shift_of(int64_t M) { return std::min((ilog2_ceil(M) + 1) / 2, __builtin_ctzll(M)); }
 
-// split: nominal log2 M1 of the chirp convolutions whose lengths allow it (0: the default)
-static PairDesc make_pair(int64_t src, int64_t Nn, int has2, int split) {
+static PairDesc make_pair(const birk_plan* p, int64_t src, int64_t Nn, int has2) {
   PairDesc d;
   d.src = src;
   d.Nn = Nn;
@@ -538,8 +537,8 @@ static PairDesc make_pair(int64_t src, int64_t Nn, int has2, int split) {
       d.logM1 = (d.logM + 1) / 2;
       d.logM2 = d.logM - d.logM1;
     } else {
-      blu_length(d);
-      blu_set_split(d, split && blu_split_ok(d, split) ? split : blu_default_split(d));
+      blu_length(d, p->prec);
+      blu_set_split(d, p->blu_split && blu_split_ok(d, p->blu_split) ? p->blu_split : blu_default_split(d));
     }
     d.tw_shift = tw_shift_of(d.M);
   }
@@ -620,7 +619,7 @@ void plan_products(birk_plan* p) {
     }
     const int np = (in.nx + 1) / 2;
     for (int q = 0; q < np; ++q) {
-      PairDesc d = make_pair(in.off + 2 * (int64_t)q * in.Nn, in.Nn, 2 * q + 1 < in.nx, p->blu_split);
+      PairDesc d = make_pair(p, in.off + 2 * (int64_t)q * in.Nn, in.Nn, 2 * q + 1 < in.nx);
       const int chirp = d.L == d.slot && d.L > 4 ? 0 : 1;
       p->noalloc_nbuf = 3;
       if (d.cls > kLdsMaxLog) {

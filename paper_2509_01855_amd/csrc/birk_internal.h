@@ -294,7 +294,7 @@ hipError_t upload_raw(birk_plan* p, const void* h, size_t bytes, void** d);
 // ---- chirp convolutions beyond one workgroup (birk_blu.hip) ----
 // R and logM of the pair's convolution length; its two-step split from the nominal log2 M1
 // x (and back); whether the kernels cover x; the split a pair starts with.
-void blu_length(PairDesc& d);
+void blu_length(PairDesc& d, birk_precision prec);
 void blu_set_split(PairDesc& d, int x);
 int blu_split(const PairDesc& d);
 bool blu_split_ok(const PairDesc& d, int x);

@@ -14,19 +14,27 @@
 namespace birk {
 
 // Reciprocal of a positive integer-valued x: in double the hardware estimate refined by two
-// Newton steps (within an ulp of 1/x, several times cheaper than a division); a plain
-// division for the other storage types.
+// Newton steps (within an ulp of 1/x, several times cheaper than a division), which double-floats
+// take too (their own division is two float divisions and a correction); a plain division for
+// float.
 template <typename T>
 __device__ __forceinline__ T recip_int(T x) {
   return T(1) / x;
 }
 template <>
 __device__ __forceinline__ double recip_int<double>(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = __builtin_fma(-x, r, 1.0);
-  r = __builtin_fma(r, e, r);
-  e = __builtin_fma(-x, r, 1.0);
-  return __builtin_fma(r, e, r);
+  return recip(x);
+}
+template <>
+__device__ __forceinline__ df32 recip_int<df32>(df32 x) {
+  return df32(recip((double)x));
+}
+
+// p a for p a power of two: exact, and for double-floats two products instead of a rounded one.
+template <typename T>
+__device__ __forceinline__ T pow2_times(float p, T a) {
+  if constexpr (std::is_floating_point<T>::value) return T(p) * a;
+  else return T(p * a.hi, p * a.lo);
 }
 
 // d_k for 1 <= k <= N from Y_{k-1} and Y_{k+1} (Yp is not used at k = N):
@@ -37,8 +45,8 @@ struct FwdStencil {
   __device__ __forceinline__ FwdStencil(int k, int N, T invN, T inv4N1) {
     i2k = recip_int<T>(T(2 * k));   // 1/(2k); at k = 1 also e_0 = 1/2
     cp = T(0);
-    if (k < N) cp = (k + 1 == N) ? T(0.5) * i2k - inv4N1 : i2k;
-    sc = (k == N) ? T(2) * invN : invN;
+    if (k < N) cp = (k + 1 == N) ? pow2_times(0.5f, i2k) - inv4N1 : i2k;
+    sc = pow2_times(k == N ? 2.0f : 1.0f, invN);
   }
   __device__ __forceinline__ T operator()(T Ym, T Yp) const { return (cp * Yp - i2k * Ym) * sc; }
 };
@@ -63,10 +71,9 @@ struct TrStencil {
   T cm, cp, c0;
   int j;
   __device__ __forceinline__ TrStencil(int j_, int N, T inv2N1) : j(j_) {
-    const T h = T(0.5);
     const T rm = recip_int<T>(T(max(j, 2) - 1)), rp = recip_int<T>(T(j + 1));
-    cm = h * rm;
-    cp = h * rp;
+    cm = pow2_times(0.5f, rm);
+    cp = pow2_times(0.5f, rp);
     if (j == N) {
       cm -= inv2N1;
       cp = T(0);
@@ -74,10 +81,8 @@ struct TrStencil {
     c0 = rm * rp;
   }
   __device__ __forceinline__ T operator()(T Y0, T Ym, T Yp) const {
-    const T h = T(0.5);
-    if (j == 0) return h * (Y0 - Yp);
-    if (j == 1) return T(0.125) * (Y0 - Yp);
-    return h * (cm * Ym - cp * Yp - c0 * Y0);
+    if (j < 2) return pow2_times(j == 0 ? 0.5f : 0.125f, Y0 - Yp);
+    return pow2_times(0.5f, cm * Ym - cp * Yp - c0 * Y0);
   }
 };
 template <typename T>

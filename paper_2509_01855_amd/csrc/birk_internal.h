@@ -13,6 +13,8 @@
 
 namespace birk {
 
+constexpr int kCus = 256;   // compute units
+
 // Longest transform a single workgroup performs in LDS (complex elements).
 constexpr int kLdsMaxLog = 12;
 constexpr int kLdsMax = 1 << kLdsMaxLog;
@@ -152,6 +154,7 @@ struct LdsSet {
   PairDesc* dev = nullptr;
   int2* tiles = nullptr;
   int ntiles = 0;
+  int nlong = 0;      // of them, at the end, those of the longest length
   int threads = 0;    // workgroup size: an eighth of the longest length, at least one wave
   int lds_reals = 0;  // dynamic LDS of a workgroup
 };

@@ -52,8 +52,9 @@ __device__ __forceinline__ cplx<T> get(const T* sm, int t, int n) {
 
 // The pairs [tile.x, tile.x + tile.y) of one length M = 2^LOGM: one pair from M = 512 on, up
 // to 512 / M below; CHIRP: Bluestein.  NT threads work, any others only keep the barriers.
+// HOLD: chirp and filter stay in registers between their uses, else they are read again.
 // sm: 8 NT complex values in split padded rows; red: the c^_0 partial sums.
-template <typename T, int LOGM, bool CHIRP>
+template <typename T, int LOGM, bool CHIRP, bool HOLD>
 __device__ __forceinline__ void lds_product(const T* __restrict__ x, T* __restrict__ out,
                                             const PairDesc* __restrict__ pd, int2 tile,
                                             const cplx<T>* __restrict__ tw, int trans, T* sm, double* red) {
@@ -73,6 +74,28 @@ __device__ __forceinline__ void lds_product(const T* __restrict__ x, T* __restri
   };
   auto desc = [&](int t) -> const PairDesc& { return pd[tile.x + (COUNT > 1 ? min(t, tile.y - 1) : 0)]; };
   cplx<T> v[kPPT], fv[CHIRP ? kPPT : 1], cv[CHIRP ? kPPT : 1];
+  auto load_chirp = [&] {
+    if constexpr (CHIRP) {
+#pragma unroll
+      for (int i = 0; i < kPPT; ++i) {
+        int t, n;
+        where(i, t, n);
+        const PairDesc& d = desc(t);
+        const int N = (int)d.N, L = 2 * N;
+        cv[i] = ((const cplx<T>*)d.chirp[pi])[n <= N ? n : n < L ? L - n : 0];
+      }
+    }
+  };
+  auto load_filter = [&] {
+    if constexpr (CHIRP) {
+#pragma unroll
+      for (int i = 0; i < kPPT; ++i) {
+        int t, n;
+        where(i, t, n);
+        fv[i] = ((const cplx<T>*)desc(t).filt[pi])[n];
+      }
+    }
+  };
   if (on) {
     // every load of the thread from a valid address, none behind a branch
     T va[kPPT], vb[kPPT];
@@ -86,11 +109,9 @@ __device__ __forceinline__ void lds_product(const T* __restrict__ x, T* __restri
       const T* xa = x + d.src;
       va[i] = xa[k];
       vb[i] = xa[(d.has2 ? d.Nn : 0) + k];
-      if constexpr (CHIRP) {
-        cv[i] = ((const cplx<T>*)d.chirp[pi])[k];
-        fv[i] = ((const cplx<T>*)d.filt[pi])[n];
-      }
     }
+    load_chirp();
+    if (HOLD) load_filter();
 #pragma unroll
     for (int i = 0; i < kPPT; ++i) {
       int t, n;
@@ -104,6 +125,7 @@ __device__ __forceinline__ void lds_product(const T* __restrict__ x, T* __restri
 #pragma unroll 1
   for (int dct = 0; dct < 2; ++dct) {
     if (on) {
+      if (!HOLD && dct == 1) load_chirp();
 #pragma unroll
       for (int i = 0; i < kPPT; ++i) {
         int t, n;
@@ -117,6 +139,7 @@ __device__ __forceinline__ void lds_product(const T* __restrict__ x, T* __restri
     if constexpr (CHIRP) {
       // x filter, inverse transform as conj FFT conj, x chirp: Y_n, n <= N
       if (on) {
+        if (!HOLD) load_filter();
 #pragma unroll
         for (int i = 0; i < kPPT; ++i) {
           int t, n;
@@ -127,6 +150,7 @@ __device__ __forceinline__ void lds_product(const T* __restrict__ x, T* __restri
       __syncthreads();
       fast::fft_ct<T, LOGM, COUNT, true>(sm, tw);
       if (on) {
+        if (!HOLD) load_chirp();
 #pragma unroll
         for (int i = 0; i < kPPT; ++i) {
           int t, n;
@@ -238,7 +262,7 @@ __global__ __launch_bounds__(kLdsMax / kPPT) void k_lds_product(const T* __restr
   const int2 tile = tiles[blockIdx.x];
   switch (pd[tile.x].logM) {
 #define BIRK_LDS_CASE(LG) \
-  case LG: lds_product<T, LG, CHIRP>(x, out, pd, tile, tw, trans, sm, red); break;
+  case LG: lds_product<T, LG, CHIRP, true>(x, out, pd, tile, tw, trans, sm, red); break;
     BIRK_LDS_CASE(3)
     BIRK_LDS_CASE(4)
     BIRK_LDS_CASE(5)
@@ -252,6 +276,20 @@ __global__ __launch_bounds__(kLdsMax / kPPT) void k_lds_product(const T* __restr
 #undef BIRK_LDS_CASE
     default: break;
   }
+}
+
+// The longest chirp products in float, where there are more of them than CUs: chirp and filter are
+// read again at each use (from the L2), since the registers they would take in between leave room
+// for one workgroup a CU instead of two.  N = 1000, 1536 pairs: 151 -> 113 us; 96 pairs 26.0, as
+// with the tables held.
+template <typename T>
+__global__ __launch_bounds__(kLdsMax / kPPT, 4) void k_lds_long(const T* __restrict__ x, T* __restrict__ out,
+                                                                const PairDesc* __restrict__ pd,
+                                                                const int2* __restrict__ tiles,
+                                                                const cplx<T>* __restrict__ tw, int trans) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ double red[2 * kLdsMax / 64];
+  lds_product<T, kLdsMaxLog, true, false>(x, out, pd, tiles[blockIdx.x], tw, trans, reinterpret_cast<T*>(smem_raw), red);
 }
 
 // One component of N = 2^LOGN per workgroup, N / 8 threads.  The even extension y_m,
@@ -408,12 +446,22 @@ int lds_reals(int logM) { return 2 * lds_pairs(logM) * fast::padded_ld(1 << logM
 
 template <typename T, bool CHIRP>
 hipError_t launch(birk_plan* p, const LdsSet& ls, const T* v, T* out, int transpose, hipStream_t s) {
-  if (ls.ntiles == 0) return hipSuccess;
-  const auto f = k_lds_product<T, CHIRP>;
+  const cplx<T>* tw = (const cplx<T>*)p->lds_tw[prec_index<T>()];
   const int bytes = ls.lds_reals * (int)sizeof(T);
-  lds_limit(f, lds_reals(kLdsMaxLog) * (int)sizeof(T));
-  hipLaunchKernelGGL(f, dim3(ls.ntiles), dim3(ls.threads), bytes, s, v, out, ls.dev, ls.tiles,
-                     (const cplx<T>*)p->lds_tw[prec_index<T>()], transpose);
+  int n = ls.ntiles;
+  if constexpr (CHIRP && std::is_same<T, float>::value) {
+    if (ls.nlong > kCus) {   // the last tiles of the list
+      n -= ls.nlong;
+      lds_limit(k_lds_long<T>, bytes);
+      hipLaunchKernelGGL(k_lds_long<T>, dim3(ls.nlong), dim3(ls.threads), bytes, s, v, out, ls.dev, ls.tiles + n, tw,
+                         transpose);
+    }
+  }
+  if (n > 0) {
+    const auto f = k_lds_product<T, CHIRP>;
+    lds_limit(f, lds_reals(kLdsMaxLog) * (int)sizeof(T));
+    hipLaunchKernelGGL(f, dim3(n), dim3(ls.threads), bytes, s, v, out, ls.dev, ls.tiles, tw, transpose);
+  }
   return hipGetLastError();
 }
 
@@ -432,6 +480,7 @@ hipError_t finalize_lds(birk_plan* p, LdsSet& ls) {
     int cnt = 1;
     while (q + cnt < np && cnt < per && ls.host[q + cnt].logM == logM) ++cnt;
     tiles.push_back(make_int2(q, cnt));
+    if (logM == kLdsMaxLog) ++ls.nlong;
     ls.lds_reals = std::max(ls.lds_reals, lds_reals(logM));
     q += cnt;
   }

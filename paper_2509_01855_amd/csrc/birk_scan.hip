@@ -723,7 +723,6 @@ void launch(birk_plan* p, const ScanClass& sc, const double* J, const T* y, T* o
 // runs for a few tiles.  Below n_x = 5 what counts is the number of groups of 64 tiles that
 // the last tiles' start state walks (n_x = 3, 4 at N = 3e5: 12 a CU 33.6 and 44.6 us, 8 a CU
 // 34.1 and 54; n_x = 1: 16 a CU 13.8, 24 a CU 15.5).
-constexpr int kCus = 256;
 int scan_rounds(int64_t Nn, int nx) {
   static constexpr int waves[kScanNx + 1] = {0, 16, 16, 12, 12, 8, 7, 5, 4};
   const int64_t per_round = (int64_t)64 * kCus * waves[nx];

@@ -85,31 +85,45 @@ __device__ __forceinline__ cplx<T> get(const T* sm, int t, int n) {
   return fast::mk<T>(sm[2 * t * LD + fast::pad(n)], sm[(2 * t + 1) * LD + fast::pad(n)]);
 }
 
-// X_j = sum_s g_s exp(-2 pi i s j / R) in place.  R = 5: cos(2 pi / 5), cos(4 pi / 5) =
-// -1/4 +- sqrt(5)/4.
+// X_j = sum_s g_s exp(-2 pi i s j / R) in place.  Double-floats form each product once (R = 5 from
+// cos(2 pi / 5), cos(4 pi / 5) = -1/4 +- sqrt(5)/4); the others fuse them with the sums.
 template <typename T, int R>
 __device__ __forceinline__ void dft_odd(cplx<T> (&g)[R]) {
   auto add = [](cplx<T> a, cplx<T> b) { return fast::mk<T>(a.x + b.x, a.y + b.y); };
   auto sub = [](cplx<T> a, cplx<T> b) { return fast::mk<T>(a.x - b.x, a.y - b.y); };
+  constexpr bool kFused = std::is_floating_point<T>::value;
   if constexpr (R == 3) {
     const T s = T(0.86602540378443864676);
     const cplx<T> t = add(g[1], g[2]), u = sub(g[1], g[2]);
     const cplx<T> m = fast::mk<T>(g[0].x - pow2_times(0.5f, t.x), g[0].y - pow2_times(0.5f, t.y));
-    const cplx<T> su = fast::mk<T>(s * u.x, s * u.y);
     g[0] = add(g[0], t);
-    g[1] = fast::mk<T>(m.x + su.y, m.y - su.x);
-    g[2] = fast::mk<T>(m.x - su.y, m.y + su.x);
+    if constexpr (kFused) {
+      g[1] = fast::mk<T>(m.x + s * u.y, m.y - s * u.x);
+      g[2] = fast::mk<T>(m.x - s * u.y, m.y + s * u.x);
+    } else {
+      const cplx<T> su = fast::mk<T>(s * u.x, s * u.y);
+      g[1] = fast::mk<T>(m.x + su.y, m.y - su.x);
+      g[2] = fast::mk<T>(m.x - su.y, m.y + su.x);
+    }
   } else if constexpr (R == 5) {
-    const T q = T(0.55901699437494742410);   // sqrt(5)/4
     const T s1 = T(0.95105651629515357212), s2 = T(0.58778525229247312917);
     const cplx<T> t1 = add(g[1], g[4]), t2 = add(g[2], g[3]), u1 = sub(g[1], g[4]), u2 = sub(g[2], g[3]);
-    const cplx<T> t = add(t1, t2), v = sub(t1, t2);
-    const cplx<T> m = fast::mk<T>(g[0].x - pow2_times(0.25f, t.x), g[0].y - pow2_times(0.25f, t.y));
-    const cplx<T> qv = fast::mk<T>(q * v.x, q * v.y);
-    const cplx<T> m1 = add(m, qv), m2 = sub(m, qv);
+    cplx<T> m1, m2;
+    if constexpr (kFused) {
+      const T c1 = T(0.30901699437494742410), c2 = T(-0.80901699437494742410);
+      m1 = fast::mk<T>(g[0].x + c1 * t1.x + c2 * t2.x, g[0].y + c1 * t1.y + c2 * t2.y);
+      m2 = fast::mk<T>(g[0].x + c2 * t1.x + c1 * t2.x, g[0].y + c2 * t1.y + c1 * t2.y);
+    } else {
+      const T q = T(0.55901699437494742410);   // sqrt(5)/4
+      const cplx<T> t = add(t1, t2), v = sub(t1, t2);
+      const cplx<T> m = fast::mk<T>(g[0].x - pow2_times(0.25f, t.x), g[0].y - pow2_times(0.25f, t.y));
+      const cplx<T> qv = fast::mk<T>(q * v.x, q * v.y);
+      m1 = add(m, qv);
+      m2 = sub(m, qv);
+    }
     const cplx<T> n1 = fast::mk<T>(s1 * u1.x + s2 * u2.x, s1 * u1.y + s2 * u2.y);
     const cplx<T> n2 = fast::mk<T>(s2 * u1.x - s1 * u2.x, s2 * u1.y - s1 * u2.y);
-    g[0] = add(g[0], t);
+    g[0] = add(g[0], add(t1, t2));
     g[1] = fast::mk<T>(m1.x + n1.y, m1.y - n1.x);
     g[4] = fast::mk<T>(m1.x - n1.y, m1.y + n1.x);
     g[2] = fast::mk<T>(m2.x + n2.y, m2.y - n2.x);

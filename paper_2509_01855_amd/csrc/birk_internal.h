@@ -171,7 +171,13 @@ struct ScanDesc {
   int rounds;                // nodes per tile / 64 (16 above kScanNx)
   int ntile;
 };
+struct ScanTiles {           // another tiling of a class: descriptors, tiles and groups as below
+  ScanDesc* dev = nullptr;
+  int2 *tiles = nullptr, *groups = nullptr;
+  int n_tile = 0, n_group = 0;
+};
 struct ScanClass {
+  ScanTiles four;            // one J per instance: four nodes a lane (or empty)
   int nx = 0;
   ScanDesc* dev = nullptr;
   int2* tiles = nullptr;     // (instance, tile)

@@ -595,6 +595,258 @@ __global__ __launch_bounds__(64) void k_lane_apply(const double* __restrict__ J,
   }
 }
 
+// One J per instance, n_x = 2 to 5, from 10^5 nodes on: nothing but y and w comes from memory, and
+// the scan of 64 maps is most of the arithmetic above.  Here a lane carries four consecutive
+// nodes: it composes their maps itself, the wave scans once for 256 nodes and keeps the scanned
+// maps (F doubles per four nodes) for the second pass, which only replays; y, w and the outputs
+// pass through LDS, so that global accesses stay whole runs.  Bound: FP64 VALU.  n_x = 2, 3, 4, 5:
+// 300001 nodes 17.5, 28.5, 37.3, 52.5 us with the kernels above (a node per lane, or chunks of
+// sixteen) and 15.2, 21.4, 30.6, 44.1 here; 2^20 + 1 nodes 34.9, 60.5, 75.7, 120 and 28.7, 43.5,
+// 65.4, 94.3; 65537 nodes 13.8, 15.9, 19.6, 24.7 and 13.7, 15.2, 19.8, 27.3.  n_x = 1: 17 us either
+// way at 2^20 + 1.
+constexpr int kFour = 4;           // nodes of a lane
+constexpr int kFourNx = 5;
+constexpr bool four_nx(int nx) { return nx >= 2 && nx <= kFourNx; }
+constexpr int kFourRound = 64 * kFour;
+template <int NX>
+struct FourLds {
+  static constexpr int LD = kFourRound + kFourRound / kFour;   // a row, one place of skew per lane
+  double v[NX + 1][LD];                                        // y (then the output), w
+};
+__device__ __forceinline__ int four_at(int p) { return p + p / kFour; }
+
+// The round's y and w, zero past the instance.
+template <int NX, bool BACK, typename T>
+__device__ __forceinline__ void four_load(const ScanDesc& d, const T* __restrict__ yv, int64_t first, FourLds<NX>& sm) {
+  const int l = (int)threadIdx.x;
+  const int64_t Nn = d.Nn;
+  double y[kFour][NX], w[kFour];
+#pragma unroll
+  for (int i = 0; i < kFour; ++i) {
+    const int64_t pos = first + l + 64 * i;
+    const bool ok = pos < Nn;
+    const int64_t p = ok ? pos : 0;
+    const uint32_t k = (uint32_t)(BACK ? Nn - 1 - p : p);
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+      const double x = (double)(yv + d.off + r * Nn)[k];
+      y[i][r] = ok ? x : 0.0;
+    }
+    const double x = d.w[k];
+    w[i] = ok ? x : 0.0;
+  }
+#pragma unroll
+  for (int i = 0; i < kFour; ++i) {
+    const int a = four_at(l + 64 * i);
+#pragma unroll
+    for (int r = 0; r < NX; ++r) sm.v[r][a] = y[i][r];
+    sm.v[NX][a] = w[i];
+  }
+}
+
+// Node i of the lane: H_k, y_k and g (see form_h); left: nodes from the round's first on.
+template <int NX, bool BACK>
+__device__ __forceinline__ void four_node(const FourLds<NX>& sm, int i, int64_t left, const double* __restrict__ Jc,
+                                          double (&h)[NX * NX], double (&y)[NX], double (&g)[NX], int* flag) {
+  Node<NX, kConst> nd;
+  const int a = four_at((int)threadIdx.x * kFour + i);
+#pragma unroll
+  for (int r = 0; r < NX; ++r) nd.y[r] = y[r] = sm.v[r][a];
+  nd.w = sm.v[NX][a];
+  nd.ok = (int)threadIdx.x * kFour + i < left;
+  form_h<NX, kConst, BACK>(nd, Jc, h, g, flag);
+}
+
+// A round's scanned maps in the scratch: field e of lane l's at 64 e + l.
+template <int NX, typename P>
+__device__ __forceinline__ P* four_maps(P* scan, const ScanDesc& d, int tile, int round) {
+  return scan + d.cmap + ((int64_t)tile * d.rounds + round) * 64 * Lay<NX>::F + threadIdx.x;
+}
+
+// The lane's four nodes as one map, scanned over the wave.
+template <int NX, bool BACK>
+__device__ __forceinline__ void four_map(const FourLds<NX>& sm, int64_t left, const double* __restrict__ Jc, Aff<NX>& m) {
+#pragma unroll 1
+  for (int i = 0; i < kFour; ++i) {
+    double h[NX * NX], y[NX], g[NX];
+    four_node<NX, BACK>(sm, i, left, Jc, h, y, g, nullptr);
+    if (i == 0) {
+#pragma unroll
+      for (int r = 0; r < NX; ++r) {
+        m.b[r] = g[r];
+#pragma unroll
+        for (int c = 0; c < NX; ++c) m.A[r][c] = (r == c ? 1.0 : 0.0) + h[r * NX + c];
+      }
+      continue;
+    }
+    Aff<NX> n = m;   // m <- m + H m, and the constant + g
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+      n.b[r] += g[r];
+#pragma unroll
+      for (int q = 0; q < NX; ++q) {
+        n.b[r] += h[r * NX + q] * m.b[q];
+#pragma unroll
+        for (int c = 0; c < NX; ++c) n.A[r][c] += h[r * NX + q] * m.A[q][c];
+      }
+    }
+    m = n;
+  }
+  wave_scan<NX>(m);
+}
+
+template <int NX, bool BACK, typename T>
+__global__ __launch_bounds__(64) void k_four_reduce(const double* __restrict__ J, const T* __restrict__ y,
+                                                    const ScanDesc* __restrict__ sd, const int2* __restrict__ tiles,
+                                                    double* __restrict__ scan) {
+  __shared__ FourLds<NX> sm;
+  const int2 t = tiles[blockIdx.x];
+  const ScanDesc& d = sd[t.x];
+  const int R = d.rounds;
+  Aff<NX> tm;
+#pragma unroll 1
+  for (int j = 0; j < R; ++j) {
+    const int64_t first = ((int64_t)t.y * R + j) * kFourRound;
+    four_load<NX, BACK, T>(d, y, first, sm);
+    wave_sync();
+    Aff<NX> m;
+    four_map<NX, BACK>(sm, d.Nn - first, J + d.jcoff, m);
+    wave_sync();
+    double* o = four_maps<NX>(scan, d, t.y, j);
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+#pragma unroll
+      for (int c = 0; c < NX; ++c) o[64 * (c * NX + r)] = m.A[r][c];
+      o[64 * (NX * NX + r)] = m.b[r];
+    }
+    if (j == 0) {
+      tm = m;
+      continue;
+    }
+    Aff<NX> n = m;   // of interest in lane 63 only, as tm is
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+#pragma unroll
+      for (int q = 0; q < NX; ++q) n.b[r] += m.A[r][q] * tm.b[q];
+#pragma unroll
+      for (int c = 0; c < NX; ++c) {
+        double acc = 0.0;
+#pragma unroll
+        for (int q = 0; q < NX; ++q) acc += m.A[r][q] * tm.A[q][c];
+        n.A[r][c] = acc;
+      }
+    }
+    tm = n;
+  }
+  if (threadIdx.x == 63 && t.y + 1 < d.ntile) {   // the last tile's map is not needed
+    double* o = scan + d.tmap + t.y;
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+#pragma unroll
+      for (int c = 0; c < NX; ++c) o[(int64_t)(c * NX + r) * d.ntile] = tm.A[r][c];
+      o[(int64_t)(NX * NX + r) * d.ntile] = tm.b[r];
+    }
+  }
+}
+
+template <int NX, bool BACK, typename T>
+__global__ __launch_bounds__(64) void k_four_apply(const double* __restrict__ J, const T* __restrict__ y,
+                                                   const ScanDesc* __restrict__ sd, const int2* __restrict__ tiles,
+                                                   const double* __restrict__ scan, T* __restrict__ out,
+                                                   T* __restrict__ jout, int* flag) {
+  constexpr int F = Lay<NX>::F;
+  __shared__ FourLds<NX> sm;
+  const int2 t = tiles[blockIdx.x];
+  const ScanDesc& d = sd[t.x];
+  const int R = d.rounds, l = (int)threadIdx.x;
+  double s[NX];   // the tile's start state, in every lane
+#pragma unroll
+  for (int r = 0; r < NX; ++r) s[r] = 0.0;
+  auto step = [&](const double* __restrict__ m, int64_t fs) {
+    double n[NX];
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+      n[r] = m[(NX * NX + r) * fs];
+#pragma unroll
+      for (int q = 0; q < NX; ++q) n[r] += m[(q * NX + r) * fs] * s[q];
+    }
+#pragma unroll
+    for (int r = 0; r < NX; ++r) s[r] = n[r];
+  };
+  const int ng = t.y >> 6;
+#pragma unroll 4
+  for (int q = 0; q < ng; ++q) step(scan + d.gmap + (int64_t)q * F, 1);
+  if (t.y & 63) step(scan + d.tmap + t.y - 1, d.ntile);
+  const bool keep_v = !BACK && jout;
+#pragma unroll 1
+  for (int j = 0; j < R; ++j) {
+    const int64_t first = ((int64_t)t.y * R + j) * kFourRound;
+    four_load<NX, BACK, T>(d, y, first, sm);
+    wave_sync();
+    double S[NX], e[NX];   // the states before the lane's nodes and after them
+    {
+      const double* o = four_maps<NX>(scan, d, t.y, j);
+#pragma unroll
+      for (int r = 0; r < NX; ++r) {
+        e[r] = o[64 * (NX * NX + r)];
+#pragma unroll
+        for (int q = 0; q < NX; ++q) e[r] += o[64 * (q * NX + r)] * s[q];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+      const double before = __shfl_up(e[r], 1, 64);
+      S[r] = l == 0 ? s[r] : before;
+    }
+#pragma unroll
+    for (int r = 0; r < NX; ++r) s[r] = lane63(e[r]);
+    double vo[kFour][NX];
+#pragma unroll
+    for (int i = 0; i < kFour; ++i) {
+      double h[NX * NX], yn[NX], g[NX], u[NX];
+      four_node<NX, BACK>(sm, i, d.Nn - first, J + d.jcoff, h, yn, g, flag);
+#pragma unroll
+      for (int r = 0; r < NX; ++r) u[r] = S[r] + (BACK ? 0.5 * yn[r] : yn[r]);
+      const int a = four_at(l * kFour + i);
+#pragma unroll
+      for (int r = 0; r < NX; ++r) {
+        double v = 0.0;
+#pragma unroll
+        for (int q = 0; q < NX; ++q) v += h[r * NX + q] * u[q];
+        const double x = BACK ? yn[r] + v : u[r] + 0.5 * v;
+        S[r] += BACK ? x : v;
+        vo[i][r] = v;
+        sm.v[r][a] = x;   // xi (x) in place of the lane's own y
+      }
+    }
+    wave_sync();
+    auto put = [&](T* __restrict__ o) {
+#pragma unroll
+      for (int i = 0; i < kFour; ++i) {
+        const int64_t pos = first + l + 64 * i;
+        if (pos >= d.Nn) continue;
+        const int64_t k = BACK ? d.Nn - 1 - pos : pos;
+#pragma unroll
+        for (int r = 0; r < NX; ++r) o[d.off + (int64_t)r * d.Nn + k] = (T)sm.v[r][four_at(l + 64 * i)];
+      }
+    };
+    put(out);
+    wave_sync();
+    if (keep_v) {   // J xi = v / w
+#pragma unroll
+      for (int i = 0; i < kFour; ++i) {
+        const int a = four_at(l * kFour + i);
+        const double iw = 1.0 / sm.v[NX][a];
+#pragma unroll
+        for (int r = 0; r < NX; ++r) sm.v[r][a] = vo[i][r] * iw;
+      }
+      wave_sync();
+      put(jout);
+      wave_sync();
+    }
+  }
+}
+
 // Instances of at most 64 nodes per wave of the workgroup (d.ntile waves, R = 1): reduce and
 // apply in one launch, H_k formed once and kept in LDS.
 template <int NX, int MODE, bool BACK, typename T>
@@ -687,6 +939,17 @@ void launch(birk_plan* p, const ScanClass& sc, const double* J, const T* y, T* o
     hipLaunchKernelGGL(f, dim3(sc.n_small), dim3(64 * sc.small_waves), bytes, s, J, ht, y, sc.dev, sc.small, out, jout,
                        flag);
   }
+  if constexpr (MODE == kConst && four_nx(NX)) {
+    if (sc.four.n_tile > 0) {
+      const ScanTiles& f = sc.four;
+      const dim3 g(f.n_tile), b(64);
+      hipLaunchKernelGGL((k_four_reduce<NX, BACK, T>), g, b, 0, s, J, y, f.dev, f.tiles, p->scan);
+      hipLaunchKernelGGL(k_scan_tiles<NX>, dim3(f.n_group), b, 0, s, p->scan, f.dev, f.groups);
+      hipLaunchKernelGGL((k_four_apply<NX, BACK, T>), g, b, 0, s, J, y, f.dev, f.tiles, (const double*)p->scan, out, jout,
+                         flag);
+      return;
+    }
+  }
   if (sc.n_tile > 0) {
     const dim3 g(sc.n_tile), b(64);
     if constexpr (NX <= kLaneNx)
@@ -729,6 +992,14 @@ int scan_rounds(int64_t Nn, int nx) {
   return (int)((Nn + per_round - 1) / per_round);
 }
 
+// Four nodes a lane: rounds per tile (8 waves a CU), and the nodes of a class, its one-launch
+// instances aside, from which on it is taken.
+int four_rounds(int64_t Nn) {
+  const int64_t per_round = (int64_t)kFourRound * kCus * 8;
+  return (int)((Nn + per_round - 1) / per_round);
+}
+constexpr int64_t kFourNodes = 100000;
+
 }  // namespace
 
 int64_t scan_scratch(int64_t Nn, int nx) {
@@ -738,7 +1009,10 @@ int64_t scan_scratch(int64_t Nn, int nx) {
     return ((int64_t)nx * nx + nx) * (nt + (nt + kWideGroup - 1) / kWideGroup);
   }
   const int64_t F = (int64_t)nx * nx + nx, R = scan_rounds(Nn, nx), nt = (Nn + 64 * R - 1) / (64 * R);
-  return F * (nt * (kC * R + 1) + (nt + 63) / 64);
+  const int64_t need = F * (nt * (kC * R + 1) + (nt + 63) / 64);
+  if (!four_nx(nx)) return need;
+  const int64_t R4 = four_rounds(Nn), nt4 = (Nn + kFourRound * R4 - 1) / (kFourRound * R4);
+  return std::max(need, F * (nt4 * (64 * R4 + 1) + (nt4 + 63) / 64));
 }
 
 int64_t scan_htab(int64_t Nn, int nx, birk_precision prec) {
@@ -753,9 +1027,10 @@ hipError_t plan_scan(birk_plan* p) {
     const int per = wide ? kWideNodes : 64, group = wide ? kWideGroup : 64;
     ScanClass sc;
     sc.nx = nx;
-    std::vector<ScanDesc> h;
-    std::vector<int2> tt, tg, tn;
+    std::vector<ScanDesc> h, h4;
+    std::vector<int2> tt, tg, tn, t4, g4;
     std::vector<int> ts;
+    int64_t nodes = 0;   // of the instances worked in tiles
     int most = 0;
     if (!wide) SCAN_NX_SWITCH(nx, most = small_waves<NXC>())
     for (const Instance& in : p->inst) {
@@ -775,6 +1050,13 @@ hipError_t plan_scan(birk_plan* p) {
       d.tmap = d.cmap + (wide ? 0 : F * kC * d.rounds * d.ntile);
       d.gmap = d.tmap + F * d.ntile;
       h.push_back(d);
+      // four nodes a lane
+      ScanDesc f = d;
+      f.rounds = four_rounds(in.Nn);
+      f.ntile = (int)((in.Nn + kFourRound * f.rounds - 1) / (kFourRound * f.rounds));
+      f.tmap = d.cmap + 64 * F * f.rounds * f.ntile;
+      f.gmap = f.tmap + F * f.ntile;
+      h4.push_back(f);
       for (int64_t b = 0; b * 256 < in.Nn; ++b) tn.push_back(make_int2(k, (int)b));
       if (d.ntile <= most) {
         ts.push_back(k);
@@ -784,6 +1066,9 @@ hipError_t plan_scan(birk_plan* p) {
       for (int b = 0; b < d.ntile; ++b) tt.push_back(make_int2(k, b));
       if (d.ntile > 1)
         for (int b = 0; b * group + 1 < d.ntile; ++b) tg.push_back(make_int2(k, b));
+      nodes += in.Nn;
+      for (int b = 0; b < f.ntile; ++b) t4.push_back(make_int2(k, b));
+      for (int b = 0; b * 64 + 1 < f.ntile; ++b) g4.push_back(make_int2(k, b));
     }
     if (h.empty()) continue;
     sc.n_tile = (int)tt.size();
@@ -800,6 +1085,13 @@ hipError_t plan_scan(birk_plan* p) {
     sc.groups = (int2*)up(tg.data(), tg.size() * sizeof(int2));
     sc.nodes = (int2*)up(tn.data(), tn.size() * sizeof(int2));
     sc.small = (int*)up(ts.data(), ts.size() * sizeof(int));
+    if (four_nx(nx) && nodes >= kFourNodes && !g4.empty()) {
+      sc.four.dev = (ScanDesc*)up(h4.data(), h4.size() * sizeof(ScanDesc));
+      sc.four.tiles = (int2*)up(t4.data(), t4.size() * sizeof(int2));
+      sc.four.groups = (int2*)up(g4.data(), g4.size() * sizeof(int2));
+      sc.four.n_tile = (int)t4.size();
+      sc.four.n_group = (int)g4.size();
+    }
     if (e != hipSuccess) return e;
     p->sclass.push_back(sc);
   }

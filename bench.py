@@ -49,7 +49,8 @@ if ROOT not in sys.path:
 
 METRIC = "Birkhoff matvec Gpts/s at N=2^20; solve time mixed vs FP64 at 1e-10 resid"
 KERNEL_SOURCES = ["paper_2509_01855_amd/csrc/birk_fast.hip", "paper_2509_01855_amd/csrc/birk_dct.hip",
-                  "paper_2509_01855_amd/csrc/birk_fft.h"]
+                  "paper_2509_01855_amd/csrc/birk_fft.h", "paper_2509_01855_amd/csrc/birk_mid.h",
+                  "paper_2509_01855_amd/csrc/birk_dense.h"]
 HBM_PEAK_GBS = 8000.0
 
 

@@ -26,7 +26,8 @@ import sys
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
 SOURCES = ["paper_2509_01855_amd/csrc/birk_fast.hip", "paper_2509_01855_amd/csrc/birk_dct.hip",
-           "paper_2509_01855_amd/csrc/birk_fft.h"]
+           "paper_2509_01855_amd/csrc/birk_fft.h", "paper_2509_01855_amd/csrc/birk_mid.h",
+           "paper_2509_01855_amd/csrc/birk_dense.h"]
 
 
 def schedule_key(split, tb, xcd, narrow=0):

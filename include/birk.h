@@ -299,8 +299,8 @@ birk_status birk_krylov_solve(birk_plan* plan, birk_jac_kind jac_kind, const dou
  * opts->use_x0 = 1, which needs lam).  BIRK_F64 plans only.  opts: rtol, max_iter (total
  * MINRES iterations), use_precond and use_x0 are used; NULL = defaults.  info: inner =
  * MINRES iterations, outer = restarts, rel_resid = the final relative KKT residual.
- * The first call allocates the KKT workspace (nine pairs of vectors and the scan
- * scratch), kept with the plan.  Synchronous.  Errors: BIRK_ERR_ARG (NULL, overlaps,
+ * The first call allocates the KKT workspace (eight pairs of vectors and the scalars),
+ * kept with the plan.  Synchronous.  Errors: BIRK_ERR_ARG (NULL, overlaps,
  * bad options), BIRK_ERR_UNSUPPORTED (plans other than BIRK_F64, n_x > 12 with the
  * preconditioner), BIRK_ERR_NOMEM, BIRK_ERR_NOCONV, BIRK_ERR_NONFINITE, BIRK_ERR_DEVICE. */
 birk_status birk_kkt_solve(birk_plan* plan, birk_jac_kind jac_kind, const double* J, const double* h,

@@ -9,9 +9,9 @@
 // With a double Krylov precision this is restarted GMRES whose restarts use the true
 // residual; with float it is mixed-precision iterative refinement.  The Arnoldi
 // process uses classical Gram-Schmidt with one re-orthogonalisation (CGS2); dot
-// products and norms accumulate in double; the Hessenberg least-squares problem is
-// solved with Givens rotations on the host, one small device-to-host copy per
-// iteration.
+// products and norms accumulate in double; the Hessenberg columns, their Givens rotations
+// and the small least-squares problem stay on the device (birk_krylov.hip), and the host
+// reads one running flag per instance after each chunk of steps.
 
 #include <hip/hip_runtime.h>
 

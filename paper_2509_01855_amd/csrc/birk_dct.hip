@@ -82,7 +82,7 @@ __host__ __device__ __forceinline__ cplx<T> mk(T x, T y) {
 // already formed.  All reads of the stage complete before any write (in place).
 template <typename T, int R, int NB>
 __device__ __forceinline__ void stockham_stage(cplx<T>* buf, int logL, int count, int logNs,
-                                               const cplx<T>* __restrict__ tw, int inverse) {
+                                               const cplx<T>* __restrict__ tw) {
   constexpr int logR = (R == 4) ? 2 : 1;
   const int logNb = logL - logR;
   const int nb = 1 << logNb;  // butterflies per transform
@@ -104,9 +104,7 @@ __device__ __forceinline__ void stockham_stage(cplx<T>* buf, int logL, int count
       const int jm = j & (Ns - 1);
 #pragma unroll
       for (int r = 1; r < R; ++r) {
-        cplx<T> w = tw[(jm * r) << tshift];
-        if (inverse) w.y = -w.y;
-        v[i][r] = cmul<T>(v[i][r], w);
+        v[i][r] = cmul<T>(v[i][r], tw[(jm * r) << tshift]);
       }
       if (R == 2) {
         cplx<T> a = v[i][0], c = v[i][1];
@@ -117,8 +115,7 @@ __device__ __forceinline__ void stockham_stage(cplx<T>* buf, int logL, int count
         cplx<T> t1 = csub<T>(v[i][0], v[i][2]);
         cplx<T> t2 = cadd<T>(v[i][1], v[i][3]);
         cplx<T> d = csub<T>(v[i][1], v[i][3]);
-        // forward: multiply by -i; inverse: by +i
-        cplx<T> t3 = inverse ? mk<T>(-d.y, d.x) : mk<T>(d.y, -d.x);
+        cplx<T> t3 = mk<T>(d.y, -d.x);   // x -i
         v[i][0] = cadd<T>(t0, t2);
         v[i][2] = csub<T>(t0, t2);
         v[i][1] = cadd<T>(t1, t3);
@@ -140,14 +137,13 @@ __device__ __forceinline__ void stockham_stage(cplx<T>* buf, int logL, int count
 
 // `count` in-place FFTs of length 2^logL in LDS (count << logL <= 4 * NB * blockDim.x).
 template <typename T, int NB>
-__device__ void lds_fft(cplx<T>* buf, int logL, int count, const cplx<T>* __restrict__ tw,
-                        int inverse) {
+__device__ void lds_fft(cplx<T>* buf, int logL, int count, const cplx<T>* __restrict__ tw) {
   int logNs = 0;
   if (logL & 1) {
-    stockham_stage<T, 2, 2 * NB>(buf, logL, count, 0, tw, inverse);
+    stockham_stage<T, 2, 2 * NB>(buf, logL, count, 0, tw);
     logNs = 1;
   }
-  for (; logNs < logL; logNs += 2) stockham_stage<T, 4, NB>(buf, logL, count, logNs, tw, inverse);
+  for (; logNs < logL; logNs += 2) stockham_stage<T, 4, NB>(buf, logL, count, logNs, tw);
 }
 
 
@@ -156,7 +152,7 @@ __device__ void lds_fft(cplx<T>* buf, int logL, int count, const cplx<T>* __rest
 template <typename T>
 __global__ __launch_bounds__(kFftThreads) void k_fft_lds(cplx<T>* __restrict__ data, const PairDesc* __restrict__ pd,
                                                         const int2* __restrict__ tiles,
-                                                        const cplx<T>* __restrict__ tw, int inverse) {
+                                                        const cplx<T>* __restrict__ tw) {
   __shared__ cplx<T> buf[kLdsMax];
   const int2 tile = tiles[blockIdx.x];
   const PairDesc& d = pd[tile.x];
@@ -165,16 +161,14 @@ __global__ __launch_bounds__(kFftThreads) void k_fft_lds(cplx<T>* __restrict__ d
   cplx<T>* g = data + d.work;
   for (int e = threadIdx.x; e < n; e += blockDim.x) buf[e] = g[e];
   __syncthreads();
-  lds_fft<T, 4>(buf, logM, tile.y, tw, inverse);
+  lds_fft<T, 4>(buf, logM, tile.y, tw);
   for (int e = threadIdx.x; e < n; e += blockDim.x) g[e] = buf[e];
 }
 
 template <typename T>
 __device__ __forceinline__ cplx<T> tw4(const cplx<T>* __restrict__ hi, const cplx<T>* __restrict__ lo,
-                                       int shift, int64_t t, int inverse) {
-  cplx<T> w = cmul<T>(hi[t >> shift], lo[t & ((1 << shift) - 1)]);
-  if (inverse) w.y = -w.y;
-  return w;
+                                       int shift, int64_t t) {
+  return cmul<T>(hi[t >> shift], lo[t & ((1 << shift) - 1)]);
 }
 
 // Four-step, pass 1: columns n2 of x[M2 n1 + n2], FFT over n1 (length M1), twiddle
@@ -183,7 +177,7 @@ template <typename T>
 __global__ __launch_bounds__(kFftThreads) void k_fft4_cols(const cplx<T>* __restrict__ x, cplx<T>* __restrict__ tmp,
                                                           const PairDesc* __restrict__ pd,
                                                           const int2* __restrict__ tiles,
-                                                          const cplx<T>* __restrict__ tw, int inverse) {
+                                                          const cplx<T>* __restrict__ tw) {
   __shared__ cplx<T> buf[kLdsMax];
   constexpr int pi = prec_index<T>();
   const int2 tile = tiles[blockIdx.x];
@@ -203,11 +197,11 @@ __global__ __launch_bounds__(kFftThreads) void k_fft4_cols(const cplx<T>* __rest
     buf[(w << logM1) + n1] = xs[((int64_t)n1 << logM2) + c0 + w];
   }
   __syncthreads();
-  lds_fft<T, 4>(buf, logM1, W, tw, inverse);
+  lds_fft<T, 4>(buf, logM1, W, tw);
   for (int e = threadIdx.x; e < n; e += blockDim.x) {
     const int w = e & (W - 1), k1 = e >> logW;
     const int64_t t = (int64_t)(c0 + w) * k1;
-    ts[((int64_t)k1 << logM2) + c0 + w] = cmul<T>(buf[(w << logM1) + k1], tw4<T>(thi, tlo, d.tw_shift, t, inverse));
+    ts[((int64_t)k1 << logM2) + c0 + w] = cmul<T>(buf[(w << logM1) + k1], tw4<T>(thi, tlo, d.tw_shift, t));
   }
 }
 
@@ -217,7 +211,7 @@ template <typename T>
 __global__ __launch_bounds__(kFftThreads) void k_fft4_rows(const cplx<T>* __restrict__ tmp, cplx<T>* __restrict__ x,
                                                           const PairDesc* __restrict__ pd,
                                                           const int2* __restrict__ tiles,
-                                                          const cplx<T>* __restrict__ tw, int inverse) {
+                                                          const cplx<T>* __restrict__ tw) {
   __shared__ cplx<T> buf[kLdsMax];
   const int2 tile = tiles[blockIdx.x];
   const PairDesc& d = pd[tile.x];
@@ -231,7 +225,7 @@ __global__ __launch_bounds__(kFftThreads) void k_fft4_rows(const cplx<T>* __rest
   const int n = M2 << logW;
   for (int e = threadIdx.x; e < n; e += blockDim.x) buf[e] = ts[e];
   __syncthreads();
-  lds_fft<T, 4>(buf, logM2, W, tw, inverse);
+  lds_fft<T, 4>(buf, logM2, W, tw);
   for (int e = threadIdx.x; e < n; e += blockDim.x) {
     const int w = e & (W - 1), k2 = e >> logW;
     xs[r0 + w + ((int64_t)k2 << logM1)] = buf[(w << logM2) + k2];
@@ -241,17 +235,13 @@ __global__ __launch_bounds__(kFftThreads) void k_fft4_rows(const cplx<T>* __rest
 // FFTs of length M over every pair of the set, in place in `data` (tmp: four-step
 // intermediate).
 template <typename T>
-static hipError_t fft_set(const birk_plan* p, const PairSet& ps, cplx<T>* data, cplx<T>* tmp, int inverse,
-                          hipStream_t s) {
+static hipError_t fft_set(const birk_plan* p, const PairSet& ps, cplx<T>* data, cplx<T>* tmp, hipStream_t s) {
   const cplx<T>* tw = (const cplx<T>*)p->lds_tw[prec_index<T>()];
   if (ps.n_lds > 0)
-    hipLaunchKernelGGL(k_fft_lds<T>, dim3(ps.n_lds), dim3(kFftThreads), 0, s, data, ps.dev, ps.tiles_lds, tw,
-                       inverse);
+    hipLaunchKernelGGL(k_fft_lds<T>, dim3(ps.n_lds), dim3(kFftThreads), 0, s, data, ps.dev, ps.tiles_lds, tw);
   if (ps.n_c4 > 0) {
-    hipLaunchKernelGGL(k_fft4_cols<T>, dim3(ps.n_c4), dim3(kFftThreads), 0, s, data, tmp, ps.dev, ps.tiles_c4, tw,
-                       inverse);
-    hipLaunchKernelGGL(k_fft4_rows<T>, dim3(ps.n_r4), dim3(kFftThreads), 0, s, tmp, data, ps.dev, ps.tiles_r4, tw,
-                       inverse);
+    hipLaunchKernelGGL(k_fft4_cols<T>, dim3(ps.n_c4), dim3(kFftThreads), 0, s, data, tmp, ps.dev, ps.tiles_c4, tw);
+    hipLaunchKernelGGL(k_fft4_rows<T>, dim3(ps.n_r4), dim3(kFftThreads), 0, s, tmp, data, ps.dev, ps.tiles_r4, tw);
   }
   return hipGetLastError();
 }
@@ -403,7 +393,7 @@ static hipError_t product_set(birk_plan* p, const PairSet& ps, const T* v, T* ou
   cplx<T>* z2 = (cplx<T>*)p->work[1];
   cplx<T>* tmp = (cplx<T>*)p->work[2];
   hipLaunchKernelGGL(k_pack<T>, dim3(ps.n_m), dim3(256), 0, s, v, z, ps.dev, ps.tiles_m, transpose);
-  hipError_t e = fft_set<T>(p, ps, z, tmp, 0, s);
+  hipError_t e = fft_set<T>(p, ps, z, tmp, s);
   if (e != hipSuccess) return e;
   if (!transpose) {
     hipLaunchKernelGGL(k_mid_fwd<T>, dim3(ps.n_n), dim3(256), 0, s, z, z2, ps.dev, ps.tiles_n, p->partials);
@@ -411,7 +401,7 @@ static hipError_t product_set(birk_plan* p, const PairSet& ps, const T* v, T* ou
   } else {
     hipLaunchKernelGGL(k_mid_tr<T>, dim3(ps.n_n), dim3(256), 0, s, z, z2, ps.dev, ps.tiles_n);
   }
-  e = fft_set<T>(p, ps, z2, tmp, 0, s);
+  e = fft_set<T>(p, ps, z2, tmp, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_final<T>, dim3(ps.n_n), dim3(256), 0, s, z2, out, ps.dev, ps.tiles_n, transpose);
   return hipGetLastError();
@@ -904,7 +894,7 @@ hipError_t build_tables(birk_plan* p) {
       hipLaunchKernelGGL(k_build_filter<double>, dim3((unsigned)((f.M + 255) / 256)), dim3(256), 0, p->stream,
                          (cplx<double>*)p->work[0] + f.work, (const cplx<double>*)f.chirp[0], f.L, f.M);
     if ((e = finalize_set(p, small)) != hipSuccess) return e;
-    e = fft_set<double>(p, small, (cplx<double>*)p->work[0], (cplx<double>*)p->work[2], 0, p->stream);
+    e = fft_set<double>(p, small, (cplx<double>*)p->work[0], (cplx<double>*)p->work[2], p->stream);
     if (e != hipSuccess) return e;
     for (const PairDesc& f : small.host) {
       const cplx<double>* bw = (const cplx<double>*)p->work[0] + f.work;

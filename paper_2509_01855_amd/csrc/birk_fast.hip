@@ -1255,7 +1255,8 @@ __global__ __launch_bounds__((1 << LOGW) << (LOGL1 - 4)) void k_fastC2(
 
 // ---------------------------------------------------------------- host side
 
-// Shape of the fast path for one transform size and precision (chosen at plan creation).
+// Lengths of the three passes, and of the plan sizes counted as theirs: up to N = 2^11 plans send
+// the components to birk_lds.hip.
 bool fast_eligible(int64_t N) {
   if (N < 512 || (N & (N - 1)) != 0) return false;
   int s = 0;

@@ -1,5 +1,6 @@
 // Radix-8 Stockham FFTs in LDS on split real/imaginary rows, shared by the three-pass
-// power-of-two product (birk_fast.hip) and the fused Bluestein passes (birk_dct.hip).
+// power-of-two product (birk_fast.hip), the one-launch products (birk_lds.hip) and the chirp
+// convolutions (birk_blu.hip).
 //
 // Twiddles come from one table of W_4096^j = exp(-2 pi i j / 4096), j < 4096 (2^kLdsMaxLog
 // entries): W_L^m = tw[m << (kLdsMaxLog - log2 L)].
@@ -118,8 +119,7 @@ __device__ __forceinline__ void load_tw_stage(cplx<T> (&w)[3], int logL, int log
 }
 
 // ---- fixed-length transforms: COUNT transforms of length 2^LOGL, blockDim = COUNT 2^LOGL / 8 ----
-// (COUNT = 0: 8 blockDim / 2^LOGL of them, blockDim known at run time; GUARD: the workgroup may
-// have further threads, which only keep the barriers)
+// (GUARD: the workgroup may have further threads, which only keep the barriers)
 // Transform t has its real part in row 2t and its imaginary part in row 2t + 1 of a
 // split array with padded rows of padded_ld(2^LOGL) reals.  With the length known at
 // compile time every LDS address of a butterfly is the padded position of its first
@@ -132,7 +132,7 @@ __device__ __forceinline__ void stage_ct(T* __restrict__ buf, const cplx<T> (&w)
   constexpr int NB = kPPT / R;             // butterflies per thread
   constexpr int LOGNBF = LOGL - logR;
   constexpr int NBF = 1 << LOGNBF;         // butterflies per transform
-  const int NTHR = COUNT > 0 ? COUNT << (LOGL - 3) : (int)blockDim.x;  // threads
+  constexpr int NTHR = COUNT << (LOGL - 3);  // threads
   constexpr int NS = 1 << LOGNS;
   constexpr int LD = padded_ld(1 << LOGL);
   T vr[NB][R], vi[NB][R];

@@ -211,7 +211,7 @@ struct birk_plan {
   birk::LdsSet lds[2];            // pairs that fit one workgroup: [0] 2N a power of two, [1] Bluestein
   birk::LdsSet lds_even;          // single components, N = 512, 1024, 2048 (logM = log2 N)
   int noalloc_nbuf = 3;           // work buffers that birk_apply_noalloc accounts for
-  std::vector<birk::ScanClass> sclass;  // its wave scans, n_x <= kScanNx
+  std::vector<birk::ScanClass> sclass;  // its instances by n_x, up to kWideNx
   birk::SegSet seg;               // Krylov segmentation of the batch
   std::vector<void*> allocs;      // device tables owned by the plan
   int64_t total_len = 0;
@@ -223,7 +223,7 @@ struct birk_plan {
   void* work[3] = {nullptr, nullptr, nullptr};   // complex work buffers sized for double
   double* partials = nullptr;
   double* scan = nullptr;     // preconditioner scan scratch
-  float* htab = nullptr;      // H_k in float (per-node J, n_x <= 8; mixed plans)
+  float* htab = nullptr;      // H_k in float (per-node J, n_x <= kScanNx; mixed plans)
   const void* lds_tw[birk::kNumPrec] = {nullptr, nullptr, nullptr};  // exp(-2 pi i t / kLdsMax)
   void* tmp_vec[4] = {nullptr, nullptr, nullptr, nullptr};  // vectors of total_len doubles
   // Krylov workspace, allocated by the first solve that needs it.

@@ -1,4 +1,4 @@
-// Jacobian products, the Birkhoff preconditioner and the Krylov BLAS-1 kernels (gfx950).
+// Jacobian products and the Birkhoff preconditioner's P y (gfx950).
 //
 // Preconditioner (arXiv 2509.01855, "Development of a Special Birkhoff-Centric
 // Preconditioner"): P = I - B~^a J with B~^a lower triangular, w_j below the diagonal

@@ -65,7 +65,9 @@ __device__ __forceinline__ double c0_weight(int k, int N) {
 }
 
 // q_j for 0 <= j <= N from Y_0, Y_{j-1}, Y_{j+1} (Yp is not used at j = N
-// nor Ym at j <= 1): inv2N1 = 1/(2 (N + 1)).
+// nor Ym at j <= 1): inv2N1 = 1/(2 (N + 1)).  A pair branches on the two first j once, before the
+// reciprocals (N = 100002, six components, double: J^T x 79.7 us with a choice in each component,
+// 78.4 so).
 template <typename T>
 struct TrStencil {
   T cm, cp, c0;
@@ -82,13 +84,20 @@ struct TrStencil {
   }
   __device__ __forceinline__ T operator()(T Y0, T Ym, T Yp) const {
     if (j < 2) return pow2_times(j == 0 ? 0.5f : 0.125f, Y0 - Yp);
+    return inner(Y0, Ym, Yp);
+  }
+  __device__ __forceinline__ T inner(T Y0, T Ym, T Yp) const {   // j >= 2
     return pow2_times(0.5f, cm * Ym - cp * Yp - c0 * Y0);
   }
 };
 template <typename T>
 __device__ __forceinline__ cplx<T> mid_tr(int j, int N, cplx<T> Y0, cplx<T> Ym, cplx<T> Yp, T inv2N1) {
+  if (j < 2) {
+    const float h = j == 0 ? 0.5f : 0.125f;
+    return fast::mk<T>(pow2_times(h, Y0.x - Yp.x), pow2_times(h, Y0.y - Yp.y));
+  }
   const TrStencil<T> f(j, N, inv2N1);
-  return fast::mk<T>(f(Y0.x, Ym.x, Yp.x), f(Y0.y, Ym.y, Yp.y));
+  return fast::mk<T>(f.inner(Y0.x, Ym.x, Yp.x), f.inner(Y0.y, Ym.y, Yp.y));
 }
 
 }  // namespace birk

@@ -353,6 +353,11 @@ hipError_t dispatch(birk_plan* p, const ScanClass& sc, const double* J, const T*
 // 65537 nodes and 207 at 131072, 1024 tiles 87 and 126, 2048 tiles 84 and 121; but where a
 // batch fills the chip the longer chain of groups before a tile costs more (64 instances, 20 of
 // them n_x = 12, mixed precision solve: 4741 us at 1024, 5042 at 2048).
+// Longer instances, against a table of H_k made once per J and a hierarchical scan over it:
+// P^{-1} at 2^20 + 1 nodes, n_x = 9, 10, 12, one J: 681, 757, 804 us (1057, 1257, 1786), J per
+// node: 912, 975, 1006 (2470, 2971, 4157).  A solve of 12 iterations at 2^19 + 1 nodes, where the
+// table is made once: n_x = 12, one J 10.5 ms (12.1), J per node 11.7 (13.1); n_x = 9, one J 8.7
+// (8.8), but J per node 9.9 against 9.4.
 int wide_rounds(int64_t Nn) {
   const int64_t per_round = (int64_t)kWideNodes * 1024;
   return (int)((Nn + per_round - 1) / per_round);
